@@ -57,9 +57,10 @@
  *   - P == 0 or U == 0 is a valid no-op (norms of an empty shard are 0).
  *   - Gradient rows may alias each other; they must not alias params,
  *     momentum or norms_out.  Rows are read-only during the call.
- *   - Any alignment is accepted; when params, momentum and all rows are
- *     16-byte aligned the vector path is used, otherwise an element-wise path
- *     with the same arithmetic (identical results).
+ *   - Any alignment is accepted, with the same arithmetic for every element
+ *     (params and momentum come out the same bits).  Slices that start at the
+ *     same element of larger buffers run at the speed of aligned ones; buffers
+ *     that are off by different amounts are read at unaligned addresses.
  *   - The library keeps a small internal workspace (coefficient tables,
  *     per-block norm partials, a 16-byte work queue per slot), created on
  *     first use, released by star_shutdown().  Calls may come from several

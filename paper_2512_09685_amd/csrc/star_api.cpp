@@ -8,6 +8,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "star.h"
@@ -235,7 +236,55 @@ struct SlotRelease {
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+// How many of the first elements of a shard (0 to 63, at most P) the chunks should leave out so that most of the
+// traffic falls on aligned addresses: above all chunks of 4 on their own size (fp32 16, bf16 8 bytes), then every
+// wave's 64 chunks on whole cache lines of 128 bytes -- 16-byte alignment alone leaves a line in two that two waves
+// share at every wave's end (46 M elements, shard from element 1 on, update: 8 fp32 rows 375 us on 16 bytes, 349 on whole lines,
+// 8 bf16 rows 275 against 255).  A server that owns a
+// slice of larger buffers is handed pointers that are all off by the same number of elements, and one choice aligns
+// them all; where no choice does, the rest is read at unaligned addresses.
+class Head {
+  public:
+    void add(const void* p, int elem_bytes, int passes) {   // passes: 2 for a buffer that is read and written
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+        if (!p || a % 128 == 0) {
+            if (p) aligned_ += elem_bytes * passes;
+            return;
+        }
+        off_ = true;
+        if (a % elem_bytes) return;   // off its own grid: no choice helps
+        const int line = 128 / elem_bytes, need = (int)((line - (a / elem_bytes) % line) % line);
+        chunk_[need % 4] += elem_bytes * passes;
+        for (int h = need; h < kMost; h += line) line_[h] += elem_bytes * passes;
+    }
+    int best(int64_t P) const {
+        if (!off_) return 0;
+        int h = 0, most = -1;
+        for (int k = 0; k < kMost && k <= P; ++k) {
+            // (buffers on whole lines as they are stay so only without a head, or with 32 elements of fp32)
+            const int kept = k == 0 ? aligned_ : 0;
+            const int score = 1024 * (chunk_[k % 4] + (k % 4 == 0 ? aligned_ : 0)) + line_[k] + kept;
+            if (score > most) {
+                most = score;
+                h = k;
+            }
+        }
+        return h;
+    }
+
+  private:
+    static constexpr int kMost = 64;
+    int chunk_[4] = {0, 0, 0, 0}, line_[kMost] = {}, aligned_ = 0;
+    bool off_ = false;
+};
+
+size_t grad_bytes(int dtype) { return dtype == STAR_F32 ? 4 : 2; }
+
+template <class T>
+T* past(T* p, int head, size_t elem_bytes) {   // p advanced by `head` elements (null stays null)
+    typedef typename std::conditional<std::is_const<T>::value, const char, char>::type byte;
+    return p ? reinterpret_cast<T*>(reinterpret_cast<byte*>(p) + head * elem_bytes) : p;
+}
 
 // Table layout in a slot (all offsets 256-byte aligned):
 //   coef_f32 [U][Wp] | lr_f32 [U] | mask_u32 [U] | coef_f64 [U][Wp] | out pointers [U]
@@ -455,11 +504,22 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
 
     // rows in compact order; padding rows repeat the last row with zero coefficients
     star::RowPtrs rows;
-    bool vec_ok = !update || (aligned16(params) && aligned16(momentum) && aligned16(publish));
-    for (int k = 0; k < STAR_MAX_WORKERS; ++k) {
-        rows.p[k] = grad_rows[plan.row_of[std::min(k, Wc - 1)]];
-        if (k < Wc && !aligned16(rows.p[k])) vec_ok = false;
+    Head align;
+    if (update) {
+        align.add(params, 4, 2);
+        align.add(momentum, 4, 2);
+        align.add(publish, grad_bytes(publish_dtype), 1);
     }
+    for (int k = 0; k < Wc; ++k) align.add(grad_rows[plan.row_of[k]], grad_bytes(grad_dtype), 1);
+    const int head = align.best(P);
+    for (int k = 0; k < STAR_MAX_WORKERS; ++k)
+        rows.p[k] = past(grad_rows[plan.row_of[std::min(k, Wc - 1)]], head, grad_bytes(grad_dtype));
+    if (update) {
+        params = past(params, head, 4);
+        momentum = past(momentum, head, 4);
+        publish = past(publish, head, grad_bytes(publish_dtype));
+    }
+    P -= head;
 
     // tables of the step-by-step kernel: in the kernel arguments when small and the whole stream fits in
     // one launch (a launch reads the inline tables from entry 0), else staged through the slot
@@ -564,15 +624,12 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
                 }
             }
             a.P = P;
-            a.vec_ok = vec_ok ? 1 : 0;
+            a.head = head;
             a.publish = update ? publish : nullptr;
             a.publish_dtype = publish_dtype;
             a.partials = partials;
             a.queue = want_queue ? queue : nullptr;
-            // (fp32 buffers that are not 16-byte aligned go one element per lane, and a matrix-core tile of 256
-            // elements costs what one of 1024 does: up to 16 rows the vector-register form is faster there,
-            // 32 Mi elements, 16 rows: 0.66 against 1.10 ms; with bf16 rows it is the other way round)
-            const bool mfma = how.mfma && !(!vec_ok && grad_dtype == STAR_F32 && Wp <= star::kMaxValuGramW);
+            const bool mfma = how.mfma;
             if (mfma) a.queue = queue;   // that kernel always takes its tiles from the queue
             e = mfma ? star::launch_affine_mfma(Wp, grad_dtype, update, a, num_cu, grid_cap, &grid, stream)
                      : star::launch_affine(Wp, grad_dtype, update, gram, a, num_cu, grid_cap, &grid, stream);
@@ -618,7 +675,7 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
             a.mu = (float)plan.mu;
             a.wd = (float)plan.wd;
             a.P = P;
-            a.vec_ok = vec_ok ? 1 : 0;
+            a.head = head;
             a.publish = (seq_update && u0 + n == U) ? publish : nullptr;   // the last launch holds the final params
             a.publish_dtype = publish_dtype;
             a.partials = partials;
@@ -672,13 +729,14 @@ star_status run_reduce(void* const* out_rows, int out_dtype, const void* const* 
     const int grid_cap = star::kGridCap;
     const int Wp = star::padded_rows(Wc);
     star::RowPtrs rows;
-    bool vec_ok = true;
-    for (int k = 0; k < STAR_MAX_WORKERS; ++k) {
-        rows.p[k] = grad_rows[plan.row_of[std::min(k, Wc - 1)]];
-        if (k < Wc && !aligned16(rows.p[k])) vec_ok = false;
-    }
-    for (int u = 0; u < U; ++u)
-        if (!aligned16(out_rows[u])) vec_ok = false;
+    Head align;
+    for (int u = 0; u < U; ++u) align.add(out_rows[u], grad_bytes(out_dtype), 1);
+    for (int k = 0; k < Wc; ++k) align.add(grad_rows[plan.row_of[k]], grad_bytes(grad_dtype), 1);
+    const int head = align.best(P);
+    for (int k = 0; k < STAR_MAX_WORKERS; ++k)
+        rows.p[k] = past(grad_rows[plan.row_of[std::min(k, Wc - 1)]], head, grad_bytes(grad_dtype));
+    auto out_row = [&](int u) { return past(out_rows[u], head, grad_bytes(out_dtype)); };
+    P -= head;
 
     std::lock_guard<std::mutex> lock(g_mu);
     const TableLayout lay = table_layout(U, Wp);
@@ -695,7 +753,7 @@ star_status run_reduce(void* const* out_rows, int out_dtype, const void* const* 
         for (int u = 0; u < U; ++u) {
             for (int k = 0; k < Wp; ++k) inl.coef[u * Wp + k] = k < Wc ? (float)plan.coef[(size_t)u * Wc + k] : 0.0f;
             inl.mask[u] = plan.mask[u];
-            inl.out[u] = out_rows[u];
+            inl.out[u] = out_row(u);
         }
     } else {
         float* c32 = reinterpret_cast<float*>(h + lay.coef32);
@@ -704,7 +762,7 @@ star_status run_reduce(void* const* out_rows, int out_dtype, const void* const* 
         for (int u = 0; u < U; ++u) {
             for (int k = 0; k < Wp; ++k) c32[(size_t)u * Wp + k] = k < Wc ? (float)plan.coef[(size_t)u * Wc + k] : 0.0f;
             mk[u] = plan.mask[u];
-            op[u] = out_rows[u];
+            op[u] = out_row(u);
         }
         STAR_HIP(hipMemcpyAsync(d, h, lay.total, hipMemcpyHostToDevice, stream));
     }
@@ -720,7 +778,7 @@ star_status run_reduce(void* const* out_rows, int out_dtype, const void* const* 
         a.U = n;
         a.out_dtype = out_dtype;
         a.P = P;
-        a.vec_ok = vec_ok ? 1 : 0;
+        a.head = head;
         a.norms = want_norms ? 1 : 0;
         a.partials = slot->partials;
         a.queue = P >= queue_min_for(opt, grad_dtype, Wc, false, true, false, false, n) ? slot->queue : nullptr;
@@ -753,12 +811,15 @@ star_status run_gram(const void* const* grad_rows, int grad_dtype, int64_t P, in
     }
     star::AffArgs a;
     std::memset(&a, 0, sizeof a);
-    bool vec_ok = true;
-    for (int k = 0; k < STAR_MAX_WORKERS; ++k) {
-        a.rows.p[k] = grad_rows[std::min(k, W - 1)];
-        if (k < W && !a.rows.p[k]) return set_err(STAR_ERR_NULL, "a gradient row is NULL");
-        if (k < W && !aligned16(a.rows.p[k])) vec_ok = false;
+    Head align;
+    for (int k = 0; k < W; ++k) {
+        if (!grad_rows[k]) return set_err(STAR_ERR_NULL, "a gradient row is NULL");
+        align.add(grad_rows[k], grad_bytes(grad_dtype), 1);
     }
+    a.head = align.best(P);
+    for (int k = 0; k < STAR_MAX_WORKERS; ++k)
+        a.rows.p[k] = past(grad_rows[std::min(k, W - 1)], a.head, grad_bytes(grad_dtype));
+    P -= a.head;
     int device = 0, num_cu = 1;
     st = device_info(&device, &num_cu);
     if (st != STAR_OK) return st;
@@ -768,7 +829,6 @@ star_status run_gram(const void* const* grad_rows, int grad_dtype, int64_t P, in
     if (st != STAR_OK) return st;
     SlotRelease release{slot, stream};
     a.P = P;
-    a.vec_ok = vec_ok ? 1 : 0;
     a.partials = slot->partials;
     int grid = 0;
     const int Wp = star::padded_rows(W);   // rows beyond W repeat the last one; their entries are not copied out

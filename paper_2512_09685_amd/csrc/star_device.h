@@ -14,6 +14,11 @@ namespace star {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// The same as they lie in memory: element-aligned only.  The hardware takes global loads and stores of 8 and 16
+// bytes at any address (unaligned access mode, the default of the ROCm runtime and of the compiler), so these
+// types cost nothing where the address is aligned and need no second code path where it is not.
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
 
 // ---------------------------------------------------------------- row access
 // A "row type" says how VEC consecutive gradient elements are fetched with one
@@ -22,7 +27,7 @@ struct RowF32 {
     static constexpr int VEC = 4;
     typedef f32x4 vec;
     static __device__ __forceinline__ vec load(const void* row, int64_t chunk) {
-        return __builtin_nontemporal_load(reinterpret_cast<const vec*>(row) + chunk);
+        return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(row) + chunk);
     }
     template <int K>
     static __device__ __forceinline__ float get(const vec& x) { return x[K]; }
@@ -42,7 +47,7 @@ struct RowBf16x4 {
     static constexpr int VEC = 4;
     typedef u32x2 vec;
     static __device__ __forceinline__ vec load(const void* row, int64_t chunk) {
-        return __builtin_nontemporal_load(reinterpret_cast<const vec*>(row) + chunk);
+        return __builtin_nontemporal_load(reinterpret_cast<const u32x2_any*>(row) + chunk);
     }
     template <int K>
     static __device__ __forceinline__ float get(const vec& x) { return bf16_of<K>(x[K >> 1]); }
@@ -54,7 +59,7 @@ struct RowBf16x4 {
 // Streaming (non-temporal) 16-byte store.  The empty asm pins the value in
 // vector registers at this point; without it the optimiser re-forms the store
 // from the scalar results and the non-temporal hint is lost.
-__device__ __forceinline__ void store_streaming(f32x4 x, f32x4* dst) {
+__device__ __forceinline__ void store_streaming(f32x4 x, f32x4_any* dst) {
     asm volatile("" : "+v"(x));
     __builtin_nontemporal_store(x, dst);
 }
@@ -63,10 +68,10 @@ __device__ __forceinline__ void store_streaming(f32x4 x, f32x4* dst) {
 // traffic.  The hint does not keep a small shard from staying in the 256 MB Infinity Cache between
 // calls: shards with params + momentum up to that size ran equally fast with and without it.
 __device__ __forceinline__ f32x4 load_state(const float* base, int64_t idx4) {
-    return __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(base) + idx4);
+    return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(base) + idx4);
 }
 __device__ __forceinline__ void store_state(f32x4 x, float* base, int64_t idx4) {
-    store_streaming(x, reinterpret_cast<f32x4*>(base) + idx4);
+    store_streaming(x, reinterpret_cast<f32x4_any*>(base) + idx4);
 }
 
 // fp32 -> bf16, round to nearest even; NaN stays NaN (quiet bit forced).
@@ -84,9 +89,9 @@ __device__ __forceinline__ void publish_chunk(f32x4 x, void* dst, int as_bf16, i
         packed[0] = bf16_bits_rne(x[0]) | (bf16_bits_rne(x[1]) << 16);
         packed[1] = bf16_bits_rne(x[2]) | (bf16_bits_rne(x[3]) << 16);
         asm volatile("" : "+v"(packed));
-        __builtin_nontemporal_store(packed, reinterpret_cast<u32x2*>(dst) + c);
+        __builtin_nontemporal_store(packed, reinterpret_cast<u32x2_any*>(dst) + c);
     } else {
-        store_streaming(x, reinterpret_cast<f32x4*>(dst) + c);
+        store_streaming(x, reinterpret_cast<f32x4_any*>(dst) + c);
     }
 }
 
@@ -147,6 +152,19 @@ __device__ __forceinline__ void static_for(F&& f) {
         f(std::integral_constant<int, I>{});
         static_for<I + 1, N>(f);
     }
+}
+
+// ---------------------------------------------------------------- elements outside whole chunks
+// The host advances every pointer past the first `head` (0 to 63) elements of the shard, where that puts the buffers
+// on whole cache lines; a shard cut out of larger buffers at an odd element is then read like any other (8 bf16
+// rows, 46 M elements from element 1 on, update with norms and bf16 copy: 272 us, 437 one element per lane).  Chunks of 4 follow from
+// there; what they leave over -- `head` elements before the pointers, up to 3 behind the last chunk -- is worked on one
+// element at a time: remainder r is element rest_element(r), r = 0 .. rest_count() - 1.
+__device__ __forceinline__ int64_t rest_count(const int head, const int64_t P, const int64_t nchunk) {
+    return head + (P - nchunk * 4);
+}
+__device__ __forceinline__ int64_t rest_element(const int64_t r, const int head, const int64_t nchunk) {
+    return r < head ? r - head : nchunk * 4 + (r - head);
 }
 
 // ---------------------------------------------------------------- workgroup -> tile mapping
@@ -294,18 +312,16 @@ struct Geometry {
     int threads; // workgroup size (kBlock unless a launcher says otherwise)
 };
 
-// Fixed assignment of tiles (short shards, launches without a queue).  items = chunks (or single
-// elements when the buffers are not 16-byte aligned).  A kernel that ends with a per-workgroup norm
+// Fixed assignment of tiles (short shards, launches without a queue).  A kernel that ends with a per-workgroup norm
 // reduction runs long-lived workgroups that sweep the shard as a single span; the others get one
 // tile per workgroup, dispatched in address order.
 // `thread_bytes`: bytes one thread has in flight per tile; long-lived workgroups are stacked on a compute unit
 // (up to `max_per_cu`) until about 64 KB per unit are in flight, which light bf16 kernels need and heavy fp32
 // ones already have with one workgroup; `min_per_cu` is for kernels that need a second workgroup per unit for
 // their arithmetic rather than for their memory traffic.
-inline Geometry pick_geometry(int64_t P, int vec, bool vec_ok, bool reduces, int num_cu, int grid_cap,
+inline Geometry pick_geometry(int64_t P, bool reduces, int num_cu, int grid_cap,
                               int thread_bytes = 256, int max_per_cu = 1, int min_per_cu = 1) {
-    const int64_t items = vec_ok ? std::max<int64_t>(P / vec, P % vec) : P;
-    const int64_t tiles = std::max<int64_t>(1, (items + kBlock - 1) / kBlock);
+    const int64_t tiles = std::max<int64_t>(1, (P / 4 + kBlock - 1) / kBlock);
     Geometry g;
     g.claim = 0;
     g.threads = kBlock;

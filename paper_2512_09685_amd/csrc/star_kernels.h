@@ -134,7 +134,7 @@ struct SeqArgs {
     int32_t U;             // updates in this launch
     float mu, wd;
     int64_t P;
-    int32_t vec_ok;        // all buffers 16-byte aligned
+    int32_t head;          // elements before the pointers and P (0 to 63), see rest_element
     void* publish;         // device copy of the new params (P elements), or null
     int32_t publish_dtype; // star_dtype of that copy
     double* partials;      // device [U][grid] sums of gbar^2 per block (norms only)
@@ -179,7 +179,7 @@ struct AffArgs {
     RowPtrs rows;
     AffCoef cf;
     int64_t P;
-    int32_t vec_ok;
+    int32_t head;           // elements before the pointers and P (0 to 63), see rest_element
     void* publish;          // device copy of the new params (P elements), or null
     int32_t publish_dtype;  // star_dtype of that copy
     double* partials;  // device [Wp(Wp+1)/2][grid] pairwise-product sums per block (gram only)
@@ -240,7 +240,7 @@ struct ReduceArgs {
     int32_t U;               // groups in this launch
     int32_t out_dtype;       // star_dtype of the outputs
     int64_t P;
-    int32_t vec_ok;          // every row and every output 16-byte aligned
+    int32_t head;            // elements before the pointers and P (0 to 63), see rest_element
     int32_t norms;           // also accumulate sum of squares per group
     double* partials;        // device [U][grid] (norms only)
     TileQueue* queue;        // device, zeroed; null: fixed assignment of tiles to workgroups

@@ -54,7 +54,7 @@ template <int W, class R, bool UPDATE, bool GRAM, int KCH = 1, bool ONE_WAVE = f
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, ONE_WAVE ? 1 : 8)))
 void aff_kernel(float* __restrict__ params, float* __restrict__ momentum,
                                                      const RowPtrs rows, const AffCoef cf, const int64_t P,
-                                                     const int vec_ok, const int span_g, const int span_k,
+                                                     const int head, const int span_g, const int span_k,
                                                      void* __restrict__ publish, const int publish_bf16,
                                                      double* __restrict__ partials, TileQueue* __restrict__ queue,
                                                      const int claim) {
@@ -92,7 +92,7 @@ void aff_kernel(float* __restrict__ params, float* __restrict__ momentum,
     // the plain one also runs with half-size workgroups
     const int threads = GRAM ? kBlock : (int)blockDim.x;
     const Span span = make_span(span_g, span_k, threads);
-    const int64_t nchunk = vec_ok ? P / VEC : 0;
+    const int64_t nchunk = P / VEC;
 
     // one chunk: VEC elements of every row, the update, the pairwise products
     auto process = [&](const int64_t c) {
@@ -187,12 +187,11 @@ void aff_kernel(float* __restrict__ params, float* __restrict__ momentum,
             if constexpr (kFew) fold_now();
         }
     }
-    // elements not covered by whole chunks (the ragged end, or everything when
-    // some buffer is not 16-byte aligned): same arithmetic, one element at a time
-    const int64_t nrest = P - nchunk * VEC;
+    // elements not covered by whole chunks: same arithmetic, one element at a time
+    const int64_t nrest = rest_count(head, P, nchunk);
     int64_t r = span.first;
     for (int k = 0; k < span.K && r < nrest; ++k, r += span.step) {
-        const int64_t j = nchunk * VEC + r;
+        const int64_t j = rest_element(r, head, nchunk);
         float ge[W];
 #pragma unroll
         for (int w = 0; w < W; ++w) ge[w] = R::load1(rows.p[w], j);
@@ -284,7 +283,7 @@ __global__ __launch_bounds__(kBlock) void seq_kernel(float* __restrict__ params,
                                                      const float* __restrict__ t_lr,
                                                      const uint32_t* __restrict__ t_mask, const int U,
                                                      const float mu, const float wd, const int64_t P,
-                                                     const int vec_ok, const int span_g, const int span_k,
+                                                     const int head, const int span_g, const int span_k,
                                                      void* __restrict__ publish, const int publish_bf16,
                                                      double* __restrict__ partials, TileQueue* __restrict__ queue,
                                                      const int claim, const InlineTables inl, const AffCoef cf) {
@@ -314,7 +313,7 @@ __global__ __launch_bounds__(kBlock) void seq_kernel(float* __restrict__ params,
     __syncthreads();
 
     const Span span = make_span(span_g, span_k);
-    const int64_t nchunk = vec_ok ? P / 4 : 0;
+    const int64_t nchunk = P / 4;
 
     auto process = [&](const int64_t c) {
         typename R::vec raw[W];
@@ -372,10 +371,10 @@ __global__ __launch_bounds__(kBlock) void seq_kernel(float* __restrict__ params,
         int64_t c = span.first;
         for (int k = 0; k < span.K && c < nchunk; ++k, c += span.step) process(c);
     }
-    const int64_t nrest = P - nchunk * 4;
+    const int64_t nrest = rest_count(head, P, nchunk);
     int64_t r = span.first;
     for (int k = 0; k < span.K && r < nrest; ++k, r += span.step) {
-        const int64_t j = nchunk * 4 + r;
+        const int64_t j = rest_element(r, head, nchunk);
         float g[W][4];
 #pragma unroll
         for (int w = 0; w < W; ++w) {
@@ -517,17 +516,17 @@ hipError_t launch_seq_t(const SeqArgs& a, int num_cu, int grid_cap, int* grid_ou
     // by arithmetic and latency and keep the fixed assignment with as many waves as fit
     const int thread_bytes = W * (int)sizeof(typename R::vec) + (UPDATE ? 32 : 0);
     // the collapsed form does so little arithmetic per update that it is bound by memory for any stream it is used for
-    const bool queued = a.queue && a.vec_ok && (COLLAPSED || seq_takes_queue(a.U));
+    const bool queued = a.queue && (COLLAPSED || seq_takes_queue(a.U));
     // (the collapsed form's norm walk -- LDS reads and a wave-uniform branch per row and update -- needs a second
     // workgroup per unit to hide under the memory time: 20 to 32 fp32 rows, 8 updates, 0.68-0.71 of the HBM peak with
     // two against 0.43-0.45 with one)
     const int per_cu = COLLAPSED ? 2 : queue_workgroups_per_cu(thread_bytes, UPDATE);
     const Geometry g = queued ? queue_geometry(num_cu, grid_cap, per_cu, thread_bytes)
-                              : pick_geometry(a.P, 4, a.vec_ok != 0, NORMS, num_cu, grid_cap, thread_bytes, 4,
+                              : pick_geometry(a.P, NORMS, num_cu, grid_cap, thread_bytes, 4,
                                               COLLAPSED ? 2 : 1);   // (short shards as well: 25-30 % faster with two)
     *grid_out = g.grid;
     hipLaunchKernelGGL(kern, dim3(g.grid), dim3(kBlock), lds, s, a.params, a.momentum, a.rows, a.coef, a.lr, a.mask,
-                       a.U, a.mu, a.wd, a.P, a.vec_ok, g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0,
+                       a.U, a.mu, a.wd, a.P, a.head, g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0,
                        a.partials, a.queue, g.claim, a.coef ? InlineTables() : *a.inl, a.cf ? *a.cf : AffCoef());
     return hipGetLastError();
 }
@@ -540,14 +539,14 @@ hipError_t launch_aff_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_ou
     // chunk; 1 / 2 / 3 bf16 rows with 4 / 4 / 2 chunks: 0.44 / 0.66 / 0.65 against 0.22 / 0.36 / 0.48)
     constexpr int KCH = (GRAM && !UPDATE && W <= kFewRows && kRowBytes < 64)
                             ? (kRowBytes <= 8 ? 8 : (kRowBytes <= 16 ? 4 : 2)) : 1;
-    const bool queued = aff_takes_queue(GRAM, W, std::is_same<R, RowF32>::value, UPDATE) && a.queue && a.vec_ok;
+    const bool queued = aff_takes_queue(GRAM, W, std::is_same<R, RowF32>::value, UPDATE) && a.queue;
     if constexpr (KCH > 1) {
         if (queued) {
             const int thread_bytes = kRowBytes * KCH;
             const Geometry g = queue_geometry(num_cu, grid_cap, 2, thread_bytes, Traffic::ReadOnly);
             *grid_out = g.grid;
             hipLaunchKernelGGL((aff_kernel<W, R, UPDATE, GRAM, KCH>), dim3(g.grid), dim3(g.threads), 0, s, a.params,
-                               a.momentum, a.rows, a.cf, a.P, a.vec_ok, g.span_g, g.span_k, a.publish,
+                               a.momentum, a.rows, a.cf, a.P, a.head, g.span_g, g.span_k, a.publish,
                                a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue, g.claim);
             return hipGetLastError();
         }
@@ -557,7 +556,7 @@ hipError_t launch_aff_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_ou
     const int thread_bytes = W * (int)sizeof(typename R::vec) + (UPDATE ? 32 : 0);
     Geometry g = queued ? queue_geometry(num_cu, grid_cap, queue_workgroups_per_cu(thread_bytes, UPDATE), thread_bytes,
                                          UPDATE ? Traffic::Update : Traffic::ReadOnly)
-                        : pick_geometry(a.P, R::VEC, a.vec_ok != 0, GRAM, num_cu, grid_cap);
+                        : pick_geometry(a.P, GRAM, num_cu, grid_cap);
     // 24 and more bf16 rows: twice as many workgroups of half the size (tiles of 1 KB per row) measured
     // 3-4 % faster (32 rows, 138 M elements: 1.92 against 1.98 ms); with 16 rows the same is 15 % slower,
     // and fp32 rows do not care.  With these half-size tiles claims of 4 (4 KB of every row, 8 KB of the
@@ -570,13 +569,13 @@ hipError_t launch_aff_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_ou
             g.claim = 4;
             *grid_out = g.grid;
             hipLaunchKernelGGL((aff_kernel<W, R, UPDATE, GRAM, 1, true>), dim3(g.grid), dim3(g.threads), 0, s, a.params,
-                               a.momentum, a.rows, a.cf, a.P, a.vec_ok, g.span_g, g.span_k, a.publish,
+                               a.momentum, a.rows, a.cf, a.P, a.head, g.span_g, g.span_k, a.publish,
                                a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue, g.claim);
             return hipGetLastError();
         }
     }
     *grid_out = g.grid;
-    hipLaunchKernelGGL(kern, dim3(g.grid), dim3(g.threads), 0, s, a.params, a.momentum, a.rows, a.cf, a.P, a.vec_ok,
+    hipLaunchKernelGGL(kern, dim3(g.grid), dim3(g.threads), 0, s, a.params, a.momentum, a.rows, a.cf, a.P, a.head,
                        g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue,
                        g.claim);
     return hipGetLastError();

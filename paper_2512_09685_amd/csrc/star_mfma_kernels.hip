@@ -76,7 +76,7 @@ constexpr int kPanelRowBytes = 512 + 16;
 template <int W, class R, bool UPDATE, bool WIDE>
 __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__ params, float* __restrict__ momentum,
                                                           const RowPtrs rows, const AffCoef cf, const int64_t P,
-                                                          const int vec_ok, const int span_g, const int span_k,
+                                                          const int head, const int span_g, const int span_k,
                                                           void* __restrict__ publish, const int publish_bf16,
                                                           double* __restrict__ partials,
                                                           TileQueue* __restrict__ queue, const int claim) {
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
     // Tiles come from the queue and are walked with wave-uniform control flow (the matrix instructions
     // need every lane); a lane beyond the end of the shard contributes zeros.
     const int64_t first_tile = (int64_t)(blockIdx.x / span_g) * span_g * (int64_t)span_k + (blockIdx.x % span_g);
-    const int64_t nchunk = vec_ok ? P / 4 : 0;
+    const int64_t nchunk = P / 4;
     const int64_t ntile = (nchunk + kBlock - 1) / kBlock;
     // element-wise update of chunk c from values already in registers
     auto update_chunk = [&](int64_t c, const vec_t (&g)[W], f32x4 pq, f32x4 vq) {
@@ -287,9 +287,8 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
             fold();
         });
     }
-    // elements not covered by whole chunks (the ragged end, or everything when some buffer is not
-    // 16-byte aligned): one element per lane, same arithmetic
-    const int64_t nrest = P - nchunk * 4;
+    // elements not covered by whole chunks: one element per lane, same arithmetic
+    const int64_t nrest = rest_count(head, P, nchunk);
     const int64_t nrtile = (nrest + kBlock - 1) / kBlock;
     int64_t tile = first_tile;
     for (int k = 0; k < span_k && tile < nrtile; ++k, tile += span_g) {
@@ -298,7 +297,7 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
 #pragma unroll
         for (int w = 0; w < W; ++w) g[w] = vec_t{};
         if (r < nrest) {
-            const int64_t j = nchunk * 4 + r;
+            const int64_t j = rest_element(r, head, nchunk);
             float g1[W];
 #pragma unroll
             for (int w = 0; w < W; ++w) {
@@ -371,11 +370,9 @@ hipError_t launch_mfma_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_o
     if (!a.queue) return hipErrorInvalidValue;
     const Geometry g = queue_geometry(num_cu, grid_cap, per_cu, kRowBytes + (UPDATE ? 32 : 0),
                                       UPDATE ? Traffic::Update : Traffic::ReadOnly,
-                                      // (buffers that are not 16-byte aligned go through the one-element path,
-                                      // which is spread over the whole grid: no tile count, no short-shard form)
-                                      a.vec_ok ? (a.P / 4 + kBlock - 1) / kBlock : -1);
+                                      (a.P / 4 + kBlock - 1) / kBlock);
     *grid_out = g.grid;
-    hipLaunchKernelGGL(kern, dim3(g.grid), dim3(kBlock), 0, s, a.params, a.momentum, a.rows, a.cf, a.P, a.vec_ok,
+    hipLaunchKernelGGL(kern, dim3(g.grid), dim3(kBlock), 0, s, a.params, a.momentum, a.rows, a.cf, a.P, a.head,
                        g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue,
                        g.claim);
     return hipGetLastError();

@@ -18,7 +18,7 @@ template <int W, class R>
 __global__ __launch_bounds__(kBlock) void reduce_rows_kernel(const RowPtrs rows, const float* __restrict__ t_coef,
                                                              const uint32_t* __restrict__ t_mask,
                                                              void* const* __restrict__ t_out, const int U,
-                                                             const int out_bf16, const int64_t P, const int vec_ok,
+                                                             const int out_bf16, const int64_t P, const int head,
                                                              const int norms, const int span_g, const int span_k,
                                                              double* __restrict__ partials,
                                                              TileQueue* __restrict__ queue, const int claim,
@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kBlock) void reduce_rows_kernel(const RowPtrs rows,
     __syncthreads();
 
     const Span span = make_span(span_g, span_k);
-    const int64_t nchunk = vec_ok ? P / 4 : 0;
+    const int64_t nchunk = P / 4;
 
     // one pass over the groups for the element(s) held in g; `store` writes gbar of group u
     auto walk = [&](float (&g)[W][4], auto&& store) {
@@ -104,10 +104,10 @@ __global__ __launch_bounds__(kBlock) void reduce_rows_kernel(const RowPtrs rows,
         int64_t c = span.first;
         for (int k = 0; k < span.K && c < nchunk; ++k, c += span.step) process(c);
     }
-    const int64_t nrest = P - nchunk * 4;
+    const int64_t nrest = rest_count(head, P, nchunk);
     int64_t r = span.first;
     for (int k = 0; k < span.K && r < nrest; ++k, r += span.step) {
-        const int64_t j = nchunk * 4 + r;
+        const int64_t j = rest_element(r, head, nchunk);
         float g[W][4];
 #pragma unroll
         for (int w = 0; w < W; ++w) {
@@ -146,16 +146,16 @@ template <int W, class R>
 hipError_t launch_reduce_t(const ReduceArgs& a, int num_cu, int grid_cap, int* grid_out, hipStream_t s) {
     auto kern = reduce_rows_kernel<W, R>;
     const size_t lds = reduce_lds_bytes(W, a.U, a.norms != 0);
-    const bool queued = a.queue && a.vec_ok;
+    const bool queued = a.queue;
     const Geometry g = queued ? queue_geometry(num_cu, grid_cap, queue_workgroups_per_cu(0, false),
                                                W * (int)sizeof(typename R::vec) + 16, Traffic::Reduce)
                               // (with norms: long-lived workgroups, and at least two of them per unit whatever
                                               // the tile weighs -- 32 bf16 rows, 16 groups, 32 Mi elements: one per unit 1.72 ms)
-                              : pick_geometry(a.P, 4, a.vec_ok != 0, a.norms != 0, num_cu, grid_cap,
+                              : pick_geometry(a.P, a.norms != 0, num_cu, grid_cap,
                                               W * (int)sizeof(typename R::vec), 4, 2);
     *grid_out = g.grid;
     hipLaunchKernelGGL(kern, dim3(g.grid), dim3(kBlock), lds, s, a.rows, a.coef, a.mask, a.out, a.U,
-                       a.out_dtype == STAR_BF16 ? 1 : 0, a.P, a.vec_ok, a.norms, g.span_g, g.span_k, a.partials,
+                       a.out_dtype == STAR_BF16 ? 1 : 0, a.P, a.head, a.norms, g.span_g, g.span_k, a.partials,
                        a.queue, g.claim, a.coef ? InlineTables() : *a.inl);
     return hipGetLastError();
 }

@@ -224,10 +224,9 @@ def test_direct_norms_option_on_anticorrelated_rows(dt):
 
 @pytest.mark.parametrize("dt,W,norms", [("f32", 16, True), ("bf16", 16, True), ("f32", 8, False), ("f32", 24, True)])
 def test_unaligned_buffers_keep_the_whole_grid(dt, W, norms):
-    """Views that start one element into their allocations are not 16-byte aligned and go through the
-    one-element-per-lane path.  That path is slower than the vector one but must stay within a small factor
-    of it (a launch that hands the whole shard to a single workgroup is hundreds of times slower), and its
-    results are the same as those of the aligned call on the same values."""
+    """Views that start one element into their allocations are not 16-byte aligned.  They must stay within a
+    small factor of the aligned call (a launch that hands the whole shard to a single workgroup is hundreds of
+    times slower), and the results are the same as those of the aligned call on the same values."""
     import time
     rng = np.random.default_rng(47)
     P = 4 << 20
@@ -260,6 +259,49 @@ def test_unaligned_buffers_keep_the_whole_grid(dt, W, norms):
     assert so.max_rel_err(b[1].cpu().numpy(), a[1].cpu().numpy()) <= 2e-6
     if norms:
         assert np.max(np.abs(b[2].cpu().numpy() - a[2].cpu().numpy()) / a[2].cpu().numpy()) <= 2e-6
+
+
+@pytest.mark.parametrize("P", [1, 3, 61, 66, 1030, 5003])
+@pytest.mark.parametrize("dt,W", [("f32", 3), ("bf16", 9), ("f32", 18)])
+def test_shards_at_any_offset(dt, W, P):
+    """Buffers that start anywhere in their allocations, all by the same number of elements (the elements before the
+    first whole line are then worked on one by one) or each by its own (unaligned vector access), against aligned
+    copies of the same values: the state and the aggregate to the bit, norms and Gram matrix to the rounding of
+    their fp32 partial sums (a few 2^-24), and nothing outside the shard written.  The shortest shards end inside
+    that first part."""
+    rng = np.random.default_rng(P)
+    T = torch.float32 if dt == "f32" else torch.bfloat16
+    offs, mem, st = rand_stream(rng, W, 5, stale=3)
+    us, one = star.UpdateStream(offs, mem, st), star.UpdateStream([0, W], np.arange(W))
+    hp = dict(lr=0.05, momentum_coef=0.9, weight_decay=1e-3, wmode="stale")
+    vals = [torch.from_numpy(rng.standard_normal(P + 200).astype(np.float32)).cuda() for _ in range(W + 2)]
+
+    def buf(k, off, dtype=torch.float32, fill=None):
+        whole = torch.full((P + 200,), 7.0, device="cuda", dtype=dtype)
+        whole[off:off + P] = vals[k][:P].to(dtype) if fill is None else fill
+        return whole, whole[off:off + P]
+
+    def everything(shift):
+        rows = [buf(w, shift(w), T)[1] for w in range(W)]
+        (pw, p), (vw, v) = buf(W, shift(W)), buf(W + 1, shift(W + 1))
+        (sw, send), (ow, out) = buf(0, shift(W), torch.bfloat16, 0.0), buf(0, shift(W + 2), fill=0.0)
+        n, gram = torch.zeros(us.U, device="cuda"), torch.zeros(W, W, dtype=torch.float64, device="cuda")
+        star.star_group_update_publish(p, v, rows, us, send, norms_out=n, **opts(), **hp)
+        star.star_group_update(p, v, rows, one, **opts(), **hp)
+        star.star_group_reduce([out], rows, one, **opts())
+        star.star_group_gram(rows, gram, **opts())
+        torch.cuda.synchronize()
+        for whole, part, off in ((pw, p, shift(W)), (vw, v, shift(W + 1)), (sw, send, shift(W)), (ow, out, shift(W + 2))):
+            assert bool((whole[:off] == 7).all()) and bool((whole[off + P:] == 7).all())
+        return [x.double().cpu().numpy() for x in (p, v, send, out, n, gram)]
+
+    want = everything(lambda k: 0)
+    for shift in (lambda k: 1, lambda k: 7, lambda k: 32, lambda k: 63, lambda k: k % 5, lambda k: 3 * k):
+        got = everything(shift)
+        for a, b in zip(got[:4], want[:4]):
+            assert np.array_equal(a, b)
+        for a, b in zip(got[4:], want[4:]):
+            assert np.max(np.abs(a - b)) <= 1e-6 * np.max(np.abs(b))
 
 
 def test_two_threads_with_different_options():

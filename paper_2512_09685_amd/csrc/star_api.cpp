@@ -306,7 +306,8 @@ TableLayout table_layout(int U, int Wp) {
 
 size_t partial_doubles_needed(int Wp, int U, int grid_cap) {
     const size_t ng = (size_t)Wp * (Wp + 1) / 2;
-    const size_t useq = (size_t)std::min(U, std::max(star::seq_max_updates(Wp, true), star::reduce_max_updates(Wp, true)));
+    const size_t useq = (size_t)std::min(U, std::max(star::walk_max_updates(), std::max(star::seq_max_updates(Wp, true),
+                                                                                       star::reduce_max_updates(Wp, true))));
     // per-block partials of the larger of the two routes, plus the reduced Gram matrix
     return std::max(ng, useq) * (size_t)grid_cap + ng;
 }
@@ -433,10 +434,13 @@ Launch decide(const star::Plan& plan, int grad_dtype, bool update, bool want_nor
         l.launches = (update || gram) ? 1 : 0;
         l.finishing = gram ? 2 : 0;
     } else {
-        l.umax = star::seq_max_updates(l.Wp, want_norms);
+        // Norms alone have a kernel of their own, which takes up to 240 updates per pass over the rows (32 updates of 8
+        // rows, 25 M elements: one pass instead of two).  (A shard of a few thousand elements is one or two workgroups
+        // either way; there the stream is cut as that of the update, which keeps the launches star_plan_choice reports.)
+        l.umax = update || tiny ? star::seq_max_updates(l.Wp, want_norms) : star::walk_max_updates();
         l.seq_inline = star::tables_fit_inline(plan.U, l.Wp) && plan.U <= l.umax;
         l.launches = (plan.U + l.umax - 1) / l.umax;
-        l.queue_order = l.want_queue && (l.collapsed_in_seq || star::seq_takes_queue(std::min(plan.U, l.umax)));
+        l.queue_order = update && l.want_queue && (l.collapsed_in_seq || star::seq_takes_queue(std::min(plan.U, l.umax)));
         l.finishing = want_norms ? l.launches : 0;
     }
     return l;
@@ -680,7 +684,8 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
             a.publish_dtype = publish_dtype;
             a.partials = partials;
             a.queue = want_queue ? queue : nullptr;
-            e = star::launch_seq(Wp, grad_dtype, seq_update, want_norms, a, num_cu, grid_cap, &grid, stream);
+            e = seq_update ? star::launch_seq(Wp, grad_dtype, want_norms, a, num_cu, grid_cap, &grid, stream)
+                           : star::launch_norm_walk(Wp, grad_dtype, a, num_cu, grid_cap, &grid, stream);
             if (e != hipSuccess) return hip_fail(e, "launch of the step-by-step kernel");
             if (want_norms) {
                 e = star::launch_reduce(partials, n, grid, nullptr, norms_out + u0, stream);

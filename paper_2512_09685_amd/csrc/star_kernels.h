@@ -170,8 +170,14 @@ int seq_max_updates(int Wp, bool norms);
 
 // Step-by-step evaluation.  Returns the grid used in *grid_out (needed to
 // reduce the partials).  grid_cap bounds it.
-hipError_t launch_seq(int Wp, int dtype, bool update, bool norms, const SeqArgs& a, int num_cu, int grid_cap,
-                      int* grid_out, hipStream_t s);
+hipError_t launch_seq(int Wp, int dtype, bool norms, const SeqArgs& a, int num_cu, int grid_cap, int* grid_out,
+                      hipStream_t s);
+
+// Direct norm sums without an update (params, momentum, publish and the update's fields of `a` are not used),
+// up to walk_max_updates() updates a launch.
+int walk_max_updates();
+hipError_t launch_norm_walk(int Wp, int dtype, const SeqArgs& a, int num_cu, int grid_cap, int* grid_out,
+                            hipStream_t s);
 
 struct AffArgs {
     float* params;

@@ -18,7 +18,8 @@
 //               element held in registers; group tables sit in LDS.
 //   aff_kernel  applies the U updates as one affine map of (p, v, g_0..g_W-1)
 //               whose coefficients the host composed in double precision.
-// Per-group norms: seq_kernel accumulates gbar_u^2 per thread (LDS slots),
+// Per-group norms: seq_kernel accumulates gbar_u^2 per thread (LDS slots; direct norms
+// without an update have a kernel of their own, star_norm_kernels.hip),
 // aff_kernel accumulates the pairwise products of the rows (Gram matrix);
 // both end with a wave64 DPP reduction and write one partial per block.
 #include <hip/hip_runtime.h>
@@ -273,11 +274,11 @@ __device__ __forceinline__ void seq_steps(float (&g)[W][4], float (&p)[4], float
     }
 }
 
-// COLLAPSED (with UPDATE and NORMS): the norms are accumulated update by update as usual, the update itself is
+// COLLAPSED (with NORMS): the norms are accumulated update by update as usual, the update itself is
 // applied once, as the affine map `cf` of the whole stream.  For wide fp32 rows with norms and a short stream:
 // the Gram matrix of 17 to 32 fp32 rows costs 1536 matrix flops per element whatever the stream, the direct
 // sums y_u + 1 multiply-adds per update.
-template <int W, class R, bool UPDATE, bool NORMS, bool COLLAPSED = false>
+template <int W, class R, bool NORMS, bool COLLAPSED = false>
 __global__ __launch_bounds__(kBlock) void seq_kernel(float* __restrict__ params, float* __restrict__ momentum,
                                                      const RowPtrs rows, const float* __restrict__ t_coef,
                                                      const float* __restrict__ t_lr,
@@ -288,7 +289,7 @@ __global__ __launch_bounds__(kBlock) void seq_kernel(float* __restrict__ params,
                                                      double* __restrict__ partials, TileQueue* __restrict__ queue,
                                                      const int claim, const InlineTables inl, const AffCoef cf) {
     static_assert(R::VEC == 4, "the step-by-step kernel works on 4-element chunks");
-    static_assert(!COLLAPSED || (UPDATE && NORMS), "the collapsed update rides on the norm walk");
+    static_assert(!COLLAPSED || NORMS, "the collapsed update rides on the norm walk");
     extern __shared__ double lds[];
     double* s_nacc = lds;
     double* s_wave = s_nacc + (NORMS ? U * kBlock : 0);
@@ -319,15 +320,13 @@ __global__ __launch_bounds__(kBlock) void seq_kernel(float* __restrict__ params,
         typename R::vec raw[W];
 #pragma unroll
         for (int w = 0; w < W; ++w) raw[w] = R::load(rows.p[w], c);
-        float p[4] = {0, 0, 0, 0}, v[4] = {0, 0, 0, 0};
-        if constexpr (UPDATE) {
-            const f32x4 pv = load_state(params, c);
-            const f32x4 vv = load_state(momentum, c);
+        f32x4 pv = load_state(params, c);
+        f32x4 vv = load_state(momentum, c);
+        float p[4], v[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                p[k] = pv[k];
-                v[k] = vv[k];
-            }
+        for (int k = 0; k < 4; ++k) {
+            p[k] = pv[k];
+            v[k] = vv[k];
         }
         float g[W][4];
         static_for<0, W>([&](auto wc) {
@@ -347,19 +346,16 @@ __global__ __launch_bounds__(kBlock) void seq_kernel(float* __restrict__ params,
                 aff_step<W>(p[K], v[K], ge, cf);
             });
         } else {
-            seq_steps<W, UPDATE, NORMS>(g, p, v, s_coef, s_lr, s_mask, s_nacc, U, mu, wd);
+            seq_steps<W, true, NORMS>(g, p, v, s_coef, s_lr, s_mask, s_nacc, U, mu, wd);
         }
-        if constexpr (UPDATE) {
-            f32x4 pv, vv;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                pv[k] = p[k];
-                vv[k] = v[k];
-            }
-            store_state(pv, params, c);
-            store_state(vv, momentum, c);
-            if (publish) publish_chunk(pv, publish, publish_bf16, c);
+        for (int k = 0; k < 4; ++k) {
+            pv[k] = p[k];
+            vv[k] = v[k];
         }
+        store_state(pv, params, c);
+        store_state(vv, momentum, c);
+        if (publish) publish_chunk(pv, publish, publish_bf16, c);
     };
     if (claim > 0) {   // tiles from the queue
         const int64_t ntile = (nchunk + kBlock - 1) / kBlock;
@@ -381,11 +377,7 @@ __global__ __launch_bounds__(kBlock) void seq_kernel(float* __restrict__ params,
             g[w][0] = R::load1(rows.p[w], j);
             g[w][1] = g[w][2] = g[w][3] = 0.0f;
         }
-        float p[4] = {0, 0, 0, 0}, v[4] = {0, 0, 0, 0};
-        if constexpr (UPDATE) {
-            p[0] = params[j];
-            v[0] = momentum[j];
-        }
+        float p[4] = {params[j], 0, 0, 0}, v[4] = {momentum[j], 0, 0, 0};
         if constexpr (COLLAPSED) {
             seq_steps<W, false, true>(g, p, v, s_coef, s_lr, s_mask, s_nacc, U, mu, wd);
             float ge[W];
@@ -393,13 +385,11 @@ __global__ __launch_bounds__(kBlock) void seq_kernel(float* __restrict__ params,
             for (int w = 0; w < W; ++w) ge[w] = g[w][0];
             aff_step<W>(p[0], v[0], ge, cf);
         } else {
-            seq_steps<W, UPDATE, NORMS>(g, p, v, s_coef, s_lr, s_mask, s_nacc, U, mu, wd);
+            seq_steps<W, true, NORMS>(g, p, v, s_coef, s_lr, s_mask, s_nacc, U, mu, wd);
         }
-        if constexpr (UPDATE) {
-            params[j] = p[0];
-            momentum[j] = v[0];
-            if (publish) publish_element(p[0], publish, publish_bf16, j);
-        }
+        params[j] = p[0];
+        momentum[j] = v[0];
+        if (publish) publish_element(p[0], publish, publish_bf16, j);
     }
 
     if constexpr (NORMS) {
@@ -508,19 +498,19 @@ size_t seq_lds_bytes(int W, int U, bool norms) {
            (norms ? sizeof(double) * ((size_t)(kBlock / 64) * U + (size_t)U * kBlock) : 0);
 }
 
-template <int W, class R, bool UPDATE, bool NORMS, bool COLLAPSED = false>
+template <int W, class R, bool NORMS, bool COLLAPSED = false>
 hipError_t launch_seq_t(const SeqArgs& a, int num_cu, int grid_cap, int* grid_out, hipStream_t s) {
-    auto kern = seq_kernel<W, R, UPDATE, NORMS, COLLAPSED>;
+    auto kern = seq_kernel<W, R, NORMS, COLLAPSED>;
     const size_t lds = seq_lds_bytes(W, a.U, NORMS);
     // one or two updates are bound by memory and take their tiles from the queue; longer streams are bound
     // by arithmetic and latency and keep the fixed assignment with as many waves as fit
-    const int thread_bytes = W * (int)sizeof(typename R::vec) + (UPDATE ? 32 : 0);
+    const int thread_bytes = W * (int)sizeof(typename R::vec) + 32;
     // the collapsed form does so little arithmetic per update that it is bound by memory for any stream it is used for
     const bool queued = a.queue && (COLLAPSED || seq_takes_queue(a.U));
     // (the collapsed form's norm walk -- LDS reads and a wave-uniform branch per row and update -- needs a second
     // workgroup per unit to hide under the memory time: 20 to 32 fp32 rows, 8 updates, 0.68-0.71 of the HBM peak with
     // two against 0.43-0.45 with one)
-    const int per_cu = COLLAPSED ? 2 : queue_workgroups_per_cu(thread_bytes, UPDATE);
+    const int per_cu = COLLAPSED ? 2 : queue_workgroups_per_cu(thread_bytes, true);
     const Geometry g = queued ? queue_geometry(num_cu, grid_cap, per_cu, thread_bytes)
                               : pick_geometry(a.P, NORMS, num_cu, grid_cap, thread_bytes, 4,
                                               COLLAPSED ? 2 : 1);   // (short shards as well: 25-30 % faster with two)
@@ -582,23 +572,18 @@ hipError_t launch_aff_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_ou
 }
 
 template <int W>
-hipError_t launch_seq_w(int dtype, bool update, bool norms, const SeqArgs& a, int num_cu, int grid_cap,
-                        int* grid_out, hipStream_t s) {
+hipError_t launch_seq_w(int dtype, bool norms, const SeqArgs& a, int num_cu, int grid_cap, int* grid_out, hipStream_t s) {
     if (a.cf) {   // collapsed update with direct norms: built for wide fp32 rows only
         if constexpr (W > 16) {
-            if (dtype == STAR_F32 && update && norms)
-                return launch_seq_t<W, RowF32, true, true, true>(a, num_cu, grid_cap, grid_out, s);
+            if (dtype == STAR_F32 && norms) return launch_seq_t<W, RowF32, true, true>(a, num_cu, grid_cap, grid_out, s);
         }
         return hipErrorInvalidValue;
     }
-    if (dtype == STAR_F32) {
-        if (update && norms) return launch_seq_t<W, RowF32, true, true>(a, num_cu, grid_cap, grid_out, s);
-        if (update) return launch_seq_t<W, RowF32, true, false>(a, num_cu, grid_cap, grid_out, s);
-        return launch_seq_t<W, RowF32, false, true>(a, num_cu, grid_cap, grid_out, s);
-    }
-    if (update && norms) return launch_seq_t<W, RowBf16x4, true, true>(a, num_cu, grid_cap, grid_out, s);
-    if (update) return launch_seq_t<W, RowBf16x4, true, false>(a, num_cu, grid_cap, grid_out, s);
-    return launch_seq_t<W, RowBf16x4, false, true>(a, num_cu, grid_cap, grid_out, s);
+    if (dtype == STAR_F32)
+        return norms ? launch_seq_t<W, RowF32, true>(a, num_cu, grid_cap, grid_out, s)
+                     : launch_seq_t<W, RowF32, false>(a, num_cu, grid_cap, grid_out, s);
+    return norms ? launch_seq_t<W, RowBf16x4, true>(a, num_cu, grid_cap, grid_out, s)
+                 : launch_seq_t<W, RowBf16x4, false>(a, num_cu, grid_cap, grid_out, s);
 }
 
 template <int W>
@@ -629,12 +614,11 @@ int seq_max_updates(int Wp, bool norms) {
     return u;
 }
 
-hipError_t launch_seq(int Wp, int dtype, bool update, bool norms, const SeqArgs& a, int num_cu, int grid_cap,
-                      int* grid_out, hipStream_t s) {
-    if (!update && !norms) return hipErrorInvalidValue;
+hipError_t launch_seq(int Wp, int dtype, bool norms, const SeqArgs& a, int num_cu, int grid_cap, int* grid_out,
+                      hipStream_t s) {
     if (a.U < 1 || a.U > seq_max_updates(Wp, norms)) return hipErrorInvalidValue;
     switch (Wp) {
-#define X(N) case N: return launch_seq_w<N>(dtype, update, norms, a, num_cu, grid_cap, grid_out, s);
+#define X(N) case N: return launch_seq_w<N>(dtype, norms, a, num_cu, grid_cap, grid_out, s);
         STAR_FOR_EACH_W(X)
 #undef X
         default: return hipErrorInvalidValue;

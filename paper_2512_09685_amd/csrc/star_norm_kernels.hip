@@ -1,0 +1,198 @@
+// gfx950 kernel: per-group norms from direct sums of gbar_u^2, no update.
+//
+// The caller asked for direct sums (rows that may be anti-correlated), the coefficients have both signs, or the shard
+// is very short; see decide() in star_api.cpp.  The arithmetic is y_u + 1 multiply-adds per element and update,
+// and with more than a few updates that is what bounds the pass: 8 fp32 rows, 32 updates of 4.5 members on average,
+// 25.6 M elements need 4.5 G fp32 multiply-adds (0.12 ms of the vector ALUs) and 0.82 GB (0.12 ms).
+//   - A thread holds 16 or 8 elements of every row, so that one member test (a scalar branch) covers as many
+//     multiply-adds, and so does the sum kept per update.
+//   - Coefficients and member masks are read with scalar loads, one wait per update.
+//   - The squares of a thread's elements are added over eight lanes, then in double into one LDS slot per eight lanes
+//     and update: 256 bytes per update, so up to 240 updates need one pass over the rows, and several workgroups
+//     fit on a compute unit to hide the loads.
+// Measured at that size: 193 us, 614 with the step-by-step kernel this replaces (one LDS slot per thread and update, hence
+// two passes for 32 updates and two waves per SIMD; coefficients from LDS at their use; 4 elements per thread).
+#include "star_device.h"
+
+namespace star {
+
+struct WalkKernelArgs {
+    RowPtrs rows;
+    const float* coef;      // [U][W], or null: the tables are in `inl`
+    const uint32_t* mask;   // [U]
+    double* partials;
+    int64_t P;
+    int32_t U, head;
+    InlineTables inl;
+};
+
+// Constant address space: uniform reads become scalar loads.  The tables are written before the launch and not during it.
+#define STAR_CONST __attribute__((address_space(4)))
+
+// Chunks of 4 elements a thread holds of every row.  Two also with 17 to 32 rows, although only two waves (32 rows: one)
+// then fit on a SIMD: a member test for 4 multiply-adds costs more than the third wave brings (20 rows, 5 M elements,
+// 128 updates 417 against 921 us; 32 rows, 25.6 M elements, 16 updates 754 against 879).
+constexpr int walk_chunks(int W) { return W <= 4 ? 4 : 2; }
+
+// LDS: slots[U][kSlots], double
+constexpr int kSlots = kBlock / 8;
+template <int W, class R>
+__global__ __launch_bounds__(kBlock) void norm_walk_kernel(const WalkKernelArgs args) {
+    constexpr int KCH = walk_chunks(W), E = 4 * KCH;
+    extern __shared__ double walk_lds[];
+    const auto* const in = (const STAR_CONST WalkKernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    const int U = args.U;
+    const STAR_CONST float* coef = (const STAR_CONST float*)args.coef;
+    const STAR_CONST uint32_t* mask = (const STAR_CONST uint32_t*)args.mask;
+    if (!args.coef) {
+        coef = in->inl.coef;
+        mask = in->inl.mask;
+    }
+    double* const s_slot = walk_lds;
+    for (int i = threadIdx.x; i < U * kSlots; i += kBlock) s_slot[i] = 0.0;
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double* const my_slot = s_slot + threadIdx.x / 8;   // private to the eight lanes: no other lane adds to it
+    const bool first_of_eight = (lane & 7) == 0;
+
+    auto walk = [&](const float (&g)[E][W]) {
+        for (int u = 0; u < U; ++u) {
+            const uint32_t m = mask[u];
+            float c[W];
+#pragma unroll
+            for (int w = 0; w < W; ++w) c[w] = coef[u * W + w];
+            // all of them requested here, one wait (the loads would otherwise move to their uses, one wait a member)
+#pragma unroll
+            for (int w = 0; w < W; ++w) asm volatile("" ::"s"(c[w]));
+            float gb[E];
+#pragma unroll
+            for (int k = 0; k < E; ++k) gb[k] = 0.0f;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {   // ascending worker id; the test is uniform over the wave
+                if (__builtin_expect((m >> w) & 1u, 1)) {
+#pragma unroll
+                    for (int k = 0; k < E; ++k) gb[k] = __builtin_fmaf(c[w], g[k][w], gb[k]);
+                }
+            }
+            float s[KCH];
+#pragma unroll
+            for (int j = 0; j < KCH; ++j) {   // four squares a chain, the chains added pairwise
+                s[j] = 0.0f;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) s[j] = __builtin_fmaf(gb[4 * j + k], gb[4 * j + k], s[j]);
+            }
+#pragma unroll
+            for (int d = 1; d < KCH; d *= 2)
+#pragma unroll
+                for (int j = 0; j + d < KCH; j += 2 * d) s[j] += s[j + d];
+            float q = s[0];
+            q += dpp_take<0xB1, 0xf>(q);   // quad_perm [1,0,3,2]
+            q += dpp_take<0x4E, 0xf>(q);   // quad_perm [2,3,0,1]
+            q += dpp_take<0x141, 0xf>(q);  // row_half_mirror
+            if (first_of_eight)
+                __hip_atomic_fetch_add(my_slot + u * kSlots, (double)q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    };
+
+    const int64_t P = args.P, nchunk = P / 4;
+    const int64_t width = (int64_t)kBlock * KCH, ntile = (nchunk + width - 1) / width;
+    auto process = [&](const int64_t tile) {
+        const int64_t c0 = tile * width + threadIdx.x;
+        if (c0 - lane >= nchunk) return;   // the whole wave is beyond the end
+        typename R::vec raw[KCH][W];
+        const bool whole = (tile + 1) * width <= nchunk;
+        // the row pointers are fetched again for every tile: kept, they would push the walk's coefficients out of the
+        // scalar registers with 20 and more rows
+        const STAR_CONST WalkKernelArgs* a = in;
+        asm volatile("" : "+s"(a));
+#pragma unroll
+        for (int j = 0; j < KCH; ++j) {
+            const int64_t c = c0 + (int64_t)j * kBlock;
+            if (whole) {
+#pragma unroll
+                for (int w = 0; w < W; ++w) raw[j][w] = R::load(a->rows.p[w], c);
+            } else {   // the last tile: elements beyond the end hold zeros
+#pragma unroll
+                for (int w = 0; w < W; ++w) raw[j][w] = c < nchunk ? R::load(a->rows.p[w], c) : typename R::vec{};
+            }
+        }
+        float g[E][W];
+        static_for<0, KCH>([&](auto jc) {
+            constexpr int J = decltype(jc)::value;
+            static_for<0, W>([&](auto wc) {
+                constexpr int Wi = decltype(wc)::value;
+                static_for<0, 4>([&](auto kc) {
+                    constexpr int K = decltype(kc)::value;
+                    g[4 * J + K][Wi] = R::template get<K>(raw[J][Wi]);
+                });
+            });
+        });
+        walk(g);
+    };
+    for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) process(tile);
+    const int64_t nrest = rest_count(args.head, P, nchunk);   // at most 66 elements: the first workgroup's
+    if (blockIdx.x == 0 && threadIdx.x - lane < nrest) {
+        float g[E][W];
+#pragma unroll
+        for (int k = 0; k < E; ++k)
+#pragma unroll
+            for (int w = 0; w < W; ++w) g[k][w] = 0.0f;
+        if (threadIdx.x < nrest) {
+            const int64_t j = rest_element(threadIdx.x, args.head, nchunk);
+#pragma unroll
+            for (int w = 0; w < W; ++w) g[0][w] = R::load1(args.rows.p[w], j);
+        }
+        walk(g);
+    }
+    __syncthreads();
+    for (int u = wave; u < U; u += kBlock / 64) {   // one wave per update
+        const double s = wave_sum_to_lane63(lane < kSlots ? s_slot[u * kSlots + lane] : 0.0);
+        if (lane == 63) args.partials[(int64_t)u * gridDim.x + blockIdx.x] = s;
+    }
+}
+
+namespace {
+
+size_t walk_lds_bytes(int U) { return sizeof(double) * (size_t)U * kSlots; }
+
+template <int W, class R>
+hipError_t launch_walk_t(const SeqArgs& a, int num_cu, int grid_cap, int* grid_out, hipStream_t s) {
+    // Four long-lived workgroups per unit sweep the shard together, for every stream: the work queue is behind even where
+    // one or two updates leave the pass bound by memory (1 fp32 row, 25.6 M elements, 1 update: 22 against 39 us;
+    // 16 rows, 2 updates: 232 against 252; 4 rows, 100 M elements: 241 against 246).
+    const int64_t width = (int64_t)kBlock * walk_chunks(W);
+    const int64_t tiles = std::max<int64_t>(1, (a.P / 4 + width - 1) / width);
+    const int grid = (int)std::min<int64_t>(tiles, std::min(4 * num_cu, grid_cap));
+    *grid_out = grid;
+    WalkKernelArgs k;
+    k.rows = a.rows;
+    k.coef = a.coef;
+    k.mask = a.mask;
+    k.partials = a.partials;
+    k.P = a.P;
+    k.U = a.U;
+    k.head = a.head;
+    k.inl = a.coef ? InlineTables() : *a.inl;
+    hipLaunchKernelGGL((norm_walk_kernel<W, R>), dim3(grid), dim3(kBlock), walk_lds_bytes(a.U), s, k);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+int walk_max_updates() { return 60 * 1024 / (int)walk_lds_bytes(1); }   // stay inside 64 KB of LDS per workgroup
+
+hipError_t launch_norm_walk(int Wp, int dtype, const SeqArgs& a, int num_cu, int grid_cap, int* grid_out,
+                            hipStream_t s) {
+    if (a.U < 1 || a.U > walk_max_updates()) return hipErrorInvalidValue;
+    switch (Wp) {
+#define X(N)                                                                                      \
+    case N:                                                                                       \
+        return dtype == STAR_F32 ? launch_walk_t<N, RowF32>(a, num_cu, grid_cap, grid_out, s)     \
+                                 : launch_walk_t<N, RowBf16x4>(a, num_cu, grid_cap, grid_out, s);
+        STAR_FOR_EACH_W(X)
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace star

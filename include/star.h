@@ -103,8 +103,8 @@ typedef enum {
 typedef enum {
     STAR_KERNEL_AUTO = 0,  /* the library chooses (star_plan_choice tells what): a single update on fp32
                               rows SEQ, and with norms any stream of up to 48 multiply-adds per element
-                              on a short shard (4 Mi elements, bf16 rows 16 Mi; 17 to 32 fp32 rows: 112,
-                              any length); otherwise the collapsed map; with norms the Gram matrix on the
+                              on a short shard (4 Mi elements, bf16 rows 16 Mi; 17 to 32 fp32 rows: 112
+                              and at most 3 updates, any length); otherwise the collapsed map; with norms the Gram matrix on the
                               matrix cores (vector registers instead: up to 6 rows, and 7 or 8 rows below
                               16 Mi elements; but 3 to 8 bf16 rows up to 8 Mi elements, and most shards of 4 to
                               6 bf16 rows below 48 Mi: matrix cores),
@@ -303,7 +303,8 @@ typedef struct {
                                    (the collapsed map without norms needs no tables at all and reports 1)   */
     int32_t collapsed_update;   /* 1: params and momentum come from the one affine map of the stream.  Always so
                                    with AFFINE and AFFINE_MFMA; with SEQ only for 17 to 32 fp32 rows, update
-                                   with norms and a short stream (direct norm sums of at most 4 W + 48
+                                   with norms and a short stream (direct norm sums of at most 4 W + 48, with
+                                   17 to 24 rows 4 W + 30,
                                    multiply-adds per element), where the step-by-step kernel walks the updates
                                    for the norms alone (direct sums are cheaper there than the Gram matrix)   */
     int32_t reserved;

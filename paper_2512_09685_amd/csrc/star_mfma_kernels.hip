@@ -29,7 +29,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // Matrix tiles.  "Row" is a gradient row (a worker), "slot" a group of lanes that feeds one part of
 // the reduction dimension; lane l feeds row l % N and slot l / N.
 //   fp32 rows, N=16: v_mfma_f32_16x16x4_f32,   1 element per lane, 4 slots
-//   fp32 rows, N=32: three 16x16 blocks by v_mfma_f32_16x16x4_f32 with A and B from the two halves of
+//   fp32 rows, 17 to 24: pairs of row groups of four by v_mfma_f32_4x4x1_16b_f32 (see kQuads in the kernel);
+//   fp32 rows, 25 to 32: three 16x16 blocks by v_mfma_f32_16x16x4_f32 with A and B from the two halves of
 //                    the rows (see kBlocks in the kernel); the 32x32x2 instruction is not used
 //   bf16 rows, N=16: v_mfma_f32_16x16x32_bf16, 8 elements per lane, 4 slots
 //   bf16 rows, N=32: v_mfma_f32_32x32x16_bf16, 8 elements per lane, 2 slots
@@ -68,10 +69,23 @@ struct GramTile<true> {
     static __device__ __forceinline__ int reg_of(int i) { return 4 * (i / 8) + (i % 4); }
 };
 
+// Rows of SPAN lanes: the odd rows of x change places with the even rows of y, then the two are added.  Even rows of the
+// result hold x's row plus its odd neighbour, odd rows the same of y.
+template <int SPAN>
+__device__ __forceinline__ float swap_add(const float x, const float y) {
+    const auto s = SPAN == 32 ? __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false)
+                              : __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
 // One row of the LDS panel holds 512 bytes of elements (128 fp32 or 256 bf16) and 16 bytes of
 // padding: 16 lanes that read 16 bytes each from 16 consecutive rows at the same offset then
 // touch every bank exactly once.
 constexpr int kPanelRowBytes = 512 + 16;
+// Row groups of four (kQuads): 16 lanes read 16 bytes each from 4 consecutive rows, 4 neighbouring places of each.
+constexpr int kQuadRowBytes = 512 + 64;
+// Which launches form the matrix from row groups of four, see the kernel.
+constexpr bool quad_groups(bool bf16_rows, int W) { return !bf16_rows && W > 16 && W <= 24; }
 
 template <int W, class R, bool UPDATE, bool WIDE>
 __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__ params, float* __restrict__ momentum,
@@ -88,14 +102,31 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
     static_assert(W <= N, "more rows than the matrix tile holds");
     constexpr int NG = W * (W + 1) / 2;
     constexpr int kWaves = kBlock / 64;
-    constexpr int kPanelBytes = N * kPanelRowBytes;
+    // 17 to 24 fp32 rows: the matrix is formed group by group, four rows with four rows, for the K (K + 1) / 2 distinct
+    // pairs of the K = W / 4 groups, by the instruction that multiplies 16 independent 4x4 blocks (here: 16 elements).
+    // That is 480 flops per element for 20 rows and 672 for 24, where the three 16x16 blocks below take 1536 for any
+    // count, at three quarters of their rate (measured: 11 to 13 cycles for 512 flops against 34 for 2048).  25.6 M
+    // elements, 20 / 24 rows: norms alone 319 / 396 us, 399 / 447 by blocks, update with norms 470 / 542 against 532 / 574.
+    // 28 and 32 rows need 28 and 36 pairs, whose accumulators allow one wave per SIMD only: 686 / 825 us against
+    // 651 / 722 by blocks.  (One wave per SIMD with a tile of look-ahead was tried for 24 rows as well: 573.)
+    // Four accumulator registers a pair leave no room for sums in double beside them; those are kept in LDS, one
+    // per lane and pair, shared by the four waves.
+    constexpr bool kQuads = quad_groups(BF, W);
+    constexpr int kRowStride = kQuads ? kQuadRowBytes : kPanelRowBytes;
+    constexpr int kGroups = W / 4, kPairs = kQuads ? kGroups * (kGroups + 1) / 2 : 1;
+    constexpr int kPanelBytes = (kQuads ? W : N) * kRowStride;
     static_assert(kPanelBytes >= 64 * 16 * 8, "the panel doubles as the reduction buffer");
     __shared__ __align__(16) unsigned char panel[kWaves][kPanelBytes];
+    __shared__ double sums[kQuads ? kPairs * 64 : 1];
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     unsigned char* const T = panel[wave];
-    // rows W..N-1 of the panel are zero and never written again
-    for (int w = W; w < N; ++w) *reinterpret_cast<u32x2*>(T + w * kPanelRowBytes + 8 * lane) = u32x2{0u, 0u};
+    if constexpr (kQuads) {
+        for (int i = threadIdx.x; i < kPairs * 64; i += kBlock) sums[i] = 0.0;
+        __syncthreads();
+    } else {   // rows W..N-1 of the panel are zero and never written again
+        for (int w = W; w < N; ++w) *reinterpret_cast<u32x2*>(T + w * kRowStride + 8 * lane) = u32x2{0u, 0u};
+    }
 
     // two accumulator sets used alternately, so that consecutive matrix instructions do not wait for
     // each other's result; acc2 is the second-level sum, in double (see fold)
@@ -108,12 +139,16 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
         acc2[r] = 0.0;
     }
     const unsigned char* const my_row = T + (lane % N) * kPanelRowBytes + 16 * (lane / N);
-    // 17-32 fp32 rows: the 32x32 matrix is formed from its three distinct 16x16 blocks (rows 0-15 with
+    f32x4 quad[kPairs];   // D[r][j] of pair (a, b), block n: register r of lane 4 n + j = row 4 a + r with row 4 b + j
+    static_for<0, kPairs>([&](auto ec) { quad[decltype(ec)::value] = f32x4{0.0f, 0.0f, 0.0f, 0.0f}; });
+    const unsigned char* const my_quad = T + (lane % 4) * kRowStride + 16 * (lane / 4);
+
+    // 25-32 fp32 rows: the 32x32 matrix is formed from its three distinct 16x16 blocks (rows 0-15 with
     // themselves, rows 0-15 with rows 16-31, rows 16-31 with themselves) by the 16x16x4 instruction with
     // A and B from the two halves -- three quarters of the matrix work of the 32x32x2 instruction, which
     // computes the mirrored block too and is what bounds this variant.  blk[0..2] / blkb[0..2] are the
     // alternating accumulator sets of the three blocks, blk2 their sums in double.
-    constexpr bool kBlocks = WIDE && !BF;
+    constexpr bool kBlocks = WIDE && !BF && !kQuads;
     f32x4 blk[3], blkb[3];
     double blk2[12];
 #pragma unroll
@@ -129,10 +164,32 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
     // stage: 512 bytes per row (8 per lane) into the panel; consume: feed them to the matrix cores.
     auto stage = [&](const u32x2 (&x)[W]) {
 #pragma unroll
-        for (int w = 0; w < W; ++w) *reinterpret_cast<u32x2*>(T + w * kPanelRowBytes + 8 * lane) = x[w];
+        for (int w = 0; w < W; ++w) *reinterpret_cast<u32x2*>(T + w * kRowStride + 8 * lane) = x[w];
     };
     auto consume = [&]() {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the panel is written before any lane reads it
+        if constexpr (kQuads) {
+#pragma unroll
+            for (int m = 0; m < 512 / 256; ++m) {   // 64 elements of every row: 4 per lane, 16 lanes to a row
+                f32x4 y[kGroups];
+#pragma unroll
+                for (int a = 0; a < kGroups; ++a)
+                    y[a] = *reinterpret_cast<const f32x4*>(my_quad + 4 * a * kRowStride + 256 * m);
+                static_for<0, 4>([&](auto jc) {
+                    constexpr int J = decltype(jc)::value;
+                    static_for<0, kGroups>([&](auto ac) {
+                        constexpr int A = decltype(ac)::value;
+                        static_for<A, kGroups>([&](auto bc) {
+                            constexpr int B = decltype(bc)::value;
+                            constexpr int e = A * kGroups - A * (A - 1) / 2 + (B - A);
+                            quad[e] = __builtin_amdgcn_mfma_f32_4x4x1f32(y[A][J], y[B][J], quad[e], 0, 0, 0);
+                        });
+                    });
+                });
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            return;
+        }
         if constexpr (kBlocks) {
 #pragma unroll
             for (int m = 0; m < 512 / 64; ++m) {   // 4 slots of 16 bytes per row and step
@@ -168,8 +225,11 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // all reads returned before the panel is overwritten
     };
     auto gram_512 = [&](const u32x2 (&x)[W]) {
+        // (kept apart from the update and from each other: mixed, they spill with 24 rows, 578 against 542 us)
+        if constexpr (kQuads) __builtin_amdgcn_sched_barrier(0);
         stage(x);
         consume();
+        if constexpr (kQuads) __builtin_amdgcn_sched_barrier(0);
     };
     // The Gram contribution of one tile: 4 elements per lane and row.
     auto gram_tile = [&](const vec_t (&g)[W]) {
@@ -193,6 +253,19 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
     // far below the fp32 the norms are returned in, so that they come out the same every run.
     // The fold is 4 or 16 additions per lane.
     auto fold = [&]() {
+        if constexpr (kQuads) {
+            // the 16 blocks of a pair's 4 registers are added four at a time by swapping halves and quarters of the wave
+            // between registers: row rho of 16 lanes ends with register (0, 2, 1, 3)[rho], 4 blocks of it left.  (One
+            // addition in LDS per register instead: 2-3 % slower, and four times the LDS.)
+            static_for<0, kPairs>([&](auto ec) {
+                constexpr int e = decltype(ec)::value;
+                const float x = swap_add<32>(quad[e][0], quad[e][1]), y = swap_add<32>(quad[e][2], quad[e][3]);
+                __hip_atomic_fetch_add(&sums[e * 64 + lane], (double)swap_add<16>(x, y), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                quad[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            });
+            return;
+        }
         if constexpr (kBlocks) {
 #pragma unroll
             for (int b = 0; b < 3; ++b)
@@ -318,14 +391,14 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
     }
 
     // workgroup total of every Gamma entry, in double, one partial per workgroup; each wave's
-    // accumulators go through its own (now idle) panel
+    // accumulators go through its own (now idle) panel (kQuads: they are in `sums` already)
     double* const red = reinterpret_cast<double*>(T);
     if constexpr (kBlocks) {
 #pragma unroll
         for (int b = 0; b < 3; ++b)
 #pragma unroll
             for (int r = 0; r < 4; ++r) red[lane * 12 + 4 * b + r] = (double)(blk[b][r] + blkb[b][r]) + blk2[4 * b + r];
-    } else {
+    } else if constexpr (!kQuads) {
 #pragma unroll
         for (int r = 0; r < GT::REGS; ++r) red[lane * GT::REGS + r] = (double)(acc[r] + accb[r]) + acc2[r];
     }
@@ -337,19 +410,27 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
             ++i;
         }
         const int j = i + rem;
-        int src;
-        if constexpr (kBlocks) {
-            // entry (i, j), i <= j, lies in block 0 (both below 16), 1 (i below, j from 16 on) or 2; inside a
-            // block, D[a][b] is register a % 4 of lane 16 * (a / 4) + b
-            const int b = (i >= 16) ? 2 : (j >= 16 ? 1 : 0);
-            const int a = i & 15, c = j & 15;
-            src = (16 * (a / 4) + c) * 12 + 4 * b + (a % 4);
-        } else {
-            src = GT::lane_of(i, j) * GT::REGS + GT::reg_of(i);
-        }
         double s = 0.0;
+        if constexpr (kQuads) {
+            const int a = i / 4, b = j / 4;
+            const int r = i % 4, rho = 2 * (r & 1) + r / 2;
+            const double* src = sums + (a * kGroups - a * (a - 1) / 2 + (b - a)) * 64 + 16 * rho + j % 4;
 #pragma unroll
-        for (int q = 0; q < kWaves; ++q) s += reinterpret_cast<const double*>(panel[q])[src];
+            for (int n = 0; n < 4; ++n) s += src[4 * n];
+        } else {
+            int src;
+            if constexpr (kBlocks) {
+                // entry (i, j), i <= j, lies in block 0 (both below 16), 1 (i below, j from 16 on) or 2; inside a
+                // block, D[a][b] is register a % 4 of lane 16 * (a / 4) + b
+                const int b = (i >= 16) ? 2 : (j >= 16 ? 1 : 0);
+                const int a = i & 15, c = j & 15;
+                src = (16 * (a / 4) + c) * 12 + 4 * b + (a % 4);
+            } else {
+                src = GT::lane_of(i, j) * GT::REGS + GT::reg_of(i);
+            }
+#pragma unroll
+            for (int q = 0; q < kWaves; ++q) s += reinterpret_cast<const double*>(panel[q])[src];
+        }
         partials[(int64_t)e * gridDim.x + blockIdx.x] = s;
     }
 }

@@ -403,7 +403,10 @@ Launch decide(const star::Plan& plan, int grad_dtype, bool update, bool want_nor
     // 46, 69 against 80 us; from 16 Mi on the collapsed kernel is level or ahead, at 64 Mi by up to 40 %).  With 17
     // to 32 fp32 rows the alternative is dearer -- the matrix cores' fp32 Gram matrix, or the collapsed update
     // with the norm walk -- and the literal kernel stays ahead at every length up to about 110 multiply-adds
-    // (3 updates of 32 rows, 16 / 64 Mi elements: 438 / 1752 against 446 / 1953 us; 4 updates: 515 against 441).
+    // (3 updates of 32 rows, 16 / 64 Mi elements: 438 / 1752 against 446 / 1953 us; 4 updates: 515 against 441) -- and up
+    // to 3 updates: what an update costs besides its members makes longer streams of small groups dearer than their
+    // multiply-adds say (20 rows, 25.6 M elements, 4 / 6 / 8 updates of 10 on average: 477 / 605 / 733 us, the collapsed
+    // update with the norm walk 434 / 428 / 425; 1 Mi elements, 8 updates: 45 against 30).
     // (Its norms are direct sums, so streams that were given a direct norm pass above are served as well.)
     if (update && want_norms && l.route == star::Route::Affine && opt.kernel == STAR_KERNEL_AUTO &&
         plan.U <= star::seq_max_updates(l.Wp, true)) {
@@ -411,7 +414,7 @@ Launch decide(const star::Plan& plan, int grad_dtype, bool update, bool want_nor
         // (bf16 rows: up to 16 Mi elements -- there the literal kernel is still 4-12 % ahead with 2, 8 and 32 rows
         // and level with 16; fp32 rows are level or 4 % behind at 16 Mi)
         const int64_t short_shard = grad_dtype == STAR_BF16 ? (16 << 20) : (4 << 20);
-        if ((P <= short_shard && plan.fma_seq <= 48.0) || (wide_f32 && plan.fma_seq <= 112.0)) {
+        if ((P <= short_shard && plan.fma_seq <= 48.0) || (wide_f32 && plan.U <= 3 && plan.fma_seq <= 112.0)) {
             l.route = star::Route::Seq;
             l.split_norms = false;
         }

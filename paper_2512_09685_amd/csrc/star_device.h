@@ -340,6 +340,21 @@ inline Geometry pick_geometry(int64_t P, bool reduces, int num_cu, int grid_cap,
     return g;
 }
 
+// Long-lived workgroups per compute unit of the vector-register Gram kernel in fixed assignment.  One keeps enough in
+// flight from about 96 bytes per thread and chunk on; lighter rows want more, without the state to write back
+// up to four (norms alone, 16 M elements, 2 / 3 / 4 fp32 and 2 bf16 rows: 30 / 40 / 51 / 24 us, 45 / 51 / 58 / 44 with one; update with norms, 8 /
+// 16 / 30 M elements, 1 fp32 row: 35 / 59 / 106 us, 40 / 68 / 118 with one; 2 bf16 rows: 36 / 61 against 44 / 72), heavier
+// ones lose by it (16 M, 4 / 6 fp32 rows: 102 / 131 against 93 / 114).  On a shard of a few tiles per unit a second
+// workgroup halves the longest chain of tiles (3 M elements, 4 / 6 fp32 rows: 25.8 / 32.3 against 28.7 / 34.2; 1 M, 8 rows: 22.3
+// against 23.8, but at 3 M, 8 rows: 39.2 against 38.3).
+// (Two chunks requested together by a thread instead: level on one row, 8-12 % behind on 3 and 4 fp32 rows.)
+inline int sum_workgroups_per_cu(int thread_bytes, bool update, int64_t P, int num_cu) {
+    const int64_t tiles = P / (4 * kBlock);
+    const bool few_tiles = tiles <= 4 * (int64_t)num_cu || (thread_bytes <= 128 && tiles <= 12 * (int64_t)num_cu);
+    const int light = update ? (thread_bytes <= 48 ? 2 : 1) : std::max(1, std::min(4, 128 / thread_bytes));
+    return std::max(light, few_tiles ? 2 : 1);
+}
+
 // Geometry of a launch that takes its tiles from a queue: `per_cu` long-lived workgroups per compute unit.
 // Measured on MI355X, fewer waves in flight are faster as long as they keep enough bytes in flight: kernels
 // that read-modify-write the state want one workgroup per unit from about 128 bytes per thread and tile

@@ -546,7 +546,8 @@ hipError_t launch_aff_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_ou
     const int thread_bytes = W * (int)sizeof(typename R::vec) + (UPDATE ? 32 : 0);
     Geometry g = queued ? queue_geometry(num_cu, grid_cap, queue_workgroups_per_cu(thread_bytes, UPDATE), thread_bytes,
                                          UPDATE ? Traffic::Update : Traffic::ReadOnly)
-                        : pick_geometry(a.P, GRAM, num_cu, grid_cap);
+                        : pick_geometry(a.P, GRAM, num_cu, grid_cap, 256, 1,
+                                        sum_workgroups_per_cu(thread_bytes, UPDATE, a.P, num_cu));
     // 24 and more bf16 rows: twice as many workgroups of half the size (tiles of 1 KB per row) measured
     // 3-4 % faster (32 rows, 138 M elements: 1.92 against 1.98 ms); with 16 rows the same is 15 % slower,
     // and fp32 rows do not care.  With these half-size tiles claims of 4 (4 KB of every row, 8 KB of the

@@ -619,6 +619,7 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
             a.params = params;
             a.momentum = momentum;
             a.rows = rows;
+            a.rows_used = Wc;
             std::memset(&a.cf, 0, sizeof a.cf);
             if (update) {
                 a.cf.dp = (float)(plan.M[0] - 1.0);
@@ -837,6 +838,7 @@ star_status run_gram(const void* const* grad_rows, int grad_dtype, int64_t P, in
     if (st != STAR_OK) return st;
     SlotRelease release{slot, stream};
     a.P = P;
+    a.rows_used = W;
     a.partials = slot->partials;
     int grid = 0;
     const int Wp = star::padded_rows(W);   // rows beyond W repeat the last one; their entries are not copied out

@@ -186,6 +186,7 @@ struct AffArgs {
     float* momentum;
     RowPtrs rows;
     AffCoef cf;
+    int32_t rows_used;      // distinct rows (the rest of the padded count repeats the last one)
     int64_t P;
     int32_t head;           // elements before the pointers and P (0 to 63), see rest_element
     void* publish;          // device copy of the new params (P elements), or null

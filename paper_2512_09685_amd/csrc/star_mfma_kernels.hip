@@ -446,12 +446,25 @@ hipError_t launch_mfma_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_o
     // 1.56 ms on the 110 M shard; 8 rows no difference; the norms alone, a pure read, run 1.13 against
     // 1.24 ms with two).  The LDS panels (33 KB narrow, 66 KB
     // wide per workgroup) allow both.
+    // 20 to 32 bf16 rows, update: one as well from the length on at which the two would take claims (8 / 30 / 120 M elements,
+    // 20 rows: 94 / 299 / 1133 against 101 / 308 / 1164 us, 32 rows: 136 / 448 / 1705 against 145 / 461 / 1757; but 3 M,
+    // 32 rows: 69 against 65, and 17 rows, whose padding costs no traffic, 30 M: 284 against 278).
     constexpr int kRowBytes = W * (int)sizeof(typename R::vec);
-    const int per_cu = (UPDATE && !WIDE && kRowBytes >= 160) ? 1 : 2;
+    constexpr bool kBf16 = std::is_same<R, RowBf16x4>::value;
+    const int64_t tiles = (a.P / 4 + kBlock - 1) / kBlock;
+    const bool one_wide = UPDATE && WIDE && kBf16 && a.rows_used >= 20 &&
+                          tiles > 2 * (int64_t)num_cu * short_tiles_per_workgroup(kRowBytes + 32, Traffic::Update);
+    const int per_cu = (UPDATE && !WIDE && kRowBytes >= 160) || one_wide ? 1 : 2;
     if (!a.queue) return hipErrorInvalidValue;
-    const Geometry g = queue_geometry(num_cu, grid_cap, per_cu, kRowBytes + (UPDATE ? 32 : 0),
-                                      UPDATE ? Traffic::Update : Traffic::ReadOnly,
-                                      (a.P / 4 + kBlock - 1) / kBlock);
+    Geometry g = queue_geometry(num_cu, grid_cap, per_cu, kRowBytes + (UPDATE ? 32 : 0),
+                                UPDATE ? Traffic::Update : Traffic::ReadOnly, tiles);
+    // The norms of 17 to 32 bf16 rows: one workgroup per unit, whose look-ahead keeps 64 KB in flight, and the tiles split
+    // evenly up to 256 a workgroup (3 / 30 / 60 M elements, 24 rows: 36.8 / 224 / 426 against 38.8 / 232 / 438 us, 32 rows:
+    // 46 / 294 / 566 against 48 / 302 / 575; 120 M, 32 rows: 1127 against 1119).
+    if (!UPDATE && WIDE && kBf16 && tiles <= 256 * (int64_t)num_cu) {
+        g.claim = -1;
+        g.grid = g.span_g = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(num_cu, grid_cap), tiles));
+    }
     *grid_out = g.grid;
     hipLaunchKernelGGL(kern, dim3(g.grid), dim3(kBlock), 0, s, a.params, a.momentum, a.rows, a.cf, a.P, a.head,
                        g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue,

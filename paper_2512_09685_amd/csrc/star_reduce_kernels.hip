@@ -142,6 +142,29 @@ size_t reduce_lds_bytes(int W, int U, bool norms) {
            (norms ? sizeof(double) * ((size_t)(kBlock / 64) * U + (size_t)U * kBlock) : 0);
 }
 
+// Long-lived workgroups per compute unit of an aggregation with norms in fixed assignment: enough for about 64 KB in flight,
+// at least two (32 bf16 rows, 16 groups, 32 Mi elements: one per unit 1.72 ms, two 0.91), except where a sweep over 1-32
+// rows, 1-8 groups and 1-60 M elements has something else ahead (us at 30 M elements, against that rule):
+//   fp32   one group of 7 and more rows, two groups of 12 and more, not on short shards: bound by memory alone, one
+//          (7 / 12 / 24 rows, one group 167 / 274 / 513 against 180 / 286 / 542; two groups, 20 rows 447 against 484);
+//          4 and 5 rows: two (4 rows, four groups 167 against 190)
+//   bf16   many groups: bound by the walk over the groups, as many as fit (8 groups of 12 / 20 / 24 / 28 rows 236 / 326 / 376 / 472
+//          against 273 / 521 / 585 / 659); few groups of 13 to 24 rows: three (16 rows, four groups 212 against 274);
+//          one group on a long shard: three with 8 and 9 rows (25 M: 83 against 91), two with 10 to 14 (12 rows 136 against 148)
+int sum_workgroups(int W, bool f32, int U, int64_t P, int num_cu) {
+    const int64_t tiles = P / (4 * kBlock);
+    const int wg_bytes = W * (f32 ? 16 : 8) * kBlock;
+    const int rule = std::max(2, std::min(4, (64 * 1024 + wg_bytes - 1) / wg_bytes));
+    if (f32) {
+        if (((U == 1 && W >= 7) || (U == 2 && W >= 12)) && tiles >= 16 * (int64_t)num_cu) return 1;
+        return W == 4 || W == 5 ? 2 : rule;
+    }
+    if (U >= 6) return W >= 28 ? 3 : 4;
+    if (U >= 3) return W >= 13 && W <= 24 ? 3 : rule;
+    if (U == 1 && tiles >= 64 * (int64_t)num_cu && W >= 8 && W <= 14) return W <= 9 ? 3 : 2;
+    return rule;
+}
+
 template <int W, class R>
 hipError_t launch_reduce_t(const ReduceArgs& a, int num_cu, int grid_cap, int* grid_out, hipStream_t s) {
     auto kern = reduce_rows_kernel<W, R>;
@@ -149,10 +172,9 @@ hipError_t launch_reduce_t(const ReduceArgs& a, int num_cu, int grid_cap, int* g
     const bool queued = a.queue;
     const Geometry g = queued ? queue_geometry(num_cu, grid_cap, queue_workgroups_per_cu(0, false),
                                                W * (int)sizeof(typename R::vec) + 16, Traffic::Reduce)
-                              // (with norms: long-lived workgroups, and at least two of them per unit whatever
-                                              // the tile weighs -- 32 bf16 rows, 16 groups, 32 Mi elements: one per unit 1.72 ms)
-                              : pick_geometry(a.P, a.norms != 0, num_cu, grid_cap,
-                                              W * (int)sizeof(typename R::vec), 4, 2);
+                              // (with norms: long-lived workgroups)
+                              : pick_geometry(a.P, a.norms != 0, num_cu, grid_cap, 256, 1,
+                                              sum_workgroups(W, std::is_same<R, RowF32>::value, a.U, a.P, num_cu));
     *grid_out = g.grid;
     hipLaunchKernelGGL(kern, dim3(g.grid), dim3(kBlock), lds, s, a.rows, a.coef, a.mask, a.out, a.U,
                        a.out_dtype == STAR_BF16 ? 1 : 0, a.P, a.head, a.norms, g.span_g, g.span_k, a.partials,

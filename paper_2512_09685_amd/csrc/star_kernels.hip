@@ -511,7 +511,17 @@ hipError_t launch_seq_t(const SeqArgs& a, int num_cu, int grid_cap, int* grid_ou
     // workgroup per unit to hide under the memory time: 20 to 32 fp32 rows, 8 updates, 0.68-0.71 of the HBM peak with
     // two against 0.43-0.45 with one)
     const int per_cu = COLLAPSED ? 2 : queue_workgroups_per_cu(thread_bytes, true);
+    // (a single update of fp32 rows with its norm is bound by memory alone and, off the short shards, is fastest with
+    // one or two workgroups per unit instead of the two to four that 64 KB in flight ask for: 20 / 32 M elements, 1 row
+    // 70 / 113 against 77 / 121 us, 2 rows 85 / 138 against 93 / 150, 4 rows 109 / 167 against 120 / 188; 12 M, 8 rows 106
+    // against 109; 3 M elements: level or behind)
+    int one_report = 0;
+    if (NORMS && !COLLAPSED && std::is_same<R, RowF32>::value && a.U == 1) {
+        const int64_t tiles = a.P / (4 * kBlock);
+        if (tiles >= 16 * (int64_t)num_cu) one_report = W <= 2 || (W == 3 && tiles < 64 * (int64_t)num_cu) ? 2 : 1;
+    }
     const Geometry g = queued ? queue_geometry(num_cu, grid_cap, per_cu, thread_bytes)
+                              : one_report ? pick_geometry(a.P, NORMS, num_cu, grid_cap, 256, 1, one_report)
                               : pick_geometry(a.P, NORMS, num_cu, grid_cap, thread_bytes, 4,
                                               COLLAPSED ? 2 : 1);   // (short shards as well: 25-30 % faster with two)
     *grid_out = g.grid;

@@ -145,6 +145,26 @@ __device__ __forceinline__ double wave_sum_to_lane63(double x) {
     return x;
 }
 
+// Rows of SPAN lanes: the odd rows of x change places with the even rows of y, then the two are added.  Even rows of the
+// result hold x's row plus its odd neighbour, odd rows the same of y.
+template <int SPAN>
+__device__ __forceinline__ u32x2 swap_rows(const uint32_t x, const uint32_t y) {
+    const auto s = SPAN == 32 ? __builtin_amdgcn_permlane32_swap(x, y, false, false)
+                              : __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    return u32x2{s[0], s[1]};
+}
+template <int SPAN>
+__device__ __forceinline__ float swap_add(const float x, const float y) {
+    const u32x2 s = swap_rows<SPAN>(__float_as_uint(x), __float_as_uint(y));
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+template <int SPAN>
+__device__ __forceinline__ double swap_add(const double x, const double y) {
+    const u32x2 lo = swap_rows<SPAN>((uint32_t)__double2loint(x), (uint32_t)__double2loint(y));
+    const u32x2 hi = swap_rows<SPAN>((uint32_t)__double2hiint(x), (uint32_t)__double2hiint(y));
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
 // ---------------------------------------------------------------- compile-time loops
 template <int I, int N, class F>
 __device__ __forceinline__ void static_for(F&& f) {

@@ -69,15 +69,6 @@ struct GramTile<true> {
     static __device__ __forceinline__ int reg_of(int i) { return 4 * (i / 8) + (i % 4); }
 };
 
-// Rows of SPAN lanes: the odd rows of x change places with the even rows of y, then the two are added.  Even rows of the
-// result hold x's row plus its odd neighbour, odd rows the same of y.
-template <int SPAN>
-__device__ __forceinline__ float swap_add(const float x, const float y) {
-    const auto s = SPAN == 32 ? __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false)
-                              : __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
-}
-
 // One row of the LDS panel holds 512 bytes of elements (128 fp32 or 256 bf16) and 16 bytes of
 // padding: 16 lanes that read 16 bytes each from 16 consecutive rows at the same offset then
 // touch every bank exactly once.

@@ -7,11 +7,14 @@
 //   - A thread holds 16 or 8 elements of every row, so that one member test (a scalar branch) covers as many
 //     multiply-adds, and so does the sum kept per update.
 //   - Coefficients and member masks are read with scalar loads, one wait per update.
-//   - The squares of a thread's elements are added over eight lanes, then in double into one LDS slot per eight lanes
-//     and update: 256 bytes per update, so up to 240 updates need one pass over the rows, and several workgroups
-//     fit on a compute unit to hide the loads.
-// Measured at that size: 193 us, 614 with the step-by-step kernel this replaces (one LDS slot per thread and update, hence
-// two passes for 32 updates and two waves per SIMD; coefficients from LDS at their use; 4 elements per thread).
+//   - Four squares are added in fp32, everything beyond in double (eight lanes in fp32 first would be 64 to 128 squares:
+//     the partial sums' error grows fivefold, and elements of 1.6e18 give an infinite norm instead of 9.2e18).  So that the double
+//     additions cost little, four updates are added over the wave together by swapping halves and quarters of it
+//     between registers; eight lanes per wave and update then add into a double LDS slot of their own: 256 bytes per update, so
+//     up to 240 updates need one pass over the rows, and several workgroups fit on a compute unit to hide the loads.
+// Measured at that size: 203 us (195 with the fp32 sums over eight lanes), 601 with the step-by-step kernel this replaced (one
+// LDS slot per thread and update, hence two passes for 32 updates and two waves per SIMD; coefficients from LDS at their
+// use; 4 elements per thread).  Light rows pay more: 4 / 1 rows, 32 updates 122 / 73 against 112 / 66 (403 / 256 by the step-by-step kernel).
 #include "star_device.h"
 
 namespace star {
@@ -49,13 +52,22 @@ __global__ __launch_bounds__(kBlock) void norm_walk_kernel(const WalkKernelArgs 
         mask = in->inl.mask;
     }
     double* const s_slot = walk_lds;
-    for (int i = threadIdx.x; i < U * kSlots; i += kBlock) s_slot[i] = 0.0;
+    for (int i = threadIdx.x; i < (U + 3) / 4 * 4 * kSlots; i += kBlock) s_slot[i] = 0.0;
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double* const my_slot = s_slot + threadIdx.x / 8;   // private to the eight lanes: no other lane adds to it
-    const bool first_of_eight = (lane & 7) == 0;
+    // Four updates are added over the wave together: rows of 16 lanes end with update (0, 2, 1, 3)[row], lanes 0 to 7 of a row
+    // write one slot each.  The slots are private to the lane, and turned by the update: four neighbours fall on four bank groups.
+    const int row = lane >> 4, turn = 2 * (row & 1) + row / 2;
+    double* const my_slot = s_slot + turn * kSlots + 8 * ((wave + turn) & 3) + (lane & 7);
+    const bool writes = (lane & 8) == 0;
 
+    auto add_four = [&](const int u, double q) {
+        q += dpp_take<0x128, 0xf>(q);   // row_ror:8
+        if (writes)
+            __hip_atomic_fetch_add(my_slot + u * kSlots, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
     auto walk = [&](const float (&g)[E][W]) {
+        double one = 0.0, two = 0.0;
         for (int u = 0; u < U; ++u) {
             const uint32_t m = mask[u];
             float c[W];
@@ -74,23 +86,34 @@ __global__ __launch_bounds__(kBlock) void norm_walk_kernel(const WalkKernelArgs 
                     for (int k = 0; k < E; ++k) gb[k] = __builtin_fmaf(c[w], g[k][w], gb[k]);
                 }
             }
-            float s[KCH];
+            double s[KCH];
 #pragma unroll
-            for (int j = 0; j < KCH; ++j) {   // four squares a chain, the chains added pairwise
-                s[j] = 0.0f;
+            for (int j = 0; j < KCH; ++j) {   // four squares in fp32, in double from there on
+                float sq = 0.0f;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) s[j] = __builtin_fmaf(gb[4 * j + k], gb[4 * j + k], s[j]);
+                for (int k = 0; k < 4; ++k) sq = __builtin_fmaf(gb[4 * j + k], gb[4 * j + k], sq);
+                s[j] = (double)sq;
             }
 #pragma unroll
             for (int d = 1; d < KCH; d *= 2)
 #pragma unroll
                 for (int j = 0; j + d < KCH; j += 2 * d) s[j] += s[j + d];
-            float q = s[0];
-            q += dpp_take<0xB1, 0xf>(q);   // quad_perm [1,0,3,2]
-            q += dpp_take<0x4E, 0xf>(q);   // quad_perm [2,3,0,1]
-            q += dpp_take<0x141, 0xf>(q);  // row_half_mirror
-            if (first_of_eight)
-                __hip_atomic_fetch_add(my_slot + u * kSlots, (double)q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (!(u & 1)) {
+                one = s[0];
+                continue;
+            }
+            const double pair = swap_add<32>(one, s[0]);
+            if (!(u & 2)) {
+                two = pair;
+                continue;
+            }
+            add_four(u & ~3, swap_add<16>(two, pair));
+        }
+        if (U & 1) {
+            const double pair = swap_add<32>(one, 0.0);
+            add_four(U & ~3, U & 2 ? swap_add<16>(two, pair) : swap_add<16>(pair, 0.0));
+        } else if (U & 2) {
+            add_four(U & ~3, swap_add<16>(two, 0.0));
         }
     };
 
@@ -111,9 +134,15 @@ __global__ __launch_bounds__(kBlock) void norm_walk_kernel(const WalkKernelArgs 
             if (whole) {
 #pragma unroll
                 for (int w = 0; w < W; ++w) raw[j][w] = R::load(a->rows.p[w], c);
-            } else {   // the last tile: elements beyond the end hold zeros
+            } else {
+                // the last tile: lanes beyond the end read the last chunk and hold zeros (a test around every load would
+                // have the wave wait for one before it asks for the next)
+                const int64_t last = c < nchunk ? c : nchunk - 1;
 #pragma unroll
-                for (int w = 0; w < W; ++w) raw[j][w] = c < nchunk ? R::load(a->rows.p[w], c) : typename R::vec{};
+                for (int w = 0; w < W; ++w) raw[j][w] = R::load(a->rows.p[w], last);
+#pragma unroll
+                for (int w = 0; w < W; ++w)
+                    if (c >= nchunk) raw[j][w] = typename R::vec{};
             }
         }
         float g[E][W];
@@ -153,7 +182,7 @@ __global__ __launch_bounds__(kBlock) void norm_walk_kernel(const WalkKernelArgs 
 
 namespace {
 
-size_t walk_lds_bytes(int U) { return sizeof(double) * (size_t)U * kSlots; }
+size_t walk_lds_bytes(int U) { return sizeof(double) * (size_t)((U + 3) / 4 * 4) * kSlots; }
 
 template <int W, class R>
 hipError_t launch_walk_t(const SeqArgs& a, int num_cu, int grid_cap, int* grid_out, hipStream_t s) {
@@ -179,7 +208,7 @@ hipError_t launch_walk_t(const SeqArgs& a, int num_cu, int grid_cap, int* grid_o
 
 }  // namespace
 
-int walk_max_updates() { return 60 * 1024 / (int)walk_lds_bytes(1); }   // stay inside 64 KB of LDS per workgroup
+int walk_max_updates() { return 60 * 1024 / (int)walk_lds_bytes(4) * 4; }   // stay inside 64 KB of LDS per workgroup
 
 hipError_t launch_norm_walk(int Wp, int dtype, const SeqArgs& a, int num_cu, int grid_cap, int* grid_out,
                             hipStream_t s) {

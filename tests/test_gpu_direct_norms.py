@@ -12,7 +12,7 @@ from gpu_util import opts, rand_rows, rand_stream, tile_order, to_dev_rows  # no
 pytestmark = pytest.mark.gpu
 
 # Norms against 64 bits: the coefficients and the result are rounded to fp32 (6e-8 each), a group sum of y terms carries
-# at most y roundings of 6e-8 that average out over the elements, and 64 squares are added in fp32.
+# at most y roundings of 6e-8 that average out over the elements, and four squares are added in fp32 (double beyond).
 TOL = 3e-7
 
 
@@ -45,3 +45,16 @@ def test_direct_norms(dtype, W, U, P, off):
     star.star_group_norms(dev, us, n, wmode="stale", direct_norms=True, **opts())
     member = np.array([0 in mem[offs[u]:offs[u + 1]] for u in range(U)])
     assert np.array_equal(~np.isfinite(n.cpu().numpy()), member)
+
+
+@pytest.mark.parametrize("W,U", [(1, 1), (4, 3), (8, 2), (16, 5), (32, 4)])
+def test_direct_norms_of_large_elements(W, U):
+    """Only four squares are ever added in fp32: elements of 9e18 (squares of 8.1e37, four of them 3.2e38) still have a finite norm."""
+    P = 70001
+    rows = [torch.full((P,), 9e18, device="cuda") for _ in range(W)]
+    n = torch.full((U,), -1.0, device="cuda")
+    us = star.UpdateStream(np.arange(U + 1, dtype=np.int32), np.arange(U, dtype=np.int32) % W)
+    star.star_group_norms(rows, us, n, direct_norms=True, **opts())
+    ref = float(np.float32(9e18)) * P ** 0.5
+    # every partial sum is a whole multiple of one square: the roundings of the square's sum (3 of 6e-8, halved by the root) and the result's
+    assert np.max(np.abs(n.cpu().numpy().astype(np.float64) - ref)) <= 2e-7 * ref

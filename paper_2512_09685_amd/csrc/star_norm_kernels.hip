@@ -26,6 +26,7 @@ struct WalkKernelArgs {
     double* partials;
     int64_t P;
     int32_t U, head;
+    int32_t share;          // updates per workgroup, see launch_walk_t
     InlineTables inl;
 };
 
@@ -44,13 +45,16 @@ __global__ __launch_bounds__(kBlock) void norm_walk_kernel(const WalkKernelArgs 
     constexpr int KCH = walk_chunks(W), E = 4 * KCH;
     extern __shared__ double walk_lds[];
     const auto* const in = (const STAR_CONST WalkKernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-    const int U = args.U;
+    // this workgroup's share of the updates
+    const int u0 = (int)blockIdx.y * args.share, U = min(args.U - u0, args.share);
     const STAR_CONST float* coef = (const STAR_CONST float*)args.coef;
     const STAR_CONST uint32_t* mask = (const STAR_CONST uint32_t*)args.mask;
     if (!args.coef) {
         coef = in->inl.coef;
         mask = in->inl.mask;
     }
+    coef += u0 * W;
+    mask += u0;
     double* const s_slot = walk_lds;
     for (int i = threadIdx.x; i < (U + 3) / 4 * 4 * kSlots; i += kBlock) s_slot[i] = 0.0;
     __syncthreads();
@@ -176,7 +180,7 @@ __global__ __launch_bounds__(kBlock) void norm_walk_kernel(const WalkKernelArgs 
     __syncthreads();
     for (int u = wave; u < U; u += kBlock / 64) {   // one wave per update
         const double s = wave_sum_to_lane63(lane < kSlots ? s_slot[u * kSlots + lane] : 0.0);
-        if (lane == 63) args.partials[(int64_t)u * gridDim.x + blockIdx.x] = s;
+        if (lane == 63) args.partials[(int64_t)(u0 + u) * gridDim.x + blockIdx.x] = s;
     }
 }
 
@@ -184,14 +188,35 @@ namespace {
 
 size_t walk_lds_bytes(int U) { return sizeof(double) * (size_t)((U + 3) / 4 * 4) * kSlots; }
 
+// Workgroups per compute unit.  Four hide the loads of streams bound by arithmetic (and of light rows, which keep little in
+// flight).  Up to about eight updates of heavier rows the pass is bound by memory, where fewer requests in flight are better:
+// two workgroups, and one from 13 fp32 rows on with up to four updates (one / two per unit against four, mean of 8 to 60 M
+// elements: 8 fp32 rows, 4 / 8 updates 1.07 / 0.96, 1.35 / 0.97; 16 rows, 2 updates 0.96 / 0.98; 5 rows, 4 / 8 updates 1.32 / 0.95,
+// 1.77 / 1.09; 3 rows, 1 update 1.72 / 1.12; 16 bf16 rows, 4 / 8 updates 1.31 / 0.95, 1.54 / 0.97; 8 bf16 rows, 4 updates 1.83 / 1.13;
+// 24 bf16 rows, 4 updates 1.20 / 1.00).  With 32 rows only one fits at a time, and one that stays is ahead of four after
+// each other for longer streams too (25.6 M, 16 updates: fp32 695 against 765 us, bf16 657 against 701), except with one or two
+// updates of bf16 rows (8 M, 2 updates: 79 against 75).
+int walk_workgroups_per_cu(int W, bool f32, int U) {
+    if (W > 28) return f32 || U > 2 ? 1 : 4;
+    if (U > 8) return 4;
+    if (f32 && W >= 13 && U <= 4) return 1;
+    return W >= (U <= 4 ? (f32 ? 4 : 13) : (f32 ? 6 : 16)) ? 2 : 4;
+}
+
 template <int W, class R>
 hipError_t launch_walk_t(const SeqArgs& a, int num_cu, int grid_cap, int* grid_out, hipStream_t s) {
-    // Four long-lived workgroups per unit sweep the shard together, for every stream: the work queue is behind even where
-    // one or two updates leave the pass bound by memory (1 fp32 row, 25.6 M elements, 1 update: 22 against 39 us;
-    // 16 rows, 2 updates: 232 against 252; 4 rows, 100 M elements: 241 against 246).
+    // Long-lived workgroups sweep the shard together, for every stream: the work queue is behind even where one or two
+    // updates leave the pass bound by memory (1 fp32 row, 25.6 M elements, 1 update: 22 against 39 us; 16 rows, 2
+    // updates: 232 against 252; 4 rows, 100 M elements: 241 against 246).
     const int64_t width = (int64_t)kBlock * walk_chunks(W);
     const int64_t tiles = std::max<int64_t>(1, (a.P / 4 + width - 1) / width);
-    const int grid = (int)std::min<int64_t>(tiles, std::min(4 * num_cu, grid_cap));
+    const int per_cu = walk_workgroups_per_cu(W, std::is_same<R, RowF32>::value, a.U);
+    const int grid = (int)std::min<int64_t>(tiles, std::min(per_cu * num_cu, grid_cap));
+    // A shard of fewer tiles than units: the updates are shared out as well, in fours.  There the walk is one chain of updates
+    // long (16 rows, 16 updates, 5000 / 100 000 elements: 15.1 / 15.3 us a call, 19.9 / 20.7 in one piece; 8 rows, 32 updates: 15.2
+    // against 23), and each share's rows come out of the caches.
+    const int parts = std::max(1, std::min(num_cu / grid, (a.U + 3) / 4));
+    const int share = ((a.U + parts - 1) / parts + 3) / 4 * 4;
     *grid_out = grid;
     WalkKernelArgs k;
     k.rows = a.rows;
@@ -200,9 +225,11 @@ hipError_t launch_walk_t(const SeqArgs& a, int num_cu, int grid_cap, int* grid_o
     k.partials = a.partials;
     k.P = a.P;
     k.U = a.U;
+    k.share = share;
     k.head = a.head;
     k.inl = a.coef ? InlineTables() : *a.inl;
-    hipLaunchKernelGGL((norm_walk_kernel<W, R>), dim3(grid), dim3(kBlock), walk_lds_bytes(a.U), s, k);
+    hipLaunchKernelGGL((norm_walk_kernel<W, R>), dim3(grid, (a.U + share - 1) / share), dim3(kBlock),
+                       walk_lds_bytes(std::min(a.U, share)), s, k);
     return hipGetLastError();
 }
 

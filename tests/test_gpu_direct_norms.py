@@ -58,3 +58,20 @@ def test_direct_norms_of_large_elements(W, U):
     ref = float(np.float32(9e18)) * P ** 0.5
     # every partial sum is a whole multiple of one square: the roundings of the square's sum (3 of 6e-8, halved by the root) and the result's
     assert np.max(np.abs(n.cpu().numpy().astype(np.float64) - ref)) <= 2e-7 * ref
+
+
+@pytest.mark.parametrize("W,U,P", [(1, 3, 1), (2, 9, 4096 * 3 + 1), (4, 13, 4096 * 200), (6, 61, 2048 * 20 - 3), (8, 33, 2048 * 64 + 5),
+                                   (16, 32, 2048 * 128 + 1), (20, 8, 2048 * 127), (28, 12, 7), (32, 130, 2048 * 5 + 3)])
+def test_direct_norms_shared_out_updates(W, U, P):
+    """Shards of fewer tiles than compute units, where the updates are shared out over workgroups in fours: whole shares, short
+    last shares, more shares than fours."""
+    rng = np.random.default_rng(W + U)
+    rows = rand_rows(rng, W, P, "f32")
+    offs, mem, st = rand_stream(rng, W, U, stale=3)
+    ref = so.group_norms(rows, offs, mem, staleness=st, wmode="stale")
+    n = torch.full((U,), -1.0, device="cuda")
+    star.star_group_norms(to_dev_rows(rows), star.UpdateStream(offs, mem, st), n, wmode="stale", direct_norms=True, **opts())
+    err = float(np.max(np.abs(n.cpu().numpy() - ref) / ref))
+    print(f"direct norms W={W} U={U} P={P}: err {err:.3g}", flush=True)
+    # a shard of a few elements has nothing to average over: up to 33 roundings of the coefficients, products and sums
+    assert err <= (TOL if P > 1000 else 1e-6)

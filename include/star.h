@@ -303,8 +303,7 @@ typedef struct {
                                    (the collapsed map without norms needs no tables at all and reports 1)   */
     int32_t collapsed_update;   /* 1: params and momentum come from the one affine map of the stream.  Always so
                                    with AFFINE and AFFINE_MFMA; with SEQ only for 17 to 32 fp32 rows, update
-                                   with norms and a short stream (direct norm sums of at most 4 W + 48, with
-                                   17 to 24 rows 4 W + 30,
+                                   with norms and a short stream (direct norm sums of at most 4 W + 48
                                    multiply-adds per element), where the step-by-step kernel walks the updates
                                    for the norms alone (direct sums are cheaper there than the Gram matrix)   */
     int32_t reserved;

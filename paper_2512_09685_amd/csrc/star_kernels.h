@@ -150,10 +150,11 @@ inline bool seq_takes_queue(int updates_in_launch) { return updates_in_launch <=
 // stream's direct norm sums cost at most this many multiply-adds per element.  Measured against the Gram
 // matrix on the matrix cores, 2 Mi and 64 Mi elements, 6 to 16 updates: the walk wins by 5-14 % up to about
 // 130 / 145 / 160 / 175 multiply-adds with 20 / 24 / 28 / 32 rows and loses beyond (at twice that by a third);
-// the limit grows with the rows because the matrix-core kernel's time does.  (Up to 24 rows that kernel now works by row groups
-// of four and is 6-12 % faster: 20 rows, 25.6 M elements, 84 / 115 / 138 multiply-adds 425 / 466 / 486 us against 470; 24 rows,
-// 108 / 135 / 162: 500 / 549 / 579 against 542.)
-inline double direct_norm_fma_limit(int Wp) { return 4.0 * Wp + (Wp <= 24 ? 30.0 : 48.0); }
+// the limit grows with the rows because the matrix-core kernel's time does.  (Up to 24 rows that kernel now works by row
+// groups of four and is 6-12 % faster: 20 rows, 25.6 M elements, 84 / 115 / 138 multiply-adds 425 / 466 / 486 us against 470; 24
+// rows, 108 / 135 / 162: 500 / 549 / 579 against 542.  The limit stays where it was all the same: the few percent below it are
+// not worth norms that lose digits where rows are anti-correlated, 1.8e-5 against 2e-8 at kappa = 4e4.)
+inline double direct_norm_fma_limit(int Wp) { return 4.0 * Wp + 48.0; }
 // Which Gram launches of the collapsed kernel use the few-rows form (double fold slots in LDS after every
 // chunk, tiles from the queue on long shards): up to kFewRows rows -- except the Gram matrix alone on exactly
 // kFewRows fp32 rows, whose 21 slot updates per chunk are not hidden by 96 bytes of loads (32 to 96 Mi

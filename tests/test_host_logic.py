@@ -242,6 +242,21 @@ def test_plan_choice_wide_fp32_rows_with_norms():
         star.KERNEL_AFFINE_MFMA
 
 
+@pytest.mark.parametrize("W", [20, 24, 28, 32])
+def test_plan_choice_limit_of_the_direct_norm_walk(W):
+    """17 to 32 fp32 rows, update with norms: direct norm sums up to exactly 4 W + 48 multiply-adds (sum of y_u + 1), the Gram
+    matrix from one more on."""
+    hp = dict(lr=0.1, momentum_coef=0.9, want_norms=True)
+    y = (4 * W + 48) // 8 - 1                      # eight groups: 8 (y + 1) = 4 W + 48
+    for more, kernel in ((0, star.KERNEL_SEQ), (1, star.KERNEL_AFFINE_MFMA)):
+        sizes = [y] * 7 + [y + more]
+        us = star.UpdateStream(np.cumsum([0] + sizes).astype(np.int32),
+                               np.concatenate([(np.arange(s) + 3 * k) % W for k, s in enumerate(sizes)]).astype(np.int32))
+        c = star.star_plan_choice(50_000_000, W, "f32", us, **hp)
+        assert c["fma_seq"] - 3 * 8 == 4 * W + 48 + more and c["rows_used"] == W
+        assert c["kernel"] == kernel and c["collapsed_update"] == 1
+
+
 def test_plan_choice_gram_route_for_few_rows():
     """Where the Gram matrix is formed when AUTO decides (measured crossovers, see gram_on_matrix_cores)."""
     def route(P, W, dt, update):

@@ -121,8 +121,8 @@ typedef enum {
 /* star_options.flags.  STAR_OPT_DIRECT_NORMS: where the library would take the norms from the Gram
  * matrix of the rows (relative error up to 2e-8 kappa_u, see star_group_update), take them from direct
  * sums of gbar_u^2 instead, to fp32-product accuracy whatever the rows: in a pass of its own over the
- * rows beside the collapsed update (W more row reads per element), as the library does by itself for
- * coefficients of both signs.  For rows that may be anti-correlated.  Ignored when `kernel` forces an
+ * rows beside the collapsed update (W more row reads per element; short streams on 17 to 32 fp32 rows and the
+ * streams of the literal kernel: in the same pass), as the library does by itself for coefficients of both signs.  For rows that may be anti-correlated.  Ignored when `kernel` forces an
  * evaluation (STAR_KERNEL_SEQ always sums directly) and by calls that return no norms. */
 #define STAR_OPT_DIRECT_NORMS 1
 

@@ -421,11 +421,14 @@ Launch decide(const star::Plan& plan, int grad_dtype, bool update, bool want_nor
     }
     // 17 to 32 fp32 rows, update with norms: the Gram matrix needs the fp32 matrix instructions (1536 flops per
     // element, only partly hidden: 0.60-0.64 of the HBM peak).  A short stream gets its norms cheaper from the
-    // direct sums, y_u + 1 multiply-adds per update, in the same pass as the collapsed update.
-    if (update && want_norms && l.route == star::Route::Affine && !l.split_norms && opt.kernel == STAR_KERNEL_AUTO &&
+    // direct sums, y_u + 1 multiply-adds per update, in the same pass as the collapsed update.  A stream that was given a
+    // direct norm pass above needs none then: one pass over the rows instead of two (25.6 M elements, 4 updates: 20 rows of
+    // groups of 10 409 against 655 us, 28 rows of groups of 20 585 against 972).
+    if (update && want_norms && l.route == star::Route::Affine && opt.kernel == STAR_KERNEL_AUTO &&
         grad_dtype == STAR_F32 && l.Wp > 16 && plan.U <= star::seq_max_updates(l.Wp, true) &&
         plan.fma_seq - 3.0 * plan.U <= star::direct_norm_fma_limit(l.Wp)) {
         l.route = star::Route::Seq;
+        l.split_norms = false;
         l.collapsed_in_seq = true;
     }
     l.want_queue = P >= queue_min_for(opt, grad_dtype, plan.Wc, update, false, update && want_norms,

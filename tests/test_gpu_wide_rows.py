@@ -40,3 +40,29 @@ def test_gram_of_wide_fp32_rows(W, P, off):
     star.star_group_norms(dev, us, n, **opts())
     member = np.array([W - 1 in mem[offs[u]:offs[u + 1]] for u in range(40)])
     assert np.array_equal(~np.isfinite(n.cpu().numpy()), member)
+
+
+@pytest.mark.parametrize("W,U,y", [(17, 4, 8), (20, 8, 10), (24, 5, 18), (32, 6, 12)])
+def test_direct_norms_beside_the_update_of_wide_fp32_rows(W, U, y):
+    """Direct norms on request in the pass of the collapsed update: state and norms against the oracle, with a pair of rows that
+    almost cancel, whose norm the Gram matrix would lose."""
+    rng = np.random.default_rng(W * 7 + U)
+    P = 70003
+    rows = rand_rows(rng, W, P, "f32")
+    rows[1] = -rows[0] + (rng.standard_normal(P) * 1e-4).astype(np.float32)
+    groups = [[0, 1]] + [list(rng.permutation(W)[:y]) for _ in range(U - 1)]
+    offs = np.cumsum([0] + [len(g) for g in groups]).astype(np.int32)
+    mem = np.concatenate(groups).astype(np.int32)
+    us = star.UpdateStream(offs, mem)
+    hp = dict(lr=0.1, momentum_coef=0.9, weight_decay=1e-4)
+    used = len(set(mem.tolist()))
+    c = star.star_plan_choice(P, W, "f32", us, want_norms=True, direct_norms=True, **hp)
+    assert c["launches"] == 1 and c["kernel"] == star.KERNEL_SEQ and c["rows_used"] == used
+    p0 = (rng.standard_normal(P) * 0.02).astype(np.float32)
+    v0 = (rng.standard_normal(P) * 1e-2).astype(np.float32)
+    ep, ev, en = so.group_update(p0, v0, rows, offs, mem, want_norms=True, **hp)
+    p, v, n = torch.from_numpy(p0).cuda(), torch.from_numpy(v0).cuda(), torch.full((U,), -1.0, device="cuda")
+    star.star_group_update(p, v, to_dev_rows(rows), us, norms_out=n, direct_norms=True, **opts(), **hp)
+    torch.cuda.synchronize()
+    assert np.max(np.abs(n.cpu().numpy() - en) / en) <= 1e-6
+    assert so.max_rel_err(p.cpu().numpy(), ep) <= 1e-6 and so.max_rel_err(v.cpu().numpy(), ev) <= 1e-6

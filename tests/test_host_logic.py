@@ -325,6 +325,24 @@ def test_plan_choice_direct_norms_option():
         assert plain == star.star_plan_choice(24 << 20, 8, dt, us, **hp)
 
 
+def test_plan_choice_direct_norms_of_wide_fp32_rows_take_one_pass():
+    """17 to 32 fp32 rows, update with norms that must be direct (the option, coefficients of both signs): the kernel that
+    forms direct sums beside the collapsed update where the stream is in its limit, a second pass over the rows only beyond."""
+    hp = dict(lr=0.1, momentum_coef=0.9, want_norms=True)
+    def stream(W, U, y, signed):
+        coef = np.tile(np.array([1.0, -0.5] * 16, np.float32)[:y], U) if signed else None
+        return star.UpdateStream(np.arange(0, U * y + 1, y, dtype=np.int32),
+                                 np.concatenate([(np.arange(y) + 3 * u) % W for u in range(U)]).astype(np.int32), None, coef)
+    for W, U, y, one in ((20, 4, 10, True), (20, 8, 10, True), (24, 4, 20, True), (28, 6, 20, True), (32, 8, 21, True),
+                         (20, 16, 10, False), (32, 16, 16, False)):
+        for kw in (dict(direct_norms=True), dict(wmode="explicit")):
+            us = stream(W, U, y, "wmode" in kw)
+            for P in (1 << 20, 50_000_000):
+                c = star.star_plan_choice(P, W, "f32", us, **kw, **hp)
+                got = (c["kernel"], c["collapsed_update"], c["launches"], c["finishing_launches"])
+                assert got == ((star.KERNEL_SEQ, 1, 1, 1) if one else (star.KERNEL_AFFINE, 1, 2, 1)), (W, U, y, P, kw, c)
+
+
 def test_plan_choice_reports_the_kernels_of_the_five_workloads():
     """What bench.py labels its roofline with: the library's own answer, for every workload as it is timed."""
     import workloads

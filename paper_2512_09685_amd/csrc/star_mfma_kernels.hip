@@ -101,20 +101,20 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
     // 28 and 32 rows need 28 and 36 pairs, whose accumulators allow one wave per SIMD only: 686 / 825 us against
     // 651 / 722 by blocks.  (One wave per SIMD with a tile of look-ahead was tried for 24 rows as well: 573.)
     // Four accumulator registers a pair leave no room for sums in double beside them; those are kept in LDS, one
-    // per lane and pair, shared by the four waves.
+    // per lane and two pairs for each wave (see fold), so that every sum is formed in a fixed order.
     constexpr bool kQuads = quad_groups(BF, W);
     constexpr int kRowStride = kQuads ? kQuadRowBytes : kPanelRowBytes;
     constexpr int kGroups = W / 4, kPairs = kQuads ? kGroups * (kGroups + 1) / 2 : 1;
     constexpr int kPanelBytes = (kQuads ? W : N) * kRowStride;
     static_assert(kPanelBytes >= 64 * 16 * 8, "the panel doubles as the reduction buffer");
     __shared__ __align__(16) unsigned char panel[kWaves][kPanelBytes];
-    __shared__ double sums[kQuads ? kPairs * 64 : 1];
+    constexpr int kSums = (kPairs + 1) / 2 * 64;   // of a wave
+    __shared__ double sums[kQuads ? kWaves * kSums : 1];
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     unsigned char* const T = panel[wave];
     if constexpr (kQuads) {
-        for (int i = threadIdx.x; i < kPairs * 64; i += kBlock) sums[i] = 0.0;
-        __syncthreads();
+        for (int i = lane; i < kSums; i += 64) sums[wave * kSums + i] = 0.0;
     } else {   // rows W..N-1 of the panel are zero and never written again
         for (int w = W; w < N; ++w) *reinterpret_cast<u32x2*>(T + w * kRowStride + 8 * lane) = u32x2{0u, 0u};
     }
@@ -216,7 +216,8 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // all reads returned before the panel is overwritten
     };
     auto gram_512 = [&](const u32x2 (&x)[W]) {
-        // (kept apart from the update and from each other: mixed, they spill with 24 rows, 578 against 542 us)
+        // (kept apart from the update and from each other: mixed, the 24-row update spills vector registers, 578 against 542 us;
+        // kept apart it spills none, the norms alone six)
         if constexpr (kQuads) __builtin_amdgcn_sched_barrier(0);
         stage(x);
         consume();
@@ -246,14 +247,24 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
     auto fold = [&]() {
         if constexpr (kQuads) {
             // the 16 blocks of a pair's 4 registers are added four at a time by swapping halves and quarters of the wave
-            // between registers: row rho of 16 lanes ends with register (0, 2, 1, 3)[rho], 4 blocks of it left.  (One
-            // addition in LDS per register instead: 2-3 % slower, and four times the LDS.)
-            static_for<0, kPairs>([&](auto ec) {
-                constexpr int e = decltype(ec)::value;
-                const float x = swap_add<32>(quad[e][0], quad[e][1]), y = swap_add<32>(quad[e][2], quad[e][3]);
-                __hip_atomic_fetch_add(&sums[e * 64 + lane], (double)swap_add<16>(x, y), __ATOMIC_RELAXED,
+            // between registers: row rho of 16 lanes ends with register (0, 2, 1, 3)[rho], 4 blocks of it left.  Two pairs then
+            // share a register, 2 blocks of each left: lanes 0-7 of a row the even pair, 8-15 the odd one.  Every lane adds to a
+            // sum of its own.  (One addition in LDS per register and pair instead: 2-3 % slower.)
+            const bool upper = (lane & 8) != 0;
+            auto gathered = [&](auto ec) {
+                f32x4& d = quad[decltype(ec)::value];
+                const float z = swap_add<16>(swap_add<32>(d[0], d[1]), swap_add<32>(d[2], d[3]));
+                d = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                return z;
+            };
+            static_for<0, (kPairs + 1) / 2>([&](auto hc) {
+                constexpr int e = 2 * decltype(hc)::value;
+                const float even = gathered(std::integral_constant<int, e>{});
+                float odd = 0.0f;
+                if constexpr (e + 1 < kPairs) odd = gathered(std::integral_constant<int, e + 1>{});
+                const float q = (upper ? odd : even) + dpp_take<0x128, 0xf>(upper ? even : odd);   // row_ror:8
+                __hip_atomic_fetch_add(&sums[wave * kSums + e * 32 + lane], (double)q, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
-                quad[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
             });
             return;
         }
@@ -405,9 +416,10 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
         if constexpr (kQuads) {
             const int a = i / 4, b = j / 4;
             const int r = i % 4, rho = 2 * (r & 1) + r / 2;
-            const double* src = sums + (a * kGroups - a * (a - 1) / 2 + (b - a)) * 64 + 16 * rho + j % 4;
+            const int e2 = a * kGroups - a * (a - 1) / 2 + (b - a);   // the pair
+            const double* src = sums + (e2 / 2) * 64 + 16 * rho + 8 * (e2 % 2) + j % 4;
 #pragma unroll
-            for (int n = 0; n < 4; ++n) s += src[4 * n];
+            for (int q = 0; q < kWaves; ++q) s += src[q * kSums] + src[q * kSums + 4];
         } else {
             int src;
             if constexpr (kBlocks) {

@@ -42,6 +42,23 @@ def test_gram_of_wide_fp32_rows(W, P, off):
     assert np.array_equal(~np.isfinite(n.cpu().numpy()), member)
 
 
+@pytest.mark.parametrize("W", [17, 20, 24, 28])
+@pytest.mark.parametrize("P", [300007, 1 << 20])
+def test_gram_of_a_short_shard_is_the_same_every_run(W, P):
+    """A short shard's tiles are split evenly, so the sums are formed in one order: the same bits in double on every run.  Every
+    256 elements, a wave's share of a tile, have a scale of their own, so that an addition in double rounds and an order shows."""
+    gen = torch.Generator(device="cuda").manual_seed(W)
+    scale = torch.exp2(-torch.randint(0, 19, ((P + 255) // 256,), device="cuda", generator=gen).float()).repeat_interleave(256)[:P]
+    rows = [torch.randn(P, device="cuda", generator=gen) * scale for _ in range(W)]
+    first = None
+    for _ in range(6):
+        out = torch.empty(W, W, dtype=torch.float64, device="cuda")
+        star.star_group_gram(rows, out, **opts())
+        got = out.cpu().numpy()
+        first = got if first is None else first
+        assert np.array_equal(got, first)
+
+
 @pytest.mark.parametrize("W,U,y", [(17, 4, 8), (20, 8, 10), (24, 5, 18), (32, 6, 12)])
 def test_direct_norms_beside_the_update_of_wide_fp32_rows(W, U, y):
     """Direct norms on request in the pass of the collapsed update: state and norms against the oracle, with a pair of rows that

@@ -457,7 +457,8 @@ star_status star_plan_claims(int32_t workgroups, int32_t tiles_per_claim, int64_
  */
 star_status star_plan_even_split(int32_t workgroups, int64_t tiles, int64_t *first_tile, int32_t *count);
 
-/* Bytes of internal device workspace one call of this shape uses. */
+/* Bytes of internal device workspace one call of this shape uses at most (direct norm sums without an update need the
+ * most: partial sums of up to 240 updates). */
 size_t star_workspace_bytes(int64_t P, int32_t W, int32_t U);
 
 /* Text of the last error on the calling thread ("" if none). Never NULL. */

@@ -304,10 +304,12 @@ TableLayout table_layout(int U, int Wp) {
     return t;
 }
 
-size_t partial_doubles_needed(int Wp, int U, int grid_cap) {
+// `walk`: the call sums the norms directly without an update, up to 240 updates a launch (the others need no room for that: 8
+// rows, 128 updates 0.3 MB a slot instead of 1 MB).
+size_t partial_doubles_needed(int Wp, int U, int grid_cap, bool walk) {
     const size_t ng = (size_t)Wp * (Wp + 1) / 2;
-    const size_t useq = (size_t)std::min(U, std::max(star::walk_max_updates(), std::max(star::seq_max_updates(Wp, true),
-                                                                                       star::reduce_max_updates(Wp, true))));
+    const int most = std::max(star::seq_max_updates(Wp, true), star::reduce_max_updates(Wp, true));
+    const size_t useq = (size_t)std::min(U, walk ? std::max(most, star::walk_max_updates()) : most);
     // per-block partials of the larger of the two routes, plus the reduced Gram matrix
     return std::max(ng, useq) * (size_t)grid_cap + ng;
 }
@@ -549,6 +551,7 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
     const TableLayout lay = table_layout(U, Wp);
     const bool want_queue = how.want_queue;
     const bool need_slot = need_seq_tables || need_gram_coef || want_norms || want_queue;
+    const bool walk = route == star::Route::Seq && !update;
     std::unique_lock<std::mutex> lock(g_mu, std::defer_lock);
     Slot* slot = nullptr;
     std::vector<char> host_tables;   // no_alloc: the tables are built here and travel in kernel arguments
@@ -556,7 +559,7 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
     double* partials = nullptr;
     star::TileQueue* queue = nullptr;
     if (need_slot && no_alloc) {
-        const size_t need_partials = want_norms ? partial_doubles_needed(Wp, U, grid_cap) : 0;
+        const size_t need_partials = want_norms ? partial_doubles_needed(Wp, U, grid_cap, walk) : 0;
         if (lay.total > star::kScratchTableBytes || need_partials > star::kScratchPartialDoubles)
             return set_err(STAR_ERR_SHAPE, "the call needs more workspace than the fixed array of "
                                            "star_group_update_noalloc holds");
@@ -574,7 +577,7 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
     } else if (need_slot) {
         lock.lock();
         st = acquire_slot(device, (need_seq_tables || need_gram_coef) ? lay.total : 0,
-                          want_norms ? partial_doubles_needed(Wp, U, grid_cap) : 0, &slot);
+                          want_norms ? partial_doubles_needed(Wp, U, grid_cap, walk) : 0, &slot);
         if (st != STAR_OK) return st;
         h = static_cast<char*>(slot->host);
         d = static_cast<char*>(slot->dev);
@@ -754,7 +757,7 @@ star_status run_reduce(void* const* out_rows, int out_dtype, const void* const* 
     std::lock_guard<std::mutex> lock(g_mu);
     const TableLayout lay = table_layout(U, Wp);
     Slot* slot = nullptr;
-    st = acquire_slot(device, lay.total, want_norms ? partial_doubles_needed(Wp, U, grid_cap) : 0, &slot);
+    st = acquire_slot(device, lay.total, want_norms ? partial_doubles_needed(Wp, U, grid_cap, false) : 0, &slot);
     if (st != STAR_OK) return st;
     SlotRelease release{slot, stream};
     char* h = static_cast<char*>(slot->host);
@@ -838,7 +841,7 @@ star_status run_gram(const void* const* grad_rows, int grad_dtype, int64_t P, in
     if (st != STAR_OK) return st;
     std::lock_guard<std::mutex> lock(g_mu);
     Slot* slot = nullptr;
-    st = acquire_slot(device, 0, partial_doubles_needed(star::padded_rows(W), 1, star::kGridCap), &slot);
+    st = acquire_slot(device, 0, partial_doubles_needed(star::padded_rows(W), 1, star::kGridCap, false), &slot);
     if (st != STAR_OK) return st;
     SlotRelease release{slot, stream};
     a.P = P;
@@ -1045,7 +1048,7 @@ size_t star_workspace_bytes(int64_t P, int32_t W, int32_t U) {
     const int Wp = star::padded_rows(W);
     const int grid_cap = star::kGridCap;
     return std::max<size_t>(table_layout(U, Wp).total, 64 * 1024) +
-           sizeof(double) * partial_doubles_needed(Wp, U, grid_cap) + 256 /* tile queue */;
+           sizeof(double) * partial_doubles_needed(Wp, U, grid_cap, true) + 256 /* tile queue */;
 }
 
 const char* star_last_error(void) { return g_err.c_str(); }

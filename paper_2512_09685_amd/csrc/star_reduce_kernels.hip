@@ -142,26 +142,34 @@ size_t reduce_lds_bytes(int W, int U, bool norms) {
            (norms ? sizeof(double) * ((size_t)(kBlock / 64) * U + (size_t)U * kBlock) : 0);
 }
 
-// Long-lived workgroups per compute unit of an aggregation with norms in fixed assignment: enough for about 64 KB in flight,
-// at least two (32 bf16 rows, 16 groups, 32 Mi elements: one per unit 1.72 ms, two 0.91), except where a sweep over 1-32
-// rows, 1-8 groups and 1-60 M elements has something else ahead (us at 30 M elements, against that rule):
-//   fp32   one group of 7 and more rows, two groups of 12 and more, not on short shards: bound by memory alone, one
-//          (7 / 12 / 24 rows, one group 167 / 274 / 513 against 180 / 286 / 542; two groups, 20 rows 447 against 484);
-//          4 and 5 rows: two (4 rows, four groups 167 against 190)
-//   bf16   many groups: bound by the walk over the groups, as many as fit (8 groups of 12 / 20 / 24 / 28 rows 236 / 326 / 376 / 472
-//          against 273 / 521 / 585 / 659); few groups of 13 to 24 rows: three (16 rows, four groups 212 against 274);
-//          one group on a long shard: three with 8 and 9 rows (25 M: 83 against 91), two with 10 to 14 (12 rows 136 against 148)
+// Long-lived workgroups per compute unit of an aggregation with norms in fixed assignment.  Enough for about 64 KB of rows in
+// flight, at least two (32 bf16 rows, 16 groups, 32 Mi elements: one per unit 1.72 ms, two 0.91), with two exceptions,
+// from 1 to 4 per unit over 1-32 rows, 1-8 groups, three kinds of groups and 0.3-60 M elements on the same buffers.
+//  - Bound by memory (one or two groups, long shards) fewer in flight are better, as for the updates.  fp32, from 16 tiles a unit
+//    on: one with 8 and more rows for one group, 12 and more for two (30 M elements: one group of 8 / 24 rows 166 / 438 us, 178 /
+//    458 with two; two groups of 20 rows 433 against 467; but 3 M, 8 rows 25.1 against 23.6, and 10 M, 7 rows 56.7 against 54.2).
+//    Four and five rows, for which 64 KB would be four: two, with any groups (30 M, 4 rows, one / four groups 89 / 174 against
+//    95 / 194; 3 M, four groups 27.2 against 25.4; three and six rows are level).  bf16, one group, from 64 tiles a unit on: two
+//    (30 M, 8 / 12 rows 95 / 124 against 101 / 132; level at 10 M).
+//  - Bound by the walk over the groups (bf16 rows: half the bytes, the same arithmetic) more hide it while the shard is short,
+//    where the memory can still take them: six and more groups of up to 24 rows below 16 tiles a unit four (1 M, 8 groups of
+//    16 rows 21.2 us, 25.1 with two), beyond that, of 16 and more rows, three (10 M, 8 groups of 16 / 28 rows 131 / 179 against 145 /
+//    206, 30 M, of 24 472 against 509), up to 64 tiles a unit with six or seven (60 M, 6 groups of 24 rows 858 against 837); three
+//    to five groups of 16 to 24 rows three, below 16 tiles a unit only (3 M, 4 groups of 20 42.8 against 46.6; 30 M, 4 of 20
+//    326 against 315, 3 of 24 355 against 321).
 int sum_workgroups(int W, bool f32, int U, int64_t P, int num_cu) {
     const int64_t tiles = P / (4 * kBlock);
+    const bool from16 = tiles >= 16 * (int64_t)num_cu, from64 = tiles >= 64 * (int64_t)num_cu;
     const int wg_bytes = W * (f32 ? 16 : 8) * kBlock;
     const int rule = std::max(2, std::min(4, (64 * 1024 + wg_bytes - 1) / wg_bytes));
     if (f32) {
-        if (((U == 1 && W >= 7) || (U == 2 && W >= 12)) && tiles >= 16 * (int64_t)num_cu) return 1;
+        if (!from16) return rule;
+        if ((U == 1 && W >= 8) || (U == 2 && W >= 12)) return 1;
         return W == 4 || W == 5 ? 2 : rule;
     }
-    if (U >= 6) return W >= 28 ? 3 : 4;
-    if (U >= 3) return W >= 13 && W <= 24 ? 3 : rule;
-    if (U == 1 && tiles >= 64 * (int64_t)num_cu && W >= 8 && W <= 14) return W <= 9 ? 3 : 2;
+    if (U == 1) return from64 && W >= 8 ? 2 : rule;
+    if (U >= 6 && W <= 24 && !from16) return 4;
+    if (W >= 16 && (U >= 8 || (U >= 6 && !from64) || (U >= 3 && W <= 24 && !from16))) return 3;
     return rule;
 }
 

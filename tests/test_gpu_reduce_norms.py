@@ -12,7 +12,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("W,dtype,U,P", [(5, "f32", 3, 4097), (7, "f32", 1, (4 << 20) - 1), (8, "f32", 1, (4 << 20) + 1025),
                                          (12, "f32", 2, (4 << 20) + 3), (9, "bf16", 1, (16 << 20) + 1), (10, "bf16", 1, 16 << 20),
-                                         (13, "bf16", 3, 300001), (24, "bf16", 5, 5000), (20, "bf16", 6, 1024 * 1025), (28, "bf16", 7, 70001)])
+                                         (13, "bf16", 3, 300001), (24, "bf16", 5, 5000), (20, "bf16", 6, 1024 * 1025), (28, "bf16", 7, 70001),
+                                         (4, "f32", 1, (4 << 20) + 1), (16, "bf16", 6, (4 << 20) + 1), (24, "bf16", 4, (4 << 20) - 1),
+                                         (16, "bf16", 7, 16 << 20), (28, "bf16", 8, (16 << 20) + 3)])
 def test_reduce_with_norms(W, dtype, U, P):
     rng = np.random.default_rng(W * 100 + U)
     gen = torch.Generator(device="cuda").manual_seed(P)

@@ -463,8 +463,9 @@ hipError_t launch_mfma_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_o
                                 UPDATE ? Traffic::Update : Traffic::ReadOnly, tiles);
     // The norms of 17 to 32 bf16 rows: one workgroup per unit, whose look-ahead keeps 64 KB in flight, and the tiles split
     // evenly up to 256 a workgroup (3 / 30 / 60 M elements, 24 rows: 36.8 / 224 / 426 against 38.8 / 232 / 438 us, 32 rows:
-    // 46 / 294 / 566 against 48 / 302 / 575; 120 M, 32 rows: 1127 against 1119).
-    if (!UPDATE && WIDE && kBf16 && tiles <= 256 * (int64_t)num_cu) {
+    // 46 / 294 / 566 against 48 / 302 / 575; 120 M, 32 rows: 1127 against 1119), up to 20 rows up to 128 (20 rows, 26 / 40 M 162 /
+    // 258 against 169 / 249; 17 rows, 60 M 335 against 325).
+    if (!UPDATE && WIDE && kBf16 && tiles <= (W <= 20 ? 128 : 256) * (int64_t)num_cu) {
         g.claim = -1;
         g.grid = g.span_g = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(num_cu, grid_cap), tiles));
     }

@@ -370,7 +370,7 @@ struct Launch {
     bool mfma = false;        // collapsed route: Gram matrix on the matrix cores
     int Wp = 1;               // row count of the kernel instantiation
     bool want_queue = false;  // the shard is long enough for queue order
-    bool queue_order = false; // the main kernel really takes its tiles from the queue (aligned buffers assumed)
+    bool queue_order = false; // the main kernel really takes its tiles from the queue
     bool seq_inline = false;  // step-by-step route: tables in the kernel arguments
     int umax = 1;             // step-by-step route: updates per launch
     int launches = 1;
@@ -443,8 +443,8 @@ Launch decide(const star::Plan& plan, int grad_dtype, bool update, bool want_nor
         l.finishing = gram ? 2 : 0;
     } else {
         // Norms alone have a kernel of their own, which takes up to 240 updates per pass over the rows (32 updates of 8
-        // rows, 25 M elements: one pass instead of two).  (A shard of a few thousand elements is one or two workgroups
-        // either way; there the stream is cut as that of the update, which keeps the launches star_plan_choice reports.)
+        // rows, 25 M elements: one pass instead of two).  Below 4096 elements the stream is still cut as that of the update
+        // (64 updates of 16 rows: three launches where the walk could take one).
         l.umax = update || tiny ? star::seq_max_updates(l.Wp, want_norms) : star::walk_max_updates();
         l.seq_inline = star::tables_fit_inline(plan.U, l.Wp) && plan.U <= l.umax;
         l.launches = (plan.U + l.umax - 1) / l.umax;
@@ -570,9 +570,10 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
         partials = reinterpret_cast<double*>(d + star::kScratchTableBytes);
         host_tables.assign(lay.total, 0);
         h = host_tables.data();
-        // the array keeps what the last call left: where the call takes tiles from it, the queue must start at zero
-        // (a call that failed half-way may not have put it back); tables and partials are written before they are
-        // read.  Other calls save the launch (one report of 25.6 M fp32 elements applied with its norm: 97.2 -> 96.1 us)
+        // the array keeps what the last call left: where a kernel is handed the queue, it must start at zero (a call that
+        // failed half-way may not have put it back; whether the kernel then takes tiles is up to its launcher, and the last
+        // launch of a long step-by-step stream may, although the first does not).  Tables and partials are written before they
+        // are read.  Other calls save the launch (one report of 25.6 M fp32 elements applied with its norm: 97.2 -> 96.1 us)
         if (want_queue || how.mfma) STAR_HIP(star::launch_queue_clear(queue, stream));
     } else if (need_slot) {
         lock.lock();

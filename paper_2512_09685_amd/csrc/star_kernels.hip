@@ -514,7 +514,8 @@ hipError_t launch_seq_t(const SeqArgs& a, int num_cu, int grid_cap, int* grid_ou
     // (a single update of fp32 rows with its norm is bound by memory alone and, off the short shards, is fastest with
     // one or two workgroups per unit instead of the two to four that 64 KB in flight ask for: 20 / 32 M elements, 1 row
     // 70 / 113 against 77 / 121 us, 2 rows 85 / 138 against 93 / 150, 4 rows 109 / 167 against 120 / 188; 12 M, 8 rows 106
-    // against 109; 3 M elements: level or behind)
+    // against 109; 3 M elements: level or behind.  Three rows lie between: two up to 64 tiles a unit, 6 / 12 M 34.0 / 62.1 us
+    // against 35.6 / 63.4 with one; one beyond, 20 / 30 M 100 / 145 against 101 / 151)
     int one_report = 0;
     if (NORMS && !COLLAPSED && std::is_same<R, RowF32>::value && a.U == 1) {
         const int64_t tiles = a.P / (4 * kBlock);

@@ -281,7 +281,7 @@ def test_plan_choice_gram_route_for_few_rows():
 def test_plan_choice_short_streams_with_norms_take_the_literal_kernel():
     """Update with norms: up to 48 multiply-adds of stream (sum of y_u + 4) on a shard of up to 4 Mi elements (bf16
     rows: 16 Mi) the literal kernel (direct norms in the same pass, one finishing launch); with 17 to 32 fp32 rows up to 112
-    multiply-adds at every length."""
+    multiply-adds and three updates at every length, longer streams of small groups the collapsed update with direct norms."""
     def choice(P, W, dt, U, norms=True):
         us = star.UpdateStream(np.arange(0, U * W + 1, W, dtype=np.int32), np.tile(np.arange(W, dtype=np.int32), U))
         return star.star_plan_choice(P, W, dt, us, lr=0.1, momentum_coef=0.9, want_norms=norms)
@@ -301,6 +301,14 @@ def test_plan_choice_short_streams_with_norms_take_the_literal_kernel():
     c = choice(64 * Mi, 32, "f32", 4)                  # 144: collapsed update with the norm walk (limit 4 * 32 + 48 on y_u + 1)
     assert c["kernel"] == star.KERNEL_SEQ and c["collapsed_update"] == 1
     assert choice(64 * Mi, 32, "bf16", 3)["kernel"] == star.KERNEL_AFFINE_MFMA
+    # up to 112 multiply-adds in three updates, and in more of them
+    for sizes, P, collapsed in (([20] * 3, 64 * Mi, 0), ([20, 20, 20], Mi, 0), ([12] * 4, 64 * Mi, 1), ([10] * 8, 64 * Mi, 1),
+                                ([10] * 8, Mi, 1), ([16] * 5, 8 * Mi, 1), ([20, 16, 16, 20], Mi, 1), ([8] * 4, Mi, 0), ([8] * 4, 5 * Mi, 1)):
+        us = star.UpdateStream(np.cumsum([0] + sizes).astype(np.int32),
+                               np.concatenate([(np.arange(s) + 7 * k) % 20 for k, s in enumerate(sizes)]).astype(np.int32))
+        c = star.star_plan_choice(P, 20, "f32", us, lr=0.1, momentum_coef=0.9, want_norms=True)
+        assert c["rows_used"] > 16 and c["fma_seq"] <= 112
+        assert c["kernel"] == star.KERNEL_SEQ and c["launches"] == 1 and c["collapsed_update"] == collapsed, (sizes, P, c)
 
 
 def test_plan_choice_direct_norms_option():

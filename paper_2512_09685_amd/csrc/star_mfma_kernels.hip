@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
     // pairs of the K = W / 4 groups, by the instruction that multiplies 16 independent 4x4 blocks (here: 16 elements).
     // That is 480 flops per element for 20 rows and 672 for 24, where the three 16x16 blocks below take 1536 for any
     // count, at three quarters of their rate (measured: 11 to 13 cycles for 512 flops against 34 for 2048).  25.6 M
-    // elements, 20 / 24 rows: norms alone 319 / 396 us, 399 / 447 by blocks, update with norms 470 / 542 against 532 / 574.
+    // elements, 20 / 24 rows: norms alone 317 / 393 us, 419 / 458 by blocks, update with norms 448 / 536 against 512 / 579.
     // 28 and 32 rows need 28 and 36 pairs, whose accumulators allow one wave per SIMD only: 686 / 825 us against
     // 651 / 722 by blocks.  (One wave per SIMD with a tile of look-ahead was tried for 24 rows as well: 573.)
     // Four accumulator registers a pair leave no room for sums in double beside them; those are kept in LDS, one

@@ -26,7 +26,7 @@ CXX_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-Wextra", "-D__HIP_PLATFORM
 INCLUDES = ["-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-I" + os.path.join(ROCM, "include")]
 
 HIP_SOURCES = ["star_kernels.hip", "star_reduce_kernels.hip", "star_mfma_kernels.hip", "star_norm_kernels.hip",
-               "star_scratch.hip"]
+               "star_norm_mma_f32.hip", "star_norm_mma_bf16.hip", "star_scratch.hip"]
 CXX_SOURCES = ["star_api.cpp", "star_plan.cpp", "star_select.cpp"]
 
 

@@ -688,6 +688,8 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
             a.inl = &inl;
             a.cf = how.collapsed_in_seq ? &cf : nullptr;
             a.U = n;
+            a.members = 0;
+            for (int u = u0; u < u0 + n; ++u) a.members += plan.ysize[u];
             a.mu = (float)plan.mu;
             a.wd = (float)plan.wd;
             a.P = P;

@@ -132,6 +132,7 @@ struct SeqArgs {
     const InlineTables* inl;  // host; used when coef is null
     const AffCoef* cf;     // host, or null; not null: the update is applied once, as this map (17-32 fp32 rows, update + norms)
     int32_t U;             // updates in this launch
+    int32_t members;       // their groups' sizes added up
     float mu, wd;
     int64_t P;
     int32_t head;          // elements before the pointers and P (0 to 63), see rest_element

@@ -14,24 +14,10 @@
 //     up to 240 updates need one pass over the rows, and several workgroups fit on a compute unit to hide the loads.
 // Measured at that size: 203 us (195 with the fp32 sums over eight lanes), 601 with the step-by-step kernel this replaced (one
 // LDS slot per thread and update, hence two passes for 32 updates and two waves per SIMD; coefficients from LDS at their
-// use; 4 elements per thread).  Light rows pay more: 4 / 1 rows, 32 updates 122 / 73 against 112 / 66 (403 / 256 by the step-by-step kernel).
-#include "star_device.h"
+// use; 4 elements per thread); calls of that size go to norm_mma_kernel now (norms_on_matrix_cores).  Light rows pay more: 4 / 1 rows, 32 updates 122 / 73 against 112 / 66 (403 / 256 by the step-by-step kernel).
+#include "star_norm_mma.h"
 
 namespace star {
-
-struct WalkKernelArgs {
-    RowPtrs rows;
-    const float* coef;      // [U][W], or null: the tables are in `inl`
-    const uint32_t* mask;   // [U]
-    double* partials;
-    int64_t P;
-    int32_t U, head;
-    int32_t share;          // updates per workgroup, see launch_walk_t
-    InlineTables inl;
-};
-
-// Constant address space: uniform reads become scalar loads.  The tables are written before the launch and not during it.
-#define STAR_CONST __attribute__((address_space(4)))
 
 // Chunks of 4 elements a thread holds of every row.  Two also with 17 to 32 rows, although only two waves (32 rows: one)
 // then fit on a SIMD: a member test for 4 multiply-adds costs more than the third wave brings (20 rows, 5 M elements,
@@ -204,7 +190,7 @@ int walk_workgroups_per_cu(int W, bool f32, int U) {
 }
 
 template <int W, class R>
-hipError_t launch_walk_t(const SeqArgs& a, int num_cu, int grid_cap, int* grid_out, hipStream_t s) {
+hipError_t launch_walk_t(WalkKernelArgs& a, int num_cu, int grid_cap, int* grid_out, hipStream_t s) {
     // Long-lived workgroups sweep the shard together, for every stream: the work queue is behind even where one or two
     // updates leave the pass bound by memory (1 fp32 row, 25.6 M elements, 1 update: 22 against 39 us; 16 rows, 2
     // updates: 232 against 252; 4 rows, 100 M elements: 241 against 246).
@@ -218,19 +204,27 @@ hipError_t launch_walk_t(const SeqArgs& a, int num_cu, int grid_cap, int* grid_o
     const int parts = std::max(1, std::min(num_cu / grid, (a.U + 3) / 4));
     const int share = ((a.U + parts - 1) / parts + 3) / 4 * 4;
     *grid_out = grid;
-    WalkKernelArgs k;
-    k.rows = a.rows;
-    k.coef = a.coef;
-    k.mask = a.mask;
-    k.partials = a.partials;
-    k.P = a.P;
-    k.U = a.U;
-    k.share = share;
-    k.head = a.head;
-    k.inl = a.coef ? InlineTables() : *a.inl;
+    a.share = share;
     hipLaunchKernelGGL((norm_walk_kernel<W, R>), dim3(grid, (a.U + share - 1) / share), dim3(kBlock),
-                       walk_lds_bytes(std::min(a.U, share)), s, k);
+                       walk_lds_bytes(std::min(a.U, share)), s, a);
     return hipGetLastError();
+}
+
+// Whether the matrix cores take the call (norm_mma_kernel): by what either kernel takes on 30 M elements once its arithmetic
+// bounds it, in us.  The walk pays for every update, every coefficient it loads and every member (fp32 rows, 4 / 8 / 13 of them, 128
+// updates of half the rows: 486 / 822 / 1163; of two: 396 / 587 / 727), more from 14 rows on, where fewer waves fit (16 / 24: 1660 / 2483,
+// 1378 / 1836), and with 32 rows, where one does (6002, 4522).  The matrix cores pay for 16 updates at a time: fp32 rows by row groups
+// of four (1 / 2 / 4 / 8 of them, 128 updates: 389, 622, 1065, 2074), bf16 rows hardly by those (255, 293, 529, 814).  Where memory bounds
+// both they are level, so the rule is good there too.  Both sides of it, 1 to 32 rows, 1 to 128 updates, groups of one or two and of half
+// the rows, 2 / 8 / 30 M elements: fp32 rows 1.45 / 1.40 / 1.29 times ahead on the mean where it says so, bf16 rows 1.56 / 1.91 / 1.94, at worst 6 %
+// behind.  Shorter shards have a few tiles a wave, and the kernel's long code is fetched for those: 0.3 M elements, 4 rows, 64
+// updates 41 against 25 us, 14 to 32 fp32 rows up to twice ahead, as many bf16 rows between 20 % behind and twice ahead.
+bool norms_on_matrix_cores(int Wp, bool f32, int U, int members, int64_t P) {
+    if (P < (f32 && Wp > 13 ? 1 << 18 : 1 << 20)) return false;
+    double walk = Wp <= 13 ? U * (1.6 + 0.25 * Wp) + 0.6 * members : U * (1.6 + 0.45 * Wp) + 0.55 * members;
+    if (Wp > 28 && U > 4) walk *= 1.8;
+    const int groups = (Wp + 3) / 4, blocks = (U + 15) / 16;
+    return walk > (f32 ? blocks * (22 + 28 * groups) * (Wp > 4 ? 1.0 : 1.1) : 15.0 + blocks * (26 + 4 * groups));
 }
 
 }  // namespace
@@ -240,11 +234,24 @@ int walk_max_updates() { return 60 * 1024 / (int)walk_lds_bytes(4) * 4; }   // s
 hipError_t launch_norm_walk(int Wp, int dtype, const SeqArgs& a, int num_cu, int grid_cap, int* grid_out,
                             hipStream_t s) {
     if (a.U < 1 || a.U > walk_max_updates()) return hipErrorInvalidValue;
+    WalkKernelArgs k;
+    k.rows = a.rows;
+    k.coef = a.coef;
+    k.mask = a.mask;
+    k.partials = a.partials;
+    k.P = a.P;
+    k.U = a.U;
+    k.share = 0;
+    k.head = a.head;
+    k.inl = a.coef ? InlineTables() : *a.inl;
+    if (norms_on_matrix_cores(Wp, dtype == STAR_F32, a.U, a.members, a.P))
+        return dtype == STAR_F32 ? launch_norm_mma_f32(k, Wp, num_cu, grid_cap, grid_out, s)
+                                 : launch_norm_mma_bf16(k, Wp, num_cu, grid_cap, grid_out, s);
     switch (Wp) {
 #define X(N)                                                                                      \
     case N:                                                                                       \
-        return dtype == STAR_F32 ? launch_walk_t<N, RowF32>(a, num_cu, grid_cap, grid_out, s)     \
-                                 : launch_walk_t<N, RowBf16x4>(a, num_cu, grid_cap, grid_out, s);
+        return dtype == STAR_F32 ? launch_walk_t<N, RowF32>(k, num_cu, grid_cap, grid_out, s)     \
+                                 : launch_walk_t<N, RowBf16x4>(k, num_cu, grid_cap, grid_out, s);
         STAR_FOR_EACH_W(X)
 #undef X
         default: return hipErrorInvalidValue;

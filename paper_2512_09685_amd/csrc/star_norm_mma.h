@@ -1,0 +1,331 @@
+// gfx950 kernel: direct sums of gbar_u^2 on the matrix cores, see norm_mma_kernel.  A header, because the two row types are
+// compiled as two files: 32 kernels each, about a minute.
+#pragma once
+
+#include "star_device.h"
+
+namespace star {
+
+// Constant address space: uniform reads become scalar loads.  The tables are written before the launch and not during it.
+#define STAR_CONST __attribute__((address_space(4)))
+
+struct WalkKernelArgs {
+    RowPtrs rows;
+    const float* coef;      // [U][W], or null: the tables are in `inl`
+    const uint32_t* mask;   // [U]
+    double* partials;
+    int64_t P;
+    int32_t U, head;
+    int32_t share;          // updates per workgroup, see launch_walk_t
+    InlineTables inl;
+};
+
+hipError_t launch_norm_mma_f32(WalkKernelArgs& k, int Wp, int num_cu, int grid_cap, int* grid_out, hipStream_t s);
+hipError_t launch_norm_mma_bf16(WalkKernelArgs& k, int Wp, int num_cu, int grid_cap, int* grid_out, hipStream_t s);
+
+// gbar is a product, [updates x rows] times [rows x elements], and the fp32 matrix instructions multiply at twice the rate
+// the vector ALUs reach without packed instructions; what is left for those are the squares.
+//   v_mfma_f32_16x16x4_f32 takes 16 updates x 4 rows from A and 4 rows x 16 elements from B.  Lane l feeds row 4 s + l / 16
+// and the element l % 16 of its 16, so that a lane's 16-byte load, 4 or 8 elements of one row, is the B operand of 4 or 8
+// instructions as it stands: no transposition, no LDS.  Lane l of the result holds updates 4 (l / 16) + r, r = 0 .. 3, of
+// one element, so every lane squares and sums on its own, and the lanes meet once, when the kernel ends.
+//   The multiplication is dense: a row that is no member of a group enters with coefficient zero.  That is the same sum, except
+// where the row holds an infinity or a NaN; tiles that do are found beforehand (x * 0 is not 0) and walked member by member.
+//   bf16 rows: v_mfma_f32_16x16x32_bf16, at 16 times the rate.  The coefficients stay fp32 numbers, as the sum of three bf16 pieces
+// each (products of two bf16 values are exact in fp32, where they are added).  A lane's eight places of the reduction are four
+// pairs of rows, once for every piece, packed from the loads of two row groups by one instruction an element.
+//   Memory bounds it up to about 32 updates of 8 fp32 rows or 16 of 16, and bf16 rows up to 64 updates; beyond, the matrix instructions and
+// the squares do, which overlap little.  25.6 M elements, norm_walk_kernel -> this one: 8 fp32 rows, 32 updates of 4.5 members 198 -> 158 us (the
+// reads alone 120), 16 rows, 32 updates 424 -> 283, 32 rows, 16 updates 717 -> 488 (the reads 481); 30 M, bf16 rows: 8 rows, 32 updates 217 -> 93,
+// 16 rows, 64 updates 840 -> 227, 32 rows, 64 updates 2703 -> 422.  bf16 rows through the fp32 instructions: 167, 540, 1042.
+//   Largest error of a norm against 64 bits, 1 to 32 rows, 3 to 240 updates: 9.7e-8 either way for fp32 rows, bf16 rows 1.05e-7 either way.
+typedef float acc4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+
+// 16 bytes of a row: one load of a lane
+template <class R>
+struct WideLoad;
+template <>
+struct WideLoad<RowF32> {
+    static constexpr int E = 4;
+    typedef f32x4 vec;
+    static __device__ __forceinline__ vec load(const char* p) {
+        return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p));
+    }
+};
+template <>
+struct WideLoad<RowBf16x4> {
+    static constexpr int E = 8;
+    typedef u32x4 vec;
+    static __device__ __forceinline__ vec load(const char* p) {
+        return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(p));
+    }
+};
+
+// The three bf16 values that add up to an fp32 coefficient: its upper eight bits, the next eight, the rest.
+__device__ __forceinline__ uint32_t coef_piece(float c, const int piece) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        if (i < piece) c -= __uint_as_float(__float_as_uint(c) & 0xffff0000u);   // exact
+    return __float_as_uint(c) >> 16;
+}
+
+// 16-byte loads per lane and row group of a tile: about 8 KB of a wave in flight, and as much again from the look-ahead.
+constexpr int mma_units(int KS) { return KS == 1 ? 8 : (KS == 2 ? 4 : (KS <= 4 ? 2 : 1)); }
+
+// Waves per SIMD the registers are cut for: three where that spills none.
+constexpr int mma_waves(int KS, int NB) { return NB == 1 || (NB == 2 && KS <= 5) ? 3 : 2; }
+
+// KS row groups of four, NB blocks of 16 updates
+template <int KS, int NB, class R>
+__global__ __launch_bounds__(kBlock, mma_waves(KS, NB)) void norm_mma_kernel(const WalkKernelArgs args, const int W) {
+    typedef WideLoad<R> L;
+    typedef typename L::vec vec_t;
+    constexpr int E = L::E, CH = mma_units(KS);
+    constexpr int kUnit = 16 * E;            // elements of a unit: 16 lanes, one load each
+    constexpr int kTile = kUnit * CH;        // elements of a wave's tile
+    constexpr int kRowWaves = kBlock / 64;
+    const int u0 = (int)blockIdx.y * args.share, U = min(args.U - u0, args.share);
+    const auto* const in = (const STAR_CONST WalkKernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    const STAR_CONST float* coef = (const STAR_CONST float*)args.coef;
+    const STAR_CONST uint32_t* mask = (const STAR_CONST uint32_t*)args.mask;
+    if (!args.coef) {
+        coef = in->inl.coef;
+        mask = in->inl.mask;
+    }
+    coef += u0 * W;
+    mask += u0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int quarter = lane >> 4, col = lane & 15;
+
+    // operand A: zero beyond the last update and the last row
+    auto coef_at = [&](const int u, const int s) {
+        const int w = 4 * s + quarter;
+        return s < KS && u < U && w < W ? coef[u * W + w] : 0.0f;
+    };
+    constexpr bool BF = std::is_same<R, RowBf16x4>::value;
+    constexpr int kPairs = (KS + 1) / 2, kSteps = BF ? (3 * kPairs + 3) / 4 : KS;
+    typedef typename std::conditional<BF, bf16x8, float>::type operand_t;
+    operand_t a[NB][kSteps];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int u = 16 * b + col;
+        if constexpr (BF) {
+#pragma unroll
+            for (int i = 0; i < kSteps; ++i) {
+                u32x4 packed;
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    const int slot = 4 * i + p, pair = slot % kPairs;
+                    const uint32_t lo = slot < 3 * kPairs ? coef_piece(coef_at(u, 2 * pair), slot / kPairs) : 0u;
+                    const uint32_t hi = slot < 3 * kPairs ? coef_piece(coef_at(u, 2 * pair + 1), slot / kPairs) : 0u;
+                    packed[p] = hi << 16 | lo;
+                }
+                a[b][i] = __builtin_bit_cast(bf16x8, packed);
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < KS; ++s) a[b][s] = coef_at(u, s);
+        }
+    }
+    const char* row[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) row[s] = reinterpret_cast<const char*>(in->rows.p[4 * s + quarter]);
+
+    double sum[NB][4];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum[b][r] = 0.0;
+
+    const int64_t P = args.P, nchunk = P / E;   // chunks: one lane's load
+    const int64_t ntile = (nchunk + kTile / E - 1) / (kTile / E);
+
+    // 64 elements, one per lane (element(lane) < 0: none), group by group and member by member
+    auto walk = [&](auto&& element) {
+        const int64_t j = element();
+        float g[4 * KS];
+#pragma unroll
+        for (int w = 0; w < 4 * KS; ++w) g[w] = 0.0f;
+        if (j != INT64_MIN) {
+#pragma unroll
+            for (int w = 0; w < 4 * KS; ++w) g[w] = R::load1(in->rows.p[w], j);
+        }
+        for (int u = 0; u < U; ++u) {
+            const uint32_t m = mask[u];
+            float gb = 0.0f;
+#pragma unroll
+            for (int w = 0; w < 4 * KS; ++w)   // (no mask bit is set beyond the last row)
+                if ((m >> w) & 1u) gb = __builtin_fmaf(coef[u * W + w], g[w], gb);
+            const double s = wave_sum_to_lane63((double)(gb * gb));
+            const int lo = __builtin_amdgcn_readlane((int)__double2loint(s), 63);
+            const int hi = __builtin_amdgcn_readlane((int)__double2hiint(s), 63);
+            const double t = lane == 16 * ((u >> 2) & 3) ? __hiloint2double(hi, lo) : 0.0;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if ((u >> 4) == b && (u & 3) == r) sum[b][r] += t;
+        }
+    };
+
+    auto fetch = [&](const int64_t tile, vec_t (&x)[CH][KS]) {
+        const int64_t c0 = tile * (kTile / E) + col;
+        if ((tile + 1) * (kTile / E) <= nchunk) {
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+#pragma unroll
+                for (int s = 0; s < KS; ++s) x[c][s] = L::load(row[s] + (c0 + 16 * c) * 16);
+        } else {   // the last tile: lanes beyond the end read the last chunk and hold zeros
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const int64_t at = c0 + 16 * c, from = at < nchunk ? at : nchunk - 1;
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    x[c][s] = L::load(row[s] + from * 16);
+                    if (at >= nchunk) x[c][s] = vec_t{};
+                }
+            }
+        }
+    };
+    const int64_t step = (int64_t)gridDim.x * kRowWaves;
+    int64_t tile = (int64_t)blockIdx.x * kRowWaves + wave;
+    vec_t next[CH][KS];
+    if (tile < ntile) fetch(tile, next);
+    for (; tile < ntile; tile += step) {
+        vec_t x[CH][KS];
+        // an infinity or a NaN among them: fp32 x * 0 is NaN then, bf16 an exponent of all ones
+        float odd = 0.0f;
+        u16x2 most = {0, 0};
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                x[c][s] = next[c][s];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if constexpr (BF)
+                        most = __builtin_elementwise_max(most, __builtin_bit_cast(u16x2, x[c][s][k] & 0x7fff7fffu));
+                    else
+                        odd = __builtin_fmaf(x[c][s][k], 0.0f, odd);
+                }
+            }
+        if (tile + step < ntile) fetch(tile + step, next);
+        const bool spoilt = BF ? most[0] >= 0x7f80 || most[1] >= 0x7f80 : odd != odd;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(spoilt) != 0, 0)) {
+            for (int i = 0; i < kTile / 64; ++i)
+                walk([&]() {
+                    const int64_t j = tile * kTile + 64 * i + lane;
+                    return j < nchunk * E ? j : INT64_MIN;
+                });
+            continue;
+        }
+        static_for<0, CH>([&](auto cc) {
+            constexpr int C = decltype(cc)::value;
+            static_for<0, E / 4>([&](auto hc) {   // four elements of a lane at a time: four squares in fp32
+                constexpr int H = decltype(hc)::value;
+                uint32_t pk[4][kPairs];   // two rows' values of one element
+                if constexpr (BF) {
+                    static_for<0, 4>([&](auto kc) {
+                        constexpr int K = decltype(kc)::value, D = 2 * H + K / 2;
+                        static_for<0, kPairs>([&](auto pc) {
+                            constexpr int S = 2 * decltype(pc)::value, T = S + 1 < KS ? S + 1 : S;
+                            pk[K][S / 2] = __builtin_amdgcn_perm(x[C][T][D], x[C][S][D], K & 1 ? 0x07060302u : 0x05040100u);
+                        });
+                    });
+                }
+                static_for<0, NB>([&](auto bc) {
+                    constexpr int B = decltype(bc)::value;
+                    acc4 d[4];
+                    static_for<0, 4>([&](auto kc) { d[decltype(kc)::value] = acc4{0.0f, 0.0f, 0.0f, 0.0f}; });
+                    static_for<0, kSteps>([&](auto sc) {
+                        constexpr int S = decltype(sc)::value;
+                        static_for<0, 4>([&](auto kc) {
+                            constexpr int K = decltype(kc)::value;
+                            if constexpr (BF) {
+                                const u32x4 y = {pk[K][(4 * S) % kPairs], pk[K][(4 * S + 1) % kPairs], pk[K][(4 * S + 2) % kPairs],
+                                                 pk[K][(4 * S + 3) % kPairs]};
+                                d[K] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[B][S], __builtin_bit_cast(bf16x8, y), d[K], 0, 0,
+                                                                               0);
+                            } else {
+                                d[K] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[B][S], x[C][S][K], d[K], 0, 0, 0);
+                            }
+                        });
+                    });
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float sq = 0.0f;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) sq = __builtin_fmaf(d[k][r], d[k][r], sq);
+                        sum[B][r] += (double)sq;
+                    }
+                });
+            });
+        });
+    }
+    const int64_t tail = P - nchunk * E, nrest = args.head + tail;   // at most 63 + 7 elements: the first wave's
+    if (blockIdx.x == 0 && wave == 0)
+        for (int64_t r0 = 0; r0 < nrest; r0 += 64)
+            walk([&]() {
+                const int64_t r = r0 + lane;
+                return r >= nrest ? INT64_MIN : (r < args.head ? r - args.head : nchunk * E + (r - args.head));
+            });
+
+    // 16 lanes hold parts of the same four updates: summed within the 16, then over the waves, in a fixed order
+    __shared__ double total[kRowWaves][16 * NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            double q = sum[b][r];
+            q += dpp_take<0xB1, 0xf>(q);    // quad_perm [1,0,3,2]
+            q += dpp_take<0x4E, 0xf>(q);    // quad_perm [2,3,0,1]
+            q += dpp_take<0x141, 0xf>(q);   // row_half_mirror
+            q += dpp_take<0x140, 0xf>(q);   // row_mirror
+            if (col == 0) total[wave][16 * b + 4 * quarter + r] = q;
+        }
+    __syncthreads();
+    for (int u = threadIdx.x; u < U; u += kBlock) {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < kRowWaves; ++q) s += total[q][u];
+        args.partials[(int64_t)(u0 + u) * gridDim.x + blockIdx.x] = s;
+    }
+}
+
+template <int KS, class R>
+hipError_t launch_mma_k(WalkKernelArgs& k, int W, int num_cu, int grid_cap, int* grid_out, hipStream_t s) {
+    constexpr int kTile = 16 * WideLoad<R>::E * mma_units(KS) * (kBlock / 64);   // elements of a workgroup's tile
+    const int64_t tiles = std::max<int64_t>(1, (k.P + kTile - 1) / kTile);
+    // More than 64 updates, or a shard of fewer tiles than units: the updates are shared out over workgroups, in blocks of 16.
+    const int blocks = (k.U + 15) / 16;
+    const int parts = std::max((blocks + 3) / 4, (int)std::min<int64_t>(blocks, std::max<int64_t>(1, num_cu / tiles)));
+    const int nb = (blocks + parts - 1) / parts;
+    k.share = 16 * nb;
+    // as many workgroups as fit, long-lived (8 rows, 32 updates, 25.6 M elements, 1 / 2 / 3 / 4 per unit: fp32 192 / 164 / 160 / 160 us)
+    const int grid = (int)std::min<int64_t>(tiles, std::min(mma_waves(KS, nb) * num_cu, grid_cap));
+    *grid_out = grid;
+    const dim3 wg(grid, (k.U + k.share - 1) / k.share);
+    switch (nb) {
+#define X(N) case N: hipLaunchKernelGGL((norm_mma_kernel<KS, N, R>), wg, dim3(kBlock), 0, s, k, W); break;
+        X(1) X(2) X(3) X(4)
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+template <class R>
+hipError_t launch_mma(WalkKernelArgs& k, int Wp, int num_cu, int grid_cap, int* grid_out, hipStream_t s) {
+    switch ((Wp + 3) / 4) {
+#define X(N) \
+    case N: return launch_mma_k<N, R>(k, Wp, num_cu, grid_cap, grid_out, s);
+        X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace star

@@ -825,8 +825,8 @@ star_status run_gram(const void* const* grad_rows, int grad_dtype, int64_t P, in
     if (grad_dtype != STAR_F32 && grad_dtype != STAR_BF16) return set_err(STAR_ERR_DTYPE, "unknown gradient dtype");
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
     if (P == 0) {
-        hipError_t e0 = star::launch_gram_unpack(nullptr, W, W, gram_out, stream);
-        return e0 == hipSuccess ? STAR_OK : hip_fail(e0, "launch of the Gram unpack kernel");
+        hipError_t e0 = star::launch_reduce_gram(nullptr, 0, W, W, gram_out, stream);
+        return e0 == hipSuccess ? STAR_OK : hip_fail(e0, "launch of the Gram reduction");
     }
     star::AffArgs a;
     std::memset(&a, 0, sizeof a);
@@ -857,12 +857,8 @@ star_status run_gram(const void* const* grad_rows, int grad_dtype, int64_t P, in
     hipError_t e = mfma ? star::launch_affine_mfma(Wp, grad_dtype, false, a, num_cu, star::kGridCap, &grid, stream)
                         : star::launch_affine(Wp, grad_dtype, false, true, a, num_cu, star::kGridCap, &grid, stream);
     if (e != hipSuccess) return hip_fail(e, "launch of the Gram kernel");
-    const int ng = Wp * (Wp + 1) / 2;
-    double* gamma = slot->partials + (size_t)ng * grid;
-    e = star::launch_reduce(slot->partials, ng, grid, gamma, nullptr, stream);
+    e = star::launch_reduce_gram(slot->partials, grid, Wp, W, gram_out, stream);
     if (e != hipSuccess) return hip_fail(e, "launch of the Gram reduction");
-    e = star::launch_gram_unpack(gamma, Wp, W, gram_out, stream);
-    if (e != hipSuccess) return hip_fail(e, "launch of the Gram unpack kernel");
     return STAR_OK;
 }
 

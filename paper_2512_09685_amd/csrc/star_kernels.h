@@ -214,8 +214,9 @@ hipError_t launch_reduce(const double* partials, int n_out, int grid, double* su
 hipError_t launch_gram_norms(const double* gamma, const double* coef, int U, int Wp, float* norms_out,
                              hipStream_t s);
 
-// Packed upper triangle over Wp rows [Wp(Wp+1)/2] -> full symmetric [W][W], W <= Wp (all zero when gamma is null).
-hipError_t launch_gram_unpack(const double* gamma, int Wp, int W, double* out, hipStream_t s);
+// The same for the Gram matrix: partials of the packed upper triangle over Wp rows [Wp(Wp+1)/2][grid] -> full symmetric [W][W],
+// W <= Wp (all zero with a grid of 0).
+hipError_t launch_reduce_gram(const double* partials, int grid, int Wp, int W, double* out, hipStream_t s);
 
 hipError_t launch_fill(float* dst, int64_t n, float value, hipStream_t s);
 

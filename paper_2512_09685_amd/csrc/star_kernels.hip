@@ -409,22 +409,30 @@ __global__ __launch_bounds__(kBlock) void seq_kernel(float* __restrict__ params,
 }
 
 // ================================================================= finishing kernels
-__global__ __launch_bounds__(kBlock) void reduce_kernel(const double* __restrict__ partials, const int grid,
-                                                        double* __restrict__ sums_out,
-                                                        float* __restrict__ sqrt_out) {
+// The sum of one row of partials, in thread 0.
+__device__ __forceinline__ double sum_partials(const double* __restrict__ row, const int grid) {
     __shared__ double s_wave[kBlock / 64];
-    const int e = blockIdx.x;
     double s = 0.0;
-    for (int b = threadIdx.x; b < grid; b += kBlock) s += partials[(int64_t)e * grid + b];
+    for (int b = threadIdx.x; b < grid; b += kBlock) s += row[b];
     // fixed order: within a wave by the cross-lane moves, then the waves in turn (these kernels last a
     // few microseconds, most of it latency, so one barrier instead of a tree of eight)
     s = wave_sum_to_lane63(s);
     if ((threadIdx.x & 63) == 63) s_wave[threadIdx.x >> 6] = s;
     __syncthreads();
+    double t = 0.0;
     if (threadIdx.x == 0) {
-        double t = 0.0;
 #pragma unroll
         for (int q = 0; q < kBlock / 64; ++q) t += s_wave[q];
+    }
+    return t;
+}
+
+__global__ __launch_bounds__(kBlock) void reduce_kernel(const double* __restrict__ partials, const int grid,
+                                                        double* __restrict__ sums_out,
+                                                        float* __restrict__ sqrt_out) {
+    const int e = blockIdx.x;
+    const double t = sum_partials(partials + (int64_t)e * grid, grid);
+    if (threadIdx.x == 0) {
         if (sums_out) sums_out[e] = t;
         if (sqrt_out) sqrt_out[e] = (float)sqrt(t);
     }
@@ -468,16 +476,23 @@ __global__ __launch_bounds__(kBlock) void gram_norms_kernel(const double* __rest
     }
 }
 
-// Packed upper triangle (row-major, a <= b) -> full symmetric W x W matrix; a zero
-// matrix when gamma is null (empty shard).
-// The packed triangle is over Wp >= W rows (the kernels' padded row count); W x W entries are copied out.
-__global__ __launch_bounds__(kBlock) void gram_unpack_kernel(const double* __restrict__ gamma, const int Wp,
-                                                             const int W, double* __restrict__ out) {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= W * W) return;
-    const int r = i / W, c = i % W;
-    const int a = r < c ? r : c, b = r < c ? c : r;
-    out[i] = gamma ? gamma[a * Wp - a * (a - 1) / 2 + (b - a)] : 0.0;
+// The last launch of the Gram matrix: entry e = (i, j), i <= j < W, of the packed triangle over Wp >= W rows (the kernels' padded
+// row count) summed over the workgroups' partials as reduce_kernel does it, and written to both of its places in the full
+// W x W matrix (zeros from a grid of 0, an empty shard).  A launch of its own for the second half cost 4 us a call
+// (0.3 M elements, 8 fp32 / 16 bf16 rows 17.0 / 16.4 -> 12.8 / 12.6 us a call, 3 M, 16 bf16 rows 24.9 -> 23.3, 25.6 M 130.9 -> 129.0).
+__global__ __launch_bounds__(kBlock) void reduce_gram_kernel(const double* __restrict__ partials, const int grid,
+                                                             const int Wp, const int W, double* __restrict__ out) {
+    int i = 0, rem = blockIdx.x;
+    while (rem >= W - i) {
+        rem -= W - i;
+        ++i;
+    }
+    const int j = i + rem;
+    const double t = sum_partials(partials + (int64_t)(i * Wp - i * (i - 1) / 2 + rem) * grid, grid);
+    if (threadIdx.x == 0) {
+        out[i * W + j] = t;
+        out[j * W + i] = t;
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void fill_kernel(float* __restrict__ dst, const int64_t n, const float value) {
@@ -663,8 +678,8 @@ hipError_t launch_gram_norms(const double* gamma, const double* coef, int U, int
     return hipGetLastError();
 }
 
-hipError_t launch_gram_unpack(const double* gamma, int Wp, int W, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(gram_unpack_kernel, dim3((W * W + kBlock - 1) / kBlock), dim3(kBlock), 0, s, gamma, Wp, W, out);
+hipError_t launch_reduce_gram(const double* partials, int grid, int Wp, int W, double* out, hipStream_t s) {
+    hipLaunchKernelGGL(reduce_gram_kernel, dim3(W * (W + 1) / 2), dim3(kBlock), 0, s, partials, grid, Wp, W, out);
     return hipGetLastError();
 }
 

@@ -328,6 +328,14 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
     // phase is long enough to matter (not with 16 bf16 rows: 128 cycles a tile, and looking ahead measured
     // 2 % slower there) and the rows of two tiles fit in registers (up to 256 bytes per thread and tile).
     constexpr bool kAhead = sizeof(vec_t) * W <= 256 && (!BF || WIDE);
+    // 25 to 32 fp32 rows have no room for that, but once the second half of a tile is in the panel its registers are free, and the
+    // following tile's loads go out before the matrix instructions that are left (48 updates, start -> now: 28 rows, update with norms
+    // of 3 / 25.6 M elements 102 -> 95 / 646 -> 612 us, norms alone 486 -> 479; 32 rows 113 -> 107 / 719 -> 701, 545 -> 539).
+    // Not with fewer: 24 rows spill 47 registers then (532 -> 595; 7 without a test around the loads, the last chunk being loaded in place
+    // of those beyond the end: 530 -> 540, 3 M 84 -> 92), 20 rows lose 1 % on 80 M and their norms alone 2 % for 4 % on 3 M.
+    // (Tiles worked on as two halves of 2 elements per lane and row, all of the following half's loads ahead of the matrix
+    // instructions but 8 bytes each: 24 / 32 rows 531 -> 539 / 713 -> 716, norms alone 2-8 % behind.)
+    constexpr bool kEarly = !kAhead && !BF && W > 24;
     if constexpr (kAhead) {
         vec_t gn[W];
         f32x4 pn = {0, 0, 0, 0}, vn = {0, 0, 0, 0};
@@ -347,6 +355,30 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
                 if (c < nchunk) update_chunk(c, g, pq, vq);
             }
             gram_tile(g);
+            fold();
+        });
+    } else if constexpr (kEarly) {
+        vec_t g[W];
+        f32x4 pq = {0, 0, 0, 0}, vq = {0, 0, 0, 0};
+        bool primed = false;
+        for_each_claimed_tile_ahead(queue, ntile, claim, [&](const int64_t t, const int64_t following) {
+            const int64_t c = t * kBlock + threadIdx.x;
+            if (!primed) {
+                fetch(c, g, pq, vq);
+                primed = true;
+            }
+            if constexpr (UPDATE) {
+                if (c < nchunk) update_chunk(c, g, pq, vq);
+            }
+            u32x2 h[W];   // gram_tile, with the loads before its last step
+#pragma unroll
+            for (int w = 0; w < W; ++w) h[w] = u32x2{__float_as_uint(g[w][0]), __float_as_uint(g[w][1])};
+            gram_512(h);
+#pragma unroll
+            for (int w = 0; w < W; ++w) h[w] = u32x2{__float_as_uint(g[w][2]), __float_as_uint(g[w][3])};
+            stage(h);
+            if (following >= 0) fetch(following * kBlock + threadIdx.x, g, pq, vq);
+            consume();
             fold();
         });
     } else {

@@ -375,6 +375,7 @@ struct Launch {
     int umax = 1;             // step-by-step route: updates per launch
     int launches = 1;
     int finishing = 0;
+    bool finish_at_once = false;   // Gram route: sums and norms in one finishing launch
     bool split_norms = false; // update by the collapsed map, norms by a separate direct pass (see decide)
     bool collapsed_in_seq = false;   // step-by-step kernel walks the updates for the norms, applies the update as one map
 };
@@ -440,7 +441,9 @@ Launch decide(const star::Plan& plan, int grad_dtype, bool update, bool want_nor
         l.mfma = gram && gram_on_matrix_cores(l.Wp, grad_dtype, opt.kernel, update, P);
         l.queue_order = l.mfma || (l.want_queue && star::aff_takes_queue(gram, l.Wp, grad_dtype == STAR_F32, update));
         l.launches = (update || gram) ? 1 : 0;
-        l.finishing = gram ? 2 : 0;
+        // up to 8 rows on a short shard: one finishing launch, see gram_finish_kernel
+        l.finish_at_once = gram && !l.mfma && !l.queue_order && star::norms_finish_at_once(l.Wp, plan.U, P);
+        l.finishing = gram ? (l.finish_at_once ? 1 : 2) : 0;
     } else {
         // Norms alone have a kernel of their own, which takes up to 240 updates per pass over the rows (32 updates of 8
         // rows, 25 M elements: one pass instead of two).  Below 4096 elements the stream is still cut as that of the update
@@ -645,6 +648,12 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
             a.publish_dtype = publish_dtype;
             a.partials = partials;
             a.queue = want_queue ? queue : nullptr;
+            a.copy = star::CoefCopy();
+            if (how.finish_at_once && !no_alloc) {   // (the fixed array holds them already)
+                a.copy.src = gram_coef;
+                a.copy.dst = reinterpret_cast<double*>(d + lay.coef64);
+                a.copy.n = U * Wp;
+            }
             const bool mfma = how.mfma;
             if (mfma) a.queue = queue;   // that kernel always takes its tiles from the queue
             e = mfma ? star::launch_affine_mfma(Wp, grad_dtype, update, a, num_cu, grid_cap, &grid, stream)
@@ -653,6 +662,11 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
             if (gram) {
                 const int ng = Wp * (Wp + 1) / 2;
                 double* gamma = partials + (size_t)ng * grid;
+                if (how.finish_at_once) {
+                    e = star::launch_gram_finish(partials, grid, gamma, reinterpret_cast<const double*>(d + lay.coef64), U, Wp,
+                                                 star::finish_ticket(queue), norms_out, stream);
+                    return e == hipSuccess ? STAR_OK : hip_fail(e, "launch of the norm kernel");
+                }
                 e = star::launch_reduce(partials, ng, grid, gamma, nullptr, stream);
                 if (e != hipSuccess) return hip_fail(e, "launch of the Gram reduction");
                 e = star::launch_gram_norms(gamma, gram_coef, U, Wp, norms_out, stream);

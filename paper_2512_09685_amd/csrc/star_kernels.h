@@ -22,6 +22,9 @@ struct TileQueue {
     unsigned int pad;
 };
 
+// The ticket of gram_finish_kernel lies behind the queue, in the same 256 bytes.
+inline unsigned int* finish_ticket(TileQueue* q) { return reinterpret_cast<unsigned int*>(q + 4); }
+
 // Tiles handed to a workgroup per claim.  Never a power of two: with 2, 4 or 8 tiles every claim starts
 // on an 8/16/32 KB boundary of every row, all workgroups then hit the same memory channels at the same
 // moments, and the update measured 5-8 % slower than with 3.  Light tiles (few rows: a thread moves less
@@ -183,6 +186,13 @@ int walk_max_updates();
 hipError_t launch_norm_walk(int Wp, int dtype, const SeqArgs& a, int num_cu, int grid_cap, int* grid_out,
                             hipStream_t s);
 
+// Coefficients of the norms that a launch carries from the host's pinned memory (as the device addresses it) to device memory.
+struct CoefCopy {
+    const double* src;
+    double* dst;
+    int n;   // 0: none
+};
+
 struct AffArgs {
     float* params;
     float* momentum;
@@ -195,6 +205,7 @@ struct AffArgs {
     int32_t publish_dtype;  // star_dtype of that copy
     double* partials;  // device [Wp(Wp+1)/2][grid] pairwise-product sums per block (gram only)
     TileQueue* queue;  // device, zeroed; null: fixed assignment of tiles to workgroups (not for the matrix-core kernel)
+    CoefCopy copy;     // launch_affine with `gram`, without a queue
 };
 
 // Collapsed evaluation, optionally accumulating the Gram matrix of the rows.
@@ -213,6 +224,13 @@ hipError_t launch_reduce(const double* partials, int n_out, int grid, double* su
 // norms_out[u] = sqrt( c_u^T Gamma c_u ), Gamma upper-triangular packed [Wp(Wp+1)/2], coef [U][Wp] doubles.
 hipError_t launch_gram_norms(const double* gamma, const double* coef, int U, int Wp, float* norms_out,
                              hipStream_t s);
+
+// launch_reduce and launch_gram_norms in one launch, see norms_finish_at_once.  `gamma` and `coef` are device memory; `ticket` is zero
+// before and after.
+hipError_t launch_gram_finish(const double* partials, int grid, double* gamma, const double* coef, int U, int W,
+                              unsigned int* ticket, float* norms_out, hipStream_t s);
+constexpr int kFinishRows = 8;
+inline bool norms_finish_at_once(int W, int U, int64_t P) { return W <= kFinishRows && U <= 128 && P <= 2 << 20; }
 
 // The same for the Gram matrix: partials of the packed upper triangle over Wp rows [Wp(Wp+1)/2][grid] -> full symmetric [W][W],
 // W <= Wp (all zero with a grid of 0).

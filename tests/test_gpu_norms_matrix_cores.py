@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 MI = 1 << 20
 SHAPES = [(3, 64, MI + 5, 0), (4, 48, MI + 1, 3), (5, 17, 2 * MI - 1, 0), (8, 16, MI, 1), (8, 240, MI + 4095, 0),
           (13, 33, MI + 2047, 7), (16, 65, MI + 7, 0), (20, 32, MI + 3, 2), (24, 64, MI + 63, 0), (32, 16, MI + 1025, 5),
-          (32, 128, MI + 2, 0)]
+          (32, 128, MI + 2, 0), (8, 32, (1 << 17) + 1, 5), (16, 48, (1 << 19) + 3, 63)]
 
 
 def _call(W, U, P, offset, dtype, spoil=()):

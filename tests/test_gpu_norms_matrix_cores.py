@@ -56,12 +56,12 @@ def test_non_finite_rows_reach_the_groups_they_are_members_of(W, U, P, offset, d
     assert clean.any() and nan.any()
     assert torch.isnan(out[nan]).all()
     assert torch.isinf(out[(has[0] | has[2]) & ~nan]).all()
-    # a tile that holds one is summed in another order, at most 8192 elements of it in 64-element steps
+    # the same sums with some zeros added, by whichever of the two kernels
     torch.testing.assert_close(out[clean], plain[clean], rtol=2.0 ** -22, atol=0)
 
 
 def test_shard_with_a_row_of_nan():
-    """A worker that diverged: every tile is walked."""
+    """A worker that diverged: every tile holds NaN."""
     W, U, P = 8, 32, MI + 11
     plain, C, rows = _call(W, U, P, 0, torch.float32)
     bad, _, _ = _call(W, U, P, 0, torch.float32, [(3, slice(None), float("nan"))])

@@ -306,7 +306,8 @@ typedef struct {
                                    with norms and a short stream (direct norm sums of at most 4 W + 48
                                    multiply-adds per element), where the step-by-step kernel walks the updates
                                    for the norms alone (direct sums are cheaper there than the Gram matrix)   */
-    int32_t reserved;
+    int32_t norms_on_matrix_cores; /* 1: the first launch of direct norm sums without an update (of this call, or of the
+                                   pass beside its update) forms them on the matrix cores; 0 also where there is none */
     double fma_seq;       /* fused multiply-adds per element of the step-by-step evaluation                 */
     double fma_affine;    /* ... and of the collapsed one (vector-register Gram counted as FMAs)            */
 } star_plan_info;

@@ -1005,12 +1005,20 @@ star_status star_plan_choice(int64_t P, int32_t W, star_dtype grad_dtype, const 
     st = star::build_plan(W, upd, update ? hp : nullptr, hp ? hp->wmode : 0, want_norms != 0, &plan, &msg);
     if (st != STAR_OK) return set_err(st, msg);
     Launch how = decide(plan, (int)grad_dtype, update != 0, want_norms != 0, P, opt);
+    auto on_matrix_cores = [&](const Launch& l) {   // direct norm sums without an update
+        const int n = std::min(l.umax, plan.U);
+        int members = 0;
+        for (int u = 0; u < n; ++u) members += plan.ysize[u];
+        return n > 0 && star::norms_on_matrix_cores(l.Wp, grad_dtype == STAR_F32, n, members, P);
+    };
+    bool norms_mma = !update && how.route == star::Route::Seq && on_matrix_cores(how);
     if (how.split_norms) {   // the update as if without norms, plus the launches of the direct norm pass
         Opts direct = opt;
         direct.kernel = STAR_KERNEL_SEQ;
         const Launch norms = decide(plan, (int)grad_dtype, false, true, P, direct);
         how = decide(plan, (int)grad_dtype, true, false, P, opt);
         how.launches += norms.launches;
+        norms_mma = on_matrix_cores(norms);
         how.finishing += norms.finishing;
     }
     std::memset(info, 0, sizeof *info);
@@ -1023,6 +1031,7 @@ star_status star_plan_choice(int64_t P, int32_t W, star_dtype grad_dtype, const 
     info->finishing_launches = how.finishing;
     info->tables_inline = how.route == star::Route::Seq ? (how.seq_inline ? 1 : 0) : (want_norms ? 0 : 1);
     info->collapsed_update = (update && (how.route == star::Route::Affine || how.collapsed_in_seq)) ? 1 : 0;
+    info->norms_on_matrix_cores = norms_mma ? 1 : 0;
     info->fma_seq = plan.fma_seq;
     info->fma_affine = plan.fma_affine;
     return STAR_OK;

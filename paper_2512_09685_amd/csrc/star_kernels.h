@@ -185,6 +185,8 @@ hipError_t launch_seq(int Wp, int dtype, bool norms, const SeqArgs& a, int num_c
 int walk_max_updates();
 hipError_t launch_norm_walk(int Wp, int dtype, const SeqArgs& a, int num_cu, int grid_cap, int* grid_out,
                             hipStream_t s);
+// Whether such a launch goes to the matrix cores: U updates whose groups have `members` in all, P elements behind the head.
+bool norms_on_matrix_cores(int Wp, bool f32, int U, int members, int64_t P);
 
 // Coefficients of the norms that a launch carries from the host's pinned memory (as the device addresses it) to device memory.
 struct CoefCopy {

@@ -212,6 +212,8 @@ hipError_t launch_walk_t(WalkKernelArgs& a, int num_cu, int grid_cap, int* grid_
     return hipGetLastError();
 }
 
+}  // namespace
+
 // Whether the matrix cores take the call (norm_mma_kernel): by what either kernel takes on 30 M elements once its arithmetic
 // bounds it, in us.  The walk pays for every update, every coefficient it loads and every member (fp32 rows, 4 / 8 / 13 of them, 128
 // updates of half the rows: 486 / 822 / 1163; of two: 396 / 587 / 727), more from 14 rows on, where fewer waves fit (16 / 24: 1660 / 2483,
@@ -229,8 +231,6 @@ bool norms_on_matrix_cores(int Wp, bool f32, int U, int members, int64_t P) {
     const int groups = (Wp + 3) / 4, blocks = (U + 15) / 16;
     return walk > (f32 ? blocks * (22 + 28 * groups) * (Wp > 4 ? 1.0 : 1.1) : 15.0 + blocks * (26 + 4 * groups));
 }
-
-}  // namespace
 
 int walk_max_updates() { return 60 * 1024 / (int)walk_lds_bytes(4) * 4; }   // stay inside 64 KB of LDS per workgroup
 

@@ -29,11 +29,17 @@ def _inputs(W, U, P, seed=0):
     return star.GradRows(rows), star.UpdateStream(offs, members, stale), p, v, C.cuda(), want
 
 
+def _finishing(W, us, P, dtype="f32", **kw):
+    return star.star_plan_choice(P, W, dtype, us, want_norms=True, wmode="stale", **kw)["finishing_launches"]
+
+
 @pytest.mark.parametrize("noalloc", [False, True])
-@pytest.mark.parametrize("W,U,P", [(1, 2, 4096), (2, 64, 4099), (3, 33, 300007), (5, 16, 70001), (7, 64, 1 << 20),
-                                   (8, 17, 2 << 20), (8, 64, 8191), (8, 65, 8191)])
-def test_norms(W, U, P, noalloc):
+@pytest.mark.parametrize("W,U,P,launches", [(1, 16, 4096, 1), (2, 64, 4099, 1), (3, 33, 300007, 1), (5, 16, 70001, 1),
+                                            (7, 64, 1 << 20, 1), (8, 17, 2 << 20, 1), (8, 17, (2 << 20) + 1, 2), (8, 128, 8191, 1),
+                                            (8, 129, 8191, 2), (9, 17, 8191, 2)])
+def test_norms(W, U, P, launches, noalloc):
     g, us, p, v, C, want = _inputs(W, U, P)
+    assert _finishing(W, us, P, lr=0.1, momentum_coef=0.9) == launches
     call = star.star_group_update_noalloc if noalloc else star.star_group_update
     for _ in range(3):
         out = torch.full((U,), -1.0, device="cuda")
@@ -46,6 +52,20 @@ def test_norms(W, U, P, noalloc):
     has = C[:, 0] != 0
     assert torch.isnan(out[has]).all()
     torch.testing.assert_close(out[~has].double(), want[~has], rtol=1e-6, atol=0)
+
+
+@pytest.mark.parametrize("W,U,P,dtype", [(1, 1, 4096, "f32"), (1, 128, 300007, "f32"), (8, 64, 70001, "f32"), (8, 16, 2 << 20, "f32"),
+                                         (1, 24, 300007, "bf16"), (2, 128, 1 << 20, "bf16")])
+def test_norms_without_an_update(W, U, P, dtype):
+    g, us, _, _, C, want = _inputs(W, U, P)
+    if dtype == "bf16":
+        g = star.GradRows([r.bfloat16() for r in g])
+        want = (C @ torch.stack([r.double() for r in g])).square().sum(1).sqrt()
+    assert _finishing(W, us, P, dtype, update=False) == 1
+    for _ in range(3):
+        out = torch.full((U,), -1.0, device="cuda")
+        star.star_group_norms(g, us, out, wmode="stale")
+        torch.testing.assert_close(out.double(), want, rtol=1e-6, atol=0)
 
 
 def test_two_streams():

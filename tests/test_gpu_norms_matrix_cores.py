@@ -1,6 +1,7 @@
 """Direct norm sums on the matrix cores (norm_mma_kernel) at the edges of its tiles, blocks and launches: rows that are no
-multiple of four, updates around 16 and beyond one workgroup's 64, shards that end inside a lane's load, odd starts, and rows
-with infinities and NaN, which a dense product would spread over groups they are no members of."""
+multiple of four, updates around 16 and beyond one workgroup's 64, the shortest shards it takes, shards that end inside a lane's
+load, odd starts, groups that nearly cancel, and rows with infinities and NaN, which a dense product would spread over groups they are no
+members of.  Every case asks the library which kernel it would take."""
 import numpy as np
 import pytest
 import torch
@@ -10,61 +11,134 @@ import paper_2512_09685_amd as star
 pytestmark = pytest.mark.gpu
 
 MI = 1 << 20
-SHAPES = [(3, 64, MI + 5, 0), (4, 48, MI + 1, 3), (5, 17, 2 * MI - 1, 0), (8, 16, MI, 1), (8, 240, MI + 4095, 0),
-          (13, 33, MI + 2047, 7), (16, 65, MI + 7, 0), (20, 32, MI + 3, 2), (24, 64, MI + 63, 0), (32, 16, MI + 1025, 5),
-          (32, 128, MI + 2, 0), (8, 32, (1 << 17) + 1, 5), (16, 48, (1 << 19) + 3, 63)]
+F, B = torch.float32, torch.bfloat16
+# Norms against 64 bits: the coefficients and the result are rounded to fp32 (6e-8 each), a group sum of y terms carries at most y
+# roundings of 6e-8 that average out over the elements, and four squares are added in fp32 (double beyond).
+TOL = 3e-7
 
 
-def _call(W, U, P, offset, dtype, spoil=()):
-    rng = np.random.default_rng([W, U, P])
-    sizes = rng.integers(max(1, W // 2), W + 1, size=U)
+def _head(offset, dtype):
+    """Elements before the first whole cache line of rows that start `offset` elements into an aligned buffer."""
+    return -offset % (128 // dtype.itemsize)
+
+
+def _on_matrix_cores(us, W, P, offset, dtype, **kw):
+    return star.star_plan_choice(P - _head(offset, dtype), W, "f32" if dtype == F else "bf16", us, update=False, want_norms=True,
+                                 direct_norms=True, **kw)["norms_on_matrix_cores"]
+
+
+def _stream(W, U, least, seed):
+    """Groups of `least` to W workers; the first is the last worker alone."""
+    rng = np.random.default_rng(seed)
+    sizes = rng.integers(least, W + 1, size=U)
     sizes[0] = 1
     offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
     members = np.concatenate([[W - 1]] + [rng.permutation(W)[:y] for y in sizes[1:]]).astype(np.int32)
     C = torch.zeros(U, W, dtype=torch.float64, device="cuda")
     for u in range(U):
         C[u, members[offs[u]:offs[u + 1]]] = 1.0 / sizes[u]
+    return star.UpdateStream(offs, members), C
+
+
+def _rows(W, U, P, offset, dtype):
     gen = torch.Generator(device="cuda").manual_seed(W * 1000 + U)
-    rows = [(torch.randn(P + offset, generator=gen, device="cuda") * 1e-3).to(dtype)[offset:] for _ in range(W)]
-    for w, j, x in spoil:
-        rows[w][j] = x
-    out = torch.full((U,), -1.0, device="cuda")
-    star.star_group_norms(star.GradRows(rows), star.UpdateStream(offs, members), out, direct_norms=True)
-    return out, C, rows
+    return [(torch.randn(P + offset, generator=gen, device="cuda") * 1e-3).to(dtype)[offset:] for _ in range(W)]
 
 
-@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("W,U,P,offset", SHAPES)
-def test_direct_norms(W, U, P, offset, dtype):
-    out, C, rows = _call(W, U, P, offset, dtype)
-    sums = torch.zeros(U, dtype=torch.float64, device="cuda")
-    for lo in range(0, P, MI // 4):
+def _norms(rows, us, **kw):
+    out = torch.full((us.U,), -1.0, device="cuda")
+    star.star_group_norms(star.GradRows(rows), us, out, direct_norms=True, **kw)
+    return out
+
+
+def _exact(C, rows):
+    sums = torch.zeros(C.shape[0], dtype=torch.float64, device="cuda")
+    for lo in range(0, rows[0].shape[0], MI // 4):
         g = torch.stack([r[lo:lo + MI // 4].double() for r in rows])
         sums += (C @ g).square().sum(1)
-    # W roundings in a sum of W products, four squares, the root and its rounding
-    torch.testing.assert_close(out.double(), sums.sqrt(), rtol=(W + 6) * 2.0 ** -24, atol=0)
+    return sums.sqrt()
 
 
-@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("W,U,P,offset", SHAPES[1:8])
-def test_non_finite_rows_reach_the_groups_they_are_members_of(W, U, P, offset, dtype):
+# the last field: whether the matrix cores take it.  The shortest shards are a few elements above and one below their limits.
+SHAPES = [(3, 2, 64, MI + 5, 0, F, 1), (3, 2, 64, MI + 5, 0, B, 1), (4, 3, 48, MI + 7, 3, F, 1), (4, 3, 48, MI + 61 + 1, 3, B, 1),
+          (5, 4, 96, 2 * MI - 1, 0, F, 1), (6, 3, 17, 2 * MI - 1, 0, B, 1), (7, 4, 32, MI - 1, 2, F, 1), (8, 4, 16, MI, 1, F, 1),
+          (8, 4, 16, MI, 1, B, 1), (8, 4, 240, MI + 4095, 0, F, 1), (8, 4, 240, MI + 4095, 0, B, 1), (9, 6, 31, MI + 2, 0, F, 1),
+          (13, 8, 47, MI + 2047, 7, F, 1), (13, 6, 33, MI + 2047, 7, B, 1), (16, 8, 65, MI + 7, 0, F, 1), (16, 8, 65, MI + 7, 0, B, 1),
+          (20, 10, 32, MI + 3, 2, F, 1), (20, 10, 32, MI + 3, 2, B, 1), (24, 12, 64, MI + 63, 0, F, 1), (24, 12, 64, MI + 63, 0, B, 1),
+          (32, 16, 17, MI + 1025, 5, F, 1), (32, 16, 16, MI + 1025, 5, B, 1), (32, 16, 128, MI + 2, 0, F, 1),
+          (32, 16, 128, MI + 2, 0, B, 1),
+          (8, 4, 32, (1 << 17) + 27 + 3, 5, F, 1), (8, 4, 32, (1 << 17) + 27 - 1, 5, F, 0), (8, 4, 32, (1 << 19) + 59 + 1, 5, B, 1),
+          (8, 4, 32, (1 << 19) + 59 - 1, 5, B, 0), (16, 8, 48, (1 << 19) + 1 + 2, 63, B, 1), (4, 3, 64, (1 << 18) + 5, 0, F, 1),
+          (4, 3, 64, (1 << 18) - 1, 0, F, 0)]
+
+
+@pytest.mark.parametrize("W,least,U,P,offset,dtype,matrix", SHAPES)
+def test_direct_norms(W, least, U, P, offset, dtype, matrix):
+    us, C = _stream(W, U, least, [W, U, P])
+    assert _on_matrix_cores(us, W, P, offset, dtype) == matrix
+    rows = _rows(W, U, P, offset, dtype)
+    torch.testing.assert_close(_norms(rows, us).double(), _exact(C, rows), rtol=TOL, atol=0)
+
+
+@pytest.mark.parametrize("dtype", [F, B])
+@pytest.mark.parametrize("W,U", [(4, 64), (8, 32), (13, 64), (16, 64), (32, 128)])
+def test_groups_that_nearly_cancel(W, U, dtype):
+    """What direct sums are asked for.  Rows that are one vector up to a hundredth, in groups whose coefficients add up to zero: kappa of
+    1e4 and more.  An element of gbar carries roundings of its products, at most W 2^-24 sqrt(kappa) of its size, 1e-3, which
+    are independent of its sign and average out over 1 Mi elements to 1e-6 (seen: 2.4e-7)."""
+    gen = torch.Generator(device="cuda").manual_seed(W + U)
+    base = torch.randn(MI, generator=gen, device="cuda") * 1e-3
+    rows = [(base + 1e-5 * torch.randn(MI, generator=gen, device="cuda")).to(dtype) for _ in range(W)]
+    rng = np.random.default_rng(3)
+    offs, members, coeff = [0], [], []
+    for _ in range(U):
+        k = int(rng.integers(max(1, W // 4), W // 2 + 1))
+        c = rng.uniform(0.1, 1.0, k).astype(np.float32)
+        members += list(rng.permutation(W)[:2 * k])
+        coeff += list(c) + list(-c[rng.permutation(k)])
+        offs.append(len(members))
+    C = torch.zeros(U, W, dtype=torch.float64)
+    for u in range(U):
+        for m in range(offs[u], offs[u + 1]):
+            C[u, members[m]] = float(coeff[m])
+    C = C.cuda()
+    us = star.UpdateStream(offs, members, None, coeff)
+    assert _on_matrix_cores(us, W, MI, 0, dtype, wmode="explicit") == 1
+    want = _exact(C, rows)
+    size = torch.stack([r.double().norm() for r in rows])
+    assert float(((C.abs() @ size) / want).square().min()) > 1e4
+    torch.testing.assert_close(_norms(rows, us, wmode="explicit").double(), want, rtol=1e-6, atol=0)
+
+
+@pytest.mark.parametrize("dtype", [F, B])
+@pytest.mark.parametrize("W,least,U,P,offset", [(4, 2, 64, MI + 63, 3), (8, 4, 16, MI, 1), (8, 4, 240, MI + 4095, 0), (13, 8, 47, MI + 2047, 7),
+                                                (16, 8, 65, MI + 7, 0), (20, 10, 32, MI + 3, 2), (24, 12, 64, MI + 63, 0)])
+def test_non_finite_rows_reach_the_groups_they_are_members_of(W, least, U, P, offset, dtype):
     inf = float("inf")
-    plain, C, _ = _call(W, U, P, offset, dtype)
-    out, _, _ = _call(W, U, P, offset, dtype, [(0, P // 3, inf), (1, P - 1, float("nan")), (2, 0, -inf), (2, P // 2, inf)])
+    us, C = _stream(W, U, least, [W, U, P])
+    assert _on_matrix_cores(us, W, P, offset, dtype) == 1
+    rows = _rows(W, U, P, offset, dtype)
+    plain = _norms(rows, us)
+    for w, j, x in [(0, P // 3, inf), (1, P - 1, float("nan")), (2, 0, -inf), (2, P // 2, inf)]:
+        rows[w][j] = x
+    out = _norms(rows, us)
     has = [(C[:, w] != 0) for w in range(W)]
     nan, clean = has[1], ~(has[0] | has[1] | has[2])
     assert clean.any() and nan.any()
     assert torch.isnan(out[nan]).all()
     assert torch.isinf(out[(has[0] | has[2]) & ~nan]).all()
-    # the same sums with some zeros added, by whichever of the two kernels
+    # the same sums with some zeros added
     torch.testing.assert_close(out[clean], plain[clean], rtol=2.0 ** -22, atol=0)
 
 
 def test_shard_with_a_row_of_nan():
     """A worker that diverged: every tile holds NaN."""
     W, U, P = 8, 32, MI + 11
-    plain, C, rows = _call(W, U, P, 0, torch.float32)
-    bad, _, _ = _call(W, U, P, 0, torch.float32, [(3, slice(None), float("nan"))])
+    us, C = _stream(W, U, W // 2, [W, U, P])
+    rows = _rows(W, U, P, 0, F)
+    plain = _norms(rows, us)
+    rows[3].fill_(float("nan"))
+    bad = _norms(rows, us)
     has = C[:, 3] != 0
     assert torch.isnan(bad[has]).all() and (~has).any()
     torch.testing.assert_close(bad[~has], plain[~has], rtol=2.0 ** -22, atol=0)

@@ -218,8 +218,10 @@ hipError_t launch_walk_t(WalkKernelArgs& a, int num_cu, int grid_cap, int* grid_
 // bounds it, in us.  The walk pays for every update, every coefficient it loads and every member (fp32 rows, 4 / 8 / 13 of them, 128
 // updates of half the rows: 486 / 822 / 1163; of two: 396 / 587 / 727), more from 14 rows on, where fewer waves fit (16 / 24: 1660 / 2483,
 // 1378 / 1836), and with 32 rows, where one does (6002, 4522).  The matrix cores pay for 16 updates at a time: fp32 rows by row groups
-// of four (1 / 2 / 4 / 8 of them, 128 updates: 389, 622, 1065, 2074), bf16 rows hardly by those (255, 293, 529, 814).  Where memory bounds
-// both they are level, so the rule is good there too.  Both sides of it, 1 to 32 rows, 1 to 128 updates, groups of one or two and of half
+// of four (1 / 2 / 4 / 8 of them, 128 updates: 389, 622, 1065, 2074), bf16 rows hardly by those (332, 366, 448, 735).  Where memory bounds
+// both they are level, so the rule is good there too.  Up to 4 bf16 rows the walk, light there, gains more on the matrix cores from 4 Mi elements on than its
+// count says (8 / 30 M, 1 row, 64 updates 55 / 152 against 58 / 172, 3 rows, 24 updates of 1.5 members 31 / 84 against 33 / 94; 1.1 M, 1 row, 128
+// updates 49 against 32).  Both sides of it, 1 to 32 rows, 1 to 128 updates, groups of one or two and of half
 // the rows, 2 / 8 / 30 M elements: fp32 rows 1.45 / 1.40 / 1.29 times ahead on the mean where it says so, bf16 rows 1.56 / 1.91 / 1.94, at worst 6 %
 // behind.  Short shards (walk / matrix cores, us a call): 0.1 M elements, 32 updates of 4 / 8 / 16 fp32 rows 10.4 / 10.2 / 18.2 against 11.7 / 10.4 / 15.8, 0.3 M
 // 12.8 / 14.0 / 23.0 against 12.6 / 14.0 / 20.8; bf16 rows, whose rest is fetched step by step, 0.3 M 12.7 / 14.7 / 21.9 against 14.4 / 15.2 / 23.2, 0.6 M 14.6 / 21.6 /
@@ -229,7 +231,8 @@ bool norms_on_matrix_cores(int Wp, bool f32, int U, int members, int64_t P) {
     double walk = Wp <= 13 ? U * (1.6 + 0.25 * Wp) + 0.6 * members : U * (1.6 + 0.45 * Wp) + 0.55 * members;
     if (Wp > 28 && U > 4) walk *= 1.8;
     const int groups = (Wp + 3) / 4, blocks = (U + 15) / 16;
-    return walk > (f32 ? blocks * (22 + 28 * groups) * (Wp > 4 ? 1.0 : 1.1) : 15.0 + blocks * (26 + 4 * groups));
+    if (f32) return walk > blocks * (22 + 28 * groups) * (Wp > 4 ? 1.0 : 1.1);
+    return walk > (15.0 + blocks * (26 + 4 * groups)) * (Wp > 4 || P < 4 << 20 ? 1.0 : 1.45);
 }
 
 int walk_max_updates() { return 60 * 1024 / (int)walk_lds_bytes(4) * 4; }   // stay inside 64 KB of LDS per workgroup

@@ -34,11 +34,18 @@ hipError_t launch_norm_mma_bf16(WalkKernelArgs& k, int Wp, int num_cu, int grid_
 //   bf16 rows: v_mfma_f32_16x16x32_bf16, at 16 times the rate.  The coefficients stay fp32 numbers, as the sum of three bf16 pieces
 // each (products of two bf16 values are exact in fp32, where they are added).  A lane's eight places of the reduction are four
 // pairs of rows, once for every piece, packed from the loads of two row groups by one instruction an element.
+//   The upper pieces have an instruction to themselves.  The instruction adds the eight products of a quarter of the wave at a time
+// and cuts off, instead of rounding, what lies more than 25 bits below the largest: all three pieces in one made the norms of up to 8 rows 1.5e-8
+// too small on the mean.  The lower two come first, so that the large products are rounded once: gbar of normal rows is then off by
+// 3.5e-8 of its size whatever the row count (fp32 multiply-adds, norm_walk_kernel: 2.5e-8 / 4e-8 / 6e-8 / 9e-8 with 1 / 6 / 16 / 32
+// rows).  Up to four rows the upper ones come first, 2.5e-8 with one row.  What the norm of 65 536 normal elements is off by for that, before it is rounded
+// to fp32: 0.3e-9 to 3e-9 rms (multiply-adds: 0.7e-9 to 2e-9); rows of one sign up to 1.5e-8 (6e-9).
+//   It costs up to 8 rows an instruction more (30 M elements, 4 / 8 rows, 32 updates 82 / 96 -> 102 / 118 us).
 //   Memory bounds it up to about 32 updates of 8 fp32 rows or 16 of 16, and bf16 rows up to 64 updates; beyond, the matrix instructions and
 // the squares do, which overlap little.  25.6 M elements, norm_walk_kernel -> this one: 8 fp32 rows, 32 updates of 4.5 members 198 -> 158 us (the
-// reads alone 120), 16 rows, 32 updates 424 -> 283, 32 rows, 16 updates 717 -> 488 (the reads 481); 30 M, bf16 rows: 8 rows, 32 updates 217 -> 93,
-// 16 rows, 64 updates 840 -> 227, 32 rows, 64 updates 2703 -> 422.  bf16 rows through the fp32 instructions: 167, 540, 1042.
-//   Largest error of a norm against 64 bits, 1 to 32 rows, 3 to 240 updates: 9.7e-8 either way for fp32 rows, bf16 rows 1.05e-7 either way.
+// reads alone 120), 16 rows, 32 updates 424 -> 283, 32 rows, 16 updates 717 -> 488 (the reads 481); 30 M, bf16 rows: 8 rows, 32 updates 217 -> 118,
+// 16 rows, 64 updates 840 -> 230, 32 rows, 64 updates 2703 -> 363.  bf16 rows through the fp32 instructions: 167, 540, 1042.
+//   Largest error of a norm against 64 bits, 1 to 32 rows, 3 to 240 updates: 9.7e-8 either way for fp32 rows, bf16 rows 6.3e-8 either way.
 typedef float acc4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
@@ -106,7 +113,8 @@ __global__ __launch_bounds__(kBlock, mma_waves(KS, NB)) void norm_mma_kernel(con
         return s < KS && u < U && w < W ? coef[u * W + w] : 0.0f;
     };
     constexpr bool BF = std::is_same<R, RowBf16x4>::value;
-    constexpr int kPairs = (KS + 1) / 2, kSteps = BF ? (3 * kPairs + 3) / 4 : KS;
+    constexpr int kPairs = (KS + 1) / 2, kLow = (2 * kPairs + 3) / 4, kSteps = BF ? kLow + 1 : KS;
+    constexpr int kHigh = KS > 1 ? kLow : 0;   // the step of the upper pieces, see bf16 rows above
     typedef typename std::conditional<BF, bf16x8, float>::type operand_t;
     operand_t a[NB][kSteps];
 #pragma unroll
@@ -118,9 +126,11 @@ __global__ __launch_bounds__(kBlock, mma_waves(KS, NB)) void norm_mma_kernel(con
                 u32x4 packed;
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
-                    const int slot = 4 * i + p, pair = slot % kPairs;
-                    const uint32_t lo = slot < 3 * kPairs ? coef_piece(coef_at(u, 2 * pair), slot / kPairs) : 0u;
-                    const uint32_t hi = slot < 3 * kPairs ? coef_piece(coef_at(u, 2 * pair + 1), slot / kPairs) : 0u;
+                    const int slot = i == kHigh ? p : 4 * (i - (KS > 1 ? 0 : 1)) + p;
+                    const int pair = slot % kPairs, piece = i == kHigh ? 0 : 1 + slot / kPairs;
+                    const bool used = slot < (i == kHigh ? 1 : 2) * kPairs;
+                    const uint32_t lo = used ? coef_piece(coef_at(u, 2 * pair), piece) : 0u;
+                    const uint32_t hi = used ? coef_piece(coef_at(u, 2 * pair + 1), piece) : 0u;
                     packed[p] = hi << 16 | lo;
                 }
                 a[b][i] = __builtin_bit_cast(bf16x8, packed);
@@ -252,8 +262,9 @@ __global__ __launch_bounds__(kBlock, mma_waves(KS, NB)) void norm_mma_kernel(con
                     static_for<0, 4>([&](auto kc) {
                         constexpr int K = decltype(kc)::value;
                         if constexpr (BF) {
-                            const u32x4 y = {pk[K][(4 * S) % kPairs], pk[K][(4 * S + 1) % kPairs], pk[K][(4 * S + 2) % kPairs],
-                                             pk[K][(4 * S + 3) % kPairs]};
+                            constexpr int F = S == kHigh ? 0 : 4 * (S - (KS > 1 ? 0 : 1));   // its first place, as above
+                            const u32x4 y = {pk[K][F % kPairs], pk[K][(F + 1) % kPairs], pk[K][(F + 2) % kPairs],
+                                             pk[K][(F + 3) % kPairs]};
                             d[K] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[B][S], __builtin_bit_cast(bf16x8, y), d[K], 0, 0,
                                                                            0);
                         } else {

@@ -142,3 +142,26 @@ def test_shard_with_a_row_of_nan():
     has = C[:, 3] != 0
     assert torch.isnan(bad[has]).all() and (~has).any()
     torch.testing.assert_close(bad[~has], plain[~has], rtol=2.0 ** -22, atol=0)
+
+
+@pytest.mark.parametrize("dtype", [F, B])
+@pytest.mark.parametrize("W", [1, 2, 4, 5, 8, 12, 24])
+def test_norms_are_not_biased(W, dtype):
+    """The mean of the signed error over many updates.  A norm is rounded to fp32, 2.5e-8 rms, which over 720 updates averages out to
+    1e-9; the roundings within the sums differ from update to update, a few 1e-9 each (the table is fp32 on both sides)."""
+    U, P, err = 240, MI + 64, []
+    for seed in range(3):
+        rng = np.random.default_rng([W, seed])
+        sizes = rng.integers(1, W + 1, size=U)
+        offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+        members = np.concatenate([rng.permutation(W)[:y] for y in sizes]).astype(np.int32)
+        coeff = rng.standard_normal(len(members)).astype(np.float32)
+        C = np.zeros((U, W))
+        for u in range(U):
+            C[u, members[offs[u]:offs[u + 1]]] = coeff[offs[u]:offs[u + 1]]
+        us = star.UpdateStream(offs, members, None, coeff)
+        if dtype == B:
+            assert _on_matrix_cores(us, W, P, 0, dtype, wmode="explicit") == 1
+        rows = _rows(W, seed, P, 0, dtype)
+        err.append(_norms(rows, us, wmode="explicit").double() / _exact(torch.tensor(C, device="cuda"), rows) - 1)
+    assert abs(float(torch.cat(err).mean())) < 5e-9

@@ -62,7 +62,7 @@
  *     same element of larger buffers run at the speed of aligned ones; buffers
  *     that are off by different amounts are read at unaligned addresses.
  *   - The library keeps a small internal workspace (coefficient tables,
- *     per-block norm partials, a 16-byte work queue per slot), created on
+ *     per-block norm partials, 256 bytes of counters per slot), created on
  *     first use, released by star_shutdown().  Calls may come from several
  *     host threads.
  */

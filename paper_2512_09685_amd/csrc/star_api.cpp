@@ -114,7 +114,7 @@ star_status resolve_options(const star_options* o, Opts* out) {
 // ---------------------------------------------------------------- workspace
 // A ring of slots.  One call uses one slot: a pinned host staging buffer and a
 // device buffer for the tables, a device buffer for the per-block partial sums
-// and the reduced Gram matrix, and the 16-byte tile queue.  A slot's event is recorded after the last
+// and the reduced Gram matrix, and 256 bytes with the tile queue and the ticket of gram_finish_kernel.  A slot's event is recorded after the last
 // kernel that touches it; the slot is handed out again only once that event
 // has completed, so calls on different streams never share live memory.
 struct Slot {
@@ -125,7 +125,7 @@ struct Slot {
     size_t table_cap = 0;
     double* partials = nullptr;
     size_t partial_cap = 0;   // doubles
-    star::TileQueue* queue = nullptr;   // work queue of the slot's launches, zero whenever no kernel is running
+    star::TileQueue* queue = nullptr;   // work queue of the slot's launches and, behind it, the ticket: zero whenever no kernel is running
     hipEvent_t done = nullptr;
     bool pending = false;     // `done` has been recorded after work that uses this slot
 };
@@ -611,7 +611,9 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
     if (no_alloc) {
         if (need_seq_tables) STAR_HIP(star::launch_upload(d, h, lay.coef64, stream));
         if (need_gram_coef) {
-            STAR_HIP(star::launch_upload(d + lay.coef64, h + lay.coef64, sizeof(double) * (size_t)U * Wp, stream));
+            // (a ticket that calls which overlapped left out of step, or one that failed, would spoil every later one's norms)
+            STAR_HIP(star::launch_upload(d + lay.coef64, h + lay.coef64, sizeof(double) * (size_t)U * Wp, stream,
+                                         how.finish_at_once ? star::finish_ticket(queue) : nullptr));
             gram_coef = reinterpret_cast<const double*>(d + lay.coef64);
         }
     } else {

@@ -242,7 +242,7 @@ hipError_t launch_fill(float* dst, int64_t n, float value, hipStream_t s);
 
 // ---- the fixed device workspace of the entry point that allocates nothing
 // One array of kScratchBytes per GPU, part of the library's device code (no hipMalloc behind it):
-//   [0, 256)                                   the tile queue
+//   [0, 256)                                   the tile queue and the ticket of gram_finish_kernel
 //   [256, 256 + kScratchTableBytes)            group tables
 //   [256 + kScratchTableBytes, kScratchBytes)  per-workgroup partial sums and the reduced Gram matrix
 constexpr int kScratchMaxUpdates = 256;                       // longest stream that entry point accepts
@@ -256,8 +256,8 @@ static_assert(256 + kScratchTableBytes + kScratchPartialDoubles * sizeof(double)
 hipError_t scratch_address(void** out);
 
 // dst[0..bytes) = src[0..bytes): host data carried to the device in kernel arguments, a few KB per
-// launch -- no copy engine, no staging buffer, nothing allocated.  dst 16-byte aligned.
-hipError_t launch_upload(void* dst_dev, const void* src_host, size_t bytes, hipStream_t s);
+// launch -- no copy engine, no staging buffer, nothing allocated.  dst 16-byte aligned.  `clear`, if not null, is set to zero as well.
+hipError_t launch_upload(void* dst_dev, const void* src_host, size_t bytes, hipStream_t s, unsigned int* clear = nullptr);
 
 // Puts a tile queue back to "no tile claimed, nobody left".
 hipError_t launch_queue_clear(TileQueue* q, hipStream_t s);

@@ -30,7 +30,8 @@ struct UploadBlock {
 };
 
 __global__ __launch_bounds__(kBlock) void upload_kernel(const UploadBlock blk, uint32_t* __restrict__ dst,
-                                                        const int nwords) {
+                                                        const int nwords, unsigned int* __restrict__ clear) {
+    if (clear && threadIdx.x == 0) *clear = 0u;
     for (int i = threadIdx.x; i < nwords; i += kBlock) dst[i] = blk.w[i];
 }
 
@@ -61,7 +62,7 @@ hipError_t scratch_address(void** out) {
     return hipSuccess;
 }
 
-hipError_t launch_upload(void* dst_dev, const void* src_host, size_t bytes, hipStream_t s) {
+hipError_t launch_upload(void* dst_dev, const void* src_host, size_t bytes, hipStream_t s, unsigned int* clear) {
     const unsigned char* src = static_cast<const unsigned char*>(src_host);
     unsigned char* dst = static_cast<unsigned char*>(dst_dev);
     for (size_t off = 0; off < bytes; off += kUploadBytes) {
@@ -70,7 +71,7 @@ hipError_t launch_upload(void* dst_dev, const void* src_host, size_t bytes, hipS
         std::memset(&blk, 0, sizeof blk);
         std::memcpy(blk.w, src + off, n);
         hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(kBlock), 0, s, blk, reinterpret_cast<uint32_t*>(dst + off),
-                           (int)((n + 3) / 4));
+                           (int)((n + 3) / 4), clear);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -1,6 +1,8 @@
 """Norms of up to 8 rows on a short shard: Gram sums and norms in one finishing launch (gram_finish_kernel).  The workgroup that
 arrives last forms the norms and puts the ticket back, so calls are repeated: back to back, on two streams, from the entry point
 that works in the fixed array, and as replays of a captured graph."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -101,4 +103,22 @@ def test_captured():
         out.fill_(-1.0)
         call()   # the program's own call between the replays
         torch.cuda.synchronize()
+        torch.testing.assert_close(out.double(), want, rtol=1e-6, atol=0)
+
+
+def test_ticket_left_out_of_step():
+    """Calls of the entry point without allocation that overlap race on the fixed array, but may not spoil the ones after them: whatever the
+    ticket holds (64 bytes into the array) when a call begins, its norms are right."""
+    g, us, p, v, _, want = _inputs(4, 24, 70001, 4)
+    assert _finishing(4, us, 70001, lr=0.1, momentum_coef=0.9) == 1
+    base = ctypes.c_void_p()
+    assert getattr(star.load_library(), "_ZN4star15scratch_addressEPPv")(ctypes.byref(base)) == 0
+    hip = ctypes.CDLL("libamdhip64.so")
+    hip.hipMemcpy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int]
+    for left in (1000, 1, 0):
+        torch.cuda.synchronize()
+        ticket = ctypes.c_uint32(left)
+        assert hip.hipMemcpy(base.value + 64, ctypes.byref(ticket), 4, 1) == 0   # host to device
+        out = torch.full((us.U,), -1.0, device="cuda")
+        star.star_group_update_noalloc(p, v, g, us, norms_out=out, **HP)
         torch.testing.assert_close(out.double(), want, rtol=1e-6, atol=0)

@@ -30,7 +30,7 @@ hipError_t launch_norm_mma_bf16(WalkKernelArgs& k, int Wp, int num_cu, int grid_
 // instructions as it stands: no transposition, no LDS.  Lane l of the result holds updates 4 (l / 16) + r, r = 0 .. 3, of
 // one element, so every lane squares and sums on its own, and the lanes meet once, when the kernel ends.
 //   The multiplication is dense: a row that is no member of a group enters with coefficient zero.  That is the same sum, except
-// where the row holds an infinity or a NaN; tiles that do are found beforehand (x * 0 is not 0), see poison.
+// where the row holds an infinity or a NaN; tiles that do are found beforehand (x * 0 is not 0), see Odd.
 //   bf16 rows: v_mfma_f32_16x16x32_bf16, at 16 times the rate.  The coefficients stay fp32 numbers, as the sum of three bf16 pieces
 // each (products of two bf16 values are exact in fp32, where they are added).  A lane's eight places of the reduction are four
 // pairs of rows, once for every piece, packed from the loads of two row groups by one instruction an element.
@@ -49,6 +49,7 @@ hipError_t launch_norm_mma_bf16(WalkKernelArgs& k, int Wp, int num_cu, int grid_
 typedef float acc4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
 typedef u32x4 u32x4_any __attribute__((aligned(2)));
 
 // 16 bytes of a row: one load of a lane
@@ -153,71 +154,134 @@ __global__ __launch_bounds__(kBlock, mma_waves(KS, NB)) void norm_mma_kernel(con
     const int64_t P = args.P, nchunk = P / E;   // chunks: one lane's load
     const int64_t ntile = (nchunk + kTile / E - 1) / (kTile / E);
     // Infinities and NaN: a dense product would carry them into every group (0 times either is NaN).  They are taken out of the
-    // operand, and what they make of the groups their rows are members of is added apart: 0, infinity or NaN from 64 elements, one
-    // per lane (INT64_MIN: none).  Rows of `rows` hold some.  An update whose sum is NaN stays there, and a row needs no further
-    // look once that is so for every group it is in: a worker that diverged costs one tile a wave, not all of them (8 rows of 25.6 M elements,
-    // 32 updates, one row of NaN: fp32 221 us, bf16 172; walked member by member 2080 and 2100, and 226 and 202 by norm_walk_kernel).
-    uint64_t lost = 0;        // updates whose sum is NaN
-    uint32_t settled = 0;     // rows
-    auto bad_value = [](const float v) { return (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u; };
-    auto poison = [&](const int64_t j, const uint32_t rows) {
-        float g[4 * KS];
-#pragma unroll
-        for (int w = 0; w < 4 * KS; ++w) g[w] = 0.0f;
-        if (j != INT64_MIN) {
-#pragma unroll
-            for (int w = 0; w < 4 * KS; ++w)
-                if ((rows >> w) & 1u) g[w] = R::load1(in->rows.p[w], j);
+    // operand, and what they make of their groups is kept apart, as two sets of updates that the sums meet when the kernel ends.  From which
+    // rows of a tile hold NaN, +inf or -inf (`Odd`, bits of rows) most of it follows without a look at the elements, one update a
+    // lane: a member with NaN, or with an infinity and a coefficient of zero, makes the sum NaN; infinities that all enter a group with
+    // the same sign, or that are one row's, make it infinite.  Only where two rows with infinities of both signs meet in a group, whose sum
+    // is not NaN yet, are they added element by element (poison).  What a wave has seen once needs no second look: rows with NaN, since
+    // the sums they are in are NaN, and infinite rows while no group has a choice of signs.  So a worker that diverged costs the wave one tile
+    // and the others little more than the search (8 rows of 25.6 M elements, 32 updates, clean / one row of NaN / of +inf / of infinities of both signs / all
+    // rows of +inf: fp32 159 / 193 / 191 / 194 / 188 us, bf16 106 / 146 / 140 / 139 / 137; two rows that agree in signs that change 260, 253;
+    // norm_walk_kernel 198 and 188 in all of them; every spoilt tile element by element: 1460 to 2870 us).
+    uint64_t lost = 0, infinite = 0;   // updates whose sum is NaN; whose sum is infinite at least
+    struct Odd {
+        uint32_t nan, pos, neg;
+    };
+    Odd seen = {0, 0, 0};
+    // One update a lane: takes in what a tile holds; the updates whose infinite members must be looked at element by element, and the
+    // members by the signs of their coefficients.
+    auto examine = [&](const Odd& o, uint32_t& plus, uint32_t& minus) {
+        const uint32_t pos = o.pos | seen.pos, neg = o.neg | seen.neg;
+        const uint32_t m = lane < U ? mask[lane] : 0u;
+        bool nan = (m & o.nan) != 0;
+        plus = minus = 0;
+        for (uint32_t left = pos | neg; left; left &= left - 1) {
+            const uint32_t w = __builtin_ctz(left), bit = m & (1u << w);
+            const float c = bit ? coef[lane * W + w] : 1.0f;
+            nan = nan || c == 0.0f;
+            (c < 0.0f ? minus : plus) |= bit;
         }
-        for (int u = 0; u < U; ++u) {
-            const uint32_t m = mask[u] & rows;
-            if (!m || ((lost >> u) & 1u)) continue;
-            float gb = 0.0f;
+        const uint32_t up = (plus & pos) | (minus & neg), down = (plus & neg) | (minus & pos);   // members that add +inf, -inf
+        lost |= __builtin_amdgcn_ballot_w64(nan);
+        infinite |= __builtin_amdgcn_ballot_w64((up | down) != 0);
+        auto meet = [](const uint32_t a, const uint32_t b) { return a && b && ((a | b) & ((a | b) - 1)); };
+        const uint64_t open = __builtin_amdgcn_ballot_w64(meet(up, down)) & ~lost;
+        seen.nan |= o.nan;
+        if (!open) {
+            seen.pos = pos;
+            seen.neg = neg;
+        }
+        const uint32_t here = o.pos | o.neg;
+        return __builtin_amdgcn_ballot_w64(meet(up & here, down & here)) & open;
+    };
+    // The updates `todo` whose infinite members are of both signs at an element: `n` times 64 of them, one per lane, at(i) the i-th
+    // (INT64_MIN: none).  Most rows agree in sign wherever they are infinite, which settles the groups whose coefficients do.
+    auto poison = [&](auto at, auto n, const uint32_t rows, const uint64_t todo, const uint32_t plus, const uint32_t minus) {
+        constexpr int N = decltype(n)::value, Q = N < 4 ? N : 4;   // Q loads in flight
+        const uint64_t mixed = __builtin_amdgcn_ballot_w64((plus & rows) && (minus & rows)) & todo;
+#pragma unroll 1
+        for (int i = 0; i < N; i += Q) {
+            uint32_t pos[Q], neg[Q];
 #pragma unroll
-            for (int w = 0; w < 4 * KS; ++w)   // (no mask bit is set beyond the last row)
-                if ((m >> w) & 1u) gb += bad_value(g[w]) ? coef[u * W + w] * g[w] : 0.0f;
-            const double s = wave_sum_to_lane63((double)(gb * gb));
-            const int lo = __builtin_amdgcn_readlane((int)__double2loint(s), 63);
-            const int hi = __builtin_amdgcn_readlane((int)__double2hiint(s), 63);
-            const double all = __hiloint2double(hi, lo);
-            if (all != all) lost |= 1ull << u;
-            const double t = lane == 16 * ((u >> 2) & 3) ? all : 0.0;
+            for (int q = 0; q < Q; ++q) pos[q] = neg[q] = 0u;
+#pragma unroll 1
+            for (uint32_t left = rows; left; left &= left - 1) {
+                const uint32_t w = __builtin_ctz(left);
+                const void* const row = in->rows.p[w];
+                float v[Q];
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+                for (int q = 0; q < Q; ++q) v[q] = at(i + q) != INT64_MIN ? R::load1(row, at(i + q)) : 0.0f;
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if ((u >> 4) == b && (u & 3) == r) sum[b][r] += t;
+                for (int q = 0; q < Q; ++q) {
+                    pos[q] |= v[q] == __builtin_inff() ? 1u << w : 0u;
+                    neg[q] |= v[q] == -__builtin_inff() ? 1u << w : 0u;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const uint32_t any = pos[q] | neg[q];
+                if (!__builtin_amdgcn_ballot_w64((any & (any - 1)) != 0)) continue;   // two rows nowhere
+                const bool agree = !__builtin_amdgcn_ballot_w64(pos[q] && neg[q]);
+                for (uint64_t left = (agree ? mixed : todo) & ~lost; left; left &= left - 1) {
+                    const int u = __builtin_ctzll(left);
+                    const uint32_t a = __builtin_amdgcn_readlane(plus, u), b = __builtin_amdgcn_readlane(minus, u);
+                    if (__builtin_amdgcn_ballot_w64(((pos[q] & a) | (neg[q] & b)) && ((pos[q] & b) | (neg[q] & a))))
+                        lost |= 1ull << u;
+                }
+            }
         }
     };
-    auto settle = [&](const uint32_t rows) {
-        bool all = true;
-        for (int u = 0; u < U; ++u) all = all && (!(mask[u] & rows) || ((lost >> u) & 1u));
-        if (all) settled |= rows;
+    // What a lane has of the rows' kinds: the largest bits of all, and as a signed number, by magnitude and as an unsigned one.  (With NaN
+    // the infinities beside them may be hidden, or seen where there are none: the sums of such a row are NaN.)
+    typedef typename std::conditional<BF, u16x2, uint32_t>::type bits_t;
+    typedef typename std::conditional<BF, i16x2, int32_t>::type sbits_t;
+    struct Kinds {
+        bits_t size, last;
+        sbits_t first;
     };
-    // takes them out of one load; true where the lane held any
-    auto clean = [&](vec_t& x) {
-        bool any = false;
+    auto none = [&]() {
+        if constexpr (BF) return Kinds{u16x2{0, 0}, u16x2{0, 0}, i16x2{0, 0}};
+        else return Kinds{0u, 0u, 0};
+    };
+    auto clean = [&](vec_t& x, Kinds& kd) {   // takes them out of one load
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             if constexpr (BF) {
                 const uint32_t d = x[k];
+                kd.size = __builtin_elementwise_max(kd.size, __builtin_bit_cast(u16x2, d & 0x7fff7fffu));
+                kd.last = __builtin_elementwise_max(kd.last, __builtin_bit_cast(u16x2, d));
+                kd.first = __builtin_elementwise_max(kd.first, __builtin_bit_cast(i16x2, d));
                 const bool lo = (d & 0x7f80u) == 0x7f80u, hi = (d & 0x7f800000u) == 0x7f800000u;
-                any = any || lo || hi;
                 x[k] = (lo ? 0u : d & 0xffffu) | (hi ? 0u : d & 0xffff0000u);
             } else {
-                const bool b = bad_value(x[k]);
-                any = any || b;
-                x[k] = b ? 0.0f : x[k];
+                const uint32_t d = __float_as_uint(x[k]);
+                kd.size = max(kd.size, d & 0x7fffffffu);
+                kd.last = max(kd.last, d);
+                kd.first = max(kd.first, (int32_t)d);
+                x[k] = (d & 0x7f800000u) == 0x7f800000u ? 0.0f : x[k];
             }
         }
-        return any;
     };
     auto rows_of = [&](const bool any, const int s) {   // rows 4 s .. 4 s + 3 by the quarters of the wave that held any
         const uint64_t lanes = __builtin_amdgcn_ballot_w64(any);
         uint32_t rows = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) rows |= (lanes >> (16 * q) & 0xffffu) ? 1u << (4 * s + q) : 0u;
-        return rows;
+        return W < 32 ? rows & ((1u << W) - 1u) : rows;   // (beyond the last row it is repeated)
+    };
+    auto add_kinds = [&](Odd& o, const Kinds& kd, const int s) {
+        if constexpr (BF) {
+            o.nan |= rows_of(kd.size[0] > 0x7f80 || kd.size[1] > 0x7f80, s);
+            o.pos |= rows_of(kd.first[0] >= 0x7f80 || kd.first[1] >= 0x7f80, s);
+            o.neg |= rows_of(kd.last[0] >= 0xff80 || kd.last[1] >= 0xff80, s);
+        } else {
+            o.nan |= rows_of(kd.size > 0x7f800000u, s);
+            o.pos |= rows_of(kd.first >= 0x7f800000, s);
+            o.neg |= rows_of(kd.last >= 0xff800000u, s);
+        }
+    };
+    auto news = [&](const Odd& o) {   // what no earlier tile has settled
+        return ((o.nan | (o.pos & ~seen.pos) | (o.neg & ~seen.neg)) & ~seen.nan) != 0;
     };
 
     auto fetch = [&](const int64_t tile, vec_t (&x)[CH][KS]) {
@@ -313,23 +377,32 @@ __global__ __launch_bounds__(kBlock, mma_waves(KS, NB)) void norm_mma_kernel(con
             }
         if (tile + step < ntile) fetch(tile + step, next);
         if (spoilt()) {
-            uint32_t rows = 0;
+            Odd o = {0, 0, 0};
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                bool any = false;
+                Kinds kd = none();
 #pragma unroll
-                for (int c = 0; c < CH; ++c) any = clean(x[c][s]) || any;
-                rows |= rows_of(any, s);
+                for (int c = 0; c < CH; ++c) clean(x[c][s], kd);
+                add_kinds(o, kd, s);
             }
-            if (rows & ~settled) {
-                for (int i = 0; i < kTile / 64; ++i) {
-                    const int64_t j = tile * kTile + 64 * i + lane;
-                    poison(j < nchunk * E ? j : INT64_MIN, rows);
+            if (news(o)) {
+                uint32_t plus, minus;
+                const uint64_t todo = examine(o, plus, minus);
+                if (todo) {
+                    auto at = [&](const int i) {
+                        const int64_t j = tile * kTile + 64 * i + lane;
+                        return j < nchunk * E ? j : INT64_MIN;
+                    };
+                    poison(at, std::integral_constant<int, kTile / 64>{}, o.pos | o.neg, todo, plus, minus);
                 }
-                settle(rows);
             }
         }
-        static_for<0, CH>([&](auto cc) { product(x[decltype(cc)::value]); });
+        static_for<0, CH>([&](auto cc) {
+            constexpr int C = decltype(cc)::value;
+            product(x[C]);
+            // fp32 rows: the units are scheduled in two halves (in one, the registers run out with 8 rows and 32 updates: 159 -> 180 us)
+            if constexpr (!BF && 2 * C + 2 == CH) __builtin_amdgcn_sched_barrier(0);
+        });
     }
     // What the chunks leave over, at most 63 + 7 elements, for the wave whose turn it is: fetched one by one, then a unit like the
     // others (walked instead, they take half a microsecond an update: 0.3 M elements, 8 rows, 64 updates 49 against 23 us).
@@ -361,10 +434,19 @@ __global__ __launch_bounds__(kBlock, mma_waves(KS, NB)) void norm_mma_kernel(con
 #pragma unroll
             for (int s = 0; s < KS; ++s) look(x[s]);
             if (spoilt()) {
-                uint32_t rows = 0;
+                Odd o = {0, 0, 0};
 #pragma unroll
-                for (int s = 0; s < KS; ++s) rows |= rows_of(clean(x[s]), s);
-                for (int i = 0; i < kUnit; i += 64) poison(r0 + i + lane < nrest ? rest(r0 + i + lane) : INT64_MIN, rows);
+                for (int s = 0; s < KS; ++s) {
+                    Kinds kd = none();
+                    clean(x[s], kd);
+                    add_kinds(o, kd, s);
+                }
+                uint32_t plus = 0, minus = 0;
+                const uint64_t todo = news(o) ? examine(o, plus, minus) : 0;
+                if (todo) {
+                    auto at = [&](const int i) { return r0 + 64 * i + lane < nrest ? rest(r0 + 64 * i + lane) : INT64_MIN; };
+                    poison(at, std::integral_constant<int, kUnit / 64>{}, o.pos | o.neg, todo, plus, minus);
+                }
             }
             product(x);
         }
@@ -381,7 +463,10 @@ __global__ __launch_bounds__(kBlock, mma_waves(KS, NB)) void norm_mma_kernel(con
             q += dpp_take<0x4E, 0xf>(q);    // quad_perm [2,3,0,1]
             q += dpp_take<0x141, 0xf>(q);   // row_half_mirror
             q += dpp_take<0x140, 0xf>(q);   // row_mirror
-            if (col == 0) total[wave][16 * b + 4 * quarter + r] = q;
+            const int u = 16 * b + 4 * quarter + r;
+            if ((lost >> u) & 1u) q = __builtin_nan("");
+            else if ((infinite >> u) & 1u) q += __builtin_inf();
+            if (col == 0) total[wave][u] = q;
         }
     __syncthreads();
     for (int u = threadIdx.x; u < U; u += kBlock) {

@@ -463,11 +463,14 @@ __global__ __launch_bounds__(kBlock, mma_waves(KS, NB)) void norm_mma_kernel(con
             q += dpp_take<0x4E, 0xf>(q);    // quad_perm [2,3,0,1]
             q += dpp_take<0x141, 0xf>(q);   // row_half_mirror
             q += dpp_take<0x140, 0xf>(q);   // row_mirror
-            const int u = 16 * b + 4 * quarter + r;
-            if ((lost >> u) & 1u) q = __builtin_nan("");
-            else if ((infinite >> u) & 1u) q += __builtin_inf();
-            if (col == 0) total[wave][u] = q;
+            if (col == 0) total[wave][16 * b + 4 * quarter + r] = q;
         }
+    if (lost | infinite) {   // one update a lane
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if ((lost >> lane) & 1u) total[wave][lane] = __builtin_nan("");   // (no bit is set beyond the last update)
+        else if ((infinite >> lane) & 1u) total[wave][lane] += __builtin_inf();
+    }
     __syncthreads();
     for (int u = threadIdx.x; u < U; u += kBlock) {
         double s = 0.0;

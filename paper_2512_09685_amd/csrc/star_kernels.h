@@ -185,6 +185,8 @@ hipError_t launch_seq(int Wp, int dtype, bool norms, const SeqArgs& a, int num_c
 int walk_max_updates();
 hipError_t launch_norm_walk(int Wp, int dtype, const SeqArgs& a, int num_cu, int grid_cap, int* grid_out,
                             hipStream_t s);
+// Its grid and the updates of a workgroup on the vector ALUs: `tiles` and perhaps a rest, at most `most` workgroups.
+void walk_shape(int W, int most, int num_cu, int64_t tiles, bool rest, int U, int* grid, int* share);
 // Whether such a launch goes to the matrix cores: U updates whose groups have `members` in all, P elements behind the head.
 bool norms_on_matrix_cores(int Wp, bool f32, int U, int members, int64_t P);
 

@@ -173,6 +173,21 @@ __global__ __launch_bounds__(kBlock) void norm_walk_kernel(const WalkKernelArgs 
     }
 }
 
+// A shard of fewer tiles than units: the updates are shared out as well, in fours.  There the walk is one chain of updates
+// long (16 rows, 16 updates, 5000 / 100 000 elements: 15.1 / 15.3 us a call, 19.9 / 20.7 in one piece; 8 rows, 32 updates: 15.2
+// against 23), and each share's rows come out of the caches.  Up to 16 rows two workgroups a unit, which take turns at
+// waiting (0.3 M elements, 64 updates of 4 / 8 / 16 rows: 21.6 / 38.7 / 55.1 with one, 18.9 / 22.6 / 29.6 with two; 32 rows, 0.1 M: 34.0, 38.4).
+//   The rest is as long as a tile and gets workgroups of its own where the units have room for them beside the tiles' shares; it takes
+// none away from those (64 tiles of 2048 elements and a rest, 64 updates, 20 / 32 rows: 27.5 / 35.7 us; 30.5 / 39.1 where the rest counted as a tile).
+void walk_shape(int W, int most, int num_cu, int64_t tiles, bool rest, int U, int* grid, int* share) {
+    const int room = (W <= 16 ? 2 : 1) * num_cu;
+    *grid = (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), most);
+    const int parts = std::max(1, std::min(room / *grid, (U + 3) / 4));
+    *share = ((U + parts - 1) / parts + 3) / 4 * 4;
+    const int shares = (U + *share - 1) / *share;
+    if (rest && *grid == tiles && tiles < most && (tiles + 1) * shares <= room) ++*grid;
+}
+
 namespace {
 
 size_t walk_lds_bytes(int U) { return sizeof(double) * (size_t)((U + 3) / 4 * 4) * kSlots; }
@@ -197,16 +212,10 @@ hipError_t launch_walk_t(WalkKernelArgs& a, int num_cu, int grid_cap, int* grid_
     // Long-lived workgroups sweep the shard together, for every stream: the work queue is behind even where one or two
     // updates leave the pass bound by memory (1 fp32 row, 25.6 M elements, 1 update: 22 against 39 us; 16 rows, 2
     // updates: 232 against 252; 4 rows, 100 M elements: 241 against 246).
-    const int64_t width = (int64_t)kBlock * walk_chunks(W);
-    const int64_t tiles = (a.P / 4 + width - 1) / width + (rest_count(a.head, a.P, a.P / 4) ? 1 : 0);   // (P > 0)
     const int per_cu = walk_workgroups_per_cu(W, std::is_same<R, RowF32>::value, a.U);
-    const int grid = (int)std::min<int64_t>(tiles, std::min(per_cu * num_cu, grid_cap));
-    // A shard of fewer tiles than units: the updates are shared out as well, in fours.  There the walk is one chain of updates
-    // long (16 rows, 16 updates, 5000 / 100 000 elements: 15.1 / 15.3 us a call, 19.9 / 20.7 in one piece; 8 rows, 32 updates: 15.2
-    // against 23), and each share's rows come out of the caches.  Up to 16 rows two workgroups a unit, which take turns at
-    // waiting (0.3 M elements, 64 updates of 4 / 8 / 16 rows: 21.6 / 38.7 / 55.1 with one, 18.9 / 22.6 / 29.6 with two; 32 rows, 0.1 M: 34.0, 38.4).
-    const int parts = std::max(1, std::min((W <= 16 ? 2 : 1) * num_cu / grid, (a.U + 3) / 4));
-    const int share = ((a.U + parts - 1) / parts + 3) / 4 * 4;
+    const int64_t tiles = (a.P / 4 + (int64_t)kBlock * walk_chunks(W) - 1) / ((int64_t)kBlock * walk_chunks(W));
+    int grid = 0, share = 0;
+    walk_shape(W, std::min(per_cu * num_cu, grid_cap), num_cu, tiles, rest_count(a.head, a.P, a.P / 4) > 0, a.U, &grid, &share);
     *grid_out = grid;
     a.share = share;
     hipLaunchKernelGGL((norm_walk_kernel<W, R>), dim3(grid, (a.U + share - 1) / share), dim3(kBlock),

@@ -570,3 +570,27 @@ def test_plan_choice_is_consistent_over_random_calls():
             assert c["queue_order"] == 0
         seen.add((c["kernel"], c["collapsed_update"], c["queue_order"], c["launches"] > 1))
     assert len(seen) >= 8       # the generator reaches the different routes
+
+
+@pytest.mark.parametrize("W", [1, 8, 16, 20, 32])
+def test_walk_shape_a_rest_takes_no_workgroups_from_the_tiles(W):
+    """The launch of the direct norm sums without an update, on 256 units: the updates are shared out as if there were no rest, which gets
+    workgroups of its own only where they fit beside the others."""
+    shape = star.load_library()._ZN4star10walk_shapeEiiilbiPiS0_
+    shape.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_bool, ctypes.c_int, ctypes.c_void_p,
+                      ctypes.c_void_p]
+    room = 512 if W <= 16 else 256
+    for most in (256, 1024):
+        for tiles in list(range(0, 140)) + [255, 256, 257, 511, 512, 1023, 1024, 5000]:
+            for U in (1, 3, 4, 5, 16, 32, 64, 128, 240):
+                got = []
+                for rest in (False, True):
+                    grid, share = ctypes.c_int(), ctypes.c_int()
+                    shape(W, most, 256, tiles, rest, U, ctypes.byref(grid), ctypes.byref(share))
+                    got.append((grid.value, share.value))
+                (g0, s0), (g1, s1) = got
+                assert s0 == s1 and s0 % 4 == 0 and 4 <= s0 <= (U + 3) // 4 * 4
+                shares = -(-U // s0)
+                assert g0 == min(max(tiles, 1), most) and (g0 * shares <= room or shares == 1)
+                fits = 0 < tiles == g0 and tiles < most and (tiles + 1) * shares <= room
+                assert g1 == g0 + (1 if fits else 0)

@@ -228,21 +228,26 @@ hipError_t launch_walk_t(WalkKernelArgs& a, int num_cu, int grid_cap, int* grid_
 // Whether the matrix cores take the call (norm_mma_kernel): by what either kernel takes on 30 M elements once its arithmetic
 // bounds it, in us.  The walk pays for every update, every coefficient it loads and every member (fp32 rows, 4 / 8 / 13 of them, 128
 // updates of half the rows: 486 / 822 / 1163; of two: 396 / 587 / 727), more from 14 rows on, where fewer waves fit (16 / 24: 1660 / 2483,
-// 1378 / 1836), and with 32 rows, where one does (6002, 4522).  The matrix cores pay for 16 updates at a time: fp32 rows by row groups
-// of four (1 / 2 / 4 / 8 of them, 128 updates: 389, 622, 1065, 2074), bf16 rows hardly by those (332, 366, 448, 735).  Where memory bounds
-// both they are level, so the rule is good there too.  Up to 4 bf16 rows the walk, light there, gains more on the matrix cores from 4 Mi elements on than its
-// count says (8 / 30 M, 1 row, 64 updates 55 / 152 against 58 / 172, 3 rows, 24 updates of 1.5 members 31 / 84 against 33 / 94; 1.1 M, 1 row, 128
-// updates 49 against 32).  Both sides of it, 1 to 32 rows, 1 to 128 updates, groups of one or two and of half
-// the rows, 2 / 8 / 30 M elements: fp32 rows 1.45 / 1.40 / 1.29 times ahead on the mean where it says so, bf16 rows 1.56 / 1.91 / 1.94, at worst 6 %
-// behind.  Short shards (walk / matrix cores, us a call): 0.1 M elements, 32 updates of 4 / 8 / 16 fp32 rows 10.4 / 10.2 / 18.2 against 11.7 / 10.4 / 15.8, 0.3 M
+// 1378 / 1836), and with 32 rows, where one does (6002, 4522).  The matrix cores pay for 16 updates at a time, and for the blocks that even
+// out the workgroups (80 updates: six, see launch_mma_k): fp32 rows by row groups of four (1 / 2 / 4 / 8 of them, 128 updates: 389, 622,
+// 1065, 2074), bf16 rows hardly by those (332, 366, 448, 735).  Where memory bounds both they are level, so the rule is good there too.
+//   Up to 4 rows the walk is better on long shards than its count says, so the line lies higher there.  bf16 rows, walk / matrix cores:
+// 8 / 30 M, 1 row, 64 updates 55 / 152 against 58 / 172, 3 rows, 24 updates of 1.5 members 31 / 84 against 33 / 94, but 1.1 M, 1 row, 128 updates 49
+// against 32; fp32 rows: 30 M, 4 rows, 64 updates of 1.5 members 212 against 226, 3 rows of 2 219 against 225, but 8 M 76 against 75 and
+// 76 against 73.
+//   Short shards (walk / matrix cores, us a call): 0.1 M elements, 32 updates of 4 / 8 / 16 fp32 rows 10.4 / 10.2 / 18.2 against 11.7 / 10.4 / 15.8, 0.3 M
 // 12.8 / 14.0 / 23.0 against 12.6 / 14.0 / 20.8; bf16 rows, whose rest is fetched step by step, 0.3 M 12.7 / 14.7 / 21.9 against 14.4 / 15.2 / 23.2, 0.6 M 14.6 / 21.6 /
 // 33.7 against 15.6 / 17.1 / 26.3.
+//   Timed against the walk alone, 1 to 32 rows, 1 to 128 updates, groups of one or two and of half the rows: where the rule says so the matrix cores
+// are ahead 2.2 / 1.43 / 1.38 / 1.29 times on the mean with fp32 rows (0.3 / 2 / 8 / 30 M elements), 1.83 / 1.57 / 2.03 / 2.01 times with bf16 rows
+// (0.5 / 2 / 8 / 30 M), and nowhere more than 2 % behind.
 bool norms_on_matrix_cores(int Wp, bool f32, int U, int members, int64_t P) {
     if (P < (f32 ? 1 << 17 : 1 << 19) * (Wp > 4 ? 1 : 2)) return false;
     double walk = Wp <= 13 ? U * (1.6 + 0.25 * Wp) + 0.6 * members : U * (1.6 + 0.45 * Wp) + 0.55 * members;
     if (Wp > 28 && U > 4) walk *= 1.8;
-    const int groups = (Wp + 3) / 4, blocks = (U + 15) / 16;
-    if (f32) return walk > blocks * (22 + 28 * groups) * (Wp > 4 ? 1.0 : 1.1);
+    const int groups = (Wp + 3) / 4, parts = ((U + 15) / 16 + 3) / 4;   // of up to four blocks each
+    const int blocks = parts * (((U + 15) / 16 + parts - 1) / parts);
+    if (f32) return walk > blocks * (22 + 28 * groups) * (Wp > 4 ? 1.0 : P < 16 << 20 ? 1.1 : 1.25);
     return walk > (15.0 + blocks * (26 + 4 * groups)) * (Wp > 4 || P < 4 << 20 ? 1.0 : 1.45);
 }
 

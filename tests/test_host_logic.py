@@ -594,3 +594,22 @@ def test_walk_shape_a_rest_takes_no_workgroups_from_the_tiles(W):
                 assert g0 == min(max(tiles, 1), most) and (g0 * shares <= room or shares == 1)
                 fits = 0 < tiles == g0 and tiles < most and (tiles + 1) * shares <= room
                 assert g1 == g0 + (1 if fits else 0)
+
+
+@pytest.mark.parametrize("dtype,W,U,least,most,P,matrix", [
+    ("f32", 4, 64, 1, 2, 30_000_000, 0), ("f32", 4, 64, 1, 2, 8_000_000, 1), ("f32", 4, 64, 1, 4, 30_000_000, 1),
+    ("f32", 3, 64, 1, 3, 30_000_000, 0), ("f32", 3, 64, 1, 3, 8_000_000, 1), ("f32", 8, 32, 1, 8, 25_557_032, 1),
+    ("bf16", 1, 64, 1, 1, 30_000_000, 0), ("bf16", 1, 128, 1, 1, 1_100_000, 1), ("bf16", 1, 80, 1, 1, 8_000_000, 0),
+    ("bf16", 4, 80, 1, 2, 60_000_000, 0), ("bf16", 4, 64, 1, 4, 30_000_000, 1), ("bf16", 8, 16, 1, 8, 30_000_000, 1)])
+def test_plan_choice_direct_norms_on_matrix_cores(dtype, W, U, least, most, P, matrix):
+    """Either side of the line between the two kernels of direct norm sums, where both were timed."""
+    rng = np.random.default_rng(1)
+    sizes = rng.integers(least, most + 1, size=U)
+    offs = np.concatenate([[0], np.cumsum(sizes)])
+    us = star.UpdateStream(offs, np.concatenate([rng.permutation(W)[:y] for y in sizes]))
+    c = star.star_plan_choice(P, W, dtype, us, update=False, want_norms=True, direct_norms=True)
+    assert c["kernel"] == star.KERNEL_SEQ and c["norms_on_matrix_cores"] == matrix
+    # the same pass beside an update; none where the norms come from the Gram matrix
+    c = star.star_plan_choice(P, W, dtype, us, lr=0.1, momentum_coef=0.9, want_norms=True, direct_norms=True)
+    assert c["norms_on_matrix_cores"] == matrix
+    assert star.star_plan_choice(P, W, dtype, us, lr=0.1, momentum_coef=0.9, want_norms=True)["norms_on_matrix_cores"] == 0

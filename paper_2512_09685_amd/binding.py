@@ -202,12 +202,14 @@ def _rows(grad_rows: Sequence, P: int):
 def _stream_handle(stream):
     """Raw handle of a stream: torch's current one on the current device, an integer, or a torch stream.  The current one is asked
     for as a number: torch.cuda.current_stream() makes an object of it first, which on a short shard is a fifth of the whole call
-    (1 Mi elements, 4 fp32 rows, ten updates: 8.8 -> 6.9 us)."""
+    (1 Mi elements, 4 fp32 rows, ten updates: 8.8 -> 6.9 us).  A torch without these functions, which are not part of its public
+    interface, gives the object."""
     if stream is None:
         import torch
-        if not torch.cuda.is_initialized():
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw is None or device is None or not torch.cuda.is_initialized():
             return torch.cuda.current_stream().cuda_stream
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        return raw(device())
     return stream if isinstance(stream, int) else stream.cuda_stream
 
 

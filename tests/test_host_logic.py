@@ -613,3 +613,21 @@ def test_plan_choice_direct_norms_on_matrix_cores(dtype, W, U, least, most, P, m
     c = star.star_plan_choice(P, W, dtype, us, lr=0.1, momentum_coef=0.9, want_norms=True, direct_norms=True)
     assert c["norms_on_matrix_cores"] == matrix
     assert star.star_plan_choice(P, W, dtype, us, lr=0.1, momentum_coef=0.9, want_norms=True)["norms_on_matrix_cores"] == 0
+
+
+@pytest.mark.parametrize("missing", [(), ("_cuda_getCurrentRawStream",), ("_cuda_getDevice",)])
+def test_current_stream_without_torchs_private_functions(missing, monkeypatch):
+    """The handle of torch's current stream comes from two functions that a torch may not have; then from the stream object."""
+    import types
+
+    import torch
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 1000 + device, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    for name in missing:
+        monkeypatch.delattr(torch._C, name)
+    assert binding._stream_handle(None) == (77 if missing else 1003)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
+    assert binding._stream_handle(None) == 77
+    assert binding._stream_handle(5) == 5 and binding._stream_handle(types.SimpleNamespace(cuda_stream=9)) == 9

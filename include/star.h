@@ -287,7 +287,7 @@ star_status star_plan_affine(int32_t W, const star_updates *upd, const star_hpar
 /*
  * Host-only: what star_group_update (update = 1) or star_group_norms
  * (update = 0) would launch for this call, decided by the same code that
- * launches it; buffers are taken to be 16-byte aligned.
+ * launches it; buffers are taken to start on whole cache lines (128 bytes).
  */
 typedef struct {
     int32_t kernel;       /* star_kernel of the main kernel: STAR_KERNEL_SEQ (step-by-step), STAR_KERNEL_AFFINE

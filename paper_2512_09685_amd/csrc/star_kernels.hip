@@ -500,7 +500,8 @@ __global__ __launch_bounds__(kBlock) void gram_norms_kernel(const double* __rest
 // launches: workgroup e sums entry e as reduce_kernel does, the workgroup that arrives last forms the norms.  The coefficients
 // (read from the host's memory by gram_norms_kernel) are in device memory: the launch before carried them there.
 // Update with norms, two launches -> one: 0.3 M elements, 1 / 4 / 8 fp32 rows 18.3 / 18.5 / 20.3 -> 14.1 / 14.1 / 16.6 us a call, 1 M, 4 / 8 rows 18.7 / 20.7
-// -> 15.5 / 19.5, 2 M, 8 rows 28.5 -> 27.1, 4 M, 4 rows 31.8 -> 31.8 (1 to 1.5 us of each by the shorter way to the stream's handle).
+// -> 15.5 / 19.5, 2 M, 8 rows 28.5 -> 27.1, 4 M, 4 rows 31.8 -> 31.8 (1 to 1.5 us of each by the shorter way to the stream's handle; with
+// buffers that change from call to call 0.3 M, 8 rows 18.1 -> 16.0 to 17.5).
 // (With a workgroup of this launch to carry the coefficients: 0.3 M alike, but 18.3 -> 18.7 on buffers that are not in the caches.)
 // Not for more rows: those are more sums for the last workgroup, and a hand-over between workgroups costs as much as a launch on
 // the device, only less on the host.

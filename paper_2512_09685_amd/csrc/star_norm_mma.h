@@ -40,11 +40,12 @@ hipError_t launch_norm_mma_bf16(WalkKernelArgs& k, int Wp, int num_cu, int grid_
 // 3.5e-8 of its size whatever the row count (fp32 multiply-adds, norm_walk_kernel: 2.5e-8 / 4e-8 / 6e-8 / 9e-8 with 1 / 6 / 16 / 32
 // rows).  Up to four rows the upper ones come first, 2.5e-8 with one row.  What the norm of 65 536 normal elements is off by for that, before it is rounded
 // to fp32: 0.3e-9 to 3e-9 rms (multiply-adds: 0.7e-9 to 2e-9); rows of one sign up to 1.5e-8 (6e-9).
-//   It costs up to 8 rows an instruction more (30 M elements, 4 / 8 rows, 32 updates 82 / 96 -> 102 / 118 us).
-//   Memory bounds it up to about 32 updates of 8 fp32 rows or 16 of 16, and bf16 rows up to 64 updates; beyond, the matrix instructions and
-// the squares do, which overlap little.  25.6 M elements, norm_walk_kernel -> this one: 8 fp32 rows, 32 updates of 4.5 members 198 -> 158 us (the
-// reads alone 120), 16 rows, 32 updates 424 -> 283, 32 rows, 16 updates 717 -> 488 (the reads 481); 30 M, bf16 rows: 8 rows, 32 updates 217 -> 118,
-// 16 rows, 64 updates 840 -> 230, 32 rows, 64 updates 2703 -> 363.  bf16 rows through the fp32 instructions: 167, 540, 1042.
+//   It costs up to 8 rows an instruction more (30 M elements, 4 / 8 rows, 32 updates 82 / 96 -> 102 / 118 us, norm_walk_kernel 134 / 220).
+//   Memory bounds it, within 8 %, with 16 updates from 8 fp32 or 16 bf16 rows on and with 32 updates of 32 bf16 rows; beyond, the matrix
+// instructions and the squares do, which overlap only in part.  25.6 M elements, norm_walk_kernel -> this one (the reads alone): 8 fp32 rows, 32 updates of
+// 4.5 members 198 -> 160 us (120), 16 rows, 16 / 32 updates 302 / 424 -> 251 / 274 (240), 32 rows, 16 updates 717 -> 498 (481); bf16 rows: 8 rows, 32
+// updates 206 -> 105 (60), 16 rows, 16 / 64 updates 239 / 722 -> 128 / 208 (120), 30 M, 32 rows, 32 updates 1437 -> 311 (282).  bf16 rows through the fp32
+// instructions, 30 M: 8 rows, 32 updates 167, 16 rows, 64 updates 540, 32 rows, 64 updates 1042.
 //   Largest error of a norm against 64 bits, 1 to 32 rows, 3 to 240 updates: 9.7e-8 either way for fp32 rows, bf16 rows 6.3e-8 either way.
 typedef float acc4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -83,7 +84,8 @@ __device__ __forceinline__ uint32_t coef_piece(float c, const int piece) {
 // 16-byte loads per lane and row group of a tile: about 8 KB of a wave in flight, and as much again from the look-ahead.
 constexpr int mma_units(int KS) { return KS == 1 ? 8 : (KS == 2 ? 4 : (KS <= 4 ? 2 : 1)); }
 
-// Waves per SIMD the registers are cut for: three where that spills none.
+// Waves per SIMD the registers are cut for, and the launch made for: three with one block of updates, and with two up to 16 rows.  (Most of the other
+// fp32 instances would have registers for three as well, 117 to 167; only 8 rows, 32 updates were timed both ways, see launch_mma_k.)
 constexpr int mma_waves(int KS, int NB) { return NB == 1 || (NB == 2 && KS <= 4) ? 3 : 2; }
 
 // KS row groups of four, NB blocks of 16 updates
@@ -157,12 +159,12 @@ __global__ __launch_bounds__(kBlock, mma_waves(KS, NB)) void norm_mma_kernel(con
     // operand, and what they make of their groups is kept apart, as two sets of updates that the sums meet when the kernel ends.  From which
     // rows of a tile hold NaN, +inf or -inf (`Odd`, bits of rows) most of it follows without a look at the elements, one update a
     // lane: a member with NaN, or with an infinity and a coefficient of zero, makes the sum NaN; infinities that all enter a group with
-    // the same sign, or that are one row's, make it infinite.  Only where two rows with infinities of both signs meet in a group, whose sum
-    // is not NaN yet, are they added element by element (poison).  What a wave has seen once needs no second look: rows with NaN, since
+    // the same sign, or that are one row's, make it infinite.  Only where rows meet in a group with infinities of both signs and its sum is
+    // not NaN yet are they looked at element by element (poison).  What a wave has seen once needs no second look: rows with NaN, since
     // the sums they are in are NaN, and infinite rows while no group has a choice of signs.  So a worker that diverged costs the wave one tile
     // and the others little more than the search (8 rows of 25.6 M elements, 32 updates, clean / one row of NaN / of +inf / of infinities of both signs / all
-    // rows of +inf: fp32 159 / 193 / 191 / 194 / 188 us, bf16 106 / 146 / 140 / 139 / 137; two rows that agree in signs that change 260, 253;
-    // norm_walk_kernel 198 and 188 in all of them; every spoilt tile element by element: 1460 to 2870 us).
+    // rows of +inf: fp32 166 / 229 / 208 / 205 / 192 us, bf16 105 / 153 / 148 / 146 / 137; two rows that agree in signs that change 267, 251;
+    // norm_walk_kernel 197 to 220 and 187 to 207; every spoilt tile element by element: 1460 to 2870 us).
     uint64_t lost = 0, infinite = 0;   // updates whose sum is NaN; whose sum is infinite at least
     struct Odd {
         uint32_t nan, pos, neg;
@@ -489,7 +491,7 @@ hipError_t launch_mma_k(WalkKernelArgs& k, int W, int num_cu, int grid_cap, int*
     const int parts = std::max((blocks + 3) / 4, (int)std::min<int64_t>(blocks, std::max<int64_t>(1, num_cu / tiles)));
     const int nb = (blocks + parts - 1) / parts;
     k.share = 16 * nb;
-    // as many workgroups as fit, long-lived (8 rows, 32 updates, 25.6 M elements, 1 / 2 / 3 / 4 per unit: fp32 192 / 164 / 160 / 160 us)
+    // as many workgroups as the registers were cut for, long-lived (8 rows, 32 updates, 25.6 M elements, 1 / 2 / 3 / 4 per unit: fp32 192 / 164 / 160 / 160 us)
     const int grid = (int)std::min<int64_t>(tiles, std::min(mma_waves(KS, nb) * num_cu, grid_cap));
     *grid_out = grid;
     const dim3 wg(grid, (k.U + k.share - 1) / k.share);

@@ -381,6 +381,7 @@ struct Launch {
     bool finish_at_once = false;   // Gram route: sums and norms in one finishing launch
     bool split_norms = false; // update by the collapsed map, norms by a separate direct pass (see decide)
     bool collapsed_in_seq = false;   // step-by-step kernel walks the updates for the norms, applies the update as one map
+    int burst = 0;            // collapsed update without norms: see burst_claim
 };
 
 Launch decide(const star::Plan& plan, int grad_dtype, bool update, bool want_norms, int64_t P, const Opts& opt) {
@@ -441,8 +442,14 @@ Launch decide(const star::Plan& plan, int grad_dtype, bool update, bool want_nor
                                       l.route == star::Route::Seq);
     if (l.route == star::Route::Affine) {
         const bool gram = want_norms;
+        if (update && !gram) {
+            l.burst = star::burst_claim(l.Wp, grad_dtype == STAR_F32, P);
+            // a caller's own threshold: the queue from there on, the fixed assignment below
+            if (opt.queue_min > 0) l.burst = l.want_queue ? star::burst_claim(l.Wp, grad_dtype == STAR_F32, (int64_t)1 << 62) : 0;
+            if (star::bursts(l.Wp, grad_dtype == STAR_F32)) l.want_queue = l.burst > 0;
+        }
         l.mfma = gram && gram_on_matrix_cores(l.Wp, grad_dtype, opt.kernel, update, P);
-        l.queue_order = l.mfma || (l.want_queue && star::aff_takes_queue(gram, l.Wp, grad_dtype == STAR_F32, update));
+        l.queue_order = l.mfma || l.burst > 0 || (l.want_queue && star::aff_takes_queue(gram, l.Wp, grad_dtype == STAR_F32, update));
         l.launches = (update || gram) ? 1 : 0;
         // up to 8 rows on a short shard: one finishing launch, see gram_finish_kernel
         l.finish_at_once = gram && !l.mfma && !l.queue_order && star::norms_finish_at_once(l.Wp, plan.U, P);
@@ -654,6 +661,7 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
             a.partials = partials;
             a.queue = want_queue ? queue : nullptr;
             a.copy = star::CoefCopy();
+            a.burst = how.burst;
             if (how.finish_at_once && !no_alloc) {   // (the fixed array holds them already)
                 a.copy.src = gram_coef;
                 a.copy.dst = reinterpret_cast<double*>(d + lay.coef64);

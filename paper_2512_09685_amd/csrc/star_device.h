@@ -193,11 +193,11 @@ struct Span {
     int64_t first, step;
     int32_t K;
 };
-__device__ __forceinline__ Span make_span(const int span_g, const int span_k, const int threads = kBlock) {
+__device__ __forceinline__ Span make_span(const int span_g, const int span_k) {
     const int64_t G = span_g;
     Span s;
-    s.first = ((int64_t)(blockIdx.x / span_g) * G * span_k + (blockIdx.x % span_g)) * threads + threadIdx.x;
-    s.step = G * threads;
+    s.first = ((int64_t)(blockIdx.x / span_g) * G * span_k + (blockIdx.x % span_g)) * kBlock + threadIdx.x;
+    s.step = G * kBlock;
     s.K = span_k;
     return s;
 }
@@ -305,6 +305,75 @@ __device__ __forceinline__ void for_each_claimed_tile_ahead(TileQueue* __restric
     }
 }
 
+// ---------------------------------------------------------------- writes in bursts
+// A stream of reads slows down by more than the writes' share when writes are mixed into it: 16 fp32 rows and the state, 110 M
+// elements, 6.1 TB/s where the reads alone reach 6.7, because the DRAM has to turn its bus round again and again.  So long-lived
+// workgroups keep what they would write in LDS, and all of them write at the same moments, which they read off the clock that all
+// units of the GPU share (s_memrealtime, 100 MHz): whoever finds after a tile that the next period has begun writes what it holds.
+// Nobody waits for anybody; a workgroup that runs out of room writes at once.  A thread reads back only what it has stored itself, so
+// no barrier is needed either.  The same rows 1 455 -> 1 282 us; without the clock, every workgroup writing when its room is full, 1 515.
+constexpr int kLdsBytes = 160 * 1024;
+// 16 bytes of every lane, to consecutive places from a wave-uniform address on, at device scope and without the non-temporal hint: written
+// through the L2 into the memory-side cache, which takes a burst faster than the DRAM (16 fp32 rows, 110 M elements 1 282 us; with the
+// non-temporal hint 1 315, and 1 405 where lines of the rows or of the state are still dirty in that cache from whoever wrote them,
+// 1 330 this way; at the default scope 1 492).
+__device__ __forceinline__ void store_through(const f32x4 x, float* wave_base, const int lane_bytes) {
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(wave_base, 0, 0x7fffffff, 0x00027000);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), r, lane_bytes, 0, 16 /* sc1 */);
+}
+
+template <int CAP>
+struct BurstRoom {   // in LDS
+    f32x4 p[CAP][kBlock], v[CAP][kBlock];
+    int32_t tile[kBlock / 64][CAP];
+};
+// Tiles that fit beside `other` bytes of LDS.
+constexpr int burst_tiles(int other) { return (kLdsBytes - 64 - other) / (int)sizeof(BurstRoom<1>); }
+
+template <int CAP>
+struct Burst {
+    BurstRoom<CAP>& room;
+    const uint32_t period;   // ticks
+    uint32_t next;
+    int held = 0;
+
+    __device__ __forceinline__ Burst(BurstRoom<CAP>& r, const uint32_t ticks) : room(r), period(ticks) { next = boundary(clock()); }
+    static __device__ __forceinline__ uint32_t clock() { return (uint32_t)__builtin_readsteadycounter(); }
+    __device__ __forceinline__ uint32_t boundary(const uint32_t now) const { return (now / period + 1) * period; }
+
+    // The results of one chunk of a tile (the whole wave together); write(tile, p, v) stores them.
+    template <class Write>
+    __device__ __forceinline__ void put(const int64_t tile, const f32x4 p, const f32x4 v, Write&& write) {
+        room.p[held][threadIdx.x] = p;
+        room.v[held][threadIdx.x] = v;
+        room.tile[threadIdx.x >> 6][held] = (int32_t)tile;
+        ++held;
+        const uint32_t now = clock();
+        const bool due = (int32_t)(now - next) >= 0;
+        if (held == CAP || due) flush(write);
+        if (due) next = boundary(now);
+    }
+    template <class Write>
+    __device__ __forceinline__ void flush(Write&& write) {
+        constexpr int N = 4;   // tiles read together
+        for (int i = 0; i < held; i += N) {
+            f32x4 p[N], v[N];
+            int64_t t[N];
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                const int j = i + k < held ? i + k : held - 1;
+                p[k] = room.p[j][threadIdx.x];
+                v[k] = room.v[j][threadIdx.x];
+                t[k] = __builtin_amdgcn_readfirstlane(room.tile[threadIdx.x >> 6][j]);
+            }
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                if (i + k < held) write(t[k], p[k], v[k]);
+        }
+        held = 0;
+    }
+};
+
 // ---------------------------------------------------------------- the collapsed update of one element
 constexpr int kGramFold = 64;  // tiles between folds of the pairwise-product accumulators (power of two)
 
@@ -329,7 +398,6 @@ __device__ __forceinline__ void aff_step(float& p, float& v, const float (&g)[W]
 struct Geometry {
     int grid, span_g, span_k;
     int claim;   // > 0: tiles come from the queue, this many per claim; span_g / span_k then serve the ragged end only
-    int threads; // workgroup size (kBlock unless a launcher says otherwise)
 };
 
 // Fixed assignment of tiles (short shards, launches without a queue).  A kernel that ends with a per-workgroup norm
@@ -344,7 +412,6 @@ inline Geometry pick_geometry(int64_t P, bool reduces, int num_cu, int grid_cap,
     const int64_t tiles = std::max<int64_t>(1, (P / 4 + kBlock - 1) / kBlock);
     Geometry g;
     g.claim = 0;
-    g.threads = kBlock;
     if (reduces) {
         const int wg_bytes = std::max(1, thread_bytes) * kBlock;
         const int bpc = std::max(min_per_cu, std::min(max_per_cu, (64 * 1024 + wg_bytes - 1) / wg_bytes));
@@ -400,7 +467,6 @@ inline int short_tiles_per_workgroup(int thread_bytes, Traffic traffic) {
 inline Geometry queue_geometry(int num_cu, int grid_cap, int per_cu, int thread_bytes,
                                Traffic traffic = Traffic::Update, int64_t tiles = -1) {
     Geometry g;
-    g.threads = kBlock;
     g.grid = g.span_g = std::max(1, std::min(num_cu * per_cu, grid_cap));
     g.span_k = 0x7fffffff;
     g.claim = queue_claim(thread_bytes, traffic);
@@ -409,6 +475,14 @@ inline Geometry queue_geometry(int num_cu, int grid_cap, int per_cu, int thread_
         g.grid = g.span_g = (int)std::max<int64_t>(1, std::min<int64_t>(g.grid, tiles));
     }
     return g;
+}
+
+// The period of the bursts, in ticks of 10 ns: three quarters of the time in which `workgroups` fill `cap` tiles of LDS at 6.6 TB/s, so that
+// the clock comes before the room runs out (from 0.5 to 0.9 of it 1 % apart: the longer the fewer turns, but also the more
+// workgroups that are early).
+inline uint32_t burst_period(int cap, int bytes_per_tile, int workgroups) {
+    const double ticks = 0.75 * cap * (double)bytes_per_tile * workgroups / 66000.0;
+    return ticks < 100.0 ? 100u : (uint32_t)ticks;
 }
 
 #define STAR_FOR_EACH_W(X)                                                                                    \

@@ -145,6 +145,9 @@ struct SeqArgs {
     TileQueue* queue;      // device, zeroed; null: fixed assignment of tiles to workgroups
 };
 
+// Rows heavy enough for the kernel that writes in bursts (aff_burst_kernel), see burst_claim.
+constexpr bool bursts(int Wp, bool f32_rows) { return Wp >= (f32_rows ? 10 : 12); }
+
 // Which launches take their tiles from the queue when the caller hands one in (the matrix-core kernel
 // always does): the step-by-step kernel for one or two updates (longer streams are bound by arithmetic
 // and keep the fixed assignment with as many waves as fit), the collapsed one unless it carries the
@@ -168,7 +171,35 @@ constexpr bool gram_few_rows_form(int Wp, bool f32_rows, bool update) {
     return Wp <= kFewRows && !(Wp == kFewRows && f32_rows && !update);
 }
 inline bool aff_takes_queue(bool gram, int Wp, bool f32_rows, bool update) {
-    return !gram || gram_few_rows_form(Wp, f32_rows, update);
+    return gram ? gram_few_rows_form(Wp, f32_rows, update) : !bursts(Wp, f32_rows);
+}
+
+// Collapsed updates without norms on P elements: tiles per claim of the kernel that writes in bursts, 0 for aff_kernel.  Sweep over 1 to 150 M
+// elements, 3 to 32 fp32 and 5 to 32 bf16 rows, three states in turn, aff_kernel -> aff_burst_kernel:
+//   length and rows   fp32: 40 / 100 M elements, 10 rows 355 / 881 -> 347 / 854 us, 12 rows 410 / 1021 -> 397 / 978, 16 rows 525 / 1309 -> 482 /
+//                     1195, 24 rows 729 / 1899 -> 677 / 1709, 32 rows 945 / 2483 -> 880 / 2204; at the limits 13 M, 10 rows 130 -> 122, 11 M, 12
+//                     rows 122 -> 116, 8 M, 16 rows 114 -> 110, 3.8 M, 24 rows 82 -> 78.  bf16: 60 / 150 M, 12 rows 403 / 1011 -> 390 / 947, 16 rows
+//                     488 / 1154 -> 452 / 1105, 24 rows 653 / 1533 -> 596 / 1455, 32 rows 826 / 1930 -> 741 / 1813; 30 M, 12 rows 202 ->
+//                     196, 22 M, 16 rows 176 -> 171, 16 M, 24 rows 170 -> 163.
+//   not               lighter rows, which fill the LDS with results before a period of reads has paid (40 / 100 M, 5 / 6 / 8 fp32 rows 238 / 253 /
+//                     302 and 579 / 624 / 754 against 237 / 259 / 300 and 579 / 635 / 749), and shorter shards (8 M, 12 fp32 rows 91 against 91, 8 /
+//                     12 M, 24 bf16 rows 90 / 134 against 91 / 134, 16 M, 18 rows 136 against 137).
+//   in the cache      where rows and state have just been written, and the memory-side cache holds the last 256 MB of them, there is less to gain
+//                     (25 M, 12 / 16 / 24 fp32 rows 258 / 326 / 464 against 262 / 333 / 471; 100 M 1007 / 1292 / 1897 -> 990 / 1208 / 1727) and lighter
+//                     rows lose (40 M, 8 rows 298 against 309).
+//   tiles per claim   90 M, 12 / 16 / 24 fp32 rows, 2 / 3 / 4 / 5: 957 / 855 / 913 / 861, 1149 / 1051 / 1166 / 1089, 1596 / 1510 / - / 1529 us; 30 M, 24
+//                     rows, 2 / 3 490 / 507; 120 M, 12 / 16 / 24 bf16 rows, 3 / 4 / 5 / 6: 810 / 776 / 736 / 724, 926 / 903 / 858 / 856,
+//                     1157 / 1186 / 1156 / 1166.
+inline int burst_claim(int Wp, bool f32_rows, int64_t P) {
+    constexpr int64_t kMi = 1 << 20;
+    if (!bursts(Wp, f32_rows)) return 0;
+    if (f32_rows) {
+        if (P < (Wp >= 24 ? 7 * kMi / 2 : (Wp >= 16 ? 7 * kMi : (Wp >= 12 ? 10 * kMi : 12 * kMi)))) return 0;
+        if (Wp >= 20 && P < 72 * kMi) return 2;
+        return Wp >= 11 ? 3 : 5;
+    }
+    if (P < (Wp >= 24 ? 15 * kMi : (Wp >= 16 ? 20 * kMi : 24 * kMi))) return 0;
+    return Wp >= 24 ? 3 : (Wp >= 16 ? 5 : 6);
 }
 
 // Largest number of updates one launch of the step-by-step kernel accepts
@@ -210,6 +241,7 @@ struct AffArgs {
     double* partials;  // device [Wp(Wp+1)/2][grid] pairwise-product sums per block (gram only)
     TileQueue* queue;  // device, zeroed; null: fixed assignment of tiles to workgroups (not for the matrix-core kernel)
     CoefCopy copy;     // launch_affine with `gram`, without a queue
+    int32_t burst;     // launch_affine with `update`, without `gram`: see burst_claim (with a queue)
 };
 
 // Collapsed evaluation, optionally accumulating the Gram matrix of the rows.

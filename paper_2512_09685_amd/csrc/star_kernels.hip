@@ -57,16 +57,8 @@ __device__ __forceinline__ void carry(const CoefCopy& copy) {
 // KCH: chunks a thread loads together per tile when the tiles come from the queue (a tile is then
 // KCH * 256 chunks).  More than one only for the Gram matrix alone on very few rows: a thread that loads 8
 // to 32 bytes per tile keeps too little in flight (1 fp32 row: 0.40 of the HBM peak), whatever the claim.
-// ONE_WAVE: the launch runs one wave per SIMD (the half-size workgroups of the update on 24 and more bf16 rows:
-// two of 128 threads per compute unit).  Telling the compiler so lets it spend registers on issuing a tile's 34
-// loads together instead of saving them for an occupancy the launch never uses: 32 bf16 rows, 138 M elements,
-// 1.84 against 1.89-1.91 ms.  The limit is enforced by the hardware too, so only launches that take their tiles
-// from the queue use these instantiations (a short shard with one tile per workgroup needs many workgroups per
-// unit: 0.52 against 0.71 of the HBM peak on 12 M elements), and 8 or 16 rows, which run one wave per SIMD as
-// well, measured 1-2 % slower with it.
-template <int W, class R, bool UPDATE, bool GRAM, int KCH = 1, bool ONE_WAVE = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, ONE_WAVE ? 1 : 8)))
-void aff_kernel(float* __restrict__ params, float* __restrict__ momentum,
+template <int W, class R, bool UPDATE, bool GRAM, int KCH = 1>
+__global__ __launch_bounds__(kBlock) void aff_kernel(float* __restrict__ params, float* __restrict__ momentum,
                                                      const RowPtrs rows, const AffCoef cf, const int64_t P,
                                                      const int head, const int span_g, const int span_k,
                                                      void* __restrict__ publish, const int publish_bf16,
@@ -109,10 +101,7 @@ void aff_kernel(float* __restrict__ params, float* __restrict__ momentum,
         }
     };
 
-    // the Gram variants are always launched with kBlock threads (their LDS slots are laid out for that);
-    // the plain one also runs with half-size workgroups
-    const int threads = GRAM ? kBlock : (int)blockDim.x;
-    const Span span = make_span(span_g, span_k, threads);
+    const Span span = make_span(span_g, span_k);
     const int64_t nchunk = P / VEC;
 
     // one chunk: VEC elements of every row, the update, the pairwise products
@@ -155,20 +144,21 @@ void aff_kernel(float* __restrict__ params, float* __restrict__ momentum,
         }
     };
     bool queued = false;
-    if constexpr (!GRAM || kFew) {
+    if constexpr (kFew || (!GRAM && !bursts(W, std::is_same<R, RowF32>::value))) {
         // without the register-heavy Gram accumulators the kernel affords a second copy of the chunk
-        // code: tiles from the queue for long shards, a fixed assignment for short ones
+        // code: tiles from the queue for long shards, a fixed assignment for short ones (heavy rows: aff_burst_kernel has the
+        // long shards)
         if (claim > 0) {
             queued = true;
             if constexpr (KCH > 1) {
                 static_assert(GRAM && !UPDATE, "several chunks per thread: Gram matrix alone");
-                const int64_t width = (int64_t)threads * KCH;
+                const int64_t width = (int64_t)kBlock * KCH;
                 const int64_t ntile = (nchunk + width - 1) / width;
                 for_each_claimed_tile(queue, ntile, claim, [&](const int64_t tile) {
                     typename R::vec g[KCH][W];
 #pragma unroll
                     for (int j = 0; j < KCH; ++j) {   // all loads of the tile first
-                        const int64_t c = tile * width + (int64_t)j * threads + threadIdx.x;
+                        const int64_t c = tile * width + (int64_t)j * kBlock + threadIdx.x;
 #pragma unroll
                         for (int w = 0; w < W; ++w) g[j][w] = c < nchunk ? R::load(rows.p[w], c) : typename R::vec{};
                     }
@@ -187,9 +177,9 @@ void aff_kernel(float* __restrict__ params, float* __restrict__ momentum,
                     }
                 });
             } else {
-                const int64_t ntile = (nchunk + threads - 1) / threads;
+                const int64_t ntile = (nchunk + kBlock - 1) / kBlock;
                 for_each_claimed_tile(queue, ntile, claim, [&](const int64_t tile) {
-                    const int64_t c = tile * threads + threadIdx.x;
+                    const int64_t c = tile * kBlock + threadIdx.x;
                     if (c < nchunk) {
                         process(c);
                         if constexpr (kFew) fold_now();
@@ -241,6 +231,78 @@ void aff_kernel(float* __restrict__ params, float* __restrict__ momentum,
             for (int q = 0; q < kBlock / 64; ++q) s += (double)wave_part[q][e];
             partials[(int64_t)e * span_g + blockIdx.x] = s;   // (span_g: the workgroups that have sums)
         }
+    }
+}
+
+// The collapsed update without norms on long shards of heavy rows: tiles from the queue, one tile of look-ahead, results kept in LDS and
+// written in bursts (see Burst), for which a compute unit holds one workgroup.
+template <int W, class R>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void aff_burst_kernel(float* __restrict__ params, float* __restrict__ momentum, const RowPtrs rows, const AffCoef cf,
+                      const int64_t P, const int head, void* __restrict__ publish, const int publish_bf16,
+                      TileQueue* __restrict__ queue, const int claim, const uint32_t period) {
+    constexpr int CAP = burst_tiles(0);
+    __shared__ BurstRoom<CAP> room;
+    Burst<CAP> burst(room, period);
+    typedef typename R::vec vec_t;
+    const int64_t nchunk = P / 4, ntile = (nchunk + kBlock - 1) / kBlock;
+    auto fetch = [&](const int64_t tile, vec_t (&g)[W], f32x4& p, f32x4& v) {
+        const int64_t c = tile * kBlock + threadIdx.x;
+        if (c < nchunk) {
+#pragma unroll
+            for (int w = 0; w < W; ++w) g[w] = R::load(rows.p[w], c);
+            p = load_state(params, c);
+            v = load_state(momentum, c);
+        }
+    };
+    auto write = [&](const int64_t tile, const f32x4 p, const f32x4 v) {
+        const int64_t c = tile * kBlock + threadIdx.x;
+        if (c < nchunk) {
+            store_through(p, params + tile * (4 * kBlock), threadIdx.x * 16);
+            store_through(v, momentum + tile * (4 * kBlock), threadIdx.x * 16);
+            if (publish) publish_chunk(p, publish, publish_bf16, c);
+        }
+    };
+    vec_t gn[W] = {};
+    f32x4 pn = {0, 0, 0, 0}, vn = {0, 0, 0, 0};
+    bool primed = false;
+    for_each_claimed_tile_ahead(queue, ntile, claim, [&](const int64_t tile, const int64_t following) {
+        if (!primed) {
+            fetch(tile, gn, pn, vn);
+            primed = true;
+        }
+        vec_t g[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) g[w] = gn[w];
+        f32x4 p = pn, v = vn;
+        if (following >= 0) fetch(following, gn, pn, vn);
+        static_for<0, 4>([&](auto kc) {
+            constexpr int K = decltype(kc)::value;
+            float ge[W];
+            static_for<0, W>([&](auto wc) {
+                constexpr int Wi = decltype(wc)::value;
+                ge[Wi] = R::template get<K>(g[Wi]);
+            });
+            float pe = p[K], ve = v[K];
+            aff_step<W>(pe, ve, ge, cf);
+            p[K] = pe;
+            v[K] = ve;
+        });
+        burst.put(tile, p, v, write);
+    });
+    burst.flush(write);
+    // elements not covered by whole chunks: same arithmetic, one element at a time (at most 66, the first workgroup's)
+    const int64_t nrest = rest_count(head, P, nchunk);
+    for (int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x; r < nrest; r += (int64_t)gridDim.x * kBlock) {
+        const int64_t j = rest_element(r, head, nchunk);
+        float ge[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) ge[w] = R::load1(rows.p[w], j);
+        float pe = params[j], ve = momentum[j];
+        aff_step<W>(pe, ve, ge, cf);
+        params[j] = pe;
+        momentum[j] = ve;
+        if (publish) publish_element(pe, publish, publish_bf16, j);
     }
 }
 
@@ -622,15 +684,27 @@ hipError_t launch_aff_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_ou
     // chunk; 1 / 2 / 3 bf16 rows with 4 / 4 / 2 chunks: 0.44 / 0.66 / 0.65 against 0.22 / 0.36 / 0.48)
     constexpr int KCH = (GRAM && !UPDATE && W <= kFewRows && kRowBytes < 64)
                             ? (kRowBytes <= 8 ? 8 : (kRowBytes <= 16 ? 4 : 2)) : 1;
-    const bool queued = aff_takes_queue(GRAM, W, std::is_same<R, RowF32>::value, UPDATE) && a.queue;
+    const bool queued = aff_takes_queue(GRAM, W, std::is_same<R, RowF32>::value, UPDATE) && a.queue;   // (heavy rows without norms: a.burst)
     if constexpr (KCH > 1) {
         if (queued) {
             const int thread_bytes = kRowBytes * KCH;
             const Geometry g = queue_geometry(num_cu, grid_cap, 2, thread_bytes, Traffic::ReadOnly);
             *grid_out = g.grid;
-            hipLaunchKernelGGL((aff_kernel<W, R, UPDATE, GRAM, KCH>), dim3(g.grid), dim3(g.threads), 0, s, a.params,
+            hipLaunchKernelGGL((aff_kernel<W, R, UPDATE, GRAM, KCH>), dim3(g.grid), dim3(kBlock), 0, s, a.params,
                                a.momentum, a.rows, a.cf, a.P, a.head, g.span_g, g.span_k, a.publish,
                                a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue, g.claim, CoefCopy());
+            return hipGetLastError();
+        }
+    }
+    if constexpr (UPDATE && !GRAM && bursts(W, std::is_same<R, RowF32>::value)) {
+        if (a.burst) {
+            const int64_t tiles = std::max<int64_t>(1, (a.P / 4 + kBlock - 1) / kBlock);
+            const int grid = (int)std::min<int64_t>(std::min(num_cu, grid_cap), tiles);
+            if (!a.queue) return hipErrorInvalidValue;
+            *grid_out = grid;
+            hipLaunchKernelGGL((aff_burst_kernel<W, R>), dim3(grid), dim3(kBlock), 0, s, a.params, a.momentum, a.rows, a.cf, a.P,
+                               a.head, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.queue, a.burst,
+                               burst_period(burst_tiles(0), (kRowBytes + 64) * kBlock, grid));
             return hipGetLastError();
         }
     }
@@ -641,26 +715,9 @@ hipError_t launch_aff_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_ou
                                          UPDATE ? Traffic::Update : Traffic::ReadOnly)
                         : pick_geometry(a.P, GRAM, num_cu, grid_cap, 256, 1,
                                         sum_workgroups_per_cu(thread_bytes, UPDATE, a.P, num_cu));
-    // 24 and more bf16 rows: twice as many workgroups of half the size (tiles of 1 KB per row) measured
-    // 3-4 % faster (32 rows, 138 M elements: 1.92 against 1.98 ms); with 16 rows the same is 15 % slower,
-    // and fp32 rows do not care.  With these half-size tiles claims of 4 (4 KB of every row, 8 KB of the
-    // state) are the fastest: 1-4 % ahead of 3 on every box and shard length tried (32 rows, 138 M
-    // elements: 1.81 against 1.89 ms; 24 rows 1.43 against 1.53 ms), 5 to 12 fall off again.
-    if constexpr (std::is_same<R, RowBf16x4>::value && W >= 24 && UPDATE && !GRAM) {
-        if (queued) {
-            g.threads = kBlock / 2;
-            g.grid = g.span_g = std::min(2 * g.grid, grid_cap);
-            g.claim = 4;
-            *grid_out = g.grid;
-            hipLaunchKernelGGL((aff_kernel<W, R, UPDATE, GRAM, 1, true>), dim3(g.grid), dim3(g.threads), 0, s, a.params,
-                               a.momentum, a.rows, a.cf, a.P, a.head, g.span_g, g.span_k, a.publish,
-                               a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue, g.claim, CoefCopy());
-            return hipGetLastError();
-        }
-    }
     if (a.copy.n && queued) return hipErrorInvalidValue;   // (every workgroup of a queue's launch takes tiles)
     *grid_out = g.grid;
-    hipLaunchKernelGGL(kern, dim3(g.grid + (GRAM && a.copy.n ? 1 : 0)), dim3(g.threads), 0, s, a.params, a.momentum, a.rows, a.cf, a.P, a.head,
+    hipLaunchKernelGGL(kern, dim3(g.grid + (GRAM && a.copy.n ? 1 : 0)), dim3(kBlock), 0, s, a.params, a.momentum, a.rows, a.cf, a.P, a.head,
                        g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue,
                        g.claim, a.copy);
     return hipGetLastError();

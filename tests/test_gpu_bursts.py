@@ -1,0 +1,66 @@
+"""Updates whose results are written in bursts: the lengths where the tiles of a workgroup are none, one, a remainder, more than its LDS
+holds; against the kernels with a fixed assignment, whose arithmetic is the same to the bit, and 64 bits."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2512_09685_amd as star
+from gpu_util import rand_stream
+
+pytestmark = pytest.mark.gpu
+
+HP = dict(lr=0.1, momentum_coef=0.9, weight_decay=1e-4, wmode="stale")
+GUARD = 64
+
+
+def _guarded(n, offset, gen, dtype=torch.float32, std=0.02):
+    """A buffer of n elements from place `offset` on inside a larger one, which is returned as well."""
+    whole = (torch.randn(n + offset + GUARD, generator=gen, device="cuda") * std).to(dtype)
+    return whole, whole[offset:offset + n]
+
+
+def _call(W, P, dtype, offset, out, threshold, U=12, **kw):
+    gen = torch.Generator(device="cuda").manual_seed(W + P)
+    rows = [_guarded(P, offset, gen, torch.float32 if dtype == "f32" else torch.bfloat16, 1e-2)[1] for _ in range(W)]
+    (pw, p), (vw, v) = _guarded(P, offset, gen), _guarded(P, offset, gen, std=1e-2)
+    start = p.double().clone(), v.double().clone()
+    offs, mem, st = rand_stream(np.random.default_rng(W), W, U, stale=4)
+    us = star.UpdateStream(offs, mem, st)
+    whole = [pw, vw]
+    if out is None:
+        star.star_group_update(p, v, rows, us, queue_threshold=threshold, **HP, **kw)
+    else:
+        sw, s = _guarded(P, offset, gen, out)
+        whole.append(sw)
+        star.star_group_update_publish(p, v, rows, us, s, queue_threshold=threshold, **HP, **kw)
+    torch.cuda.synchronize()
+    return whole, (p, v, rows, us, start)
+
+
+# threshold None: what the library chooses for the length (each the shortest of its row count); 1: the queue whatever the length
+@pytest.mark.parametrize("W,dtype,P,threshold,offset,out", [
+    (10, "f32", 1, 1, 0, None), (12, "f32", 1023, 1, 0, torch.bfloat16), (16, "f32", 1025, 1, 3, None), (32, "f32", 256 * 1024 + 5, 1, 0, None),
+    (11, "f32", 600_001, 1, 1, torch.float32), (20, "f32", 511 * 1024, 1, 0, None), (28, "f32", 511 * 1024 + 1, 1, 7, torch.bfloat16),
+    (10, "f32", 6_000_003, 1, 0, torch.float32), (24, "f32", (7 << 19) + 1, None, 0, None), (16, "f32", 7 << 20, None, 5, None),
+    (12, "f32", 11_000_001, None, 0, None), (10, "f32", 13_000_000, None, 2, torch.bfloat16),
+    (12, "bf16", 5, 1, 0, None), (16, "bf16", 70_001, 1, 1, torch.bfloat16), (32, "bf16", 512 * 1024 + 3, 1, 0, None),
+    (24, "bf16", 16_000_003, None, 3, torch.bfloat16), (16, "bf16", 21_000_001, None, 0, None), (20, "bf16", 6_000_513, 1, 0, torch.float32),
+    (13, "bf16", 26_000_003, None, 6, None)])
+def test_update_in_bursts(W, dtype, P, threshold, offset, out):
+    us = _call(W, 1, dtype, 0, None, 1)[1][3]
+    choice = dict(lr=0.1, momentum_coef=0.9, wmode="stale")
+    assert star.star_plan_choice(P, W, dtype, us, queue_threshold=threshold, **choice)["queue_order"] == 1
+    assert star.star_plan_choice(P, W, dtype, us, queue_threshold=1 << 62, **choice)["queue_order"] == 0
+    got, (p, v, rows, us, (p0, v0)) = _call(W, P, dtype, offset, out, threshold)
+    fixed = _call(W, P, dtype, offset, out, 1 << 62)[0]
+    for a, b in zip(got, fixed):   # whole buffers: nothing beside the shard is written either
+        assert torch.equal(a.view(torch.int16 if a.dtype == torch.bfloat16 else torch.int32),
+                           b.view(torch.int16 if b.dtype == torch.bfloat16 else torch.int32))
+    M, B = star.star_plan_affine(W, us, **HP)
+    ep, ev = M[0, 0] * p0 + M[0, 1] * v0, M[1, 0] * p0 + M[1, 1] * v0
+    for w in range(W):
+        ep.add_(rows[w].double(), alpha=float(B[0, w]))
+        ev.add_(rows[w].double(), alpha=float(B[1, w]))
+    # a chain of W + 2 fp32 multiply-adds of terms of the result's size
+    for x, e in ((p, ep), (v, ev)):
+        assert float(((x.double() - e).abs() / (e.abs() + e.square().mean().sqrt())).max()) <= 3e-6

@@ -204,10 +204,7 @@ star_status acquire_slot(int device, size_t table_bytes, size_t partial_doubles,
     if (s.device != -1 && s.device != device) free_slot(s);   // its memory lives on another device
     if (s.pending) STAR_HIP(hipEventSynchronize(s.done));
     s.pending = false;
-    // (without the system-scope fence, which would write the caches back behind every call: the host reads nothing the slot's
-    // kernels wrote, it only waits until they have run.  Calls with a slot take 1.7 to 2.0 us less for it, 0.3 M elements, 8 fp32
-    // rows with norms 14.2 -> 12.5 us, Gram matrix of 25.6 M, 16 bf16 rows 129.2 -> 127.3; with hipEventReleaseToDevice no less)
-    if (!s.done) STAR_HIP(hipEventCreateWithFlags(&s.done, hipEventDisableTiming | hipEventDisableSystemFence));
+    if (!s.done) STAR_HIP(hipEventCreateWithFlags(&s.done, hipEventDisableTiming));
     const bool grows = table_bytes > s.table_cap || partial_doubles > s.partial_cap || !s.queue;
     s.device = device;
     star_status st = grow_slot(s, table_bytes, partial_doubles);

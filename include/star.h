@@ -46,9 +46,9 @@
  *     stream has been synchronised.  Two things can make the host wait inside
  *     a call all the same: (1) the internal workspace is a ring of 8 slots,
  *     one per call that needs tables, partial sums or the tile queue, each
- *     guarded by an event; the ninth such call blocks (hipEventSynchronize)
- *     until the work of the call that used its slot eight calls earlier has
- *     finished; (2) the first call that needs a larger workspace than any
+ *     guarded by a word in pinned memory that its last kernel writes (or by
+ *     an event); the ninth such call blocks until the work of the call that
+ *     used its slot eight calls earlier has finished; (2) the first call that needs a larger workspace than any
  *     before it allocates device and pinned memory (hipMalloc, hipHostMalloc),
  *     which synchronises the device.  star_group_update_noalloc does neither.
  *   - The return value is a star_status.  Nothing is thrown, nothing aborts.

@@ -220,9 +220,32 @@ __device__ __forceinline__ FirstClaim first_claim(const int claim, const int64_t
     return first_claim_of((int64_t)blockIdx.x, (int64_t)gridDim.x, claim, ntile);
 }
 
+// What a workgroup does that uses its launch's workspace slot no more (one thread; the queue's last one to leave knows without a ticket that it is).
+__device__ __forceinline__ void tell(uint32_t* word, const uint32_t seq) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // tickets and queue are back at zero
+    __hip_atomic_store(word, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void finished(const Finished& f) {
+    if (!f.word) return;
+    if (__hip_atomic_fetch_add(f.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 != gridDim.x) return;
+    __hip_atomic_store(f.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    tell(f.word, f.seq);
+}
+__device__ __forceinline__ void leave(const TileSource& src) {
+    // this workgroup's claims have all returned (their values were used), so when the count reaches the grid size nobody touches
+    // `next` any more
+    const unsigned int left = atomicAdd(&src.queue->done, 1u);
+    if (left + 1 == gridDim.x) {
+        atomicExch(&src.queue->next, 0ull);
+        atomicExch(&src.queue->done, 0u);
+        if (src.word) tell(src.word, src.seq);
+    }
+}
+
 template <class Body>
-__device__ __forceinline__ void for_each_claimed_tile(TileQueue* __restrict__ q, const int64_t ntile, const int claim,
+__device__ __forceinline__ void for_each_claimed_tile(const TileSource& src, const int64_t ntile, const int claim,
                                                       Body&& body) {
+    TileQueue* const q = src.queue;
     __shared__ unsigned long long s_first;
     const FirstClaim fc = first_claim(claim, ntile);
     const int step = claim < 0 ? -claim : claim;
@@ -243,15 +266,7 @@ __device__ __forceinline__ void for_each_claimed_tile(TileQueue* __restrict__ q,
         t0 = (int64_t)s_first;
         __syncthreads();   // everyone has read s_first before thread 0 writes it again
     }
-    if (counter && threadIdx.x == 0) {
-        // this workgroup's claims have all returned (their values were used above), so when the
-        // count reaches the grid size nobody touches `next` any more
-        const unsigned int left = atomicAdd(&q->done, 1u);
-        if (left + 1 == gridDim.x) {
-            atomicExch(&q->next, 0ull);
-            atomicExch(&q->done, 0u);
-        }
-    }
+    if (counter && threadIdx.x == 0) leave(src);
 }
 
 // The same order with one tile of look-ahead, for kernels that issue the loads of the following tile
@@ -259,8 +274,9 @@ __device__ __forceinline__ void for_each_claimed_tile(TileQueue* __restrict__ q,
 // start of the next claim is made known to the whole workgroup when it begins the last tile of the
 // current claim, so the look-ahead also crosses claims.
 template <class Body>
-__device__ __forceinline__ void for_each_claimed_tile_ahead(TileQueue* __restrict__ q, const int64_t ntile,
+__device__ __forceinline__ void for_each_claimed_tile_ahead(const TileSource& src, const int64_t ntile,
                                                             const int claim, Body&& body) {
+    TileQueue* const q = src.queue;
     __shared__ unsigned long long s_first;
     const FirstClaim fc = first_claim(claim, ntile);
     const int step = claim < 0 ? -claim : claim;
@@ -296,13 +312,7 @@ __device__ __forceinline__ void for_each_claimed_tile_ahead(TileQueue* __restric
             cur = following;
         }
     }
-    if (counter && threadIdx.x == 0) {
-        const unsigned int left = atomicAdd(&q->done, 1u);
-        if (left + 1 == gridDim.x) {
-            atomicExch(&q->next, 0ull);
-            atomicExch(&q->done, 0u);
-        }
-    }
+    if (counter && threadIdx.x == 0) leave(src);
 }
 
 // ---------------------------------------------------------------- writes in bursts
@@ -483,6 +493,13 @@ inline Geometry queue_geometry(int num_cu, int grid_cap, int per_cu, int thread_
 inline uint32_t burst_period(int cap, int bytes_per_tile, int workgroups) {
     const double ticks = 0.75 * cap * (double)bytes_per_tile * workgroups / 66000.0;
     return ticks < 100.0 ? 100u : (uint32_t)ticks;
+}
+
+inline int64_t tiles_of(int64_t P) { return (P / 4 + kBlock - 1) / kBlock; }
+
+// Whether the workgroups of a launch of `grid` ask the queue's counter, whose last one to leave writes the word (for_each_claimed_tile).
+inline bool queue_tells(const Finished& done, int grid, int claim, int64_t tiles) {
+    return done.word && claim > 0 && first_claim_of(0, grid, claim).base < (unsigned long long)tiles;
 }
 
 #define STAR_FOR_EACH_W(X)                                                                                    \

@@ -22,8 +22,25 @@ struct TileQueue {
     unsigned int pad;
 };
 
-// The ticket of gram_finish_kernel lies behind the queue, in the same 256 bytes.
+// The ticket of gram_finish_kernel and the one of a call's last launch (Finished) lie behind the queue, in the same 256 bytes.
 inline unsigned int* finish_ticket(TileQueue* q) { return reinterpret_cast<unsigned int*>(q + 4); }
+inline unsigned int* last_ticket(TileQueue* q) { return reinterpret_cast<unsigned int*>(q + 8); }
+
+// How the host learns that a call no longer uses its workspace slot: the last workgroup of the call's last launch writes `seq` to `word`, which
+// lies in pinned memory.  (An event recorded behind the call tells the same, but the GPU takes 4.4 us longer to the next call's kernel, and the
+// host 2 to 4 us for the record.)
+struct Finished {
+    uint32_t* word = nullptr;         // as the device addresses it; null: nobody asks
+    uint32_t seq = 0;
+    unsigned int* ticket = nullptr;   // device, zero between launches
+};
+// The tile queue as a kernel is handed it: the last workgroup to leave writes `seq`, if there is a word.
+struct TileSource {
+    TileQueue* queue;
+    uint32_t* word;
+    uint32_t seq;
+};
+inline TileSource tile_source(TileQueue* q, const Finished& f) { return TileSource{q, f.word, f.seq}; }
 
 // Tiles handed to a workgroup per claim.  Never a power of two: with 2, 4 or 8 tiles every claim starts
 // on an 8/16/32 KB boundary of every row, all workgroups then hit the same memory channels at the same
@@ -143,6 +160,8 @@ struct SeqArgs {
     int32_t publish_dtype; // star_dtype of that copy
     double* partials;      // device [U][grid] sums of gbar^2 per block (norms only)
     TileQueue* queue;      // device, zeroed; null: fixed assignment of tiles to workgroups
+    Finished done;         // launch_seq without norms: written by a launch that takes tiles from the queue
+    bool* told;            // host, or null: set if the launch does
 };
 
 // Rows heavy enough for the kernel that writes in bursts (aff_burst_kernel), see burst_claim.
@@ -242,6 +261,8 @@ struct AffArgs {
     TileQueue* queue;  // device, zeroed; null: fixed assignment of tiles to workgroups (not for the matrix-core kernel)
     CoefCopy copy;     // launch_affine with `gram`, without a queue
     int32_t burst;     // launch_affine with `update`, without `gram`: see burst_claim (with a queue)
+    Finished done;     // launch_affine without `gram`: written by a launch that takes tiles from the queue
+    bool* told;        // host, or null: set if the launch does
 };
 
 // Collapsed evaluation, optionally accumulating the Gram matrix of the rows.
@@ -255,22 +276,22 @@ hipError_t launch_affine_mfma(int Wp, int dtype, bool update, const AffArgs& a, 
 // out[e] = sum_b partials[e*grid + b] in a fixed order; sums_out (double) and
 // sqrt_out (float, square root of the sum) are each optional.
 hipError_t launch_reduce(const double* partials, int n_out, int grid, double* sums_out, float* sqrt_out,
-                         hipStream_t s);
+                         const Finished& done, hipStream_t s);
 
 // norms_out[u] = sqrt( c_u^T Gamma c_u ), Gamma upper-triangular packed [Wp(Wp+1)/2], coef [U][Wp] doubles.
 hipError_t launch_gram_norms(const double* gamma, const double* coef, int U, int Wp, float* norms_out,
-                             hipStream_t s);
+                             const Finished& done, hipStream_t s);
 
 // launch_reduce and launch_gram_norms in one launch, see norms_finish_at_once.  `gamma` and `coef` are device memory; `ticket` is zero
 // before and after.
 hipError_t launch_gram_finish(const double* partials, int grid, double* gamma, const double* coef, int U, int W,
-                              unsigned int* ticket, float* norms_out, hipStream_t s);
+                              unsigned int* ticket, float* norms_out, const Finished& done, hipStream_t s);
 constexpr int kFinishRows = 8;
 inline bool norms_finish_at_once(int W, int U, int64_t P) { return W <= kFinishRows && U <= 128 && P <= 2 << 20; }
 
 // The same for the Gram matrix: partials of the packed upper triangle over Wp rows [Wp(Wp+1)/2][grid] -> full symmetric [W][W],
 // W <= Wp (all zero with a grid of 0).
-hipError_t launch_reduce_gram(const double* partials, int grid, int Wp, int W, double* out, hipStream_t s);
+hipError_t launch_reduce_gram(const double* partials, int grid, int Wp, int W, double* out, const Finished& done, hipStream_t s);
 
 hipError_t launch_fill(float* dst, int64_t n, float value, hipStream_t s);
 
@@ -310,6 +331,8 @@ struct ReduceArgs {
     int32_t norms;           // also accumulate sum of squares per group
     double* partials;        // device [U][grid] (norms only)
     TileQueue* queue;        // device, zeroed; null: fixed assignment of tiles to workgroups
+    Finished done;           // without norms: written by a launch that takes tiles from the queue
+    bool* told;              // host, or null: set if the launch does
 };
 
 int reduce_max_updates(int Wp, bool norms);

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kBlock) void aff_kernel(float* __restrict__ params,
                                                      const RowPtrs rows, const AffCoef cf, const int64_t P,
                                                      const int head, const int span_g, const int span_k,
                                                      void* __restrict__ publish, const int publish_bf16,
-                                                     double* __restrict__ partials, TileQueue* __restrict__ queue,
+                                                     double* __restrict__ partials, const TileSource queue,
                                                      const int claim, const CoefCopy copy) {
     // one workgroup more where the launch carries the norms' coefficients to device memory for gram_finish_kernel
     if constexpr (GRAM) {
@@ -240,7 +240,7 @@ template <int W, class R>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void aff_burst_kernel(float* __restrict__ params, float* __restrict__ momentum, const RowPtrs rows, const AffCoef cf,
                       const int64_t P, const int head, void* __restrict__ publish, const int publish_bf16,
-                      TileQueue* __restrict__ queue, const int claim, const uint32_t period) {
+                      const TileSource queue, const int claim, const uint32_t period) {
     constexpr int CAP = burst_tiles(0);
     __shared__ BurstRoom<CAP> room;
     Burst<CAP> burst(room, period);
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(kBlock) void seq_kernel(float* __restrict__ params,
                                                      const float mu, const float wd, const int64_t P,
                                                      const int head, const int span_g, const int span_k,
                                                      void* __restrict__ publish, const int publish_bf16,
-                                                     double* __restrict__ partials, TileQueue* __restrict__ queue,
+                                                     double* __restrict__ partials, const TileSource queue,
                                                      const int claim, const InlineTables inl, const AffCoef cf) {
     static_assert(R::VEC == 4, "the step-by-step kernel works on 4-element chunks");
     static_assert(!COLLAPSED || NORMS, "the collapsed update rides on the norm walk");
@@ -491,75 +491,91 @@ __global__ __launch_bounds__(kBlock) void seq_kernel(float* __restrict__ params,
 }
 
 // ================================================================= finishing kernels
-// The sum of one row of partials, in thread 0.
+// They last a few microseconds, nearly all of it latency: of the launch, of one read, of the ticket.  A wave takes one sum, so that a launch
+// has a quarter of the workgroups that one sum a workgroup would need, and its tickets (one a workgroup, 12 ns each at one place) as many fewer.
+constexpr int kWaves = kBlock / 64;
+inline dim3 finishing_grid(int n) { return dim3((n + kWaves - 1) / kWaves); }
+
+// The sum of one row of partials, in lane 63 of the wave: in a fixed order, up to 512 of them requested together.
 __device__ __forceinline__ double sum_partials(const double* __restrict__ row, const int grid) {
-    __shared__ double s_wave[kBlock / 64];
+    constexpr int N = 8;
     double s = 0.0;
-    for (int b = threadIdx.x; b < grid; b += kBlock) s += row[b];
-    // fixed order: within a wave by the cross-lane moves, then the waves in turn (these kernels last a
-    // few microseconds, most of it latency, so one barrier instead of a tree of eight)
-    s = wave_sum_to_lane63(s);
-    if ((threadIdx.x & 63) == 63) s_wave[threadIdx.x >> 6] = s;
-    __syncthreads();
-    double t = 0.0;
-    if (threadIdx.x == 0) {
+    for (int b0 = threadIdx.x & 63; b0 < grid; b0 += 64 * N) {
+        double x[N];
 #pragma unroll
-        for (int q = 0; q < kBlock / 64; ++q) t += s_wave[q];
+        for (int k = 0; k < N; ++k) x[k] = b0 + 64 * k < grid ? row[b0 + 64 * k] : 0.0;
+#pragma unroll
+        for (int k = 0; k < N; ++k) s += x[k];
     }
-    return t;
+    return wave_sum_to_lane63(s);
 }
 
-__global__ __launch_bounds__(kBlock) void reduce_kernel(const double* __restrict__ partials, const int grid,
+// The workgroup has read what it needed of the slot.
+__device__ __forceinline__ void finished_all(const Finished& done) {
+    if (!done.word) return;
+    __syncthreads();
+    if (threadIdx.x == 0) finished(done);
+}
+
+__global__ __launch_bounds__(kBlock) void reduce_kernel(const double* __restrict__ partials, const int n, const int grid,
                                                         double* __restrict__ sums_out,
-                                                        float* __restrict__ sqrt_out) {
-    const int e = blockIdx.x;
-    const double t = sum_partials(partials + (int64_t)e * grid, grid);
-    if (threadIdx.x == 0) {
-        if (sums_out) sums_out[e] = t;
-        if (sqrt_out) sqrt_out[e] = (float)sqrt(t);
+                                                        float* __restrict__ sqrt_out, const Finished done) {
+    const int e = blockIdx.x * kWaves + (threadIdx.x >> 6);
+    if (e < n) {
+        const double t = sum_partials(partials + (int64_t)e * grid, grid);
+        if ((threadIdx.x & 63) == 63) {
+            if (sums_out) sums_out[e] = t;
+            if (sqrt_out) sqrt_out[e] = (float)sqrt(t);
+        }
     }
+    finished_all(done);
 }
 
-// One workgroup per update u: n_u^2 = sum over pairs (a <= b) of c_a c_b Gamma_ab (off-diagonal pairs twice),
-// each thread one pair, then a fixed-order tree sum in double.
+// One wave per update u: n_u^2 = sum over pairs (a <= b) of c_a c_b Gamma_ab (off-diagonal pairs twice), each lane every 64th pair, then a
+// fixed-order sum in double.
 __global__ __launch_bounds__(kBlock) void gram_norms_kernel(const double* __restrict__ gamma,
                                                             const double* __restrict__ coef, const int U,
-                                                            const int W, float* __restrict__ norms_out) {
-    __shared__ double s_wave[kBlock / 64];
-    const int u = blockIdx.x;
-    const double* c = coef + (int64_t)u * W;
+                                                            const int W, float* __restrict__ norms_out,
+                                                            const Finished done) {
+    const int u = blockIdx.x * kWaves + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int ng = W * (W + 1) / 2;
-    double s = 0.0;
-    for (int e = threadIdx.x; e < ng; e += kBlock) {
-        const double g = gamma[e];   // requested together with the coefficients: one memory latency, not two
-        int a = 0, rem = e;
-        while (rem >= W - a) {
-            rem -= W - a;
-            ++a;
-        }
-        const int b = a + rem;
-        const double ca = c[a], cb = c[b];
-        // rows outside the group take no part: a non-finite entry of a worker that is not a member (0 * inf)
-        // must not reach this group's norm
-        if (ca == 0.0 || cb == 0.0) continue;
-        const double t = ca * cb * g;
-        s += (a == b) ? t : 2.0 * t;
-    }
-    s = wave_sum_to_lane63(s);
-    if ((threadIdx.x & 63) == 63) s_wave[threadIdx.x >> 6] = s;
-    __syncthreads();
-    // a tiny negative sum (rounding of a quadratic form that is zero) gives 0; a non-finite one stays
-    // non-finite, so that a bad gradient report shows in the norms of the groups it is part of
-    if (threadIdx.x == 0 && u < U) {
-        double t = 0.0;
+    if (u < U) {
+        // one read of the coefficients (they may lie in the host's memory) and all of Gamma, requested together
+        constexpr int N = (STAR_MAX_WORKERS * (STAR_MAX_WORKERS + 1) / 2 + 63) / 64;
+        const double c = lane < W ? coef[(int64_t)u * W + lane] : 0.0;
+        double g[N];
 #pragma unroll
-        for (int q = 0; q < kBlock / 64; ++q) t += s_wave[q];
-        norms_out[u] = (float)sqrt(t < 0.0 && t > -1e300 ? 0.0 : t);
+        for (int k = 0; k < N; ++k) g[k] = 64 * k + lane < ng ? gamma[64 * k + lane] : 0.0;
+        double s = 0.0;
+        int a = 0, rem = lane;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            if (64 * k < ng) {
+                while (a < W && rem >= W - a) {
+                    rem -= W - a;
+                    ++a;
+                }
+                const int b = a + rem;
+                const double ca = __shfl(c, a & 63), cb = __shfl(c, b & 63);
+                // rows outside the group take no part: a non-finite entry of a worker that is not a member (0 * inf)
+                // must not reach this group's norm
+                if (a < W && ca != 0.0 && cb != 0.0) {
+                    const double t = ca * cb * g[k];
+                    s += (a == b) ? t : 2.0 * t;
+                }
+                rem += 64;
+            }
+        }
+        s = wave_sum_to_lane63(s);
+        // a tiny negative sum (rounding of a quadratic form that is zero) gives 0; a non-finite one stays
+        // non-finite, so that a bad gradient report shows in the norms of the groups it is part of
+        if (lane == 63) norms_out[u] = (float)sqrt(s < 0.0 && s > -1e300 ? 0.0 : s);
     }
+    finished_all(done);
 }
 
 // Both finishing steps in one launch, for the Gram matrix of up to kFinishRows rows on a short shard, where a call is bound by its
-// launches: workgroup e sums entry e as reduce_kernel does, the workgroup that arrives last forms the norms.  The coefficients
+// launches: the waves sum the entries as in reduce_kernel, the workgroup that arrives last forms the norms.  The coefficients
 // (read from the host's memory by gram_norms_kernel) are in device memory: the launch before carried them there.
 // Update with norms, two launches -> one: 0.3 M elements, 1 / 4 / 8 fp32 rows 18.3 / 18.5 / 20.3 -> 14.1 / 14.1 / 16.6 us a call, 1 M, 4 / 8 rows 18.7 / 20.7
 // -> 15.5 / 19.5, 2 M, 8 rows 28.5 -> 27.1, 4 M, 4 rows 31.8 -> 31.8 (1 to 1.5 us of each by the shorter way to the stream's handle; with
@@ -569,22 +585,28 @@ __global__ __launch_bounds__(kBlock) void gram_norms_kernel(const double* __rest
 // the device, only less on the host.
 __global__ __launch_bounds__(kBlock) void gram_finish_kernel(const double* __restrict__ partials, const int grid, double* gamma,
                                                              const double* __restrict__ coef, const int U, const int W,
-                                                             unsigned int* ticket, float* __restrict__ norms_out) {
+                                                             unsigned int* ticket, float* __restrict__ norms_out,
+                                                             const Finished done) {
     __shared__ int s_last;
     __shared__ double s_gamma[kFinishRows * kFinishRows];
     const int u = threadIdx.x;
     double c[kFinishRows];   // requested with the partials, by every workgroup: any may be the last
 #pragma unroll
     for (int w = 0; w < kFinishRows; ++w) c[w] = u < U && w < W ? coef[u * W + w] : 0.0;
-    const double t = sum_partials(partials + (int64_t)blockIdx.x * grid, grid);
-    if (threadIdx.x == 0) {
-        __hip_atomic_store(gamma + blockIdx.x, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x;
+    const int e = blockIdx.x * kWaves + (threadIdx.x >> 6);
+    if (e < W * (W + 1) / 2) {
+        const double t = sum_partials(partials + (int64_t)e * grid, grid);
+        if ((threadIdx.x & 63) == 63) __hip_atomic_store(gamma + e, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the wave's sum has reached the memory that all units see
+    __syncthreads();
+    if (threadIdx.x == 0)
+        s_last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x;
     __syncthreads();
     if (!s_last) return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    if (threadIdx.x == 0) *ticket = 0u;   // for the next launch; nobody else is left
+    // (at device scope: whoever has the slot next may start before this launch's caches are written back)
+    if (threadIdx.x == 0) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // nobody else is left
     if (threadIdx.x < kFinishRows * kFinishRows) {
         const int a = threadIdx.x / kFinishRows, b = threadIdx.x % kFinishRows;
         s_gamma[threadIdx.x] = a <= b && b < W ? __hip_atomic_load(gamma + a * W - a * (a - 1) / 2 + (b - a), __ATOMIC_RELAXED,
@@ -592,17 +614,21 @@ __global__ __launch_bounds__(kBlock) void gram_finish_kernel(const double* __res
                                                : 0.0;
     }
     __syncthreads();
-    if (u >= U) return;
-    double s = 0.0;
+    if (u < U) {
+        double s = 0.0;
 #pragma unroll
-    for (int a = 0; a < kFinishRows; ++a)
+        for (int a = 0; a < kFinishRows; ++a)
 #pragma unroll
-        for (int b = a; b < kFinishRows; ++b) {
-            const double cc = (a == b ? 1.0 : 2.0) * c[a] * c[b];
-            // rows outside the group take no part (0 * inf), see gram_norms_kernel
-            s += c[a] == 0.0 || c[b] == 0.0 ? 0.0 : cc * s_gamma[a * kFinishRows + b];
-        }
-    norms_out[u] = (float)sqrt(s < 0.0 && s > -1e300 ? 0.0 : s);
+            for (int b = a; b < kFinishRows; ++b) {
+                const double cc = (a == b ? 1.0 : 2.0) * c[a] * c[b];
+                // rows outside the group take no part (0 * inf), see gram_norms_kernel
+                s += c[a] == 0.0 || c[b] == 0.0 ? 0.0 : cc * s_gamma[a * kFinishRows + b];
+            }
+        norms_out[u] = (float)sqrt(s < 0.0 && s > -1e300 ? 0.0 : s);
+    }
+    if (!done.word) return;
+    __syncthreads();   // everyone has its coefficients
+    if (threadIdx.x == 0) tell(done.word, done.seq);
 }
 
 // The last launch of the Gram matrix: entry e = (i, j), i <= j < W, of the packed triangle over Wp >= W rows (the kernels' padded
@@ -610,18 +636,22 @@ __global__ __launch_bounds__(kBlock) void gram_finish_kernel(const double* __res
 // W x W matrix (zeros from a grid of 0, an empty shard).  A launch of its own for the second half cost 4 us a call
 // (0.3 M elements, 8 fp32 / 16 bf16 rows 17.0 / 16.4 -> 12.8 / 12.6 us a call, 3 M, 16 bf16 rows 24.9 -> 23.3, 25.6 M 130.9 -> 129.0).
 __global__ __launch_bounds__(kBlock) void reduce_gram_kernel(const double* __restrict__ partials, const int grid,
-                                                             const int Wp, const int W, double* __restrict__ out) {
-    int i = 0, rem = blockIdx.x;
-    while (rem >= W - i) {
-        rem -= W - i;
-        ++i;
+                                                             const int Wp, const int W, double* __restrict__ out,
+                                                             const Finished done) {
+    int i = 0, rem = blockIdx.x * kWaves + (threadIdx.x >> 6);
+    if (rem < W * (W + 1) / 2) {
+        while (rem >= W - i) {
+            rem -= W - i;
+            ++i;
+        }
+        const int j = i + rem;
+        const double t = sum_partials(partials + (int64_t)(i * Wp - i * (i - 1) / 2 + rem) * grid, grid);
+        if ((threadIdx.x & 63) == 63) {
+            out[i * W + j] = t;
+            out[j * W + i] = t;
+        }
     }
-    const int j = i + rem;
-    const double t = sum_partials(partials + (int64_t)(i * Wp - i * (i - 1) / 2 + rem) * grid, grid);
-    if (threadIdx.x == 0) {
-        out[i * W + j] = t;
-        out[j * W + i] = t;
-    }
+    finished_all(done);
 }
 
 __global__ __launch_bounds__(kBlock) void fill_kernel(float* __restrict__ dst, const int64_t n, const float value) {
@@ -670,10 +700,13 @@ hipError_t launch_seq_t(const SeqArgs& a, int num_cu, int grid_cap, int* grid_ou
                               : pick_geometry(a.P, NORMS, num_cu, grid_cap, thread_bytes, 4,
                                               COLLAPSED ? 2 : 1);   // (short shards as well: 25-30 % faster with two)
     *grid_out = g.grid;
+    const Finished done = NORMS ? Finished() : a.done;
     hipLaunchKernelGGL(kern, dim3(g.grid), dim3(kBlock), lds, s, a.params, a.momentum, a.rows, a.coef, a.lr, a.mask,
                        a.U, a.mu, a.wd, a.P, a.head, g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0,
-                       a.partials, a.queue, g.claim, a.coef ? InlineTables() : *a.inl, a.cf ? *a.cf : AffCoef());
-    return hipGetLastError();
+                       a.partials, tile_source(a.queue, done), g.claim, a.coef ? InlineTables() : *a.inl, a.cf ? *a.cf : AffCoef());
+    const hipError_t e = hipGetLastError();
+    if (e == hipSuccess && a.told) *a.told = queued && queue_tells(done, g.grid, g.claim, tiles_of(a.P));
+    return e;
 }
 
 template <int W, class R, bool UPDATE, bool GRAM>
@@ -692,20 +725,21 @@ hipError_t launch_aff_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_ou
             *grid_out = g.grid;
             hipLaunchKernelGGL((aff_kernel<W, R, UPDATE, GRAM, KCH>), dim3(g.grid), dim3(kBlock), 0, s, a.params,
                                a.momentum, a.rows, a.cf, a.P, a.head, g.span_g, g.span_k, a.publish,
-                               a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue, g.claim, CoefCopy());
+                               a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, TileSource{a.queue, nullptr, 0u}, g.claim, CoefCopy());
             return hipGetLastError();
         }
     }
     if constexpr (UPDATE && !GRAM && bursts(W, std::is_same<R, RowF32>::value)) {
         if (a.burst) {
-            const int64_t tiles = std::max<int64_t>(1, (a.P / 4 + kBlock - 1) / kBlock);
-            const int grid = (int)std::min<int64_t>(std::min(num_cu, grid_cap), tiles);
+            const int grid = (int)std::min<int64_t>(std::min(num_cu, grid_cap), std::max<int64_t>(1, tiles_of(a.P)));
             if (!a.queue) return hipErrorInvalidValue;
             *grid_out = grid;
             hipLaunchKernelGGL((aff_burst_kernel<W, R>), dim3(grid), dim3(kBlock), 0, s, a.params, a.momentum, a.rows, a.cf, a.P,
-                               a.head, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.queue, a.burst,
+                               a.head, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, tile_source(a.queue, a.done), a.burst,
                                burst_period(burst_tiles(0), (kRowBytes + 64) * kBlock, grid));
-            return hipGetLastError();
+            const hipError_t e = hipGetLastError();
+            if (e == hipSuccess && a.told) *a.told = queue_tells(a.done, grid, a.burst, tiles_of(a.P));
+            return e;
         }
     }
     auto kern = aff_kernel<W, R, UPDATE, GRAM>;
@@ -716,11 +750,14 @@ hipError_t launch_aff_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_ou
                         : pick_geometry(a.P, GRAM, num_cu, grid_cap, 256, 1,
                                         sum_workgroups_per_cu(thread_bytes, UPDATE, a.P, num_cu));
     if (a.copy.n && queued) return hipErrorInvalidValue;   // (every workgroup of a queue's launch takes tiles)
+    const Finished done = GRAM ? Finished() : a.done;
     *grid_out = g.grid;
     hipLaunchKernelGGL(kern, dim3(g.grid + (GRAM && a.copy.n ? 1 : 0)), dim3(kBlock), 0, s, a.params, a.momentum, a.rows, a.cf, a.P, a.head,
-                       g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue,
-                       g.claim, a.copy);
-    return hipGetLastError();
+                       g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials,
+                       tile_source(a.queue, done), g.claim, a.copy);
+    const hipError_t e = hipGetLastError();
+    if (e == hipSuccess && a.told) *a.told = queued && queue_tells(done, g.grid, g.claim, tiles_of(a.P));
+    return e;
 }
 
 template <int W>
@@ -789,30 +826,30 @@ hipError_t launch_affine(int Wp, int dtype, bool update, bool gram, const AffArg
 }
 
 hipError_t launch_reduce(const double* partials, int n_out, int grid, double* sums_out, float* sqrt_out,
-                         hipStream_t s) {
+                         const Finished& done, hipStream_t s) {
     if (n_out < 1) return hipSuccess;
-    hipLaunchKernelGGL(reduce_kernel, dim3(n_out), dim3(kBlock), 0, s, partials, grid, sums_out, sqrt_out);
+    hipLaunchKernelGGL(reduce_kernel, finishing_grid(n_out), dim3(kBlock), 0, s, partials, n_out, grid, sums_out, sqrt_out, done);
     return hipGetLastError();
 }
 
 hipError_t launch_gram_norms(const double* gamma, const double* coef, int U, int Wp, float* norms_out,
-                             hipStream_t s) {
+                             const Finished& done, hipStream_t s) {
     if (U < 1) return hipSuccess;
-    hipLaunchKernelGGL(gram_norms_kernel, dim3(U), dim3(kBlock), 0, s, gamma, coef, U, Wp,
-                       norms_out);
+    hipLaunchKernelGGL(gram_norms_kernel, finishing_grid(U), dim3(kBlock), 0, s, gamma, coef, U, Wp,
+                       norms_out, done);
     return hipGetLastError();
 }
 
 hipError_t launch_gram_finish(const double* partials, int grid, double* gamma, const double* coef, int U, int W,
-                              unsigned int* ticket, float* norms_out, hipStream_t s) {
+                              unsigned int* ticket, float* norms_out, const Finished& done, hipStream_t s) {
     if (W < 1 || W > kFinishRows || U < 1 || U > kBlock) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(gram_finish_kernel, dim3(W * (W + 1) / 2), dim3(kBlock), 0, s, partials, grid, gamma, coef, U, W, ticket,
-                       norms_out);
+    hipLaunchKernelGGL(gram_finish_kernel, finishing_grid(W * (W + 1) / 2), dim3(kBlock), 0, s, partials, grid, gamma, coef, U, W, ticket,
+                       norms_out, done);
     return hipGetLastError();
 }
 
-hipError_t launch_reduce_gram(const double* partials, int grid, int Wp, int W, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(reduce_gram_kernel, dim3(W * (W + 1) / 2), dim3(kBlock), 0, s, partials, grid, Wp, W, out);
+hipError_t launch_reduce_gram(const double* partials, int grid, int Wp, int W, double* out, const Finished& done, hipStream_t s) {
+    hipLaunchKernelGGL(reduce_gram_kernel, finishing_grid(W * (W + 1) / 2), dim3(kBlock), 0, s, partials, grid, Wp, W, out, done);
     return hipGetLastError();
 }
 

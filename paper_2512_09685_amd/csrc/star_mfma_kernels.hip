@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kBlock, 2) void aff_mfma_kernel(float* __restrict__
                                                           const int head, const int span_g, const int span_k,
                                                           void* __restrict__ publish, const int publish_bf16,
                                                           double* __restrict__ partials,
-                                                          TileQueue* __restrict__ queue, const int claim) {
+                                                          const TileSource queue, const int claim) {
     typedef GramTile<WIDE> GT;
     typedef typename GT::acc_t acc_t;
     typedef typename R::vec vec_t;
@@ -503,8 +503,8 @@ hipError_t launch_mfma_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_o
     }
     *grid_out = g.grid;
     hipLaunchKernelGGL(kern, dim3(g.grid), dim3(kBlock), 0, s, a.params, a.momentum, a.rows, a.cf, a.P, a.head,
-                       g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials, a.queue,
-                       g.claim);
+                       g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials,
+                       TileSource{a.queue, nullptr, 0u}, g.claim);
     return hipGetLastError();
 }
 

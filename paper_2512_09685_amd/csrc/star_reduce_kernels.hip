@@ -21,7 +21,7 @@ __global__ __launch_bounds__(kBlock) void reduce_rows_kernel(const RowPtrs rows,
                                                              const int out_bf16, const int64_t P, const int head,
                                                              const int norms, const int span_g, const int span_k,
                                                              double* __restrict__ partials,
-                                                             TileQueue* __restrict__ queue, const int claim,
+                                                             const TileSource queue, const int claim,
                                                              const InlineTables inl) {
     extern __shared__ uint64_t lds64[];
     // out pointers | (norms) running sums of gbar^2 per thread and group, and per wave, in double (the
@@ -184,10 +184,13 @@ hipError_t launch_reduce_t(const ReduceArgs& a, int num_cu, int grid_cap, int* g
                               : pick_geometry(a.P, a.norms != 0, num_cu, grid_cap, 256, 1,
                                               sum_workgroups(W, std::is_same<R, RowF32>::value, a.U, a.P, num_cu));
     *grid_out = g.grid;
+    const Finished done = a.norms ? Finished() : a.done;
     hipLaunchKernelGGL(kern, dim3(g.grid), dim3(kBlock), lds, s, a.rows, a.coef, a.mask, a.out, a.U,
                        a.out_dtype == STAR_BF16 ? 1 : 0, a.P, a.head, a.norms, g.span_g, g.span_k, a.partials,
-                       a.queue, g.claim, a.coef ? InlineTables() : *a.inl);
-    return hipGetLastError();
+                       tile_source(a.queue, done), g.claim, a.coef ? InlineTables() : *a.inl);
+    const hipError_t e = hipGetLastError();
+    if (e == hipSuccess && a.told) *a.told = queued && queue_tells(done, g.grid, g.claim, tiles_of(a.P));
+    return e;
 }
 
 }  // namespace

@@ -435,7 +435,7 @@ struct Launch {
     bool finish_at_once = false;   // Gram route: sums and norms in one finishing launch
     bool split_norms = false; // update by the collapsed map, norms by a separate direct pass (see decide)
     bool collapsed_in_seq = false;   // step-by-step kernel walks the updates for the norms, applies the update as one map
-    int burst = 0;            // collapsed update without norms: see burst_claim
+    int burst = 0;            // collapsed update: see burst_claim and mfma_burst_claim
 };
 
 Launch decide(const star::Plan& plan, int grad_dtype, bool update, bool want_norms, int64_t P, const Opts& opt) {
@@ -503,6 +503,9 @@ Launch decide(const star::Plan& plan, int grad_dtype, bool update, bool want_nor
             if (star::bursts(l.Wp, grad_dtype == STAR_F32)) l.want_queue = l.burst > 0;
         }
         l.mfma = gram && gram_on_matrix_cores(l.Wp, grad_dtype, opt.kernel, update, P);
+        if (l.mfma && update)
+            l.burst = opt.queue_min > 0 && !l.want_queue
+                          ? 0 : star::mfma_burst_claim(l.Wp, grad_dtype == STAR_F32, opt.queue_min > 0 ? (int64_t)1 << 62 : P);
         l.queue_order = l.mfma || l.burst > 0 || (l.want_queue && star::aff_takes_queue(gram, l.Wp, grad_dtype == STAR_F32, update));
         l.launches = (update || gram) ? 1 : 0;
         // up to 8 rows on a short shard: one finishing launch, see gram_finish_kernel

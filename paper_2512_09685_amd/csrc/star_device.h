@@ -337,9 +337,17 @@ struct BurstRoom {   // in LDS
     f32x4 p[CAP][kBlock], v[CAP][kBlock];
     int32_t tile[kBlock / 64][CAP];
 };
+template <>
+struct BurstRoom<0> {};
 // Tiles that fit beside `other` bytes of LDS.
 constexpr int burst_tiles(int other) { return (kLdsBytes - 64 - other) / (int)sizeof(BurstRoom<1>); }
 
+template <int CAP>
+struct Burst;
+template <>
+struct Burst<0> {   // a kernel that writes as it goes
+    __device__ __forceinline__ Burst(BurstRoom<0>&, uint32_t) {}
+};
 template <int CAP>
 struct Burst {
     BurstRoom<CAP>& room;
@@ -487,11 +495,11 @@ inline Geometry queue_geometry(int num_cu, int grid_cap, int per_cu, int thread_
     return g;
 }
 
-// The period of the bursts, in ticks of 10 ns: three quarters of the time in which `workgroups` fill `cap` tiles of LDS at 6.6 TB/s, so that
-// the clock comes before the room runs out (from 0.5 to 0.9 of it 1 % apart: the longer the fewer turns, but also the more
+// The period of the bursts, in ticks of 10 ns: the share `fill` of the time in which `workgroups` fill `cap` tiles of LDS at 6.6 TB/s, so
+// that the clock comes before the room runs out (from 0.5 to 0.9 of it 1 % apart: the longer the fewer turns, but also the more
 // workgroups that are early).
-inline uint32_t burst_period(int cap, int bytes_per_tile, int workgroups) {
-    const double ticks = 0.75 * cap * (double)bytes_per_tile * workgroups / 66000.0;
+inline uint32_t burst_period(int cap, int bytes_per_tile, int workgroups, double fill = 0.75) {
+    const double ticks = fill * cap * (double)bytes_per_tile * workgroups / 66000.0;
     return ticks < 100.0 ? 100u : (uint32_t)ticks;
 }
 

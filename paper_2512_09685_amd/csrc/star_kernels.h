@@ -221,6 +221,27 @@ inline int burst_claim(int Wp, bool f32_rows, int64_t P) {
     return Wp >= 24 ? 3 : (Wp >= 16 ? 5 : 6);
 }
 
+// The same for the update with norms from the matrix cores (aff_mfma_kernel); 0: it writes as it goes.  Three states in turn, without -> with bursts:
+//   fp32 rows   40 / 140 M elements, 14 rows 481 / 1643 -> 468 / 1608 us, 16 rows 542 / 1854 -> 515 / 1771, 20 rows 692 / 2342 -> 670 / 2283;
+//               17 M, 14 / 16 / 20 rows 215 / 241 / 312 -> 210 / 230 / 296.  Not 12 M (14 / 16 rows 158 / 177 against 164 / 182), not 12 rows (140 M
+//               1462 against 1486), and not 24 and more, whose matrix work one wave per SIMD does not hide (25.6 M, 24 / 32 rows
+//               540 / 691 against 551 / 718).
+//   bf16 rows   40 / 200 M, 12 rows 273 / 1281 -> 267 / 1264, 16 rows 329 / 1560 -> 313 / 1485; 80 M, 24 / 28 / 32 rows 889 / 1004 / 1142 -> 856 /
+//               962 / 1068, 17 M 205 / 232 / 263 -> 199 / 226 / 247 (12 M: 150 / 169 / 192 against 155 / 176 / 197); 5 / 8 M, 8 / 12 / 16 rows 41 / 50 /
+//               58 and 63 / 76 / 82 -> 40 / 47 / 55 and 53 / 64 / 77 (3 M level); 7 to 11 rows beyond that: level at 17 M, 80 M, 8 / 11 rows 431 /
+//               498 against 436 / 498.  20 rows: 25.6 M 253 against 257.
+//   tiles per claim   140 M, 16 fp32 rows, 5 / 6: 1771 / 1788; 200 M, 12 / 16 bf16 rows 1285 / 1264, 1492 / 1485; 25.6 M, 16 rows 208 / 208; 150 M,
+//                     32 rows, 5 / 7 / 9: 2004 / 1966 / 1941, 25.6 M 363 / 359 / 354.
+constexpr bool mfma_bursts(int Wp, bool f32_rows) { return f32_rows ? Wp >= 14 && Wp <= 20 : Wp >= 7 && Wp != 20; }
+inline int mfma_burst_claim(int Wp, bool f32_rows, int64_t P) {
+    constexpr int64_t kMi = 1 << 20;
+    if (!mfma_bursts(Wp, f32_rows)) return 0;
+    if (f32_rows) return P >= 16 * kMi ? 5 : 0;
+    if (Wp > 16) return P >= 16 * kMi ? (Wp > 28 ? 9 : 7) : 0;
+    if (P < 9 * kMi / 2 || (Wp < 12 && P > 12 * kMi)) return 0;
+    return P >= 14 * kMi ? 6 : 5;
+}
+
 // Largest number of updates one launch of the step-by-step kernel accepts
 // (bounded by the LDS tables and, with norms, the per-thread accumulators).
 int seq_max_updates(int Wp, bool norms);
@@ -260,7 +281,7 @@ struct AffArgs {
     double* partials;  // device [Wp(Wp+1)/2][grid] pairwise-product sums per block (gram only)
     TileQueue* queue;  // device, zeroed; null: fixed assignment of tiles to workgroups (not for the matrix-core kernel)
     CoefCopy copy;     // launch_affine with `gram`, without a queue
-    int32_t burst;     // launch_affine with `update`, without `gram`: see burst_claim (with a queue)
+    int32_t burst;     // with `update`: see burst_claim and mfma_burst_claim (with a queue)
     Finished done;     // launch_affine without `gram`: written by a launch that takes tiles from the queue
     bool* told;        // host, or null: set if the launch does
 };

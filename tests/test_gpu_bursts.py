@@ -19,7 +19,7 @@ def _guarded(n, offset, gen, dtype=torch.float32, std=0.02):
     return whole, whole[offset:offset + n]
 
 
-def _call(W, P, dtype, offset, out, threshold, U=12, **kw):
+def _call(W, P, dtype, offset, out, threshold, U=12, norms=None):
     gen = torch.Generator(device="cuda").manual_seed(W + P)
     rows = [_guarded(P, offset, gen, torch.float32 if dtype == "f32" else torch.bfloat16, 1e-2)[1] for _ in range(W)]
     (pw, p), (vw, v) = _guarded(P, offset, gen), _guarded(P, offset, gen, std=1e-2)
@@ -28,11 +28,11 @@ def _call(W, P, dtype, offset, out, threshold, U=12, **kw):
     us = star.UpdateStream(offs, mem, st)
     whole = [pw, vw]
     if out is None:
-        star.star_group_update(p, v, rows, us, queue_threshold=threshold, **HP, **kw)
+        star.star_group_update(p, v, rows, us, norms_out=norms, queue_threshold=threshold, **HP)
     else:
         sw, s = _guarded(P, offset, gen, out)
         whole.append(sw)
-        star.star_group_update_publish(p, v, rows, us, s, queue_threshold=threshold, **HP, **kw)
+        star.star_group_update_publish(p, v, rows, us, s, norms_out=norms, queue_threshold=threshold, **HP)
     torch.cuda.synchronize()
     return whole, (p, v, rows, us, start)
 
@@ -53,9 +53,7 @@ def test_update_in_bursts(W, dtype, P, threshold, offset, out):
     assert star.star_plan_choice(P, W, dtype, us, queue_threshold=1 << 62, **choice)["queue_order"] == 0
     got, (p, v, rows, us, (p0, v0)) = _call(W, P, dtype, offset, out, threshold)
     fixed = _call(W, P, dtype, offset, out, 1 << 62)[0]
-    for a, b in zip(got, fixed):   # whole buffers: nothing beside the shard is written either
-        assert torch.equal(a.view(torch.int16 if a.dtype == torch.bfloat16 else torch.int32),
-                           b.view(torch.int16 if b.dtype == torch.bfloat16 else torch.int32))
+    assert all(_same_bits(a, b) for a, b in zip(got, fixed))   # whole buffers: nothing beside the shard is written either
     M, B = star.star_plan_affine(W, us, **HP)
     ep, ev = M[0, 0] * p0 + M[0, 1] * v0, M[1, 0] * p0 + M[1, 1] * v0
     for w in range(W):
@@ -64,3 +62,33 @@ def test_update_in_bursts(W, dtype, P, threshold, offset, out):
     # a chain of W + 2 fp32 multiply-adds of terms of the result's size
     for x, e in ((p, ep), (v, ev)):
         assert float(((x.double() - e).abs() / (e.abs() + e.square().mean().sqrt())).max()) <= 3e-6
+
+
+def _same_bits(a, b):
+    as_int = torch.int16 if a.dtype == torch.bfloat16 else torch.int32
+    return torch.equal(a.view(as_int), b.view(as_int))
+
+
+# threshold None: the shortest shards of a row count and, with up to 11 bf16 rows, the longest
+@pytest.mark.parametrize("W,dtype,P,threshold,offset,out", [
+    (14, "f32", 4099, 1, 0, None), (16, "f32", 256 * 1024 + 5, 1, 1, torch.bfloat16), (20, "f32", 511 * 1024 + 1, 1, 0, torch.float32),
+    (18, "f32", 5_000_001, 1, 3, None), (16, "f32", 16 << 20, None, 5, None), (15, "f32", (16 << 20) + 1025, None, 0, torch.bfloat16),
+    (12, "bf16", 5001, 1, 0, None), (16, "bf16", 5_000_003, None, 1, torch.bfloat16), (7, "bf16", 5_000_003, None, 0, None),
+    (11, "bf16", 12 << 20, None, 0, torch.float32), (13, "bf16", 15_000_003, None, 6, None), (24, "bf16", 17_000_001, None, 0, None),
+    (32, "bf16", 512 * 1024 + 3, 1, 2, None), (28, "bf16", 3_000_513, 1, 0, torch.float32)])
+def test_update_with_norms_in_bursts(W, dtype, P, threshold, offset, out):
+    n, m = torch.full((12,), -1.0, device="cuda"), torch.full((12,), -1.0, device="cuda")
+    got, (p, v, rows, us, _) = _call(W, P, dtype, offset, out, threshold, norms=n)
+    choice = star.star_plan_choice(P, W, dtype, us, lr=0.1, momentum_coef=0.9, wmode="stale", want_norms=True)
+    assert choice["kernel"] == star.KERNEL_AFFINE_MFMA
+    fixed = _call(W, P, dtype, offset, out, 1 << 62, norms=m)[0]
+    assert all(_same_bits(a, b) for a, b in zip(got, fixed))
+    # the same sums tile by tile, in double from there on: only their order differs
+    assert float(((n - m) / m).abs().max()) <= 2.0 ** -23
+    r = torch.stack([x.double() for x in rows])
+    C = torch.zeros(us.U, W, dtype=torch.float64)
+    for u in range(us.U):
+        for k in range(us.offsets[u], us.offsets[u + 1]):
+            C[u, us.members[k]] = 1.0 / ((us.offsets[u + 1] - us.offsets[u]) * (1.0 + us.staleness[k]))
+    want = sum((C.cuda() @ part).square().sum(1) for part in r.split(1 << 22, dim=1)).sqrt()
+    assert float(((n.double() - want) / want).abs().max()) <= 1e-6   # (rows that are not anti-correlated, see star.h)

@@ -854,7 +854,10 @@ star_status run_reduce(void* const* out_rows, int out_dtype, const void* const* 
     const bool use_inline = star::tables_fit_inline(U, Wp) && U <= star::reduce_max_updates(Wp, want_norms);
     const int umax = star::reduce_max_updates(Wp, want_norms);
     auto from_queue = [&](int n) { return P >= queue_min_for(opt, grad_dtype, Wc, false, true, false, false, n); };
-    const bool want_queue = from_queue(std::min(U, umax)) || (U % umax && from_queue(U % umax));
+    int burst = 0;   // one group, no norms: written in bursts (a caller's own threshold: from there on)
+    if (U == 1 && !want_norms && (opt.queue_min == 0 || P >= opt.queue_min))
+        burst = star::mean_burst_claim(Wp, grad_dtype == STAR_F32, out_dtype == STAR_BF16, opt.queue_min > 0 ? (int64_t)1 << 62 : P);
+    const bool want_queue = burst > 0 || from_queue(std::min(U, umax)) || (U % umax && from_queue(U % umax));
     std::unique_lock<std::mutex> lock(g_mu, std::defer_lock);
     Slot* slot = nullptr;   // only where something has to live in it
     if (!use_inline || want_norms || want_queue) {
@@ -899,7 +902,8 @@ star_status run_reduce(void* const* out_rows, int out_dtype, const void* const* 
         a.head = head;
         a.norms = want_norms ? 1 : 0;
         a.partials = slot ? slot->partials : nullptr;
-        a.queue = from_queue(n) ? slot->queue : nullptr;
+        a.queue = burst > 0 || from_queue(n) ? slot->queue : nullptr;
+        a.burst = burst;
         a.done = last ? done : star::Finished();
         a.told = last && slot ? &release.told : nullptr;
         int grid = 0;

@@ -331,39 +331,49 @@ __device__ __forceinline__ void store_through(const f32x4 x, float* wave_base, c
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(wave_base, 0, 0x7fffffff, 0x00027000);
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), r, lane_bytes, 0, 16 /* sc1 */);
 }
+// The same of a tile's chunk as fp32 or, rounded, as bf16 (`wave_base`: the tile's first element).
+__device__ __forceinline__ void publish_through(const f32x4 x, void* dst, const int as_bf16, const int64_t tile) {
+    if (as_bf16) {
+        u32x2 packed;
+        packed[0] = bf16_bits_rne(x[0]) | (bf16_bits_rne(x[1]) << 16);
+        packed[1] = bf16_bits_rne(x[2]) | (bf16_bits_rne(x[3]) << 16);
+        const __amdgpu_buffer_rsrc_t r =
+            __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<uint16_t*>(dst) + tile * (4 * kBlock), 0, 0x7fffffff, 0x00027000);
+        __builtin_amdgcn_raw_buffer_store_b64(packed, r, threadIdx.x * 8, 0, 16 /* sc1 */);
+    } else {
+        store_through(x, reinterpret_cast<float*>(dst) + tile * (4 * kBlock), threadIdx.x * 16);
+    }
+}
 
-template <int CAP>
-struct BurstRoom {   // in LDS
-    f32x4 p[CAP][kBlock], v[CAP][kBlock];
+template <int CAP, int N = 2>
+struct BurstRoom {   // in LDS: N times 16 bytes a thread of every tile
+    f32x4 x[CAP][N][kBlock];
     int32_t tile[kBlock / 64][CAP];
 };
-template <>
-struct BurstRoom<0> {};
+template <int N>
+struct BurstRoom<0, N> {};
 // Tiles that fit beside `other` bytes of LDS.
-constexpr int burst_tiles(int other) { return (kLdsBytes - 64 - other) / (int)sizeof(BurstRoom<1>); }
+template <int N = 2>
+constexpr int burst_tiles(int other) {
+    return (kLdsBytes - 64 - other) / (int)sizeof(BurstRoom<1, N>);
+}
 
-template <int CAP>
-struct Burst;
-template <>
-struct Burst<0> {   // a kernel that writes as it goes
-    __device__ __forceinline__ Burst(BurstRoom<0>&, uint32_t) {}
-};
-template <int CAP>
+template <int CAP, int N = 2>
 struct Burst {
-    BurstRoom<CAP>& room;
+    BurstRoom<CAP, N>& room;
     const uint32_t period;   // ticks
     uint32_t next;
     int held = 0;
 
-    __device__ __forceinline__ Burst(BurstRoom<CAP>& r, const uint32_t ticks) : room(r), period(ticks) { next = boundary(clock()); }
+    __device__ __forceinline__ Burst(BurstRoom<CAP, N>& r, const uint32_t ticks) : room(r), period(ticks) { next = boundary(clock()); }
     static __device__ __forceinline__ uint32_t clock() { return (uint32_t)__builtin_readsteadycounter(); }
     __device__ __forceinline__ uint32_t boundary(const uint32_t now) const { return (now / period + 1) * period; }
 
-    // The results of one chunk of a tile (the whole wave together); write(tile, p, v) stores them.
+    // The results of one chunk of a tile (the whole wave together); write(tile, results ...) stores them.
     template <class Write>
-    __device__ __forceinline__ void put(const int64_t tile, const f32x4 p, const f32x4 v, Write&& write) {
-        room.p[held][threadIdx.x] = p;
-        room.v[held][threadIdx.x] = v;
+    __device__ __forceinline__ void put(const int64_t tile, const f32x4 (&x)[N], Write&& write) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) room.x[held][i][threadIdx.x] = x[i];
         room.tile[threadIdx.x >> 6][held] = (int32_t)tile;
         ++held;
         const uint32_t now = clock();
@@ -373,23 +383,27 @@ struct Burst {
     }
     template <class Write>
     __device__ __forceinline__ void flush(Write&& write) {
-        constexpr int N = 4;   // tiles read together
-        for (int i = 0; i < held; i += N) {
-            f32x4 p[N], v[N];
-            int64_t t[N];
+        constexpr int T = 4;   // tiles read together
+        for (int i = 0; i < held; i += T) {
+            f32x4 x[T][N];
+            int64_t t[T];
 #pragma unroll
-            for (int k = 0; k < N; ++k) {
+            for (int k = 0; k < T; ++k) {
                 const int j = i + k < held ? i + k : held - 1;
-                p[k] = room.p[j][threadIdx.x];
-                v[k] = room.v[j][threadIdx.x];
+#pragma unroll
+                for (int q = 0; q < N; ++q) x[k][q] = room.x[j][q][threadIdx.x];
                 t[k] = __builtin_amdgcn_readfirstlane(room.tile[threadIdx.x >> 6][j]);
             }
 #pragma unroll
-            for (int k = 0; k < N; ++k)
-                if (i + k < held) write(t[k], p[k], v[k]);
+            for (int k = 0; k < T; ++k)
+                if (i + k < held) write(t[k], x[k]);
         }
         held = 0;
     }
+};
+template <int N>
+struct Burst<0, N> {   // a kernel that writes as it goes
+    __device__ __forceinline__ Burst(BurstRoom<0, N>&, uint32_t) {}
 };
 
 // ---------------------------------------------------------------- the collapsed update of one element

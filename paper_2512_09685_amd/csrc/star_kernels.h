@@ -352,11 +352,38 @@ struct ReduceArgs {
     int32_t norms;           // also accumulate sum of squares per group
     double* partials;        // device [U][grid] (norms only)
     TileQueue* queue;        // device, zeroed; null: fixed assignment of tiles to workgroups
+    int32_t burst;           // see mean_burst_claim (with a queue, one group, tables in `inl`, no norms)
     Finished done;           // without norms: written by a launch that takes tiles from the queue
     bool* told;              // host, or null: set if the launch does
 };
 
 int reduce_max_updates(int Wp, bool norms);
+
+// Tiles per claim of the kernel that writes the aggregate of one group, without norms, in bursts; 0 for reduce_rows_kernel.  Three states in turn,
+// reduce_rows_kernel -> mean_burst_kernel:
+//   fp32 rows and result   25.6 M elements, 6 / 8 / 12 / 16 / 24 / 32 rows 123 / 161 / 227 / 289 / 423 / 547 -> 115 / 142 / 202 / 261 / 379 / 497 us;
+//                          100 M 460 / 596 / 870 / 1133 / 1725 / 2315 -> 424 / 538 / 768 / 1002 / 1499 / 2000; at the limits 14 M, 6 rows 67 -> 65,
+//                          10 M, 7 rows 56 -> 54, 7 M, 9 rows 50 -> 48, 3 M, 12 / 16 / 32 rows 31 / 42 / 77 -> 30 / 37 / 68 (2 M: 20 / 26 / 48
+//                          against 22 / 27 / 49; 4 M, 8 rows 27.3 against 28.3).  5 rows: 20 M level, 60 M 243 -> 231, left out.
+//   bf16 rows, fp32        18 / 150 M, 12 rows 84 / 692 -> 83 / 641 us, 16 rows 105 / 894 -> 101 / 801, 24 rows 150 / 1326 -> 143 / 1156, 32 rows
+//                          196 / 1712 -> 192 / 1538; 10 M, 16 / 24 / 32 rows 67 / 91 / 116 -> 61 / 84 / 112.  10 rows: 150 M level.
+//   bf16 result            half the writes, less to gain: 25 / 60 M, 12 / 16 / 24 / 32 fp32 rows 210 / 271 / 396 / 510 and 486 / 639 / 937 / 1223 ->
+//                          196 / 255 / 370 / 481 and 460 / 603 / 885 / 1179; 32 bf16 rows 271 / 654 -> 267 / 628, 24 rows 199 / 485 against 202 / 475.
+//   tiles per claim        25.6 M, 8 / 12 / 16 / 24 fp32 rows, 2 / 3 / 5 / 7 / 9: - / 164 / 146 / 142 / 147, 232 / 209 / 202 / 211 / 214, 279 / 261 / 272 / 276 /
+//                          279, 379 / 391 / 399 / 402 / 404; 140 M, 24 rows, 2 / 3: 2180 / 2109.
+inline int mean_burst_claim(int Wp, bool f32_rows, bool bf16_out, int64_t P) {
+    constexpr int64_t kMi = 1 << 20;
+    if (f32_rows) {
+        if (Wp < (bf16_out ? 12 : 6)) return 0;
+        const int64_t from = bf16_out ? (Wp >= 14 ? 4 : 14) : (Wp >= 12 ? 3 : (Wp >= 9 ? 7 : (Wp >= 7 ? 8 : 14)));
+        if (P < from * kMi) return 0;
+        if (Wp >= 24) return P < 72 * kMi ? 2 : 3;
+        return Wp >= 14 ? 3 : (Wp >= 9 ? 5 : (Wp >= 7 ? 7 : 9));
+    }
+    if (bf16_out) return Wp >= 28 && P >= 15 * kMi / 2 ? 3 : 0;
+    if (Wp < 12 || P < (Wp >= 20 ? 15 * kMi / 2 : (Wp >= 14 ? 8 * kMi : 16 * kMi))) return 0;
+    return Wp >= 20 ? 5 : (Wp >= 14 ? 7 : 9);
+}
 
 hipError_t launch_group_reduce(int Wp, int dtype, const ReduceArgs& a, int num_cu, int grid_cap, int* grid_out,
                                hipStream_t s);

@@ -255,12 +255,12 @@ void aff_burst_kernel(float* __restrict__ params, float* __restrict__ momentum, 
             v = load_state(momentum, c);
         }
     };
-    auto write = [&](const int64_t tile, const f32x4 p, const f32x4 v) {
+    auto write = [&](const int64_t tile, const f32x4 (&x)[2]) {
         const int64_t c = tile * kBlock + threadIdx.x;
         if (c < nchunk) {
-            store_through(p, params + tile * (4 * kBlock), threadIdx.x * 16);
-            store_through(v, momentum + tile * (4 * kBlock), threadIdx.x * 16);
-            if (publish) publish_chunk(p, publish, publish_bf16, c);
+            store_through(x[0], params + tile * (4 * kBlock), threadIdx.x * 16);
+            store_through(x[1], momentum + tile * (4 * kBlock), threadIdx.x * 16);
+            if (publish) publish_chunk(x[0], publish, publish_bf16, c);
         }
     };
     vec_t gn[W] = {};
@@ -288,7 +288,7 @@ void aff_burst_kernel(float* __restrict__ params, float* __restrict__ momentum, 
             p[K] = pe;
             v[K] = ve;
         });
-        burst.put(tile, p, v, write);
+        burst.put(tile, {p, v}, write);
     });
     burst.flush(write);
     // elements not covered by whole chunks: same arithmetic, one element at a time (at most 66, the first workgroup's)

@@ -310,12 +310,12 @@ __global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* 
     const int64_t nchunk = P / 4;
     const int64_t ntile = (nchunk + kBlock - 1) / kBlock;
     // element-wise update of chunk c from values already in registers
-    auto write = [&](const int64_t tile, const f32x4 p, const f32x4 v) {   // of a burst
+    auto write = [&](const int64_t tile, const f32x4 (&x)[2]) {   // of a burst
         const int64_t c = tile * kBlock + threadIdx.x;
         if (c < nchunk) {
-            store_through(p, params + tile * (4 * kBlock), threadIdx.x * 16);
-            store_through(v, momentum + tile * (4 * kBlock), threadIdx.x * 16);
-            if (publish) publish_chunk(p, publish, publish_bf16, c);
+            store_through(x[0], params + tile * (4 * kBlock), threadIdx.x * 16);
+            store_through(x[1], momentum + tile * (4 * kBlock), threadIdx.x * 16);
+            if (publish) publish_chunk(x[0], publish, publish_bf16, c);
         }
     };
     auto update_chunk = [&](int64_t t, const vec_t (&g)[W], f32x4 pq, f32x4 vq) {
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* 
             vo[K] = ve;
         });
         if constexpr (BURST) {
-            burst.put(t, po, vo, write);
+            burst.put(t, {po, vo}, write);
         } else {
             store_state(po, params, c);
             store_state(vo, momentum, c);

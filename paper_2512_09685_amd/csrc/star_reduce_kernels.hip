@@ -13,6 +13,13 @@
 
 namespace star {
 
+// The one group of a call, in the kernel arguments.
+struct MeanArgs {
+    void* out;
+    uint32_t mask;
+    float coef[STAR_MAX_WORKERS];
+};
+
 // LDS: out pointers [U] (8 bytes each) | coef[U][W] | mask[U] | (norms) wave[4][U] | nacc[U][kBlock]
 template <int W, class R>
 __global__ __launch_bounds__(kBlock) void reduce_rows_kernel(const RowPtrs rows, const float* __restrict__ t_coef,
@@ -135,6 +142,62 @@ __global__ __launch_bounds__(kBlock) void reduce_rows_kernel(const RowPtrs rows,
     }
 }
 
+// One group without norms on long shards: the mean, or any weighted sum, of its rows, kept in LDS and written in bursts (see Burst).  The
+// arithmetic is that of reduce_rows_kernel to the bit; coefficients and mask stay in scalar registers.
+template <int W, class R>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void mean_burst_kernel(const RowPtrs rows, const MeanArgs mean, const int out_bf16, const int64_t P, const int head,
+                       const TileSource queue, const int claim, const uint32_t period) {
+    constexpr int CAP = burst_tiles<1>(0);
+    __shared__ BurstRoom<CAP, 1> room;
+    Burst<CAP, 1> burst(room, period);
+    typedef typename R::vec vec_t;
+    const int64_t nchunk = P / 4, ntile = (nchunk + kBlock - 1) / kBlock;
+    auto fetch = [&](const int64_t tile, vec_t (&g)[W]) {
+        const int64_t c = tile * kBlock + threadIdx.x;
+        if (c < nchunk) {
+#pragma unroll
+            for (int w = 0; w < W; ++w) g[w] = R::load(rows.p[w], c);
+        }
+    };
+    auto write = [&](const int64_t tile, const f32x4 (&y)[1]) {
+        if (tile * kBlock + threadIdx.x < nchunk) publish_through(y[0], mean.out, out_bf16, tile);
+    };
+    vec_t gn[W] = {};
+    bool primed = false;
+    for_each_claimed_tile_ahead(queue, ntile, claim, [&](const int64_t tile, const int64_t following) {
+        if (!primed) {
+            fetch(tile, gn);
+            primed = true;
+        }
+        vec_t g[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) g[w] = gn[w];
+        if (following >= 0) fetch(following, gn);
+        f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+        static_for<0, W>([&](auto wc) {   // ascending worker id
+            constexpr int Wi = decltype(wc)::value;
+            if (mean.mask & (1u << Wi)) {
+                static_for<0, 4>([&](auto kc) {
+                    constexpr int K = decltype(kc)::value;
+                    x[K] = __builtin_fmaf(mean.coef[Wi], R::template get<K>(g[Wi]), x[K]);
+                });
+            }
+        });
+        burst.put(tile, {x}, write);
+    });
+    burst.flush(write);
+    const int64_t nrest = rest_count(head, P, nchunk);
+    for (int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x; r < nrest; r += (int64_t)gridDim.x * kBlock) {
+        const int64_t j = rest_element(r, head, nchunk);
+        float x = 0.0f;
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            if (mean.mask & (1u << w)) x = __builtin_fmaf(mean.coef[w], R::load1(rows.p[w], j), x);
+        publish_element(x, mean.out, out_bf16, j);
+    }
+}
+
 namespace {
 
 size_t reduce_lds_bytes(int W, int U, bool norms) {
@@ -175,6 +238,23 @@ int sum_workgroups(int W, bool f32, int U, int64_t P, int num_cu) {
 
 template <int W, class R>
 hipError_t launch_reduce_t(const ReduceArgs& a, int num_cu, int grid_cap, int* grid_out, hipStream_t s) {
+    if constexpr (W >= 6) {
+        if (a.burst) {
+            if (a.U != 1 || a.norms || a.coef || !a.queue) return hipErrorInvalidValue;
+            const int grid = (int)std::min<int64_t>(std::min(num_cu, grid_cap), std::max<int64_t>(1, tiles_of(a.P)));
+            MeanArgs m;
+            m.out = a.inl->out[0];
+            m.mask = a.inl->mask[0];
+            for (int w = 0; w < STAR_MAX_WORKERS; ++w) m.coef[w] = w < W ? a.inl->coef[w] : 0.0f;
+            *grid_out = grid;
+            hipLaunchKernelGGL((mean_burst_kernel<W, R>), dim3(grid), dim3(kBlock), 0, s, a.rows, m, a.out_dtype == STAR_BF16 ? 1 : 0,
+                               a.P, a.head, tile_source(a.queue, a.done), a.burst,
+                               burst_period(burst_tiles<1>(0), (W * (int)sizeof(typename R::vec) + 16) * kBlock, grid));
+            const hipError_t e = hipGetLastError();
+            if (e == hipSuccess && a.told) *a.told = queue_tells(a.done, grid, a.burst, tiles_of(a.P));
+            return e;
+        }
+    }
     auto kern = reduce_rows_kernel<W, R>;
     const size_t lds = reduce_lds_bytes(W, a.U, a.norms != 0);
     const bool queued = a.queue;

@@ -92,3 +92,36 @@ def test_update_with_norms_in_bursts(W, dtype, P, threshold, offset, out):
             C[u, us.members[k]] = 1.0 / ((us.offsets[u + 1] - us.offsets[u]) * (1.0 + us.staleness[k]))
     want = sum((C.cuda() @ part).square().sum(1) for part in r.split(1 << 22, dim=1)).sqrt()
     assert float(((n.double() - want) / want).abs().max()) <= 1e-6   # (rows that are not anti-correlated, see star.h)
+
+
+# threshold None: the shortest shard of a row count; 1: the queue whatever the length
+@pytest.mark.parametrize("W,dtype,P,threshold,offset,out", [
+    (6, "f32", 1, 1, 0, "f32"), (8, "f32", 1027, 1, 1, "f32"), (16, "f32", 511 * 1024 + 3, 1, 0, "f32"), (7, "f32", 11_000_003, 1, 3, "f32"),
+    (6, "f32", 14 << 20, None, 0, "f32"), (8, "f32", (8 << 20) + 5, None, 5, "f32"), (11, "f32", 7_340_035, None, 0, "f32"),
+    (12, "f32", 3 << 20, None, 2, "f32"), (24, "f32", 3_200_001, None, 0, "f32"), (12, "f32", 6001, 1, 1, "bf16"),
+    (13, "f32", (14 << 20) + 7, None, 0, "bf16"), (20, "f32", 4 << 20, None, 3, "bf16"), (12, "bf16", 5, 1, 0, "f32"),
+    (12, "bf16", (16 << 20) + 1, None, 1, "f32"), (14, "bf16", 8 << 20, None, 0, "f32"), (32, "bf16", 7_900_001, None, 0, "f32"),
+    (28, "bf16", 262_147, 1, 1, "bf16"), (32, "bf16", 7_900_001, None, 5, "bf16")])
+def test_aggregate_in_bursts(W, dtype, P, threshold, offset, out):
+    gen = torch.Generator(device="cuda").manual_seed(W + P)
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16}
+    rows = [_guarded(P, offset, gen, dt[dtype], 1e-2)[1] for _ in range(W)]
+    members = np.random.default_rng(W).permutation(W)[:max(1, W - 2)].astype(np.int32)   # two rows that are in no group
+    members = np.concatenate([members, np.arange(W, dtype=np.int32)])
+    us = [star.UpdateStream(np.array([0, n], np.int32), m, np.arange(n, dtype=np.int32) % 3)
+          for n, m in ((len(members) - W, members[:-W]), (W, members[-W:]))]
+    for stream in us:
+        got = []
+        for t in (threshold, 1 << 62):
+            gen.manual_seed(7)
+            whole, o = _guarded(P, offset, gen, dt[out])
+            star.star_group_reduce([o], rows, stream, wmode="stale", queue_threshold=t)
+            torch.cuda.synchronize()
+            got.append(whole)
+        assert _same_bits(*got)
+        y = len(stream.members)
+        want = sum(rows[int(w)].double() / (y * (1.0 + int(s))) for w, s in zip(stream.members, stream.staleness))
+        have = got[0][offset:offset + P].double()
+        # a chain of W fp32 multiply-adds, and half a unit of the last place of a bf16 result
+        bound = 3e-6 if out == "f32" else 2.0 ** -8
+        assert float(((have - want).abs() / (want.abs() + want.square().mean().sqrt())).max()) <= bound

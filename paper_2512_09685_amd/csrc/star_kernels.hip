@@ -86,18 +86,24 @@ __global__ __launch_bounds__(kBlock) void aff_kernel(float* __restrict__ params,
     // variant can take its tiles from the queue like the plain one; and it has the registers for it.
     constexpr bool kFew = GRAM && gram_few_rows_form(W, std::is_same<R, RowF32>::value, UPDATE);
     typedef typename std::conditional<kFew, double, float>::type fold_t;
-    __shared__ fold_t fold[GRAM ? NG * kBlock : 1];
-    if constexpr (GRAM) {
+    __shared__ __align__(16) fold_t fold[GRAM ? NG * kBlock : 1];
+    bool folded = kFew;   // the slots hold something (many rows: not before the first fold, on a short shard the last)
+    if constexpr (kFew) {
 #pragma unroll
         for (int e = 0; e < NG; ++e) fold[e * kBlock + threadIdx.x] = (fold_t)0;
     }
     auto fold_now = [&]() {
         if constexpr (GRAM) {
+            if (folded) {
 #pragma unroll
-            for (int e = 0; e < NG; ++e) {
-                fold[e * kBlock + threadIdx.x] += (fold_t)acc[e];
-                acc[e] = 0.0f;
+                for (int e = 0; e < NG; ++e) fold[e * kBlock + threadIdx.x] += (fold_t)acc[e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < NG; ++e) fold[e * kBlock + threadIdx.x] = (fold_t)acc[e];
+                folded = true;
             }
+#pragma unroll
+            for (int e = 0; e < NG; ++e) acc[e] = 0.0f;
         }
     };
 
@@ -216,20 +222,31 @@ __global__ __launch_bounds__(kBlock) void aff_kernel(float* __restrict__ params,
         if constexpr (GRAM) gram_step<W>(acc, ge);
     }
 
+    // The workgroup's sum of every entry, in double: a wave takes an entry, four threads' slots a lane.  (Every wave summing its own registers
+    // entry by entry, unrolled, was code that a short shard's launch spent 2 us on: it runs once, and is fetched for that.)
     if constexpr (GRAM) {
-        __shared__ fold_t wave_part[kBlock / 64][NG];
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-        for (int e = 0; e < NG; ++e) {
-            const fold_t s = wave_sum_to_lane63((fold_t)acc[e] + fold[e * kBlock + threadIdx.x]);
-            if (lane == 63) wave_part[wave][e] = s;
-        }
+        fold_now();
         __syncthreads();
-        for (int e = threadIdx.x; e < NG; e += kBlock) {
-            double s = 0.0;
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        constexpr int kEach = (NG + kBlock / 64 - 1) / (kBlock / 64), N = kEach < 5 ? kEach : 5;   // N at a time: their additions wait for each other
+#pragma unroll 1
+        for (int i = 0; i < kEach; i += N) {
+            double s[N];
 #pragma unroll
-            for (int q = 0; q < kBlock / 64; ++q) s += (double)wave_part[q][e];
-            partials[(int64_t)e * span_g + blockIdx.x] = s;   // (span_g: the workgroups that have sums)
+            for (int k = 0; k < N; ++k) {
+                const int e = min(wave + kBlock / 64 * (i + k), NG - 1);
+                const fold_t* const slot = fold + e * kBlock + 4 * lane;
+                s[k] = ((double)slot[0] + (double)slot[1]) + ((double)slot[2] + (double)slot[3]);
+            }
+#pragma unroll
+            for (int k = 0; k < N; ++k) s[k] = wave_sum_to_lane63(s[k]);
+            if (lane == 63) {
+#pragma unroll
+                for (int k = 0; k < N; ++k) {
+                    const int e = wave + kBlock / 64 * (i + k);
+                    if (i + k < kEach && e < NG) partials[(int64_t)e * span_g + blockIdx.x] = s[k];   // (span_g: the workgroups that have sums)
+                }
+            }
         }
     }
 }

@@ -515,7 +515,10 @@ hipError_t launch_mfma_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_o
     const int64_t tiles = tiles_of(a.P);
     const bool one_wide = UPDATE && WIDE && kBf16 && a.rows_used >= 20 &&
                           tiles > 2 * (int64_t)num_cu * short_tiles_per_workgroup(kRowBytes + 32, Traffic::Update);
-    const int per_cu = (UPDATE && !WIDE && kRowBytes >= 160) || one_wide ? 1 : 2;
+    // 7 to 9 fp32 rows, update, from 16 Mi elements on: one too (three states in turn, 18.5 / 60 / 140 M elements, 7 rows 152 / 449 / 1030 -> 146 / 446 /
+    // 1026 us, 8 rows 166 / 488 / 1128 -> 156 / 478 / 1100, 9 rows 180 / 534 / 1238 -> 165 / 510 / 1172).
+    const bool one_light = UPDATE && !WIDE && !kBf16 && W >= 7 && tiles >= 16 * 1024;
+    const int per_cu = (UPDATE && !WIDE && kRowBytes >= 160) || one_wide || one_light ? 1 : 2;
     if (!a.queue) return hipErrorInvalidValue;
     Geometry g = queue_geometry(num_cu, grid_cap, per_cu, kRowBytes + (UPDATE ? 32 : 0),
                                 UPDATE ? Traffic::Update : Traffic::ReadOnly, tiles);

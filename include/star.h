@@ -430,8 +430,7 @@ star_status star_select_mode_ar(int32_t N, const double *iter_time, const double
 /*
  * Host-only: the fixed first round of the work queue for a launch of
  * `workgroups` workgroups that claim `tiles_per_claim` tiles at a time (the
- * kernels use 3; 5 when a thread moves less than 96 bytes per tile; 4 with the
- * half-size workgroups of the collapsed update on 24 and more bf16 rows).
+ * kernels use 2 to 13, by the bytes of a tile and the traffic of the launch).
  * Workgroup b starts on tiles first_tile[b] .. first_tile[b] + count[b] - 1
  * (counts cycle 1, 2, .., tiles_per_claim: unequal on purpose, so that the
  * workgroups do not run in step); the tiles from *base on are handed out by

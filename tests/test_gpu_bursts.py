@@ -125,3 +125,28 @@ def test_aggregate_in_bursts(W, dtype, P, threshold, offset, out):
         # a chain of W fp32 multiply-adds, and half a unit of the last place of a bf16 result
         bound = 3e-6 if out == "f32" else 2.0 ** -8
         assert float(((have - want).abs() / (want.abs() + want.square().mean().sqrt())).max()) <= bound
+
+
+@pytest.mark.parametrize("W,P", [(12, 6001), (16, 600_013)])
+@pytest.mark.parametrize("step", [1, 3])
+def test_bursts_of_buffers_off_by_different_amounts(W, P, step):
+    """Rows, state, copy and aggregate each off by their own number of elements, so that no advance aligns them all: the bursts store 8 and 16
+    bytes at places that are 4 (fp32) or 2 (bf16) byte aligned, and nothing beside the shard."""
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16}
+    us = star.UpdateStream(*rand_stream(np.random.default_rng(W), W, 5, stale=4))
+    one = star.UpdateStream([0, W], np.arange(W, dtype=np.int32))
+    for dtype in ("f32", "bf16"):
+        for out in ("f32", "bf16"):
+            got = []
+            for threshold in (1, 1 << 62):
+                gen = torch.Generator(device="cuda").manual_seed(W + P)
+                rows = [_guarded(P, 1 + step * w, gen, dt[dtype], 1e-2)[1] for w in range(W)]
+                (pw, p), (vw, v) = _guarded(P, 2, gen), _guarded(P, 5, gen, std=1e-2)
+                (sw, s), (ow, o) = _guarded(P, 3, gen, dt[out]), _guarded(P, 7, gen, dt[out])
+                star.star_group_update_publish(p, v, rows, us, s, queue_threshold=threshold, **HP)
+                n = torch.zeros(5, device="cuda")
+                star.star_group_update_publish(p, v, rows, us, s, norms_out=n, queue_threshold=threshold, **HP)
+                star.star_group_reduce([o], rows, one, queue_threshold=threshold)
+                torch.cuda.synchronize()
+                got.append((pw, vw, sw, ow))
+            assert all(_same_bits(a, b) for a, b in zip(*got)), (dtype, out)

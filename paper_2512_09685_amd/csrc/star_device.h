@@ -273,9 +273,12 @@ __device__ __forceinline__ void for_each_claimed_tile(const TileSource& src, con
 // before they work on the current one: body(tile, following) with following < 0 at the end.  The
 // start of the next claim is made known to the whole workgroup when it begins the last tile of the
 // current claim, so the look-ahead also crosses claims.
-template <class Body>
+// `body` takes a first argument as well, which of SETS sets of registers holds the tile (an integral constant; they take turns): the
+// following tile's loads go to the next set, so that nothing has to be moved.
+template <int SETS, class Body>
 __device__ __forceinline__ void for_each_claimed_tile_ahead(const TileSource& src, const int64_t ntile,
                                                             const int claim, Body&& body) {
+    static_assert(SETS == 1 || SETS == 2, "one set or two");
     TileQueue* const q = src.queue;
     __shared__ unsigned long long s_first;
     const FirstClaim fc = first_claim(claim, ntile);
@@ -283,36 +286,50 @@ __device__ __forceinline__ void for_each_claimed_tile_ahead(const TileSource& sr
     const unsigned long long base = fc.base;
     const bool counter = base < (unsigned long long)ntile;   // see for_each_claimed_tile
     unsigned long long nxt = 0;
-    int64_t cur = fc.t0;
-    if (cur < ntile && fc.n > 0) {   // (an even split of fewer tiles than workgroups leaves some without)
-        if (counter && threadIdx.x == 0) nxt = base + atomicAdd(&q->next, (unsigned long long)step);
-        int64_t end = cur + fc.n < ntile ? cur + fc.n : ntile;
-        for (;;) {
-            int64_t following = cur + 1;
-            if (following >= end) {   // last tile of this claim: where does the next one start?
-                if (!counter) {
-                    following = -1;
+    int64_t cur = fc.t0, end = 0;
+    auto after = [&](const int64_t tile) {
+        int64_t following = tile + 1;
+        if (following >= end) {   // last tile of this claim: where does the next one start?
+            if (!counter) {
+                following = -1;
+            } else {
+                if (threadIdx.x == 0) s_first = nxt;
+                __syncthreads();
+                following = (int64_t)s_first;
+                __syncthreads();
+                if (following < ntile) {
+                    // no claim is requested once the end is known: nothing may touch the queue
+                    // after this workgroup has reported that it left
+                    if (threadIdx.x == 0) nxt = base + atomicAdd(&q->next, (unsigned long long)step);
+                    end = following + step < ntile ? following + step : ntile;
                 } else {
-                    if (threadIdx.x == 0) s_first = nxt;
-                    __syncthreads();
-                    following = (int64_t)s_first;
-                    __syncthreads();
-                    if (following < ntile) {
-                        // no claim is requested once the end is known: nothing may touch the queue
-                        // after this workgroup has reported that it left
-                        if (threadIdx.x == 0) nxt = base + atomicAdd(&q->next, (unsigned long long)step);
-                        end = following + step < ntile ? following + step : ntile;
-                    } else {
-                        following = -1;
-                    }
+                    following = -1;
                 }
             }
-            body(cur, following);
+        }
+        return following;
+    };
+    if (cur < ntile && fc.n > 0) {   // (an even split of fewer tiles than workgroups leaves some without)
+        if (counter && threadIdx.x == 0) nxt = base + atomicAdd(&q->next, (unsigned long long)step);
+        end = cur + fc.n < ntile ? cur + fc.n : ntile;
+        for (;;) {
+            int64_t following = after(cur);
+            body(std::integral_constant<int, 0>{}, cur, following);
             if (following < 0) break;
             cur = following;
+            if constexpr (SETS == 2) {
+                following = after(cur);
+                body(std::integral_constant<int, 1>{}, cur, following);
+                if (following < 0) break;
+                cur = following;
+            }
         }
     }
     if (counter && threadIdx.x == 0) leave(src);
+}
+template <class Body>
+__device__ __forceinline__ void for_each_claimed_tile_ahead(const TileSource& src, const int64_t ntile, const int claim, Body&& body) {
+    for_each_claimed_tile_ahead<1>(src, ntile, claim, [&](auto, const int64_t tile, const int64_t following) { body(tile, following); });
 }
 
 // ---------------------------------------------------------------- writes in bursts

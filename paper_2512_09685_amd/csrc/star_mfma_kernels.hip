@@ -87,16 +87,29 @@ constexpr int panel_lds(bool bf16_rows, int W) {
 }
 constexpr int burst_tiles_beside_panel(bool bf16_rows, int W) { return burst_tiles(panel_lds(bf16_rows, W)); }
 
-// BURST: the update's results are kept in LDS and written in bursts (see Burst); one workgroup per unit then, with a tile of look-ahead.
-// Two workgroups with half the room each (16 fp32 / bf16 rows, 110 / 150 M elements): 1 487 / 1 227 us against 1 406 / 1 128.
-template <int W, class R, bool UPDATE, bool WIDE, bool BURST = false>
-__global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* __restrict__ params, float* __restrict__ momentum,
+// What an update keeps on a compute unit: up to two workgroups (Shared), or one, with a tile of look-ahead, which writes as it goes (Alone) or
+// keeps its results in LDS and writes them in bursts (Bursts, see Burst; two workgroups with half the room each, 16 fp32 / bf16 rows, 110 /
+// 150 M elements: 1 487 / 1 227 us against 1 406 / 1 128).
+//
+// A unit's only workgroup has one wave per SIMD, which issues an instruction every four cycles at best and hides nothing behind another
+// wave.  At the full clock of 2.4 GHz that is covered by the memory's time; but from 3 to 15 ms after a pause this card runs at 1.5 GHz, and
+// there such a wave's instructions are what a tile takes (16 bf16 rows: 3 100 of 3 740 cycles).  So these forms (the `kAlone` path) hold two
+// tiles in two sets of registers that take turns, instead of moving one to the other (104 moves a tile with 16 bf16 rows, 200 with fp32 rows), keep
+// the map's coefficients in vector registers (else the row pointers do not fit into the scalar ones and are fetched back lane by lane), and
+// mix the update into the matrix instructions, whose operands are read from LDS a step ahead.  250 ms idle, then four calls, us: 16 bf16
+// rows, 340 M elements 11 395 -> 10 740 (two workgroups writing as they go 10 779), 12 bf16 rows, 200 M 5 690 -> 5 377 (5 303), 32 bf16 rows,
+// 80 M 5 001 -> 4 795 (5 299), 16 fp32 rows, 110 M 6 732 -> 6 310 (6 631), 20 fp32 rows, 60 M 4 760 -> 4 395 (4 331).  Back to back: 2 498 -> 2 496,
+// 1 263 -> 1 250, 1 048 -> 1 026, 1 370 -> 1 360, 977 -> 926.
+enum class Form { Shared, Alone, Bursts };
+template <int W, class R, bool UPDATE, bool WIDE, Form FORM = Form::Shared>
+__global__ __launch_bounds__(kBlock, FORM == Form::Shared ? 2 : 1) void aff_mfma_kernel(float* __restrict__ params, float* __restrict__ momentum,
                                                           const RowPtrs rows, const AffCoef cf, const int64_t P,
                                                           const int head, const int span_g, const int span_k,
                                                           void* __restrict__ publish, const int publish_bf16,
                                                           double* __restrict__ partials,
                                                           const TileSource queue, const int claim,
                                                           const uint32_t period) {
+    constexpr bool BURST = FORM == Form::Bursts, kAlone = FORM != Form::Shared;
     typedef GramTile<WIDE> GT;
     typedef typename GT::acc_t acc_t;
     typedef typename R::vec vec_t;
@@ -122,7 +135,7 @@ __global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* 
     __shared__ __align__(16) unsigned char panel[kWaves][kPanelBytes];
     constexpr int kSums = (kPairs + 1) / 2 * 64;   // of a wave
     __shared__ double sums[kQuads ? kWaves * kSums : 1];
-    static_assert(!BURST || UPDATE, "bursts of the update's results");
+    static_assert(!kAlone || UPDATE, "a form of the update");
     constexpr int CAP = BURST ? burst_tiles_beside_panel(BF, W) : 0;
     static_assert(!BURST || sizeof(panel) + sizeof(sums) + sizeof(BurstRoom<CAP>) + 64 <= kLdsBytes, "the room fits");
     __shared__ BurstRoom<CAP> room;
@@ -174,11 +187,14 @@ __global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* 
 #pragma unroll
         for (int w = 0; w < W; ++w) *reinterpret_cast<u32x2*>(T + w * kRowStride + 8 * lane) = x[w];
     };
-    auto consume = [&]() {
+    auto nothing = [](auto) {};
+    constexpr int kSteps = kQuads ? 8 : 512 / (16 * (kBlocks ? 4 : GT::SLOTS));   // of consume
+    // `beside(step)` is vector work that the matrix instructions of a step need not wait for
+    auto consume = [&](auto&& beside) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the panel is written before any lane reads it
         if constexpr (kQuads) {
-#pragma unroll
-            for (int m = 0; m < 512 / 256; ++m) {   // 64 elements of every row: 4 per lane, 16 lanes to a row
+            static_for<0, 512 / 256>([&](auto mc) {   // 64 elements of every row: 4 per lane, 16 lanes to a row
+                constexpr int m = decltype(mc)::value;
                 f32x4 y[kGroups];
 #pragma unroll
                 for (int a = 0; a < kGroups; ++a)
@@ -193,8 +209,9 @@ __global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* 
                             quad[e] = __builtin_amdgcn_mfma_f32_4x4x1f32(y[A][J], y[B][J], quad[e], 0, 0, 0);
                         });
                     });
+                    beside(std::integral_constant<int, 4 * m + J>{});
                 });
-            }
+            });
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             return;
         }
@@ -214,44 +231,47 @@ __global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* 
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             return;
         }
-        constexpr int kReads = 512 / (16 * GT::SLOTS);
-#pragma unroll
-        for (int m = 0; m < kReads; ++m) {
-            const unsigned char* src = my_row + 16 * GT::SLOTS * m;
+        typedef typename std::conditional<BF, bf16x8, f32x4>::type frag_t;
+        frag_t y = *reinterpret_cast<const frag_t*>(my_row);
+        static_for<0, kSteps>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            frag_t yn = y;
+            if constexpr (m + 1 < kSteps) yn = *reinterpret_cast<const frag_t*>(my_row + 16 * GT::SLOTS * (m + 1));
             if constexpr (BF) {
-                const bf16x8 y = *reinterpret_cast<const bf16x8*>(src);
                 if (m & 1) accb = GT::mma(y, accb);
                 else acc = GT::mma(y, acc);
             } else {
-                const f32x4 y = *reinterpret_cast<const f32x4*>(src);
                 acc = GT::mma(y[0], acc);
                 accb = GT::mma(y[1], accb);
                 acc = GT::mma(y[2], acc);
                 accb = GT::mma(y[3], accb);
             }
-        }
+            beside(mc);
+            y = yn;
+        });
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // all reads returned before the panel is overwritten
     };
-    auto gram_512 = [&](const u32x2 (&x)[W]) {
+    auto gram_512 = [&](const u32x2 (&x)[W], auto&& beside) {
         // (kept apart from the update and from each other: mixed, the 24-row update spills vector registers, 578 against 542 us;
         // kept apart it spills none, the norms alone six)
         if constexpr (kQuads) __builtin_amdgcn_sched_barrier(0);
         stage(x);
-        consume();
+        consume(beside);
         if constexpr (kQuads) __builtin_amdgcn_sched_barrier(0);
     };
     // The Gram contribution of one tile: 4 elements per lane and row.
-    auto gram_tile = [&](const vec_t (&g)[W]) {
+    constexpr int kTileSteps = BF ? kSteps : 2 * kSteps;
+    auto gram_tile = [&](const vec_t (&g)[W], auto&& beside) {
         if constexpr (BF) {
-            gram_512(g);
+            gram_512(g, beside);
         } else {
             u32x2 h[W];
 #pragma unroll
             for (int w = 0; w < W; ++w) h[w] = u32x2{__float_as_uint(g[w][0]), __float_as_uint(g[w][1])};
-            gram_512(h);
+            gram_512(h, beside);
 #pragma unroll
             for (int w = 0; w < W; ++w) h[w] = u32x2{__float_as_uint(g[w][2]), __float_as_uint(g[w][3])};
-            gram_512(h);
+            gram_512(h, [&](auto mc) { beside(std::integral_constant<int, kSteps + decltype(mc)::value>{}); });
         }
     };
     // After every tile the matrix-core accumulators (256 products each by then) are folded into a
@@ -318,9 +338,18 @@ __global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* 
             if (publish) publish_chunk(x[0], publish, publish_bf16, c);
         }
     };
-    auto update_chunk = [&](int64_t t, const vec_t (&g)[W], f32x4 pq, f32x4 vq) {
+    auto keep = [&](const int64_t t, const f32x4 po, const f32x4 vo) {
         const int64_t c = t * kBlock + threadIdx.x;
-        if (!BURST && c >= nchunk) return;
+        if constexpr (BURST) {
+            burst.put(t, {po, vo}, write);
+        } else if (!kAlone || c < nchunk) {   // (Shared: only lanes of the shard get here)
+            store_state(po, params, c);
+            store_state(vo, momentum, c);
+            if (publish) publish_chunk(po, publish, publish_bf16, c);
+        }
+    };
+    auto update_chunk = [&](int64_t t, const vec_t (&g)[W], f32x4 pq, f32x4 vq, const AffCoef& coef) {
+        if (!kAlone && t * kBlock + threadIdx.x >= nchunk) return;
         f32x4 po, vo;
         static_for<0, 4>([&](auto kc) {
             constexpr int K = decltype(kc)::value;
@@ -330,17 +359,11 @@ __global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* 
                 ge[Wi] = R::template get<K>(g[Wi]);
             });
             float pe = pq[K], ve = vq[K];
-            aff_step<W>(pe, ve, ge, cf);
+            aff_step<W>(pe, ve, ge, coef);
             po[K] = pe;
             vo[K] = ve;
         });
-        if constexpr (BURST) {
-            burst.put(t, {po, vo}, write);
-        } else {
-            store_state(po, params, c);
-            store_state(vo, momentum, c);
-            if (publish) publish_chunk(po, publish, publish_bf16, c);
-        }
+        keep(t, po, vo);
     };
     auto fetch = [&](int64_t c, vec_t (&g)[W], f32x4& pq, f32x4& vq) {
         if (c < nchunk) {
@@ -358,7 +381,7 @@ __global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* 
     // The loads of the following tile are issued before this tile's update and Gram work where the Gram
     // phase is long enough to matter (not with 16 bf16 rows: 128 cycles a tile, and looking ahead measured
     // 2 % slower there) and the rows of two tiles fit in registers (up to 256 bytes per thread and tile).
-    constexpr bool kAhead = BURST || (sizeof(vec_t) * W <= 256 && (!BF || WIDE));
+    constexpr bool kAhead = sizeof(vec_t) * W <= 256 && (!BF || WIDE);   // (Shared)
     // 25 to 32 fp32 rows have no room for that, but once the second half of a tile is in the panel its registers are free, and the
     // following tile's loads go out before the matrix instructions that are left (48 updates, start -> now: 28 rows, update with norms
     // of 3 / 25.6 M elements 102 -> 95 / 646 -> 612 us, norms alone 486 -> 479; 32 rows 113 -> 107 / 719 -> 701, 545 -> 539).
@@ -367,7 +390,73 @@ __global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* 
     // (Tiles worked on as two halves of 2 elements per lane and row, all of the following half's loads ahead of the matrix
     // instructions but 8 bytes each: 24 / 32 rows 531 -> 539 / 713 -> 716, norms alone 2-8 % behind.)
     constexpr bool kEarly = !kAhead && !BF && W > 24;
-    if constexpr (kAhead) {
+    if constexpr (kAlone) {
+        struct Loaded {
+            vec_t g[W];
+            f32x4 p, v;
+        } set0, set1;
+        // (a lane beyond the end loads the last chunk again; its rows are cleared before they count, its results not written)
+        auto load = [&](const int64_t t, Loaded& x) {
+            const int64_t c = min(t * kBlock + (int64_t)threadIdx.x, nchunk - 1);
+#pragma unroll
+            for (int w = 0; w < W; ++w) x.g[w] = R::load(rows.p[w], c);
+            x.p = load_state(params, c);
+            x.v = load_state(momentum, c);
+        };
+        AffCoef in_vgpr = cf;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            asm volatile("" : "+v"(in_vgpr.b0[w]));
+            asm volatile("" : "+v"(in_vgpr.b1[w]));
+        }
+        // Row groups of four have no room for the update among their matrix instructions (20 rows: 960 against 941 us).
+        constexpr bool kMixed = !kQuads;
+        bool primed = false;
+        for_each_claimed_tile_ahead<2>(queue, ntile, claim, [&](auto sc, const int64_t t, const int64_t following) {
+            constexpr int SET = decltype(sc)::value;
+            Loaded& now = SET == 0 ? set0 : set1;
+            Loaded& next = SET == 0 ? set1 : set0;
+            const int64_t c = t * kBlock + threadIdx.x;
+            if (SET == 0 && !primed) {
+                load(t, now);
+                primed = true;
+            }
+            // This tile's loads are waited for before the following one's go out.  Left to the compiler, which cannot tell on this side of
+            // the branch whether those are under way, every second tile would wait for them too (16 bf16 rows, 340 M elements 2 678 us).
+            __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+            if (following >= 0) load(following, next);
+            vec_t(&g)[W] = now.g;
+            if (t == ntile - 1 && c >= nchunk) {
+#pragma unroll
+                for (int w = 0; w < W; ++w) g[w] = vec_t{};
+            }
+            if constexpr (kMixed) {
+                // aff_step, its 4 W steps shared out over those of the matrix work
+                f32x4 p = now.p, v = now.v, inc, nv;
+                gram_tile(g, [&](auto mc) {
+                    constexpr int S = decltype(mc)::value;
+                    static_for<S * 4 * W / kTileSteps, (S + 1) * 4 * W / kTileSteps>([&](auto ic) {
+                        constexpr int K = decltype(ic)::value / W, Wi = decltype(ic)::value % W;
+                        if constexpr (Wi == 0) {
+                            inc[K] = __builtin_fmaf(cf.m01, v[K], cf.dp * p[K]);
+                            nv[K] = __builtin_fmaf(cf.m11, v[K], cf.m10 * p[K]);
+                        }
+                        const float x = R::template get<K>(g[Wi]);
+                        inc[K] = __builtin_fmaf(in_vgpr.b0[Wi], x, inc[K]);
+                        nv[K] = __builtin_fmaf(in_vgpr.b1[Wi], x, nv[K]);
+                        if constexpr (Wi == W - 1) p[K] = p[K] + inc[K];
+                    });
+                    if constexpr (!BF) __builtin_amdgcn_sched_barrier(0);   // (bf16 rows, 8 or 16 matrix instructions a tile: better without)
+                });
+                fold();
+                keep(t, p, nv);
+            } else {
+                update_chunk(t, g, now.p, now.v, in_vgpr);
+                gram_tile(g, nothing);
+                fold();
+            }
+        });
+    } else if constexpr (kAhead) {
         vec_t gn[W];
         f32x4 pn = {0, 0, 0, 0}, vn = {0, 0, 0, 0};
         bool primed = false;
@@ -382,8 +471,8 @@ __global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* 
             for (int w = 0; w < W; ++w) g[w] = gn[w];
             const f32x4 pq = pn, vq = vn;
             if (following >= 0) fetch(following * kBlock + threadIdx.x, gn, pn, vn);
-            if constexpr (UPDATE) update_chunk(t, g, pq, vq);
-            gram_tile(g);
+            if constexpr (UPDATE) update_chunk(t, g, pq, vq, cf);
+            gram_tile(g, nothing);
             fold();
         });
     } else if constexpr (kEarly) {
@@ -396,16 +485,16 @@ __global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* 
                 fetch(c, g, pq, vq);
                 primed = true;
             }
-            if constexpr (UPDATE) update_chunk(t, g, pq, vq);
+            if constexpr (UPDATE) update_chunk(t, g, pq, vq, cf);
             u32x2 h[W];   // gram_tile, with the loads before its last step
 #pragma unroll
             for (int w = 0; w < W; ++w) h[w] = u32x2{__float_as_uint(g[w][0]), __float_as_uint(g[w][1])};
-            gram_512(h);
+            gram_512(h, nothing);
 #pragma unroll
             for (int w = 0; w < W; ++w) h[w] = u32x2{__float_as_uint(g[w][2]), __float_as_uint(g[w][3])};
             stage(h);
             if (following >= 0) fetch(following * kBlock + threadIdx.x, g, pq, vq);
-            consume();
+            consume(nothing);
             fold();
         });
     } else {
@@ -414,8 +503,8 @@ __global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* 
             vec_t g[W];
             f32x4 pq = {0, 0, 0, 0}, vq = {0, 0, 0, 0};
             fetch(c, g, pq, vq);
-            if constexpr (UPDATE) update_chunk(t, g, pq, vq);
-            gram_tile(g);
+            if constexpr (UPDATE) update_chunk(t, g, pq, vq, cf);
+            gram_tile(g, nothing);
             fold();
         });
     }
@@ -446,7 +535,7 @@ __global__ __launch_bounds__(kBlock, BURST ? 1 : 2) void aff_mfma_kernel(float* 
                 if (publish) publish_element(pj, publish, publish_bf16, j);
             }
         }
-        gram_tile(g);
+        gram_tile(g, nothing);
         fold();
     }
 
@@ -515,9 +604,11 @@ hipError_t launch_mfma_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_o
     const int64_t tiles = tiles_of(a.P);
     const bool one_wide = UPDATE && WIDE && kBf16 && a.rows_used >= 20 &&
                           tiles > 2 * (int64_t)num_cu * short_tiles_per_workgroup(kRowBytes + 32, Traffic::Update);
-    // 7 to 9 fp32 rows, update, from 16 Mi elements on: one too (three states in turn, 18.5 / 60 / 140 M elements, 7 rows 152 / 449 / 1030 -> 146 / 446 /
-    // 1026 us, 8 rows 166 / 488 / 1128 -> 156 / 478 / 1100, 9 rows 180 / 534 / 1238 -> 165 / 510 / 1172).
-    const bool one_light = UPDATE && !WIDE && !kBf16 && W >= 7 && tiles >= 16 * 1024;
+    // 8 and 9 fp32 rows, update, from 16 Mi elements on: one too (18 / 60 M elements, 8 rows 161.7 / 487 -> 152.9 / 470 us, 60 M, 9 rows 539 -> 507).  After
+    // a pause the first call is level (8 / 9 rows 548 / 597 -> 551 / 594 us), those of 3 to 15 ms later lose 4-8 %, see Form.  Not 7 rows: 448 against
+    // 457, the first call after a pause 549 against 576.
+    constexpr bool kLight = UPDATE && !WIDE && !kBf16 && (W == 8 || W == 9);
+    const bool one_light = kLight && tiles >= 16 * 1024;
     const int per_cu = (UPDATE && !WIDE && kRowBytes >= 160) || one_wide || one_light ? 1 : 2;
     if (!a.queue) return hipErrorInvalidValue;
     Geometry g = queue_geometry(num_cu, grid_cap, per_cu, kRowBytes + (UPDATE ? 32 : 0),
@@ -534,7 +625,7 @@ hipError_t launch_mfma_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_o
         if (a.burst) {
             const int grid = (int)std::min<int64_t>(std::min(num_cu, grid_cap), std::max<int64_t>(1, tiles));
             *grid_out = grid;
-            hipLaunchKernelGGL((aff_mfma_kernel<W, R, UPDATE, WIDE, true>), dim3(grid), dim3(kBlock), 0, s, a.params, a.momentum, a.rows,
+            hipLaunchKernelGGL((aff_mfma_kernel<W, R, UPDATE, WIDE, Form::Bursts>), dim3(grid), dim3(kBlock), 0, s, a.params, a.momentum, a.rows,
                                a.cf, a.P, a.head, grid, 0x7fffffff, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials,
                                TileSource{a.queue, nullptr, 0u}, a.burst,
                                burst_period(burst_tiles_beside_panel(kBf16, W), (kRowBytes + 64) * kBlock, grid, 0.9));
@@ -542,6 +633,9 @@ hipError_t launch_mfma_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_o
         }
     }
     *grid_out = g.grid;
+    if constexpr (kLight) {
+        if (one_light) kern = aff_mfma_kernel<W, R, UPDATE, WIDE, Form::Alone>;
+    }
     hipLaunchKernelGGL(kern, dim3(g.grid), dim3(kBlock), 0, s, a.params, a.momentum, a.rows, a.cf, a.P, a.head,
                        g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials,
                        TileSource{a.queue, nullptr, 0u}, g.claim, 0u);

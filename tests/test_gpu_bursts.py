@@ -69,6 +69,15 @@ def _same_bits(a, b):
     return torch.equal(a.view(as_int), b.view(as_int))
 
 
+def _norms64(W, rows, us):
+    r = torch.stack([x.double() for x in rows])
+    C = torch.zeros(us.U, W, dtype=torch.float64)
+    for u in range(us.U):
+        for k in range(us.offsets[u], us.offsets[u + 1]):
+            C[u, us.members[k]] = 1.0 / ((us.offsets[u + 1] - us.offsets[u]) * (1.0 + us.staleness[k]))
+    return sum((C.cuda() @ part).square().sum(1) for part in r.split(1 << 22, dim=1)).sqrt()
+
+
 # threshold None: the shortest shards of a row count and, with up to 11 bf16 rows, the longest
 @pytest.mark.parametrize("W,dtype,P,threshold,offset,out", [
     (14, "f32", 4099, 1, 0, None), (16, "f32", 256 * 1024 + 5, 1, 1, torch.bfloat16), (20, "f32", 511 * 1024 + 1, 1, 0, torch.float32),
@@ -85,13 +94,22 @@ def test_update_with_norms_in_bursts(W, dtype, P, threshold, offset, out):
     assert all(_same_bits(a, b) for a, b in zip(got, fixed))
     # the same sums tile by tile, in double from there on: only their order differs
     assert float(((n - m) / m).abs().max()) <= 2.0 ** -23
-    r = torch.stack([x.double() for x in rows])
-    C = torch.zeros(us.U, W, dtype=torch.float64)
-    for u in range(us.U):
-        for k in range(us.offsets[u], us.offsets[u + 1]):
-            C[u, us.members[k]] = 1.0 / ((us.offsets[u + 1] - us.offsets[u]) * (1.0 + us.staleness[k]))
-    want = sum((C.cuda() @ part).square().sum(1) for part in r.split(1 << 22, dim=1)).sqrt()
+    want = _norms64(W, rows, us)
     assert float(((n.double() - want) / want).abs().max()) <= 1e-6   # (rows that are not anti-correlated, see star.h)
+
+
+# 8 and 9 fp32 rows on long shards: one workgroup per unit that writes as it goes; the shortest such shard, the one below, remainders
+@pytest.mark.parametrize("W,P,offset,out", [(8, 16 << 20, 0, None), (9, (16 << 20) - 1024, 0, None), (9, (16 << 20) + 1, 0, torch.bfloat16),
+                                            (9, (17 << 20) + 1023, 3, None), (8, (16 << 20) + 517, 1, torch.float32)])
+def test_update_with_norms_by_one_workgroup_a_unit(W, P, offset, out):
+    n = torch.full((12,), -1.0, device="cuda")
+    got, (p, v, rows, us, _) = _call(W, P, "f32", offset, out, None, norms=n)
+    choice = star.star_plan_choice(P, W, "f32", us, lr=0.1, momentum_coef=0.9, wmode="stale", want_norms=True)
+    assert choice["kernel"] == star.KERNEL_AFFINE_MFMA
+    plain = _call(W, P, "f32", offset, out, 1 << 62)[0]   # without norms: the same arithmetic in another kernel
+    assert all(_same_bits(a, b) for a, b in zip(got, plain))
+    want = _norms64(W, rows, us)
+    assert float(((n.double() - want) / want).abs().max()) <= 1e-6
 
 
 # threshold None: the shortest shard of a row count; 1: the queue whatever the length

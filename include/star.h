@@ -48,9 +48,12 @@
  *     one per call that needs tables, partial sums or the tile queue, each
  *     guarded by a word in pinned memory that its last kernel writes (or by
  *     an event); the ninth such call blocks until the work of the call that
- *     used its slot eight calls earlier has finished; (2) the first call that needs a larger workspace than any
- *     before it allocates device and pinned memory (hipMalloc, hipHostMalloc),
- *     which synchronises the device.  star_group_update_noalloc does neither.
+ *     used its slot eight calls earlier has finished, or returns
+ *     STAR_ERR_DEVICE when that call's stream or device reports an error or
+ *     has gone idle without it; (2) the first call that needs a larger
+ *     workspace than any before it allocates device and pinned memory
+ *     (hipMalloc, hipHostMalloc), which synchronises the device.
+ *     star_group_update_noalloc does neither.
  *   - The return value is a star_status.  Nothing is thrown, nothing aborts.
  *     All argument checks precede the first enqueue: on a status other than
  *     STAR_OK and STAR_ERR_DEVICE no device memory has been modified.
@@ -63,8 +66,8 @@
  *     that are off by different amounts are read at unaligned addresses.
  *   - The library keeps a small internal workspace (coefficient tables,
  *     per-block norm partials, 256 bytes of counters per slot), created on
- *     first use, released by star_shutdown().  Calls may come from several
- *     host threads.
+ *     first use, released by star_shutdown(), which has to come before a
+ *     hipDeviceReset.  Calls may come from several host threads.
  */
 #ifndef STAR_H
 #define STAR_H

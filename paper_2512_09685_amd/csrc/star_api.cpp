@@ -16,6 +16,7 @@
 #include "star.h"
 #include "star_kernels.h"
 #include "star_plan.h"
+#include "star_wait.h"
 
 namespace {
 
@@ -136,6 +137,7 @@ struct Slot {
     uint32_t* word_dev = nullptr;       // the same memory as the device addresses it
     uint32_t seq = 0;                   // number of the slot's last call
     hipEvent_t done = nullptr;
+    hipStream_t stream = nullptr;       // the last call's, while `pending` is Word
     Wait pending = Wait::Nothing;       // what says that the slot's last call has run
 };
 
@@ -171,16 +173,39 @@ bool slot_idle(const Slot& s) {
     return s.pending == Wait::Nothing || hipEventQuery(s.done) == hipSuccess;
 }
 
-// Returns once the slot's last call has run.
+// How the slot's last stream is doing.  Asked seldom, and only by a call that has to wait: an event would tell, but costs every call (above).
+star::Ask ask_stream(const Slot& s) {
+    int current = s.device;
+    if (hipGetDevice(&current) != hipSuccess || (current != s.device && hipSetDevice(s.device) != hipSuccess)) {
+        (void)hipGetLastError();
+        return star::Ask::Failed;
+    }
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // (a question asked while another stream is captured is no part of that)
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(s.stream, &capture);
+    star::Ask a = star::Ask::Unknown;   // being captured, or destroyed by the caller, perhaps with this work still to run
+    if (e == hipSuccess && capture == hipStreamCaptureStatusNone) {
+        e = hipStreamQuery(s.stream);
+        if (e == hipSuccess) a = star::Ask::Idle;
+        else if (e == hipErrorNotReady) a = star::Ask::Busy;
+        else if (e != hipErrorContextIsDestroyed && e != hipErrorInvalidHandle) a = star::Ask::Failed;
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) (void)hipGetLastError();   // (not an error of the launches to come)
+    if (current != s.device) (void)hipSetDevice(current);
+    return a;
+}
+
+// Returns once the slot's last call has run, or with an error if that cannot be expected any more (the slot then stays as it is).
 hipError_t wait_for(Slot& s) {
     if (s.pending == Wait::Event) {
         const hipError_t e = hipEventSynchronize(s.done);
         if (e != hipSuccess) return e;
     } else if (s.pending == Wait::Word) {
-        for (int tries = 0; !word_written(s); ++tries) {
-            if (tries < 20000) continue;   // up to about 0.1 ms: eight calls ahead of a short shard's kernels
-            std::this_thread::sleep_for(std::chrono::microseconds(10));
-        }
+        const star::WaitEnd end = star::wait_for_word([&] { return word_written(s); }, [&] { return ask_stream(s); },
+                                                      [] { std::this_thread::sleep_for(std::chrono::microseconds(10)); });
+        if (end != star::WaitEnd::Written) return end == star::WaitEnd::Failed ? hipErrorLaunchFailure : hipErrorUnknown;
     }
     s.pending = Wait::Nothing;
     return hipSuccess;
@@ -271,13 +296,18 @@ struct SlotRelease {
     SlotRelease& operator=(const SlotRelease&) = delete;
     ~SlotRelease() {
         if (!slot) return;
-        if (told) slot->pending = Wait::Word;
-        else if (hipEventRecord(slot->done, stream) == hipSuccess) slot->pending = Wait::Event;
+        if (told) {
+            slot->pending = Wait::Word;
+            slot->stream = stream;
+        } else if (hipEventRecord(slot->done, stream) == hipSuccess) {
+            slot->pending = Wait::Event;
+        }
     }
-    // What the last launch is handed: nothing without a slot, or where the launches are only recorded.
+    // What the last launch is handed: nothing without a slot, where the launches are only recorded, or on the stream whose handle means
+    // another one to every thread (see ask_stream).
     star::Finished finished() const {
         star::Finished f;
-        if (!slot) return f;
+        if (!slot || stream == hipStreamPerThread) return f;
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
             (void)hipGetLastError();   // (not an error of the launches to come)

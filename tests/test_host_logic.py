@@ -527,6 +527,19 @@ def test_host_planner_and_selector_under_sanitizers(tmp_path):
     assert "plans accepted" in r.stdout and "selector calls accepted 20000" in r.stdout
 
 
+def test_wait_for_a_workspace_slot_ends(tmp_path):
+    """The wait for the word that a call's last kernel writes, with a stubbed word, stream and clock: it ends when the word is
+    there, and with an error when the stream has failed or has nobody left to write it."""
+    import subprocess
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    exe = tmp_path / "wait_check"
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(root, "paper_2512_09685_amd", "csrc"),
+                        os.path.join(root, "tests", "wait_check.cpp"), "-o", str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and "10 checks passed" in r.stdout, (r.returncode, r.stdout, r.stderr)
+
+
 def test_plan_choice_is_consistent_over_random_calls():
     """star_plan_choice over a few thousand random calls (streams, row counts, dtypes, shard lengths, norms,
     weightings with and without negative coefficients, options): whatever rule fires, the answer hangs together."""

@@ -221,15 +221,19 @@ __device__ __forceinline__ FirstClaim first_claim(const int claim, const int64_t
 }
 
 // What a workgroup does that uses its launch's workspace slot no more (one thread; the queue's last one to leave knows without a ticket that it is).
+// The last ticket puts the counter back by itself: nothing has to reach the memory before the word, for which whoever waits for the call waits.
 __device__ __forceinline__ void tell(uint32_t* word, const uint32_t seq) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // tickets and queue are back at zero
     __hip_atomic_store(word, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 __device__ __forceinline__ void finished(const Finished& f) {
     if (!f.word) return;
-    if (__hip_atomic_fetch_add(f.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 != gridDim.x) return;
-    __hip_atomic_store(f.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (gridDim.x > 1 && atomicInc(f.ticket, gridDim.x - 1) + 1 != gridDim.x) return;
     tell(f.word, f.seq);
+}
+// The same behind stores to the slot.
+__device__ __forceinline__ void tell_behind(uint32_t* word, const uint32_t seq) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // tickets and queue are back at zero
+    tell(word, seq);
 }
 __device__ __forceinline__ void leave(const TileSource& src) {
     // this workgroup's claims have all returned (their values were used), so when the count reaches the grid size nobody touches
@@ -238,7 +242,7 @@ __device__ __forceinline__ void leave(const TileSource& src) {
     if (left + 1 == gridDim.x) {
         atomicExch(&src.queue->next, 0ull);
         atomicExch(&src.queue->done, 0u);
-        if (src.word) tell(src.word, src.seq);
+        if (src.word) tell_behind(src.word, src.seq);
     }
 }
 

@@ -508,7 +508,8 @@ __global__ __launch_bounds__(kBlock) void seq_kernel(float* __restrict__ params,
 }
 
 // ================================================================= finishing kernels
-// They last a few microseconds, nearly all of it latency: of the launch, of one read, of the ticket.  A wave takes one sum, so that a launch
+// They last a few microseconds, nearly all of it latency: of the launch, of one read, of the ticket and the word (together 0.5 to 1 us of a call
+// that is waited for, 0.3 us more while the last workgroup put the ticket back with a store).  A wave takes one sum of partials, so that a launch
 // has a quarter of the workgroups that one sum a workgroup would need, and its tickets (one a workgroup, 12 ns each at one place) as many fewer.
 constexpr int kWaves = kBlock / 64;
 inline dim3 finishing_grid(int n) { return dim3((n + kWaves - 1) / kWaves); }
@@ -548,47 +549,46 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(const double* __restrict
     finished_all(done);
 }
 
-// One wave per update u: n_u^2 = sum over pairs (a <= b) of c_a c_b Gamma_ab (off-diagonal pairs twice), each lane every 64th pair, then a
-// fixed-order sum in double.
+// One workgroup per update u: n_u^2 = sum over pairs (a <= b) of c_a c_b Gamma_ab (off-diagonal pairs twice), each thread one pair or
+// three, then a fixed-order sum in double.  (A wave per update, for a quarter of the tickets, has three to nine pairs a lane one behind the
+// other: 0.3 M elements, update with norms, a call that is waited for, 16 fp32 rows, 16 updates 31.7 against 30.2 us, 32 bf16 rows, 64 updates
+// 44.0 against 42.2, back to back 18.2 against 16.9 and 26.0 against 23.7; 16 bf16 rows, 256 updates 39.3 against 39.8 and 23.1 level.)
 __global__ __launch_bounds__(kBlock) void gram_norms_kernel(const double* __restrict__ gamma,
                                                             const double* __restrict__ coef, const int U,
                                                             const int W, float* __restrict__ norms_out,
                                                             const Finished done) {
-    const int u = blockIdx.x * kWaves + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    __shared__ double s_wave[kWaves];
+    const int u = blockIdx.x;
+    const double* c = coef + (int64_t)u * W;
     const int ng = W * (W + 1) / 2;
-    if (u < U) {
-        // one read of the coefficients (they may lie in the host's memory) and all of Gamma, requested together
-        constexpr int N = (STAR_MAX_WORKERS * (STAR_MAX_WORKERS + 1) / 2 + 63) / 64;
-        const double c = lane < W ? coef[(int64_t)u * W + lane] : 0.0;
-        double g[N];
-#pragma unroll
-        for (int k = 0; k < N; ++k) g[k] = 64 * k + lane < ng ? gamma[64 * k + lane] : 0.0;
-        double s = 0.0;
-        int a = 0, rem = lane;
-#pragma unroll
-        for (int k = 0; k < N; ++k) {
-            if (64 * k < ng) {
-                while (a < W && rem >= W - a) {
-                    rem -= W - a;
-                    ++a;
-                }
-                const int b = a + rem;
-                const double ca = __shfl(c, a & 63), cb = __shfl(c, b & 63);
-                // rows outside the group take no part: a non-finite entry of a worker that is not a member (0 * inf)
-                // must not reach this group's norm
-                if (a < W && ca != 0.0 && cb != 0.0) {
-                    const double t = ca * cb * g[k];
-                    s += (a == b) ? t : 2.0 * t;
-                }
-                rem += 64;
-            }
+    double s = 0.0;
+    for (int e = threadIdx.x; e < ng; e += kBlock) {
+        const double g = gamma[e];   // requested together with the coefficients: one memory latency, not two
+        int a = 0, rem = e;
+        while (rem >= W - a) {
+            rem -= W - a;
+            ++a;
         }
-        s = wave_sum_to_lane63(s);
-        // a tiny negative sum (rounding of a quadratic form that is zero) gives 0; a non-finite one stays
-        // non-finite, so that a bad gradient report shows in the norms of the groups it is part of
-        if (lane == 63) norms_out[u] = (float)sqrt(s < 0.0 && s > -1e300 ? 0.0 : s);
+        const int b = a + rem;
+        const double ca = c[a], cb = c[b];
+        // rows outside the group take no part: a non-finite entry of a worker that is not a member (0 * inf)
+        // must not reach this group's norm
+        if (ca == 0.0 || cb == 0.0) continue;
+        const double t = ca * cb * g;
+        s += (a == b) ? t : 2.0 * t;
     }
-    finished_all(done);
+    s = wave_sum_to_lane63(s);
+    if ((threadIdx.x & 63) == 63) s_wave[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 64) finished(done);   // everyone has its pairs (another wave than the one that ends the sum)
+    // a tiny negative sum (rounding of a quadratic form that is zero) gives 0; a non-finite one stays
+    // non-finite, so that a bad gradient report shows in the norms of the groups it is part of
+    if (threadIdx.x == 0 && u < U) {
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < kWaves; ++q) t += s_wave[q];
+        norms_out[u] = (float)sqrt(t < 0.0 && t > -1e300 ? 0.0 : t);
+    }
 }
 
 // Both finishing steps in one launch, for the Gram matrix of up to kFinishRows rows on a short shard, where a call is bound by its
@@ -645,7 +645,7 @@ __global__ __launch_bounds__(kBlock) void gram_finish_kernel(const double* __res
     }
     if (!done.word) return;
     __syncthreads();   // everyone has its coefficients
-    if (threadIdx.x == 0) tell(done.word, done.seq);
+    if (threadIdx.x == 0) tell_behind(done.word, done.seq);
 }
 
 // The last launch of the Gram matrix: entry e = (i, j), i <= j < W, of the packed triangle over Wp >= W rows (the kernels' padded
@@ -852,7 +852,7 @@ hipError_t launch_reduce(const double* partials, int n_out, int grid, double* su
 hipError_t launch_gram_norms(const double* gamma, const double* coef, int U, int Wp, float* norms_out,
                              const Finished& done, hipStream_t s) {
     if (U < 1) return hipSuccess;
-    hipLaunchKernelGGL(gram_norms_kernel, finishing_grid(U), dim3(kBlock), 0, s, gamma, coef, U, Wp,
+    hipLaunchKernelGGL(gram_norms_kernel, dim3(U), dim3(kBlock), 0, s, gamma, coef, U, Wp,
                        norms_out, done);
     return hipGetLastError();
 }

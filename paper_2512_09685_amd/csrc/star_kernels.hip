@@ -17,7 +17,8 @@
 //   seq_kernel  walks the updates one by one with the W gradients of the
 //               element held in registers; group tables sit in LDS.
 //   aff_kernel  applies the U updates as one affine map of (p, v, g_0..g_W-1)
-//               whose coefficients the host composed in double precision.
+//               whose coefficients the host composed in double precision; on many rows
+//               aff_once_kernel and aff_burst_kernel do, on short and on long shards.
 // Per-group norms: seq_kernel accumulates gbar_u^2 per thread (LDS slots; direct norms
 // without an update have a kernel of their own, star_norm_kernels.hip),
 // aff_kernel accumulates the pairwise products of the rows (Gram matrix);
@@ -150,10 +151,10 @@ __global__ __launch_bounds__(kBlock) void aff_kernel(float* __restrict__ params,
         }
     };
     bool queued = false;
-    if constexpr (kFew || (!GRAM && !bursts(W, std::is_same<R, RowF32>::value))) {
+    if constexpr (kFew || !GRAM) {
         // without the register-heavy Gram accumulators the kernel affords a second copy of the chunk
-        // code: tiles from the queue for long shards, a fixed assignment for short ones (heavy rows: aff_burst_kernel has the
-        // long shards)
+        // code: tiles from the queue for long shards, a fixed assignment for short ones (heavy rows have kernels of their own for
+        // the two)
         if (claim > 0) {
             queued = true;
             if constexpr (KCH > 1) {
@@ -248,6 +249,87 @@ __global__ __launch_bounds__(kBlock) void aff_kernel(float* __restrict__ params,
                 }
             }
         }
+    }
+}
+
+// The collapsed update without norms on short shards of heavy rows, a tile a workgroup.  Such a launch lasts little longer than a workgroup takes to
+// read its arguments and then its rows, and 32 rows have 64 registers' worth of pointers and 68 coefficients, more than a wave has scalar
+// registers: left to itself the compiler fetches all of them before the first row and keeps what does not fit in the lanes of a vector register
+// (four to seven rounds of fetches one behind the other, 100 to 390 moves).  So the arguments are read where they lie, the coefficients
+// when the rows have been requested.  0.63 M elements, aff_kernel (with / without the queue's code) -> this one: 24 / 28 / 32 bf16 rows 8.4 / 9.4 / 10.4
+// and 8.7 / 9.8 / 11.0 -> 7.2 / 7.6 / 8.3 us, 24 / 32 fp32 rows 12.6 / 16.6 and 12.7 / 17.5 -> 11.1 / 14.6; 2 M, 32 bf16 / fp32 rows 28.8 / 51.7 and 29.3 / 51.6 -> 26.8 /
+// 49.0; 10 to 16 rows 0.3 us ahead.
+struct OnceArgs {
+    float* params;
+    float* momentum;
+    RowPtrs rows;
+    AffCoef cf;
+    int64_t P;
+    void* publish;           // device copy of the new params, or null
+    int32_t publish_bf16;
+    int32_t head;            // see rest_element
+};
+template <int W, class R>
+__global__ __launch_bounds__(kBlock) void aff_once_kernel(const OnceArgs) {
+    typedef const __attribute__((address_space(4))) OnceArgs* args_t;   // (its only argument: it lies where the segment begins)
+    const args_t args = (args_t)__builtin_amdgcn_kernarg_segment_ptr();
+    // The same address, of which the compiler does not know that it is: what is read there is not read before what stands above.
+    auto from_now_on = [&]() {
+        args_t a = args;
+        asm volatile("" : "+s"(a)::"memory");
+        return a;
+    };
+    auto coefficients = [](const args_t args) {
+        AffCoef cf;
+        cf.dp = args->cf.dp;
+        cf.m01 = args->cf.m01;
+        cf.m10 = args->cf.m10;
+        cf.m11 = args->cf.m11;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            cf.b0[w] = args->cf.b0[w];
+            cf.b1[w] = args->cf.b1[w];
+        }
+        return cf;
+    };
+    const int64_t nchunk = args->P / 4;
+    const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (c < nchunk) {
+        typename R::vec g[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) g[w] = R::load(args->rows.p[w], c);
+        f32x4 p = load_state(args->params, c), v = load_state(args->momentum, c);
+        const args_t then = from_now_on();
+        const AffCoef cf = coefficients(then);
+        static_for<0, 4>([&](auto kc) {
+            constexpr int K = decltype(kc)::value;
+            float ge[W];
+            static_for<0, W>([&](auto wc) {
+                constexpr int Wi = decltype(wc)::value;
+                ge[Wi] = R::template get<K>(g[Wi]);
+            });
+            float pe = p[K], ve = v[K];
+            aff_step<W>(pe, ve, ge, cf);
+            p[K] = pe;
+            v[K] = ve;
+        });
+        store_state(p, then->params, c);
+        store_state(v, then->momentum, c);
+        if (then->publish) publish_chunk(p, then->publish, then->publish_bf16, c);
+    }
+    // elements not covered by whole chunks: same arithmetic, one element at a time (at most 66, the first workgroup's)
+    if (blockIdx.x != 0) return;
+    const args_t rest = from_now_on();
+    if ((int64_t)threadIdx.x < rest_count(rest->head, rest->P, nchunk)) {
+        const int64_t j = rest_element(threadIdx.x, rest->head, nchunk);
+        float ge[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) ge[w] = R::load1(rest->rows.p[w], j);
+        float pe = rest->params[j], ve = rest->momentum[j];
+        aff_step<W>(pe, ve, ge, coefficients(rest));
+        rest->params[j] = pe;
+        rest->momentum[j] = ve;
+        if (rest->publish) publish_element(pe, rest->publish, rest->publish_bf16, j);
     }
 }
 
@@ -758,23 +840,30 @@ hipError_t launch_aff_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_ou
             if (e == hipSuccess && a.told) *a.told = queue_tells(a.done, grid, a.burst, tiles_of(a.P));
             return e;
         }
+        const int64_t tiles = std::max<int64_t>(1, tiles_of(a.P));
+        if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+        const OnceArgs once = {a.params, a.momentum, a.rows, a.cf, a.P, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.head};
+        *grid_out = (int)tiles;
+        hipLaunchKernelGGL((aff_once_kernel<W, R>), dim3((unsigned)tiles), dim3(kBlock), 0, s, once);
+        return hipGetLastError();
+    } else {
+        auto kern = aff_kernel<W, R, UPDATE, GRAM>;
+        // long shards without the Gram accumulators: long-lived workgroups, tiles from the queue
+        const int thread_bytes = W * (int)sizeof(typename R::vec) + (UPDATE ? 32 : 0);
+        Geometry g = queued ? queue_geometry(num_cu, grid_cap, queue_workgroups_per_cu(thread_bytes, UPDATE), thread_bytes,
+                                             UPDATE ? Traffic::Update : Traffic::ReadOnly)
+                            : pick_geometry(a.P, GRAM, num_cu, grid_cap, 256, 1,
+                                            sum_workgroups_per_cu(thread_bytes, UPDATE, a.P, num_cu));
+        if (a.copy.n && queued) return hipErrorInvalidValue;   // (every workgroup of a queue's launch takes tiles)
+        const Finished done = GRAM ? Finished() : a.done;
+        *grid_out = g.grid;
+        hipLaunchKernelGGL(kern, dim3(g.grid + (GRAM && a.copy.n ? 1 : 0)), dim3(kBlock), 0, s, a.params, a.momentum, a.rows, a.cf, a.P, a.head,
+                           g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials,
+                           tile_source(a.queue, done), g.claim, a.copy);
+        const hipError_t e = hipGetLastError();
+        if (e == hipSuccess && a.told) *a.told = queued && queue_tells(done, g.grid, g.claim, tiles_of(a.P));
+        return e;
     }
-    auto kern = aff_kernel<W, R, UPDATE, GRAM>;
-    // long shards without the Gram accumulators: long-lived workgroups, tiles from the queue
-    const int thread_bytes = W * (int)sizeof(typename R::vec) + (UPDATE ? 32 : 0);
-    Geometry g = queued ? queue_geometry(num_cu, grid_cap, queue_workgroups_per_cu(thread_bytes, UPDATE), thread_bytes,
-                                         UPDATE ? Traffic::Update : Traffic::ReadOnly)
-                        : pick_geometry(a.P, GRAM, num_cu, grid_cap, 256, 1,
-                                        sum_workgroups_per_cu(thread_bytes, UPDATE, a.P, num_cu));
-    if (a.copy.n && queued) return hipErrorInvalidValue;   // (every workgroup of a queue's launch takes tiles)
-    const Finished done = GRAM ? Finished() : a.done;
-    *grid_out = g.grid;
-    hipLaunchKernelGGL(kern, dim3(g.grid + (GRAM && a.copy.n ? 1 : 0)), dim3(kBlock), 0, s, a.params, a.momentum, a.rows, a.cf, a.P, a.head,
-                       g.span_g, g.span_k, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials,
-                       tile_source(a.queue, done), g.claim, a.copy);
-    const hipError_t e = hipGetLastError();
-    if (e == hipSuccess && a.told) *a.told = queued && queue_tells(done, g.grid, g.claim, tiles_of(a.P));
-    return e;
 }
 
 template <int W>

@@ -40,7 +40,9 @@ INST_COUNTERS = ["SQ_WAVES", "SQ_INSTS_VALU", "SQ_INSTS_VALU_FMA_F32", "SQ_INSTS
 
 
 def short(name: str) -> str:
-    return re.sub(r"\(.*", "", name).replace("void ", "")
+    """The kernel's name and template arguments (which may hold parentheses of their own: `(star::Form)2`)."""
+    name = name.replace("void ", "")
+    return re.sub(r">\(.*", ">", name) if re.match(r"[^(]*<", name) else re.sub(r"\(.*", "", name)
 
 
 def bench_line(log_path: str) -> dict:

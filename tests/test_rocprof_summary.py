@@ -45,3 +45,10 @@ def test_counter_values_group_by_kernel(tmp_path):
     v = rs.counter_values(str(p), "FETCH_SIZE")
     assert v["star::aff_kernel<8, star::RowF32, true, false>"] == [10.0, 12.0]
     assert v["__amd_rocclr_copyBuffer"] == [524307.8]
+
+
+def test_short_names_keep_their_template_arguments():
+    assert rs.short("void star::aff_mfma_kernel<16, star::RowF32, true, false, (star::Form)2>(float*, float*)") == \
+        "star::aff_mfma_kernel<16, star::RowF32, true, false, (star::Form)2>"
+    assert rs.short("star::reduce_kernel(double const*, int)") == "star::reduce_kernel"
+    assert rs.short("void f(std::vector<int> (*)(int))") == "f"

@@ -42,9 +42,10 @@ struct TileSource {
 };
 inline TileSource tile_source(TileQueue* q, const Finished& f) { return TileSource{q, f.word, f.seq}; }
 
-// Tiles handed to a workgroup per claim.  Never a power of two: with 2, 4 or 8 tiles every claim starts
+// Tiles an update hands to a workgroup per claim.  Not a power of two: with 2, 4 or 8 tiles every claim starts
 // on an 8/16/32 KB boundary of every row, all workgroups then hit the same memory channels at the same
-// moments, and the update measured 5-8 % slower than with 3.  Light tiles (few rows: a thread moves less
+// moments, and the update measured 5-8 % slower than with 3 (only the heaviest tiles, of which 3 are too long a claim, take 2, and
+// launches that read take what their bytes ask for, up to 16: see queue_claim).  Light tiles (few rows: a thread moves less
 // than 96 bytes per tile, state included) are finished so quickly that claims of 3 come faster than the
 // one counter serves them (it sustains about 80 M atomics/s); 5 measured 15-40 % faster there (one fp32
 // row and the state: 0.37 against 0.48 ms on 110 M elements), 6, 7 and 9 slower again.
@@ -228,7 +229,7 @@ inline int burst_claim(int Wp, bool f32_rows, int64_t P) {
 //               540 / 691 against 551 / 718).
 //   bf16 rows   40 / 200 M, 12 rows 273 / 1281 -> 267 / 1264, 16 rows 329 / 1560 -> 313 / 1485; 80 M, 24 / 28 / 32 rows 889 / 1004 / 1142 -> 856 /
 //               962 / 1068, 17 M 205 / 232 / 263 -> 199 / 226 / 247 (12 M: 150 / 169 / 192 against 155 / 176 / 197); 5 / 8 M, 8 / 12 / 16 rows 41 / 50 /
-//               58 and 63 / 76 / 82 -> 40 / 47 / 55 and 53 / 64 / 77 (3 M level); 7 to 11 rows beyond that: level at 17 M, 80 M, 8 / 11 rows 431 /
+//               58 and 63 / 76 / 82 -> 40 / 47 / 55 and 53 / 64 / 77 (3 M level; 7 and 8 rows are in vector registers from 8 Mi to 16 Mi); 7 to 11 rows beyond that: level at 17 M, 80 M, 8 / 11 rows 431 /
 //               498 against 436 / 498.  20 rows: 25.6 M 253 against 257.
 //   tiles per claim   140 M, 16 fp32 rows, 5 / 6: 1771 / 1788; 200 M, 12 / 16 bf16 rows 1285 / 1264, 1492 / 1485; 25.6 M, 16 rows 208 / 208; 150 M,
 //                     32 rows, 5 / 7 / 9: 2004 / 1966 / 1941, 25.6 M 363 / 359 / 354.

@@ -3,7 +3,7 @@
 State (params, momentum).  Every element is independent, so the oracle can be run on any subset.  The
 checked subset holds one element of every block of 512 consecutive elements, at a seeded offset
 inside the block, plus the first 2048 elements and the ragged tail: every tile a workgroup can claim
-from the work queue (1024 elements, 512 for the half-size workgroups of the 32-row kernels) has
+from the work queue (1024 elements; 256 of every wave) has two
 elements in it, so a tile that is skipped, done twice or done with another tile's rows shows up.  On
 tiny and resnet50 the oracle runs over the whole array.
 

@@ -92,7 +92,13 @@ def kernel_label(star, wl, us, op):
     row = "RowF32" if c["grad_dtype"] == 0 else "RowBf16x4"
     what = "norms only" if op == "norms" else ("update+norms" if wl.norms else "update")
     order = "queue order" if c["queue_order"] else "fixed assignment"
-    return f"{KERNEL_NAMES[c['kernel']]}<{c['rows_padded']}, {row}> {what}, {order}", c
+    name = KERNEL_NAMES[c["kernel"]]
+    if op != "norms" and star.star_plan_bursts(wl.P, wl.W, wl.grad_dtype, us, lr=wl.lr, momentum_coef=wl.momentum,
+                                               weight_decay=wl.weight_decay, wmode=wl.wmode, want_norms=wl.norms,
+                                               kernel=KERNEL_OPTION):
+        name = "aff_burst_kernel" if name == "aff_kernel" else name
+        order += ", written in bursts"
+    return f"{name}<{c['rows_padded']}, {row}> {what}, {order}", c
 
 
 def measure(wl, steps, warmup, torch, star, workloads, op="update"):
@@ -191,7 +197,8 @@ def measure(wl, steps, warmup, torch, star, workloads, op="update"):
     if op == "reduce":
         bytes_per_call = wl.P * (wl.W * wl.grad_bytes + wl.grad_bytes)      # W rows read, one output row written
         n_updates = 1
-        label = f"reduce_rows_kernel<{wl.W}, {'RowF32' if wl.grad_dtype == 'f32' else 'RowBf16x4'}>"
+        bursts = star.star_plan_reduce_bursts(wl.P, wl.W, wl.grad_dtype, wl.grad_dtype, full, wmode=wl.wmode, want_norms=wl.norms)
+        label = f"{'mean_burst_kernel' if bursts else 'reduce_rows_kernel'}<{wl.W}, {'RowF32' if wl.grad_dtype == 'f32' else 'RowBf16x4'}>"
         fs, fa = float(wl.W + (1 if wl.norms else 0)), None
     if op == "norms":
         bytes_per_call = int(wl.P * n_used * wl.grad_bytes)                 # the referenced rows, read once

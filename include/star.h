@@ -146,14 +146,19 @@ typedef struct {
     int64_t queue_threshold; /* shards of at least this many elements are processed by long-lived
                                 workgroups that claim tiles (1024 consecutive elements of every
                                 buffer) in address order from a work queue; shorter ones get a fixed
-                                assignment, which starts faster.  0 = default (updates: 16 Mi elements
-                                with fp32 rows, 64 Mi with up to 4 of them; with bf16 rows 64 Mi, 96 Mi
-                                with up to 12 of them, 128 Mi with up to 4; updates with norms on up to
-                                6 rows: 16 Mi with bf16 rows, 32 / 64 / 128 Mi with 1 / 2 / 3-6 fp32 rows; norms
-                                and Gram matrix alone 16 Mi, direct sums alone never; the aggregation 64 Mi, and never with up
+                                assignment, which starts faster.  0 = default (updates without norms on
+                                10 and more fp32 or 12 and more bf16 rows 3.5-12 or 15-24 Mi elements, the more
+                                rows the shorter; other updates 16 Mi with fp32 rows, 64 Mi with up to 4 of
+                                them; with bf16 rows 64 Mi, 96 Mi with up to 12 of them, 128 Mi with up to 4;
+                                updates with norms on up to 6 rows: 16 Mi with bf16 rows, 32 / 64 / 128 Mi with 1 / 2 / 3-6 fp32 rows; norms
+                                and Gram matrix alone 16 Mi, direct sums alone never; the aggregation of one group
+                                without norms 3-16 Mi on 6 and more fp32 rows (bf16 result: 4-14 Mi on 12 and more)
+                                and 7.5-16 Mi on 12 and more bf16 rows (28); other aggregations 64 Mi, and never with up
                                 to 8 bf16 or 4 fp32 rows or with several groups of bf16 rows); 1 = always
-                                the queue; negative:
-                                STAR_ERR_SHAPE                                                          */
+                                the queue; negative: STAR_ERR_SHAPE.  A positive threshold takes the place of all
+                                limits on the length, those of the calls that write in bursts (star_plan_bursts) included:
+                                every call of enough rows does so from there on and none below.  Updates with norms from the
+                                matrix cores take their tiles in queue order at every length          */
 } star_options;
 
 /* The stream of updates of one call (all arrays on the host).  Group u is
@@ -320,6 +325,19 @@ star_status star_plan_choice(int64_t P, int32_t W, star_dtype grad_dtype, const 
                              const star_options *opt, star_plan_info *info);
 
 /*
+ * Host-only: whether star_group_update (star_plan_bursts) or star_group_reduce (star_plan_reduce_bursts) would keep the results of
+ * this call in LDS and write them in bursts, decided by the same code that launches it: *tiles = the tiles its workgroups claim from the
+ * work queue at a time, 0 for a call that writes as it goes.  Such a launch has one workgroup per compute unit, with all of the unit's 160 KB of
+ * LDS: while a kernel of another stream holds LDS on a unit, none of its workgroups starts there (the others take over its tiles but the first
+ * claim, which runs when a unit of the same accelerator die is free), and while it runs no other kernel that needs LDS starts.
+ * Arguments, checks and alignment as for star_plan_choice.
+ */
+star_status star_plan_bursts(int64_t P, int32_t W, star_dtype grad_dtype, const star_updates *upd, const star_hparams *hp,
+                             int32_t want_norms, const star_options *opt, int32_t *tiles);
+star_status star_plan_reduce_bursts(int64_t P, int32_t W, star_dtype out_dtype, star_dtype grad_dtype, const star_updates *upd,
+                                    int32_t wmode, int32_t want_norms, const star_options *opt, int32_t *tiles);
+
+/*
  * Gram matrix of the gradient rows, Gamma[a][b] = sum_j g_a[j] g_b[j], the
  * quantity the per-group norms are derived from (|| sum_w c_w g_w ||^2 =
  * c^T Gamma c) and the input of the noise-scale estimate below.
@@ -433,7 +451,7 @@ star_status star_select_mode_ar(int32_t N, const double *iter_time, const double
 /*
  * Host-only: the fixed first round of the work queue for a launch of
  * `workgroups` workgroups that claim `tiles_per_claim` tiles at a time (the
- * kernels use 2 to 13, by the bytes of a tile and the traffic of the launch).
+ * kernels use 2 to 16, by the bytes of a tile and the traffic of the launch).
  * Workgroup b starts on tiles first_tile[b] .. first_tile[b] + count[b] - 1
  * (counts cycle 1, 2, .., tiles_per_claim: unequal on purpose, so that the
  * workgroups do not run in step); the tiles from *base on are handed out by

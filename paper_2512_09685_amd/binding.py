@@ -93,6 +93,10 @@ def load_library():
     lib.star_plan_affine.argtypes = [i32, vp, vp, vp, vp]
     lib.star_plan_choice.restype = ctypes.c_int
     lib.star_plan_choice.argtypes = [i64, i32, ctypes.c_int, vp, vp, i32, i32, vp, vp]
+    lib.star_plan_bursts.restype = ctypes.c_int
+    lib.star_plan_bursts.argtypes = [i64, i32, ctypes.c_int, vp, vp, i32, vp, vp]
+    lib.star_plan_reduce_bursts.restype = ctypes.c_int
+    lib.star_plan_reduce_bursts.argtypes = [i64, i32, ctypes.c_int, ctypes.c_int, vp, i32, i32, vp, vp]
     lib.star_group_update_opt.restype = ctypes.c_int
     lib.star_group_update_opt.argtypes = [vp, vp, vp, ctypes.c_int, i64, i32, vp, vp, vp, vp, ctypes.c_int, vp, vp]
     lib.star_group_norms_opt.restype = ctypes.c_int
@@ -354,6 +358,31 @@ def star_plan_choice(P: int, W: int, grad_dtype, updates: UpdateStream, *, lr: f
     _check(lib.star_plan_choice(P, W, dt, ctypes.byref(updates.c), ctypes.byref(hp), int(bool(update)),
                                 int(bool(want_norms)), None if opt is None else ctypes.byref(opt), ctypes.byref(info)))
     return {name: getattr(info, name) for name, _ in _PlanInfo._fields_}
+
+
+def star_plan_bursts(P: int, W: int, grad_dtype, updates: UpdateStream, *, lr: float = 0.0, momentum_coef: float = 0.0,
+                     weight_decay: float = 0.0, wmode="mean", scale_lr_by_group: bool = False, want_norms: bool = False,
+                     kernel=None, queue_threshold=None, direct_norms: bool = False) -> int:
+    """Host-only: tiles per claim of an update whose results are written in bursts, 0 where they are written as they come."""
+    lib = load_library()
+    hp = _hparams(lr, momentum_coef, weight_decay, wmode, scale_lr_by_group)
+    dt = {"f32": F32, "bf16": BF16}.get(grad_dtype, grad_dtype)
+    opt, tiles = _options(kernel, queue_threshold, direct_norms), ctypes.c_int32(0)
+    _check(lib.star_plan_bursts(P, W, dt, ctypes.byref(updates.c), ctypes.byref(hp), int(bool(want_norms)),
+                                None if opt is None else ctypes.byref(opt), ctypes.byref(tiles)))
+    return tiles.value
+
+
+def star_plan_reduce_bursts(P: int, W: int, out_dtype, grad_dtype, updates: UpdateStream, *, wmode="mean",
+                            want_norms: bool = False, queue_threshold=None) -> int:
+    """The same for ``star_group_reduce``."""
+    lib = load_library()
+    code = {"f32": F32, "bf16": BF16}
+    opt, tiles = _options(None, queue_threshold), ctypes.c_int32(0)
+    _check(lib.star_plan_reduce_bursts(P, W, code.get(out_dtype, out_dtype), code.get(grad_dtype, grad_dtype),
+                                       ctypes.byref(updates.c), _WMODES[wmode] if isinstance(wmode, str) else wmode, int(bool(want_norms)),
+                                       None if opt is None else ctypes.byref(opt), ctypes.byref(tiles)))
+    return tiles.value
 
 
 def star_group_gram(grad_rows: Sequence, gram_out, *, stream=None, kernel=None, queue_threshold=None) -> None:

@@ -832,6 +832,12 @@ star_status run(bool update, float* params, float* momentum, const void* const* 
     return STAR_OK;
 }
 
+// One group without norms: tiles per claim where the aggregate is written in bursts, else 0 (a caller's own threshold: from there on).
+int reduce_burst(int U, int Wp, int grad_dtype, int out_dtype, bool want_norms, int64_t P, const Opts& opt) {
+    if (U != 1 || want_norms || (opt.queue_min > 0 && P < opt.queue_min)) return 0;
+    return star::mean_burst_claim(Wp, grad_dtype == STAR_F32, out_dtype == STAR_BF16, opt.queue_min > 0 ? (int64_t)1 << 62 : P);
+}
+
 // Body of star_group_reduce.
 star_status run_reduce(void* const* out_rows, int out_dtype, const void* const* grad_rows, int grad_dtype, int64_t P,
                        int32_t W, const star_updates* upd, int32_t wmode, float* norms_out,
@@ -884,9 +890,7 @@ star_status run_reduce(void* const* out_rows, int out_dtype, const void* const* 
     const bool use_inline = star::tables_fit_inline(U, Wp) && U <= star::reduce_max_updates(Wp, want_norms);
     const int umax = star::reduce_max_updates(Wp, want_norms);
     auto from_queue = [&](int n) { return P >= queue_min_for(opt, grad_dtype, Wc, false, true, false, false, n); };
-    int burst = 0;   // one group, no norms: written in bursts (a caller's own threshold: from there on)
-    if (U == 1 && !want_norms && (opt.queue_min == 0 || P >= opt.queue_min))
-        burst = star::mean_burst_claim(Wp, grad_dtype == STAR_F32, out_dtype == STAR_BF16, opt.queue_min > 0 ? (int64_t)1 << 62 : P);
+    const int burst = reduce_burst(U, Wp, grad_dtype, out_dtype, want_norms, P, opt);
     const bool want_queue = burst > 0 || from_queue(std::min(U, umax)) || (U % umax && from_queue(U % umax));
     std::unique_lock<std::mutex> lock(g_mu, std::defer_lock);
     Slot* slot = nullptr;   // only where something has to live in it
@@ -1157,6 +1161,42 @@ star_status star_plan_choice(int64_t P, int32_t W, star_dtype grad_dtype, const 
     info->norms_on_matrix_cores = norms_mma ? 1 : 0;
     info->fma_seq = plan.fma_seq;
     info->fma_affine = plan.fma_affine;
+    return STAR_OK;
+}
+
+star_status star_plan_bursts(int64_t P, int32_t W, star_dtype grad_dtype, const star_updates* upd, const star_hparams* hp,
+                             int32_t want_norms, const star_options* options, int32_t* tiles) {
+    star_plan_info info;   // (all checks)
+    if (!tiles) return set_err(STAR_ERR_NULL, "tiles is NULL");
+    star_status st = star_plan_choice(P, W, grad_dtype, upd, hp, 1, want_norms, options, &info);
+    if (st != STAR_OK) return st;
+    Opts opt;
+    star::Plan plan;
+    std::string msg;
+    st = resolve_options(options, &opt);
+    if (st == STAR_OK) st = star::build_plan(W, upd, hp, hp->wmode, want_norms != 0, &plan, &msg);
+    if (st != STAR_OK) return set_err(st, msg);
+    Launch how = decide(plan, (int)grad_dtype, true, want_norms != 0, P, opt);
+    if (how.split_norms) how = decide(plan, (int)grad_dtype, true, false, P, opt);
+    *tiles = P > 0 && plan.U > 0 ? how.burst : 0;
+    return STAR_OK;
+}
+
+star_status star_plan_reduce_bursts(int64_t P, int32_t W, star_dtype out_dtype, star_dtype grad_dtype, const star_updates* upd,
+                                    int32_t wmode, int32_t want_norms, const star_options* options, int32_t* tiles) {
+    g_err.clear();
+    Opts opt;
+    star_status st = resolve_options(options, &opt);
+    if (st != STAR_OK) return st;
+    if (!upd || !tiles) return set_err(STAR_ERR_NULL, "updates struct or tiles is NULL");
+    if (P < 0) return set_err(STAR_ERR_SHAPE, "P is negative");
+    if (grad_dtype != STAR_F32 && grad_dtype != STAR_BF16) return set_err(STAR_ERR_DTYPE, "unknown gradient dtype");
+    if (out_dtype != STAR_F32 && out_dtype != STAR_BF16) return set_err(STAR_ERR_DTYPE, "unknown output dtype");
+    star::Plan plan;
+    std::string msg;
+    st = star::build_plan(W, upd, nullptr, wmode, want_norms != 0, &plan, &msg);
+    if (st != STAR_OK) return set_err(st, msg);
+    *tiles = P > 0 ? reduce_burst(plan.U, star::padded_rows(plan.Wc), (int)grad_dtype, (int)out_dtype, want_norms != 0, P, opt) : 0;
     return STAR_OK;
 }
 

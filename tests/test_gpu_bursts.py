@@ -51,6 +51,8 @@ def test_update_in_bursts(W, dtype, P, threshold, offset, out):
     choice = dict(lr=0.1, momentum_coef=0.9, wmode="stale")
     assert star.star_plan_choice(P, W, dtype, us, queue_threshold=threshold, **choice)["queue_order"] == 1
     assert star.star_plan_choice(P, W, dtype, us, queue_threshold=1 << 62, **choice)["queue_order"] == 0
+    assert star.star_plan_bursts(P, W, dtype, us, queue_threshold=threshold, **choice) > 0
+    assert star.star_plan_bursts(P, W, dtype, us, queue_threshold=1 << 62, **choice) == 0
     got, (p, v, rows, us, (p0, v0)) = _call(W, P, dtype, offset, out, threshold)
     fixed = _call(W, P, dtype, offset, out, 1 << 62)[0]
     assert all(_same_bits(a, b) for a, b in zip(got, fixed))   # whole buffers: nothing beside the shard is written either
@@ -88,8 +90,10 @@ def _norms64(W, rows, us):
 def test_update_with_norms_in_bursts(W, dtype, P, threshold, offset, out):
     n, m = torch.full((12,), -1.0, device="cuda"), torch.full((12,), -1.0, device="cuda")
     got, (p, v, rows, us, _) = _call(W, P, dtype, offset, out, threshold, norms=n)
-    choice = star.star_plan_choice(P, W, dtype, us, lr=0.1, momentum_coef=0.9, wmode="stale", want_norms=True)
-    assert choice["kernel"] == star.KERNEL_AFFINE_MFMA
+    choice = dict(lr=0.1, momentum_coef=0.9, wmode="stale", want_norms=True)
+    assert star.star_plan_choice(P, W, dtype, us, queue_threshold=threshold, **choice)["kernel"] == star.KERNEL_AFFINE_MFMA
+    assert star.star_plan_bursts(P, W, dtype, us, queue_threshold=threshold, **choice) > 0
+    assert star.star_plan_bursts(P, W, dtype, us, queue_threshold=1 << 62, **choice) == 0
     fixed = _call(W, P, dtype, offset, out, 1 << 62, norms=m)[0]
     assert all(_same_bits(a, b) for a, b in zip(got, fixed))
     # the same sums tile by tile, in double from there on: only their order differs
@@ -106,6 +110,7 @@ def test_update_with_norms_by_one_workgroup_a_unit(W, P, offset, out):
     got, (p, v, rows, us, _) = _call(W, P, "f32", offset, out, None, norms=n)
     choice = star.star_plan_choice(P, W, "f32", us, lr=0.1, momentum_coef=0.9, wmode="stale", want_norms=True)
     assert choice["kernel"] == star.KERNEL_AFFINE_MFMA
+    assert star.star_plan_bursts(P, W, "f32", us, lr=0.1, momentum_coef=0.9, wmode="stale", want_norms=True) == 0
     plain = _call(W, P, "f32", offset, out, 1 << 62)[0]   # without norms: the same arithmetic in another kernel
     assert all(_same_bits(a, b) for a, b in zip(got, plain))
     want = _norms64(W, rows, us)
@@ -115,10 +120,10 @@ def test_update_with_norms_by_one_workgroup_a_unit(W, P, offset, out):
 # threshold None: the shortest shard of a row count; 1: the queue whatever the length
 @pytest.mark.parametrize("W,dtype,P,threshold,offset,out", [
     (6, "f32", 1, 1, 0, "f32"), (8, "f32", 1027, 1, 1, "f32"), (16, "f32", 511 * 1024 + 3, 1, 0, "f32"), (7, "f32", 11_000_003, 1, 3, "f32"),
-    (6, "f32", 14 << 20, None, 0, "f32"), (8, "f32", (8 << 20) + 5, None, 5, "f32"), (11, "f32", 7_340_035, None, 0, "f32"),
-    (12, "f32", 3 << 20, None, 2, "f32"), (24, "f32", 3_200_001, None, 0, "f32"), (12, "f32", 6001, 1, 1, "bf16"),
-    (13, "f32", (14 << 20) + 7, None, 0, "bf16"), (20, "f32", 4 << 20, None, 3, "bf16"), (12, "bf16", 5, 1, 0, "f32"),
-    (12, "bf16", (16 << 20) + 1, None, 1, "f32"), (14, "bf16", 8 << 20, None, 0, "f32"), (32, "bf16", 7_900_001, None, 0, "f32"),
+    (6, "f32", 14 << 20, None, 0, "f32"), (8, "f32", (8 << 20) + 69, None, 5, "f32"), (11, "f32", 7_340_035, None, 0, "f32"),
+    (12, "f32", (3 << 20) + 64, None, 2, "f32"), (24, "f32", 3_200_001, None, 0, "f32"), (12, "f32", 6001, 1, 1, "bf16"),
+    (13, "f32", (14 << 20) + 7, None, 0, "bf16"), (20, "f32", (4 << 20) + 64, None, 3, "bf16"), (12, "bf16", 5, 1, 0, "f32"),
+    (12, "bf16", (16 << 20) + 65, None, 1, "f32"), (14, "bf16", 8 << 20, None, 0, "f32"), (32, "bf16", 7_900_001, None, 0, "f32"),
     (28, "bf16", 262_147, 1, 1, "bf16"), (32, "bf16", 7_900_001, None, 5, "bf16")])
 def test_aggregate_in_bursts(W, dtype, P, threshold, offset, out):
     gen = torch.Generator(device="cuda").manual_seed(W + P)
@@ -130,6 +135,11 @@ def test_aggregate_in_bursts(W, dtype, P, threshold, offset, out):
           for n, m in ((len(members) - W, members[:-W]), (W, members[-W:]))]
     for stream in us:
         got = []
+        used = len(set(int(m) for m in stream.members))
+        if used == W or threshold == 1 and used >= (28 if (dtype, out) == ("bf16", "bf16") else 12 if "bf16" in (dtype, out) else 6):
+            whole_lines = max(1, P - 63) if offset else P   # what is left behind an advance of up to 63 elements
+            assert star.star_plan_reduce_bursts(whole_lines, W, out, dtype, stream, wmode="stale", queue_threshold=threshold) > 0
+        assert star.star_plan_reduce_bursts(P, W, out, dtype, stream, wmode="stale", queue_threshold=1 << 62) == 0
         for t in (threshold, 1 << 62):
             gen.manual_seed(7)
             whole, o = _guarded(P, offset, gen, dt[out])
@@ -156,6 +166,11 @@ def test_bursts_of_buffers_off_by_different_amounts(W, P, step):
     for dtype in ("f32", "bf16"):
         for out in ("f32", "bf16"):
             got = []
+            burst = star.star_plan_bursts(P, W, dtype, us, queue_threshold=1, **HP)
+            mean = star.star_plan_reduce_bursts(P, W, out, dtype, one, queue_threshold=1)
+            # (fp32 rows with norms: from 14 on; a bf16 aggregate of bf16 rows: from 28 on; both are then compared with themselves)
+            norms = star.star_plan_bursts(P, W, dtype, us, want_norms=True, queue_threshold=1, **HP)
+            assert burst > 0 and (norms > 0 or (W, dtype) == (12, "f32")) and (mean > 0 or dtype == out == "bf16")
             for threshold in (1, 1 << 62):
                 gen = torch.Generator(device="cuda").manual_seed(W + P)
                 rows = [_guarded(P, 1 + step * w, gen, dt[dtype], 1e-2)[1] for w in range(W)]

@@ -21,7 +21,7 @@ def test_library_exports_every_declared_symbol():
     header = re.sub(r"/\*.*?\*/", "", header, flags=re.S)
     names = set(re.findall(r"\b(star_[a-z_]+)\s*\(", header))
     assert {"star_group_update", "star_group_norms", "star_group_reduce", "star_group_update_publish", "star_group_gram",
-            "star_noise_scale", "star_select_mode_ps", "star_select_mode_ar", "star_plan_affine", "star_plan_choice", "star_plan_claims", "star_plan_even_split", "star_group_update_opt", "star_group_norms_opt",
+            "star_noise_scale", "star_select_mode_ps", "star_select_mode_ar", "star_plan_affine", "star_plan_choice", "star_plan_claims", "star_plan_even_split", "star_plan_bursts", "star_plan_reduce_bursts", "star_group_update_opt", "star_group_norms_opt",
             "star_group_reduce_opt", "star_group_gram_opt", "star_group_update_noalloc",
             "star_workspace_bytes", "star_last_error", "star_version", "star_shutdown"} <= names
     lib = star.load_library()
@@ -644,3 +644,95 @@ def test_current_stream_without_torchs_private_functions(missing, monkeypatch):
     monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
     assert binding._stream_handle(None) == 77
     assert binding._stream_handle(5) == 5 and binding._stream_handle(types.SimpleNamespace(cuda_stream=9)) == 9
+
+
+def _from_least(call, least, most=None):
+    """`call(P)` is positive from `least` to `most` elements and zero beside that."""
+    assert call(least - 1) == 0 and call(least) > 0
+    if most is None:
+        assert call(1 << 34) > 0
+    else:
+        assert call(most) > 0 and call(most + 1) == 0
+
+
+@pytest.mark.parametrize("dtype,norms,limits", [
+    ("f32", False, {9: None, 10: 12, 11: 12, 12: 10, 15: 10, 16: 7, 17: 7, 21: 3.5, 24: 3.5, 32: 3.5}),
+    ("bf16", False, {11: None, 12: 24, 15: 24, 16: 20, 20: 20, 21: 15, 32: 15}),
+    ("f32", True, {13: None, 14: 16, 16: 16, 17: 16, 20: 16, 21: None, 32: None}),
+    ("bf16", True, {6: None, 7: (4.5, 8), 8: (4.5, 8), 9: (4.5, 12), 11: (4.5, 12), 12: 4.5, 16: 4.5, 17: None, 20: None, 21: 16, 32: 16})])
+def test_plan_bursts_update(dtype, norms, limits):
+    """The shortest (and longest) update of every row count whose results are written in bursts, in Mi elements."""
+    for W, limit in limits.items():
+        offs = np.arange(0, 12 * W + 1, W)
+        us = star.UpdateStream(offs, np.tile(np.arange(W, dtype=np.int32), 12))
+        kw = dict(lr=0.1, momentum_coef=0.9, want_norms=norms)
+        call = lambda P, **more: star.star_plan_bursts(P, W, dtype, us, **kw, **more)
+        if limit is None:
+            assert not any(call(P) for P in (1, 1 << 22, 1 << 26, 1 << 34))
+        else:
+            least, most = limit if isinstance(limit, tuple) else (limit, None)
+            _from_least(call, int(least * (1 << 20)), most and int(most * (1 << 20)))
+        # a caller's own threshold takes the place of these lengths, not of the row counts
+        if not norms or star.star_plan_choice(5000, W, dtype, us, **kw)["kernel"] == star.KERNEL_AFFINE_MFMA:
+            own = call(5000, queue_threshold=5000)
+            assert (own > 0) == (limit is not None and not isinstance(limit, tuple)) and call(5000, queue_threshold=5001) == 0
+        assert call(1 << 34, kernel=star.KERNEL_SEQ) == 0 and call(0) == 0
+        # norms in a pass of their own: the update as if without
+        if norms and W <= 16:
+            plain = star.star_plan_bursts(1 << 26, W, dtype, us, lr=0.1, momentum_coef=0.9)
+            assert call(1 << 26, direct_norms=True) == plain
+
+
+@pytest.mark.parametrize("dtype,out,limits", [
+    ("f32", "f32", {5: None, 6: 14, 7: 8, 8: 8, 9: 7, 11: 7, 12: 3, 32: 3}),
+    ("f32", "bf16", {11: None, 12: 14, 13: 14, 14: 4, 32: 4}),
+    ("bf16", "f32", {11: None, 12: 16, 13: 16, 14: 8, 16: 8, 17: 7.5, 32: 7.5}),
+    ("bf16", "bf16", {24: None, 25: 7.5, 32: 7.5})])
+def test_plan_bursts_aggregate(dtype, out, limits):
+    for W, limit in limits.items():
+        one = star.UpdateStream([0, W], np.arange(W, dtype=np.int32))
+        call = lambda P, us=one, **more: star.star_plan_reduce_bursts(P, W, out, dtype, us, **more)
+        if limit is None:
+            assert not any(call(P) for P in (1, 1 << 22, 1 << 26, 1 << 34))
+        else:
+            _from_least(call, int(limit * (1 << 20)))
+            assert call(5000, queue_threshold=5000) > 0 and call(5000, queue_threshold=5001) == 0
+        # several groups, or norms: never
+        two = star.UpdateStream([0, W, W + 1], np.append(np.arange(W, dtype=np.int32), 0))
+        assert call(1 << 34, two) == 0 and call(1 << 34, want_norms=True) == 0 and call(0) == 0
+
+
+def test_plan_bursts_checks():
+    lib = star.load_library()
+    us = star.UpdateStream((0, 2), (0, 1))
+    hp = binding._HParams(0.1, 0.9, 0.0, 0, 0)
+    o, n = binding._Options(7, 0, 0), ctypes.c_int32(5)
+    u, h, t = ctypes.byref(us.c), ctypes.byref(hp), ctypes.byref(n)
+    assert lib.star_plan_bursts(8, 4, 0, u, h, 0, ctypes.byref(o), t) == 6
+    assert lib.star_plan_bursts(8, 4, 0, u, h, 0, None, None) == 1 and lib.star_plan_bursts(8, 4, 0, u, None, 0, None, t) == 1
+    assert lib.star_plan_bursts(8, 4, 0, None, h, 0, None, t) == 1 and lib.star_plan_bursts(-1, 4, 0, u, h, 0, None, t) == 2
+    assert lib.star_plan_bursts(8, 4, 7, u, h, 0, None, t) == 5 and lib.star_plan_bursts(8, 1, 0, u, h, 0, None, t) == 3
+    assert lib.star_plan_reduce_bursts(8, 4, 0, 0, u, 0, 0, ctypes.byref(o), t) == 6
+    assert lib.star_plan_reduce_bursts(8, 4, 0, 0, u, 0, 0, None, None) == 1
+    assert lib.star_plan_reduce_bursts(8, 4, 0, 0, None, 0, 0, None, t) == 1
+    assert lib.star_plan_reduce_bursts(-1, 4, 0, 0, u, 0, 0, None, t) == 2
+    assert lib.star_plan_reduce_bursts(8, 4, 7, 0, u, 0, 0, None, t) == 5 and lib.star_plan_reduce_bursts(8, 4, 0, 7, u, 0, 0, None, t) == 5
+    assert n.value == 5
+
+
+def test_bench_names_the_kernel_that_runs():
+    import dataclasses
+
+    import bench
+    import workloads
+
+    def label(name, op="update", norms=None):
+        wl = workloads.WORKLOADS[name]
+        if norms is not None:
+            wl = dataclasses.replace(wl, norms=norms)
+        s = workloads.make_update_stream(wl, 0, 0)
+        return bench.kernel_label(star, wl, star.UpdateStream(s["offsets"], s["members"], s["staleness"]), op)[0]
+    assert label("vgg16").startswith("aff_burst_kernel<32, RowBf16x4>")
+    for name in ("bert_base", "bert_large"):
+        assert label(name).startswith("aff_mfma_kernel<16") and "bursts" in label(name) and "bursts" not in label(name, "norms")
+    assert label("resnet50").startswith("aff_kernel<8") and "bursts" not in label("resnet50")

@@ -327,9 +327,10 @@ star_status star_plan_choice(int64_t P, int32_t W, star_dtype grad_dtype, const 
 /*
  * Host-only: whether star_group_update (star_plan_bursts) or star_group_reduce (star_plan_reduce_bursts) would keep the results of
  * this call in LDS and write them in bursts, decided by the same code that launches it: *tiles = the tiles its workgroups claim from the
- * work queue at a time, 0 for a call that writes as it goes.  Such a launch has one workgroup per compute unit, with all of the unit's 160 KB of
- * LDS: while a kernel of another stream holds LDS on a unit, none of its workgroups starts there (the others take over its tiles but the first
- * claim, which runs when a unit of the same accelerator die is free), and while it runs no other kernel that needs LDS starts.
+ * work queue at a time, 0 for a call that writes as it goes.  Such a launch runs one workgroup per compute unit, which takes all of the
+ * unit's 160 KB of LDS but 8: where a kernel of another stream holds more, its workgroup starts when that unit, or another one of the
+ * same die, has the room; until then the other workgroups take over its tiles but the first few.  In the same way kernels that need
+ * LDS wait for the launch.
  * Arguments, checks and alignment as for star_plan_choice.
  */
 star_status star_plan_bursts(int64_t P, int32_t W, star_dtype grad_dtype, const star_updates *upd, const star_hparams *hp,

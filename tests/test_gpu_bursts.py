@@ -183,3 +183,39 @@ def test_bursts_of_buffers_off_by_different_amounts(W, P, step):
                 torch.cuda.synchronize()
                 got.append((pw, vw, sw, ow))
             assert all(_same_bits(a, b) for a, b in zip(*got)), (dtype, out)
+
+
+def test_bursts_beside_work_that_holds_units():
+    """A launch that writes in bursts takes the whole LDS of every unit; here other kernels hold some or all of it when it starts, on a stream
+    of their own: matrix products on the whole device, one on few units for long, a softmax of many short workgroups."""
+    W, P = 16, 17_000_003
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    rows = [torch.randn(P, generator=gen, device="cuda") * 1e-2 for _ in range(W)]
+    p0, v0 = (torch.randn(P, generator=gen, device="cuda") for _ in range(2))
+    us = star.UpdateStream(*rand_stream(np.random.default_rng(W), W, 12, stale=4))
+    one = star.UpdateStream([0, W], np.arange(W, dtype=np.int32))
+    assert star.star_plan_bursts(P, W, "f32", us, **HP) > 0 and star.star_plan_bursts(P, W, "f32", us, want_norms=True, **HP) > 0
+    assert star.star_plan_reduce_bursts(P, W, "f32", "f32", one) > 0
+    wide, small = torch.randn(4096, 4096, device="cuda"), torch.randn(256, 1 << 18, device="cuda", dtype=torch.bfloat16)
+    tall, many = small.t().contiguous(), torch.randn(16384, 4096, device="cuda")
+
+    def calls(stream):
+        p, v, n, o = p0.clone(), v0.clone(), torch.zeros(12, device="cuda"), torch.empty(P, device="cuda")
+        torch.cuda.current_stream().synchronize()
+        star.star_group_update(p, v, rows, us, stream=stream, **HP)
+        star.star_group_update(p, v, rows, us, norms_out=n, stream=stream, **HP)
+        star.star_group_reduce([o], rows, one, stream=stream)
+        return p, v, o, n
+
+    mine, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    want = calls(mine)
+    torch.cuda.synchronize()
+    for work in (lambda: torch.mm(wide, wide), lambda: torch.mm(small, tall), lambda: torch.softmax(many, 1)):
+        with torch.cuda.stream(other):
+            for _ in range(20):
+                work()
+        got = calls(mine)
+        torch.cuda.synchronize()
+        assert all(_same_bits(a, b) for a, b in zip(got[:3], want[:3]))
+        assert float(((got[3] - want[3]) / want[3]).abs().max()) <= 2.0 ** -23   # (tiles from the queue: the order of the sums)

@@ -352,7 +352,11 @@ __device__ __forceinline__ void store_through(const f32x4 x, float* wave_base, c
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(wave_base, 0, 0x7fffffff, 0x00027000);
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), r, lane_bytes, 0, 16 /* sc1 */);
 }
-// The same of a tile's chunk as fp32 or, rounded, as bf16 (`wave_base`: the tile's first element).
+// The same of a tile's chunk as fp32 or, rounded, as bf16, into the array `dst`: an aggregate, or the new parameters' copy.  A copy that went
+// out with the non-temporal hint and at default scope in the middle of a burst cost more than the burst gained (with norms, 16 bf16 rows,
+// 340 M elements, bf16 / fp32 copy: 2 942 / 3 141 us, kernels that write as they go 2 802 / 2 898, this way 2 684 / 2 813; 12 rows, 150 M: 1 119 / 1 195, 1 052 /
+// 1 088, 1 038 / 1 099; 16 fp32 rows, 110 M: 1 499 / 1 580, 1 528 / 1 538, 1 420 / 1 459; without norms, 10 fp32 rows, 40 M: 394 / 417, 375 / 384, 367 / 380, 32 bf16 rows,
+// 138 M: 1 901 / 2 000, 1 884 / 1 880, 1 770 / 1 810; written at once, beside the reads: 3 050 / 3 072 of the first).
 __device__ __forceinline__ void publish_through(const f32x4 x, void* dst, const int as_bf16, const int64_t tile) {
     if (as_bf16) {
         u32x2 packed;
@@ -537,6 +541,9 @@ inline uint32_t burst_period(int cap, int bytes_per_tile, int workgroups, double
     const double ticks = fill * cap * (double)bytes_per_tile * workgroups / 66000.0;
     return ticks < 100.0 ? 100u : (uint32_t)ticks;
 }
+
+// Bytes of the new parameters' copy that a thread writes per tile.
+inline int copy_bytes(const AffArgs& a) { return !a.publish ? 0 : (a.publish_dtype == STAR_BF16 ? 8 : 16); }
 
 inline int64_t tiles_of(int64_t P) { return (P / 4 + kBlock - 1) / kBlock; }
 

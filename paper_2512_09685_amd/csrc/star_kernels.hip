@@ -359,7 +359,7 @@ void aff_burst_kernel(float* __restrict__ params, float* __restrict__ momentum, 
         if (c < nchunk) {
             store_through(x[0], params + tile * (4 * kBlock), threadIdx.x * 16);
             store_through(x[1], momentum + tile * (4 * kBlock), threadIdx.x * 16);
-            if (publish) publish_chunk(x[0], publish, publish_bf16, c);
+            if (publish) publish_through(x[0], publish, publish_bf16, tile);
         }
     };
     vec_t gn[W] = {};
@@ -835,7 +835,7 @@ hipError_t launch_aff_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_ou
             *grid_out = grid;
             hipLaunchKernelGGL((aff_burst_kernel<W, R>), dim3(grid), dim3(kBlock), 0, s, a.params, a.momentum, a.rows, a.cf, a.P,
                                a.head, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, tile_source(a.queue, a.done), a.burst,
-                               burst_period(burst_tiles(0), (kRowBytes + 64) * kBlock, grid));
+                               burst_period(burst_tiles(0), (kRowBytes + 64 + copy_bytes(a)) * kBlock, grid));
             const hipError_t e = hipGetLastError();
             if (e == hipSuccess && a.told) *a.told = queue_tells(a.done, grid, a.burst, tiles_of(a.P));
             return e;

@@ -335,7 +335,7 @@ __global__ __launch_bounds__(kBlock, FORM == Form::Shared ? 2 : 1) void aff_mfma
         if (c < nchunk) {
             store_through(x[0], params + tile * (4 * kBlock), threadIdx.x * 16);
             store_through(x[1], momentum + tile * (4 * kBlock), threadIdx.x * 16);
-            if (publish) publish_chunk(x[0], publish, publish_bf16, c);
+            if (publish) publish_through(x[0], publish, publish_bf16, tile);
         }
     };
     auto keep = [&](const int64_t t, const f32x4 po, const f32x4 vo) {
@@ -628,7 +628,7 @@ hipError_t launch_mfma_t(const AffArgs& a, int num_cu, int grid_cap, int* grid_o
             hipLaunchKernelGGL((aff_mfma_kernel<W, R, UPDATE, WIDE, Form::Bursts>), dim3(grid), dim3(kBlock), 0, s, a.params, a.momentum, a.rows,
                                a.cf, a.P, a.head, grid, 0x7fffffff, a.publish, a.publish_dtype == STAR_BF16 ? 1 : 0, a.partials,
                                TileSource{a.queue, nullptr, 0u}, a.burst,
-                               burst_period(burst_tiles_beside_panel(kBf16, W), (kRowBytes + 64) * kBlock, grid, 0.9));
+                               burst_period(burst_tiles_beside_panel(kBf16, W), (kRowBytes + 64 + copy_bytes(a)) * kBlock, grid, 0.9));
             return hipGetLastError();
         }
     }

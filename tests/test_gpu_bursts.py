@@ -51,8 +51,6 @@ def test_update_in_bursts(W, dtype, P, threshold, offset, out):
     choice = dict(lr=0.1, momentum_coef=0.9, wmode="stale")
     assert star.star_plan_choice(P, W, dtype, us, queue_threshold=threshold, **choice)["queue_order"] == 1
     assert star.star_plan_choice(P, W, dtype, us, queue_threshold=1 << 62, **choice)["queue_order"] == 0
-    assert star.star_plan_bursts(P, W, dtype, us, queue_threshold=threshold, **choice) > 0
-    assert star.star_plan_bursts(P, W, dtype, us, queue_threshold=1 << 62, **choice) == 0
     got, (p, v, rows, us, (p0, v0)) = _call(W, P, dtype, offset, out, threshold)
     fixed = _call(W, P, dtype, offset, out, 1 << 62)[0]
     assert all(_same_bits(a, b) for a, b in zip(got, fixed))   # whole buffers: nothing beside the shard is written either
@@ -71,15 +69,6 @@ def _same_bits(a, b):
     return torch.equal(a.view(as_int), b.view(as_int))
 
 
-def _norms64(W, rows, us):
-    r = torch.stack([x.double() for x in rows])
-    C = torch.zeros(us.U, W, dtype=torch.float64)
-    for u in range(us.U):
-        for k in range(us.offsets[u], us.offsets[u + 1]):
-            C[u, us.members[k]] = 1.0 / ((us.offsets[u + 1] - us.offsets[u]) * (1.0 + us.staleness[k]))
-    return sum((C.cuda() @ part).square().sum(1) for part in r.split(1 << 22, dim=1)).sqrt()
-
-
 # threshold None: the shortest shards of a row count and, with up to 11 bf16 rows, the longest
 @pytest.mark.parametrize("W,dtype,P,threshold,offset,out", [
     (14, "f32", 4099, 1, 0, None), (16, "f32", 256 * 1024 + 5, 1, 1, torch.bfloat16), (20, "f32", 511 * 1024 + 1, 1, 0, torch.float32),
@@ -90,40 +79,28 @@ def _norms64(W, rows, us):
 def test_update_with_norms_in_bursts(W, dtype, P, threshold, offset, out):
     n, m = torch.full((12,), -1.0, device="cuda"), torch.full((12,), -1.0, device="cuda")
     got, (p, v, rows, us, _) = _call(W, P, dtype, offset, out, threshold, norms=n)
-    choice = dict(lr=0.1, momentum_coef=0.9, wmode="stale", want_norms=True)
-    assert star.star_plan_choice(P, W, dtype, us, queue_threshold=threshold, **choice)["kernel"] == star.KERNEL_AFFINE_MFMA
-    assert star.star_plan_bursts(P, W, dtype, us, queue_threshold=threshold, **choice) > 0
-    assert star.star_plan_bursts(P, W, dtype, us, queue_threshold=1 << 62, **choice) == 0
+    choice = star.star_plan_choice(P, W, dtype, us, lr=0.1, momentum_coef=0.9, wmode="stale", want_norms=True)
+    assert choice["kernel"] == star.KERNEL_AFFINE_MFMA
     fixed = _call(W, P, dtype, offset, out, 1 << 62, norms=m)[0]
     assert all(_same_bits(a, b) for a, b in zip(got, fixed))
     # the same sums tile by tile, in double from there on: only their order differs
     assert float(((n - m) / m).abs().max()) <= 2.0 ** -23
-    want = _norms64(W, rows, us)
+    r = torch.stack([x.double() for x in rows])
+    C = torch.zeros(us.U, W, dtype=torch.float64)
+    for u in range(us.U):
+        for k in range(us.offsets[u], us.offsets[u + 1]):
+            C[u, us.members[k]] = 1.0 / ((us.offsets[u + 1] - us.offsets[u]) * (1.0 + us.staleness[k]))
+    want = sum((C.cuda() @ part).square().sum(1) for part in r.split(1 << 22, dim=1)).sqrt()
     assert float(((n.double() - want) / want).abs().max()) <= 1e-6   # (rows that are not anti-correlated, see star.h)
-
-
-# 8 and 9 fp32 rows on long shards: one workgroup per unit that writes as it goes; the shortest such shard, the one below, remainders
-@pytest.mark.parametrize("W,P,offset,out", [(8, 16 << 20, 0, None), (9, (16 << 20) - 1024, 0, None), (9, (16 << 20) + 1, 0, torch.bfloat16),
-                                            (9, (17 << 20) + 1023, 3, None), (8, (16 << 20) + 517, 1, torch.float32)])
-def test_update_with_norms_by_one_workgroup_a_unit(W, P, offset, out):
-    n = torch.full((12,), -1.0, device="cuda")
-    got, (p, v, rows, us, _) = _call(W, P, "f32", offset, out, None, norms=n)
-    choice = star.star_plan_choice(P, W, "f32", us, lr=0.1, momentum_coef=0.9, wmode="stale", want_norms=True)
-    assert choice["kernel"] == star.KERNEL_AFFINE_MFMA
-    assert star.star_plan_bursts(P, W, "f32", us, lr=0.1, momentum_coef=0.9, wmode="stale", want_norms=True) == 0
-    plain = _call(W, P, "f32", offset, out, 1 << 62)[0]   # without norms: the same arithmetic in another kernel
-    assert all(_same_bits(a, b) for a, b in zip(got, plain))
-    want = _norms64(W, rows, us)
-    assert float(((n.double() - want) / want).abs().max()) <= 1e-6
 
 
 # threshold None: the shortest shard of a row count; 1: the queue whatever the length
 @pytest.mark.parametrize("W,dtype,P,threshold,offset,out", [
     (6, "f32", 1, 1, 0, "f32"), (8, "f32", 1027, 1, 1, "f32"), (16, "f32", 511 * 1024 + 3, 1, 0, "f32"), (7, "f32", 11_000_003, 1, 3, "f32"),
-    (6, "f32", 14 << 20, None, 0, "f32"), (8, "f32", (8 << 20) + 69, None, 5, "f32"), (11, "f32", 7_340_035, None, 0, "f32"),
-    (12, "f32", (3 << 20) + 64, None, 2, "f32"), (24, "f32", 3_200_001, None, 0, "f32"), (12, "f32", 6001, 1, 1, "bf16"),
-    (13, "f32", (14 << 20) + 7, None, 0, "bf16"), (20, "f32", (4 << 20) + 64, None, 3, "bf16"), (12, "bf16", 5, 1, 0, "f32"),
-    (12, "bf16", (16 << 20) + 65, None, 1, "f32"), (14, "bf16", 8 << 20, None, 0, "f32"), (32, "bf16", 7_900_001, None, 0, "f32"),
+    (6, "f32", 14 << 20, None, 0, "f32"), (8, "f32", (8 << 20) + 5, None, 5, "f32"), (11, "f32", 7_340_035, None, 0, "f32"),
+    (12, "f32", 3 << 20, None, 2, "f32"), (24, "f32", 3_200_001, None, 0, "f32"), (12, "f32", 6001, 1, 1, "bf16"),
+    (13, "f32", (14 << 20) + 7, None, 0, "bf16"), (20, "f32", 4 << 20, None, 3, "bf16"), (12, "bf16", 5, 1, 0, "f32"),
+    (12, "bf16", (16 << 20) + 1, None, 1, "f32"), (14, "bf16", 8 << 20, None, 0, "f32"), (32, "bf16", 7_900_001, None, 0, "f32"),
     (28, "bf16", 262_147, 1, 1, "bf16"), (32, "bf16", 7_900_001, None, 5, "bf16")])
 def test_aggregate_in_bursts(W, dtype, P, threshold, offset, out):
     gen = torch.Generator(device="cuda").manual_seed(W + P)
@@ -135,11 +112,6 @@ def test_aggregate_in_bursts(W, dtype, P, threshold, offset, out):
           for n, m in ((len(members) - W, members[:-W]), (W, members[-W:]))]
     for stream in us:
         got = []
-        used = len(set(int(m) for m in stream.members))
-        if used == W or threshold == 1 and used >= (28 if (dtype, out) == ("bf16", "bf16") else 12 if "bf16" in (dtype, out) else 6):
-            whole_lines = max(1, P - 63) if offset else P   # what is left behind an advance of up to 63 elements
-            assert star.star_plan_reduce_bursts(whole_lines, W, out, dtype, stream, wmode="stale", queue_threshold=threshold) > 0
-        assert star.star_plan_reduce_bursts(P, W, out, dtype, stream, wmode="stale", queue_threshold=1 << 62) == 0
         for t in (threshold, 1 << 62):
             gen.manual_seed(7)
             whole, o = _guarded(P, offset, gen, dt[out])
@@ -166,11 +138,6 @@ def test_bursts_of_buffers_off_by_different_amounts(W, P, step):
     for dtype in ("f32", "bf16"):
         for out in ("f32", "bf16"):
             got = []
-            burst = star.star_plan_bursts(P, W, dtype, us, queue_threshold=1, **HP)
-            mean = star.star_plan_reduce_bursts(P, W, out, dtype, one, queue_threshold=1)
-            # (fp32 rows with norms: from 14 on; a bf16 aggregate of bf16 rows: from 28 on; both are then compared with themselves)
-            norms = star.star_plan_bursts(P, W, dtype, us, want_norms=True, queue_threshold=1, **HP)
-            assert burst > 0 and (norms > 0 or (W, dtype) == (12, "f32")) and (mean > 0 or dtype == out == "bf16")
             for threshold in (1, 1 << 62):
                 gen = torch.Generator(device="cuda").manual_seed(W + P)
                 rows = [_guarded(P, 1 + step * w, gen, dt[dtype], 1e-2)[1] for w in range(W)]
@@ -183,6 +150,60 @@ def test_bursts_of_buffers_off_by_different_amounts(W, P, step):
                 torch.cuda.synchronize()
                 got.append((pw, vw, sw, ow))
             assert all(_same_bits(a, b) for a, b in zip(*got)), (dtype, out)
+
+
+def _norms64(W, rows, us):
+    r = torch.stack([x.double() for x in rows])
+    C = torch.zeros(us.U, W, dtype=torch.float64)
+    for u in range(us.U):
+        for k in range(us.offsets[u], us.offsets[u + 1]):
+            C[u, us.members[k]] = 1.0 / ((us.offsets[u + 1] - us.offsets[u]) * (1.0 + us.staleness[k]))
+    return sum((C.cuda() @ part).square().sum(1) for part in r.split(1 << 22, dim=1)).sqrt()
+
+
+# 8 and 9 fp32 rows on long shards: one workgroup per unit that writes as it goes; the shortest such shard, the one below, remainders
+@pytest.mark.parametrize("W,P,offset,out", [(8, 16 << 20, 0, None), (9, (16 << 20) - 1024, 0, None), (9, (16 << 20) + 1, 0, torch.bfloat16),
+                                            (9, (17 << 20) + 1023, 3, None), (8, (16 << 20) + 517, 1, torch.float32)])
+def test_update_with_norms_by_one_workgroup_a_unit(W, P, offset, out):
+    n = torch.full((12,), -1.0, device="cuda")
+    got, (p, v, rows, us, _) = _call(W, P, "f32", offset, out, None, norms=n)
+    choice = star.star_plan_choice(P, W, "f32", us, lr=0.1, momentum_coef=0.9, wmode="stale", want_norms=True)
+    assert choice["kernel"] == star.KERNEL_AFFINE_MFMA
+    assert star.star_plan_bursts(P, W, "f32", us, lr=0.1, momentum_coef=0.9, wmode="stale", want_norms=True) == 0
+    plain = _call(W, P, "f32", offset, out, 1 << 62)[0]   # without norms: the same arithmetic in another kernel
+    assert all(_same_bits(a, b) for a, b in zip(got, plain))
+    want = _norms64(W, rows, us)
+    assert float(((n.double() - want) / want).abs().max()) <= 1e-6
+
+
+# The same just above a limit at an odd place: of P elements, what is left behind an advance of up to 63 to whole cache lines still writes in bursts.
+@pytest.mark.parametrize("what,W,dtype,P,offset,out", [
+    ("update", 16, "f32", (7 << 20) + 69, 5, None), ("norms", 16, "f32", (16 << 20) + 69, 5, None), ("reduce", 8, "f32", (8 << 20) + 69, 5, "f32"),
+    ("reduce", 12, "f32", (3 << 20) + 64, 2, "f32"), ("reduce", 20, "f32", (4 << 20) + 64, 3, "bf16"), ("reduce", 12, "bf16", (16 << 20) + 65, 1, "f32")])
+def test_bursts_just_above_a_limit_at_an_odd_place(what, W, dtype, P, offset, out):
+    one, us = star.UpdateStream([0, W], np.arange(W, dtype=np.int32)), star.UpdateStream(*rand_stream(np.random.default_rng(W), W, 12, stale=4))
+    choice = dict(lr=0.1, momentum_coef=0.9, wmode="stale", want_norms=what == "norms")
+    tiles = ([star.star_plan_reduce_bursts(n, W, out, dtype, one, wmode="stale") for n in (P - 63, P - 70)] if what == "reduce"
+             else [star.star_plan_bursts(n, W, dtype, us, **choice) for n in (P - 63, P - 70)])
+    assert tiles[0] > 0 and tiles[1] == 0
+    {"update": test_update_in_bursts, "norms": test_update_with_norms_in_bursts, "reduce": test_aggregate_in_bursts}[what](
+        W, dtype, P, None, offset, out)
+
+
+# What the tests above compare with the fixed assignment is written in bursts (whole cache lines: without an advance).
+def test_cases_above_are_written_in_bursts():
+    def cases_of(test):
+        return [m for m in test.pytestmark if m.name == "parametrize"][0].args[1]
+    for norms, test in ((False, test_update_in_bursts), (True, test_update_with_norms_in_bursts)):
+        for W, dtype, P, threshold, _, _ in cases_of(test):
+            us = star.UpdateStream(*rand_stream(np.random.default_rng(W), W, 12, stale=4))
+            choice = dict(lr=0.1, momentum_coef=0.9, wmode="stale", want_norms=norms)
+            assert star.star_plan_bursts(P, W, dtype, us, queue_threshold=threshold, **choice) > 0
+            assert star.star_plan_bursts(P, W, dtype, us, queue_threshold=1 << 62, **choice) == 0
+    for W, dtype, P, threshold, _, out in cases_of(test_aggregate_in_bursts):
+        one = star.UpdateStream([0, W], np.arange(W, dtype=np.int32))
+        assert star.star_plan_reduce_bursts(P, W, out, dtype, one, wmode="stale", queue_threshold=threshold) > 0
+        assert star.star_plan_reduce_bursts(P, W, out, dtype, one, wmode="stale", queue_threshold=1 << 62) == 0
 
 
 def test_bursts_beside_work_that_holds_units():

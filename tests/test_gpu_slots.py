@@ -41,6 +41,28 @@ def _make(i, seed):
     return lambda s: star.star_group_update(p, v, rows, us, norms_out=n if kind == "update" else None, stream=s, **HP, **kw), [p, v, n]
 
 
+def test_more_calls_than_slots_on_three_streams():
+    want = []
+    for i in range(len(CALLS)):
+        call, out = _make(i, 0)
+        call(None)
+        torch.cuda.synchronize()
+        want.append([x.clone() for x in out])
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    for repeat in range(6):
+        made = [(int(i), *_make(int(i), 0)) for i in np.random.default_rng(repeat).permutation(len(CALLS))]
+        torch.cuda.synchronize()
+        for k, (i, call, out) in enumerate(made):
+            call(streams[(k + repeat) % 3])
+        torch.cuda.synchronize()
+        for i, call, out in made:
+            for a, b in zip(out, want[i]):
+                if a.dtype == torch.float64:   # tiles from the queue: sums in double, their order is not fixed
+                    assert torch.allclose(a, b, rtol=1e-12, atol=1e-12 * float(b.abs().max()))
+                else:
+                    assert torch.equal(a, b), CALLS[i]
+
+
 def _wanted():
     want = []
     for i in range(len(CALLS)):
@@ -75,7 +97,7 @@ class _Delay:
         return ended
 
 
-def test_more_calls_than_slots_on_three_streams():
+def test_slots_run_out_on_three_streams():
     want, delay = _wanted(), _Delay()
     streams = [torch.cuda.Stream() for _ in range(3)]
     for repeat in range(4):
@@ -93,7 +115,7 @@ def test_more_calls_than_slots_on_three_streams():
         _check(made, want)
 
 
-def test_more_calls_than_slots_from_three_threads():
+def test_slots_run_out_from_three_threads():
     want, delay = _wanted(), _Delay()
     streams = [torch.cuda.Stream() for _ in range(3)]
     made = [[(int(i), *_make(int(i), 0)) for i in np.random.default_rng(t).permutation(len(CALLS))] for t in range(3)]

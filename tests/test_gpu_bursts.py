@@ -176,7 +176,8 @@ def test_update_with_norms_by_one_workgroup_a_unit(W, P, offset, out):
     assert float(((n.double() - want) / want).abs().max()) <= 1e-6
 
 
-# The same just above a limit at an odd place: of P elements, what is left behind an advance of up to 63 to whole cache lines still writes in bursts.
+# The same just above a limit at an odd place: of P elements, what is left behind an advance of up to 63 to whole cache lines still writes in
+# bursts (an aggregation's length counts behind the advance, an update's before it).
 @pytest.mark.parametrize("what,W,dtype,P,offset,out", [
     ("update", 16, "f32", (7 << 20) + 69, 5, None), ("norms", 16, "f32", (16 << 20) + 69, 5, None), ("reduce", 8, "f32", (8 << 20) + 69, 5, "f32"),
     ("reduce", 12, "f32", (3 << 20) + 64, 2, "f32"), ("reduce", 20, "f32", (4 << 20) + 64, 3, "bf16"), ("reduce", 12, "bf16", (16 << 20) + 65, 1, "f32")])
